@@ -329,6 +329,61 @@ struct ZTile {
 };
 
 // ---------------------------------------------------------------------------------------------
+// The chunk's scale without a launch of its own: the last workgroup of the chunk to finish sums the
+// partials.  Arrivals are counted in two levels, TICKET_SUB tiles each (atomics on one cache line are
+// served one at a time); whoever completes a counter sets it back, so nothing changes from call to call.
+// Only the first wavefront takes part, after the workgroup's stores: nothing waits for anything.
+// ---------------------------------------------------------------------------------------------
+constexpr int TICKET_SUB = 64;
+struct ChunkTicket {
+  unsigned int* count;     // lines of CTR_STRIDE 8-byte words: [chunks] second level, [chunks * spc] first level
+  double* sub_part;        // [chunks * spc]
+  int n_chunks, spc;       // first-level counters per chunk
+  float* scales;           // [chunks]
+  float* own_scale;        // also receives the scale of chunk own_chunk (NULL: none)
+  int own_chunk;
+};
+__device__ __forceinline__ bool ticket_arrive(unsigned int* counter, unsigned int n, double* payload, double s) {
+  int last = 0;
+  if ((threadIdx.x & (WAVE - 1)) == 0) {
+    __hip_atomic_store(payload, s, __ATOMIC_RELAXED, OB_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the payload is there before the arrival
+    last = (__hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, OB_AGENT) + 1u == n);
+    if (last) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, OB_AGENT);
+  }
+  return __shfl(last, 0, WAVE) != 0;
+}
+__device__ __forceinline__ double wave_sum(double v) {   // valid in lane 0
+#pragma unroll
+  for (int o = WAVE / 2; o > 0; o >>= 1) v += __shfl_down(v, o, WAVE);
+  return v;
+}
+// s: the tile's partial (lane 0); first wavefront only
+__device__ __forceinline__ void chunk_ticket(const ChunkTicket& tk, double* partials, const TilePos& p, int tpc,
+                                             int64_t n_c, double s) {
+  constexpr int LINE = 2 * CTR_STRIDE;
+  const int lane = threadIdx.x & (WAVE - 1);
+  const int b = p.t - p.c * tpc, sub = b / TICKET_SUB, first = sub * TICKET_SUB;
+  const int n = (tpc - first < TICKET_SUB) ? tpc - first : TICKET_SUB;
+  const int64_t si = (int64_t)p.c * tk.spc + sub;
+  if (!ticket_arrive(tk.count + (tk.n_chunks + si) * LINE, (unsigned int)n, &partials[p.t], s)) return;
+  double q = (lane < n) ? __hip_atomic_load(&partials[(int64_t)p.c * tpc + first + lane], __ATOMIC_RELAXED, OB_AGENT) : 0.0;
+  q = wave_sum(q);
+  if (tk.spc > 1) {
+    if (!ticket_arrive(tk.count + (int64_t)p.c * LINE, (unsigned int)tk.spc, &tk.sub_part[si], q)) return;
+    q = 0.0;
+    for (int j = lane; j < tk.spc; j += WAVE)
+      q += __hip_atomic_load(&tk.sub_part[(int64_t)p.c * tk.spc + j], __ATOMIC_RELAXED, OB_AGENT);
+    q = wave_sum(q);
+  }
+  if (lane == 0) {
+    const float sc = (float)sqrt(q / (double)n_c);
+    tk.scales[p.c] = sc;
+    if (tk.own_scale && p.c == tk.own_chunk) *tk.own_scale = sc;
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
 // K1  z written over err, and the tile's sum of z^2 in fp64: the first of the two passes of the
 // worker compression (k_sign_pack_error is the second), or, with DEFER, all of it.
 // ---------------------------------------------------------------------------------------------
@@ -337,11 +392,11 @@ struct ZTile {
 // the sign words of z are packed and written here as well (they do not depend on the scale); the
 // scale itself follows from the tile partials in k_chunk_scale.  packed_out / pe.bits may be the
 // same buffer: a word is read and rewritten by the same 8 lanes, in program order.
-template <int U, bool HAS_K, bool PACKED_M, int GT = 0, bool DEFER = false>
+template <int U, bool HAS_K, bool PACKED_M, int GT = 0, bool DEFER = false, bool TICKET = false>
 __global__ __launch_bounds__(BLOCK) void k_momentum_z_sumsq(
     GradSrc g, const float* __restrict__ m, PackedMom pm,
     float* __restrict__ err, double* __restrict__ partials, int64_t n_c, int tpc, float beta1,
-    float omb1, LayerTab lt, PackedErr pe, uint32_t* packed_out, OwnCopy oc) {
+    float omb1, LayerTab lt, PackedErr pe, uint32_t* packed_out, OwnCopy oc, ChunkTicket tk) {
   constexpr int TILE = SPAN * U;
   __shared__ double lds[BLOCK / WAVE];
   const TilePos p = tile_pos<TILE>(n_c, tpc, (int)blockIdx.x);
@@ -390,7 +445,11 @@ __global__ __launch_bounds__(BLOCK) void k_momentum_z_sumsq(
     }
   }
   const double s = block_sum(acc, lds);
-  if (threadIdx.x == 0) partials[p.t] = s;
+  if (TICKET) {
+    if (threadIdx.x < WAVE) chunk_ticket(tk, partials, p, tpc, n_c, s);
+  } else if (threadIdx.x == 0) {
+    partials[p.t] = s;
+  }
 }
 
 // scale[c] = sqrt(sum of the chunk's tile partials / n_c), summed in a fixed order.
@@ -536,6 +595,7 @@ __device__ __forceinline__ unsigned long long barrier_publish(unsigned long long
 // Bounded wait (thread 0 of a workgroup) for a flag of generation `want`: at most spin_limit polls
 // (0: none, the wait expires at once whatever the flag holds); returns the flag word last read (0
 // if none was).  On expiry *errflag is raised; once it is raised every wait ends within 64 polls.
+template <int SLEEP = OB_POLL_SLEEP>
 __device__ __forceinline__ unsigned long long barrier_wait(const unsigned long long* flag,
                                                            unsigned int want, unsigned int* errflag,
                                                            int spin_limit) {
@@ -548,7 +608,7 @@ __device__ __forceinline__ unsigned long long barrier_wait(const unsigned long l
     f = __hip_atomic_load(flag, __ATOMIC_RELAXED, OB_AGENT);
     if ((unsigned int)(f >> 32) == want) break;
     if ((it & 63) == 63 && __hip_atomic_load(errflag, __ATOMIC_RELAXED, OB_AGENT) != 0u) break;
-    __builtin_amdgcn_s_sleep(OB_POLL_SLEEP);
+    __builtin_amdgcn_s_sleep(SLEEP);
   }
   return f;
 }
@@ -761,11 +821,11 @@ __device__ __forceinline__ void server_average(const uint32_t* __restrict__ pack
 // scale): err_s holds zb of the previous call, the carried error is err_s - C[zb] with the server's
 // own previous output `keep` (read and rewritten in place), and the sign words of the new zb are
 // written here, to packed_out and to `keep`; no second pass over the chunk is needed.
-template <int U, bool DEFER = false>
+template <int U, bool DEFER = false, bool TICKET = false>
 __global__ __launch_bounds__(BLOCK) void k_server_unpack_avg(
     const uint32_t* __restrict__ packed_in, const float* __restrict__ scales_in,
     float* __restrict__ err_s, double* __restrict__ partials, int64_t n_c, int W, float invW,
-    uint32_t* keep, const float* keep_scale, uint32_t* packed_out) {
+    uint32_t* keep, const float* keep_scale, uint32_t* packed_out, ChunkTicket tk) {
   constexpr int TILE = SPAN * U;
   __shared__ double lds[BLOCK / WAVE];
   __shared__ unsigned int lds_negs[SRV_STAGE];
@@ -779,7 +839,7 @@ __global__ __launch_bounds__(BLOCK) void k_server_unpack_avg(
   for (int u = 0; u < U; ++u) {
     const int o = u * SPAN + o0;
     if (o < p.len) {   // uniform over the wavefront, as the shuffles below require
-      v4f e = ld4(err_s + p.tile0 + o);
+      v4f e = ld4(err_s + p.tile0 + o);   // (requested before the sum over the workers: 28 instead of 22 us at 6.9M elements)
       if (DEFER) e = deferred_error(e, load_nibble(keep, p.tile0 + u * SPAN), se);
       v4f z;
       unsigned int nib = 0;
@@ -801,7 +861,11 @@ __global__ __launch_bounds__(BLOCK) void k_server_unpack_avg(
     }
   }
   const double s = block_sum(sq, lds);
-  if (threadIdx.x == 0) partials[p.t] = s;
+  if (TICKET) {
+    if (threadIdx.x < WAVE) chunk_ticket(tk, partials, p, (int)gridDim.x, n_c, s);
+  } else if (threadIdx.x == 0) {
+    partials[p.t] = s;
+  }
 }
 
 // K3+K4 in one pass: Algorithm 1 line 10 on the served chunk with zb kept in registers across the
@@ -1898,6 +1962,335 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_apply_hist(
   }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Small lists: Algorithm 1 lines 13-21 of the whole buffer in one launch.
+//
+// Where all 1024*U-element tiles of the buffer fit on the device at once, the three launches of the
+// split above cost more than the work: every launch is a chain of dependent look-ups, loads and
+// reductions of a few microseconds whatever it moves.  Here every tile, whatever layers it meets, is one
+// workgroup that runs the ratio pass, takes part in the barriers of its layers and then the update, with
+// x, v_frozen and the signs in registers.  U is the smallest of 1, 2, 4 for which the tiles fit: the time
+// of a workgroup that is alone on its CU is its own chain of divisions.
+//
+// A layer wholly inside a tile needs no barrier; only the first and the last segment of a tile can belong
+// to a layer that goes on elsewhere.  Same self-numbering counters, bounded waits and co-residency rule
+// (80 % of the workgroup slots) as the other barriers.  The spans that k_ratios_apply_hist would handle
+// from the variance's history ("lagging") do so here too, so that what the v_fresh array holds between two
+// calls does not depend on the kernel; their two values per step are formed by each thread.
+// Measured: four 512x512 tensors 11.5 us (k_ratios_apply_resident 14.5); 37 tensors of 2 to 64000 elements
+// 12.9 us (26 us in three launches, and the gaps between them).
+// ---------------------------------------------------------------------------------------------
+struct SmallTile {
+  int l0;          // layer of the first element
+  int seg0;        // first segment
+  int nseg;        // segments (0: padding)
+  int chunk_kind;  // chunk << 2 | (1: wholly inside one layer) | (2: lagging)
+  int l_last;      // layer of the last segment
+  int n_first;     // segments of the first segment's layer, over all tiles
+  int n_last;      // ... of the last segment's
+  int pad;
+};
+// workgroups per CU that the kernels are built for (their registers at each U)
+constexpr int small_min_wg(int u) { return u == 1 ? 8 : (u == 2 ? 5 : 4); }
+constexpr int SMALL_POLL_SLEEP = 2;   // (the whole launch lasts some 10 us: a poll every 128 clocks)
+struct SmallTab {
+  const SmallTile* tiles;
+  int n_tiles, tpc, max_seg;
+  int64_t n_c;
+  const int* seg_layer;         // [segments]
+  const int* layer_seg0;        // [L+1]
+  void* partial;                // [segments] float maxima, or [2 * segments] double sums
+  unsigned long long* counter;  // [L * CTR_STRIDE]
+  unsigned long long* flag;     // [L * CTR_STRIDE]
+  unsigned int* errflag;
+  int spin_limit;
+};
+struct RatioClip {
+  const float* c_avg;
+  float* r_prev;
+  float* coeff_c;
+  float one_m_thr, one_p_thr, r_min, r_max;
+};
+
+// Segment tables of a tile that meets several layers, in LDS: where each segment ends (relative to the
+// tile) and its layer; then the segment's coefficient.
+struct SmallSegs {
+  int* end;
+  int* layer;
+  float* coeff;
+  __device__ __forceinline__ void load(const SmallTab& sm, const SmallTile& ti, const TilePos& p,
+                                       const int64_t* __restrict__ off) {
+    for (int s = threadIdx.x; s < ti.nseg; s += BLOCK) {
+      const int l = sm.seg_layer[ti.seg0 + s];
+      const int64_t e = off[l + 1] - p.tile0;
+      layer[s] = l;
+      end[s] = e < p.len ? (int)e : p.len;
+    }
+  }
+  // segment of the element at `o` (ti.nseg: padding)
+  __device__ __forceinline__ int find(int nseg, int o) const {
+    int lo = 0, hi = nseg;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (end[mid] > o) hi = mid; else lo = mid + 1;
+    }
+    return lo;
+  }
+};
+
+// First half of the barriers of a tile: thread 0 arrives for its first segment, thread WAVE for its last
+// one (if that is another).  store(e): publishes the segment's partial result.  bc[e] = (generation << 32) |
+// (1: the layer's last arrival) | (2: the layer is this segment alone, no barrier).
+template <class F>
+__device__ __forceinline__ void small_arrive(const SmallTab& sm, const SmallTile& ti, int n_end, unsigned long long* bc,
+                                             F store) {
+  const int e = threadIdx.x / WAVE;
+  if (e < n_end && (threadIdx.x & (WAVE - 1)) == 0) {
+    const int n = e ? ti.n_last : ti.n_first, l = e ? ti.l_last : ti.l0;
+    if (n == 1) {
+      bc[e] = 2ull;
+    } else {
+      store(e);
+      payload_before_arrival();
+      bc[e] = barrier_arrive(&sm.counter[(int64_t)l * CTR_STRIDE], n);
+    }
+  }
+  __syncthreads();
+}
+
+template <int U, bool HAS_K, bool LPX>
+__global__ __launch_bounds__(BLOCK, small_min_wg(U)) void k_ratios_apply_small(
+    RatioArgs ra, VfHist h, ApplyArgs aa, SmallTab sm, RatioClip rc, LayerTab lt) {
+  constexpr int TILE = SPAN * U;
+  extern __shared__ int dyn_lds[];
+  __shared__ float lds[BLOCK / WAVE];
+  __shared__ unsigned long long bc[2];
+  __shared__ float c_end[2];
+  if ((int)blockIdx.x == sm.n_tiles) {   // the layers without elements go through the clips too
+    for (int l = threadIdx.x; l < lt.L; l += BLOCK)
+      if (sm.layer_seg0[l + 1] == sm.layer_seg0[l])
+        (void)ratio_clip_commit(0.0f, l, rc.r_prev[l], rc.c_avg[l], rc.r_prev, rc.coeff_c, rc.one_m_thr, rc.one_p_thr,
+                                rc.r_min, rc.r_max);
+    return;
+  }
+  const SmallTile ti = sm.tiles[blockIdx.x];
+  if (ti.nseg == 0) return;
+  TilePos p;
+  p.t = (int)blockIdx.x;
+  p.c = ti.chunk_kind >> 2;
+  const int64_t in_chunk = (int64_t)(p.t - p.c * sm.tpc) * TILE;
+  p.tile0 = (int64_t)p.c * sm.n_c + in_chunk;
+  p.len = (sm.n_c - in_chunk < TILE) ? (int)(sm.n_c - in_chunk) : TILE;
+  const bool inside = (ti.chunk_kind & 1) != 0, lagging = (ti.chunk_kind & 2) != 0;
+  const int a = lagging ? h.n_old + 1 : 1;       // steps to apply (uniform)
+  const int o0 = threadIdx.x * 4;
+  unsigned int NB[VF_MAX_OLD + 2][U];            // the lane's nibble of every plane, newest first
+  v4f V[U], VZ[U], X[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int o = u * SPAN + o0;
+    V[u] = 0.0f; VZ[u] = 0.0f; X[u] = 0.0f;
+#pragma unroll
+    for (int q = 0; q < VF_MAX_OLD + 2; ++q) {
+      NB[q][u] = 0u;
+      if (q <= a && o < p.len) NB[q][u] = load_nibble(plane_bits(ra, h, q), p.tile0 + u * SPAN);
+    }
+    if (o < p.len) {
+      V[u] = ld4(ra.v_fresh + p.tile0 + o);
+      VZ[u] = ld4(ra.v_frozen + p.tile0 + o);
+      X[u] = ld4(aa.x + p.tile0 + o);
+    }
+  }
+  const float ss = ra.sscales[p.c];
+  float* const vals = reinterpret_cast<float*>(dyn_lds);      // [TILE] quotients (tiles that meet several layers)
+  SmallSegs sg;
+  sg.end = dyn_lds + TILE; sg.layer = sg.end + sm.max_seg;
+  sg.coeff = reinterpret_cast<float*>(sg.layer + sm.max_seg);
+  const int last_seg = ti.nseg - 1;
+  const int n_end = ti.nseg > 1 ? 2 : 1;
+  const int l_end[2] = {ti.l0, ti.l_last};
+  float r_end[2] = {0.0f, 0.0f};                 // (thread 0: of the first segment; thread WAVE: of the last)
+  // what the last arriver of a layer needs, requested with everything else
+  const float rp_end[2] = {rc.r_prev[ti.l0], rc.r_prev[ti.l_last]}, ca_end[2] = {rc.c_avg[ti.l0], rc.c_avg[ti.l_last]};
+  const int s0_end[2] = {sm.layer_seg0[ti.l0], sm.layer_seg0[ti.l_last]};
+  if (inside) {
+    const float kt = HAS_K ? lt.mom_scale[ti.l0] : 1.0f;
+#pragma unroll
+    for (int s = VF_MAX_OLD + 1; s >= 1; --s) {
+      if (s <= a) {
+        float t_same, t_diff;
+        variance_terms<HAS_K>(ra, plane_scale(ra, h, s - 1, p.c), plane_scale(ra, h, s, p.c), kt, &t_same, &t_diff);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+            V[u][k] = ra.beta2 * V[u][k] + select_by_bit(NB[s][u] ^ NB[s - 1][u], k, t_diff, t_same);
+      }
+    }
+    float r = 0.0f;
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float q = VZ[u][k] / V[u][k];      // (0/0 beyond the tile's end: NaN, not taken)
+        if (q > r) r = q;
+      }
+    r_end[0] = block_max(r, lds);
+  } else {
+    sg.load(sm, ti, p, lt.off);
+    __syncthreads();
+    const float s_prev = ra.pm.scales[p.c];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int o = u * SPAN + o0;
+      if (o < p.len) {
+        int s = sg.find(ti.nseg, o);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          while (s < ti.nseg && o + k >= sg.end[s]) ++s;
+          float q = 0.0f;
+          if (s < ti.nseg) {
+            float t_same, t_diff;
+            variance_terms<HAS_K>(ra, ss, s_prev, HAS_K ? lt.mom_scale[sg.layer[s]] : 1.0f, &t_same, &t_diff);
+            V[u][k] = ra.beta2 * V[u][k] + ((((NB[0][u] ^ NB[1][u]) >> k) & 1u) ? t_diff : t_same);
+            q = VZ[u][k] / V[u][k];
+          }
+          vals[o + k] = q;
+        }
+      }
+    }
+    __syncthreads();
+    // a wavefront per segment; the layers that lie inside the tile are finished here
+    const int lane = threadIdx.x & (WAVE - 1);
+    for (int s = threadIdx.x / WAVE; s < ti.nseg; s += BLOCK / WAVE) {
+      float r = 0.0f;
+      for (int o = (s ? sg.end[s - 1] : 0) + lane; o < sg.end[s]; o += WAVE)
+        if (vals[o] > r) r = vals[o];
+#pragma unroll
+      for (int o = WAVE / 2; o > 0; o >>= 1) {
+        const float w = __shfl_down(r, o, WAVE);
+        r = (w > r) ? w : r;
+      }
+      if (lane == 0) sg.coeff[s] = r;
+    }
+    __syncthreads();
+    r_end[0] = sg.coeff[0];
+    r_end[1] = sg.coeff[last_seg];
+    __syncthreads();
+    for (int s = 1 + (int)threadIdx.x; s < last_seg; s += BLOCK) {   // the layers in between lie inside the tile
+      const int l = sg.layer[s];
+      sg.coeff[s] = ratio_clip_commit(sg.coeff[s], l, rc.r_prev[l], rc.c_avg[l], rc.r_prev, rc.coeff_c, rc.one_m_thr,
+                                      rc.one_p_thr, rc.r_min, rc.r_max);
+    }
+  }
+  float* const partial = reinterpret_cast<float*>(sm.partial);
+  small_arrive(sm, ti, n_end, bc, [&](int e) {
+    __hip_atomic_store(&partial[ti.seg0 + (e ? last_seg : 0)], r_end[e], __ATOMIC_RELAXED, OB_AGENT);
+  });
+  for (int e = 0; e < n_end; ++e) {   // (uniform)
+    if ((bc[e] & 3ull) == 0ull) continue;
+    const int l = l_end[e], s0 = s0_end[e], s1 = s0 + (e ? ti.n_last : ti.n_first);
+    float q = 0.0f;
+    if (bc[e] & 1ull) {
+      for (int s = s0 + threadIdx.x; s < s1; s += BLOCK) {
+        const float v = __hip_atomic_load(&partial[s], __ATOMIC_RELAXED, OB_AGENT);
+        if (v > q) q = v;
+      }
+      q = block_max(q, lds);
+    } else if ((int)threadIdx.x == e * WAVE) {
+      q = r_end[e];
+    }
+    if ((bc[e] & 1ull) ? threadIdx.x == 0 : (int)threadIdx.x == e * WAVE) {
+      const float c = ratio_clip_commit(q, l, rp_end[e], ca_end[e], rc.r_prev, rc.coeff_c, rc.one_m_thr, rc.one_p_thr,
+                                        rc.r_min, rc.r_max);
+      c_end[e] = c;
+      if (bc[e] & 1ull)
+        (void)barrier_publish(&sm.flag[(int64_t)l * CTR_STRIDE], &sm.counter[(int64_t)l * CTR_STRIDE], s1 - s0,
+                              (unsigned int)(bc[e] >> 32), __float_as_uint(c));
+    }
+  }
+  // while the layers complete: the variance is stored, m_t/(sqrt(v_frozen)+eta) formed in place of v_frozen
+  if (inside) {
+    const float sp = HAS_K ? ss / lt.mom_scale[ti.l0] : ss;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int o = u * SPAN + o0;
+      if (o < p.len) {
+        if (!lagging || h.write_v) st4(ra.v_fresh + p.tile0 + o, V[u]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const float mt = ((NB[0][u] >> k) & 1u) ? sp : -sp;
+          float uu = mt / (sqrtf(VZ[u][k]) + aa.eta);
+          asm volatile("" : "+v"(uu));   // evaluated here, not sunk below the wait
+          VZ[u][k] = uu;
+        }
+      }
+    }
+  } else {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int o = u * SPAN + o0;
+      if (o < p.len) {
+        int s = sg.find(ti.nseg, o);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          while (s < ti.nseg && o + k >= sg.end[s]) ++s;
+          if (s < ti.nseg) {
+            ra.v_fresh[p.tile0 + o + k] = V[u][k];
+            const float sp = HAS_K ? ss / lt.mom_scale[sg.layer[s]] : ss;
+            const float mt = ((NB[0][u] >> k) & 1u) ? sp : -sp;
+            float uu = mt / (sqrtf(VZ[u][k]) + aa.eta);
+            asm volatile("" : "+v"(uu));
+            VZ[u][k] = uu;
+          }
+        }
+      }
+    }
+  }
+  {
+    const int e = threadIdx.x / WAVE;
+    if (e < n_end && (threadIdx.x & (WAVE - 1)) == 0 && (bc[e] & 2ull) == 0ull) {
+      // (the last arriver too: with no polls left its own flag is as late as anyone's)
+      const unsigned long long f = barrier_wait<SMALL_POLL_SLEEP>(&sm.flag[(int64_t)l_end[e] * CTR_STRIDE], (unsigned int)(bc[e] >> 32),
+                                                sm.errflag, sm.spin_limit);
+      c_end[e] = __uint_as_float((unsigned int)(f & 0xffffffffull));
+    }
+  }
+  __syncthreads();
+  if (inside) {
+    const float al = aa.lr * c_end[0];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int o = u * SPAN + o0;
+      if (o < p.len) {
+        v4f xn;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) xn[k] = X[u][k] - al * VZ[u][k];
+        st4(aa.x + p.tile0 + o, xn);
+        if (LPX) st4_lp(aa.x_lp, p.tile0 + o, xn, aa.x_lp_bf16);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int o = u * SPAN + o0;
+      if (o < p.len) {
+        int s = sg.find(ti.nseg, o);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          while (s < ti.nseg && o + k >= sg.end[s]) ++s;
+          if (s < ti.nseg) {
+            const float c = (s == 0) ? c_end[0] : (s == last_seg) ? c_end[1] : sg.coeff[s];
+            const float xn = X[u][k] - (aa.lr * c) * VZ[u][k];
+            aa.x[p.tile0 + o + k] = xn;
+            if (LPX) reinterpret_cast<unsigned short*>(aa.x_lp)[p.tile0 + o + k] = float_to_lp(xn, aa.x_lp_bf16);
+          }
+        }
+      }
+    }
+  }
+}
+
 // Dense view of a momentum held in 1-bit form: m[i] = (bit ? s_c : -s_c)/k_l for i < N (the
 // padding of m is left untouched).
 template <int U, bool HAS_K>
@@ -2304,6 +2697,208 @@ __global__ __launch_bounds__(BLOCK, OB_WU_MINW) void k_warmup_resident(
       for (int k = 0; k < 4; ++k) xn[k] = X[u][k] - a * UU[u][k];
       st4(x + p.tile0 + o, xn);
       if (LPX) st4_lp(x_lp, p.tile0 + o, xn, x_lp_bf16);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Small lists: eq. (1) of the whole buffer in one launch (see k_ratios_apply_small: same tiles, segments
+// and barriers, with the fp64 sums of x^2 and u^2 in place of the maxima).
+// Measured: 2.95 M parameters, binary16 gradient: 26 us (37 us in four launches).
+// ---------------------------------------------------------------------------------------------
+struct WarmClip {
+  float* coeff_c;
+  float* c_avg;
+  float c_min, c_max, beta3, omb3;
+};
+template <int U, int GT, bool LPX>
+__global__ __launch_bounds__(BLOCK, small_min_wg(U)) void k_warmup_small(
+    GradSrc g, float* __restrict__ m, float* __restrict__ v, float* __restrict__ x, SmallTab sm, WarmClip wc,
+    float beta1, float omb1, float beta2, float omb2, float eta, float wd, float lr, LayerTab lt,
+    void* __restrict__ x_lp, int x_lp_bf16) {
+  constexpr int TILE = SPAN * U;
+  extern __shared__ int dyn_lds[];
+  __shared__ double lds[BLOCK / WAVE];
+  __shared__ double end_sum[2][2];
+  __shared__ unsigned long long bc[2];
+  __shared__ float c_end[2];
+  if ((int)blockIdx.x == sm.n_tiles) {   // the layers without elements
+    for (int l = threadIdx.x; l < lt.L; l += BLOCK)
+      if (sm.layer_seg0[l + 1] == sm.layer_seg0[l])
+        (void)warmup_coeff_commit(0.0, 0.0, l, wc.c_avg[l], wc.coeff_c, wc.c_avg, wc.c_min, wc.c_max, wc.beta3, wc.omb3);
+    return;
+  }
+  const SmallTile ti = sm.tiles[blockIdx.x];
+  if (ti.nseg == 0) return;
+  TilePos p;
+  p.t = (int)blockIdx.x;
+  p.c = ti.chunk_kind >> 2;
+  const int64_t in_chunk = (int64_t)(p.t - p.c * sm.tpc) * TILE;
+  p.tile0 = (int64_t)p.c * sm.n_c + in_chunk;
+  p.len = (sm.n_c - in_chunk < TILE) ? (int)(sm.n_c - in_chunk) : TILE;
+  const bool inside = (ti.chunk_kind & 1) != 0;
+  const int o0 = threadIdx.x * 4;
+  v4f G[U], M[U], V[U], X[U], UU[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int o = u * SPAN + o0;
+    G[u] = 0.0f; M[u] = 0.0f; V[u] = 0.0f; X[u] = 0.0f;
+    if (o < p.len) {
+      G[u] = load_grad<GT>(g, p.tile0 + o);
+      M[u] = ld4(m + p.tile0 + o);
+      V[u] = ld4(v + p.tile0 + o);
+      X[u] = ld4(x + p.tile0 + o);
+    }
+  }
+  float* const val_x = reinterpret_cast<float*>(dyn_lds);     // [TILE] (tiles that meet several layers)
+  float* const val_u = val_x + TILE;                          // [TILE]
+  SmallSegs sg;
+  sg.end = dyn_lds + 2 * TILE; sg.layer = sg.end + sm.max_seg;
+  sg.coeff = reinterpret_cast<float*>(sg.layer + sm.max_seg);
+  if (!inside) sg.load(sm, ti, p, lt.off);
+  // what the last arriver of a layer needs, requested with everything else
+  const float ca_end[2] = {wc.c_avg[ti.l0], wc.c_avg[ti.l_last]};
+  const int s0_end[2] = {sm.layer_seg0[ti.l0], sm.layer_seg0[ti.l_last]};
+  double sx = 0.0, su = 0.0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int o = u * SPAN + o0;
+    UU[u] = 0.0f;
+    if (o < p.len) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        M[u][k] = beta1 * M[u][k] + omb1 * G[u][k];
+        V[u][k] = beta2 * V[u][k] + omb2 * (G[u][k] * G[u][k]);
+        const float uu = lamb_u(M[u][k], V[u][k], X[u][k], eta, wd);
+        UU[u][k] = uu;
+        if (inside) {
+          sx += (double)X[u][k] * (double)X[u][k];
+          su += (double)uu * (double)uu;
+        } else {
+          val_x[o + k] = X[u][k];
+          val_u[o + k] = uu;
+        }
+      }
+    }
+  }
+  const int last_seg = ti.nseg - 1;
+  const int n_end = ti.nseg > 1 ? 2 : 1;
+  const int l_end[2] = {ti.l0, ti.l_last};
+  if (inside) {
+    sx = block_sum(sx, lds);
+    su = block_sum(su, lds);
+    if (threadIdx.x == 0) {
+      end_sum[0][0] = sx;
+      end_sum[0][1] = su;
+    }
+  } else {
+    __syncthreads();
+    const int lane = threadIdx.x & (WAVE - 1);
+    for (int s = threadIdx.x / WAVE; s < ti.nseg; s += BLOCK / WAVE) {   // a wavefront per segment
+      double tx = 0.0, tu = 0.0;
+      for (int o = (s ? sg.end[s - 1] : 0) + lane; o < sg.end[s]; o += WAVE) {
+        tx += (double)val_x[o] * (double)val_x[o];
+        tu += (double)val_u[o] * (double)val_u[o];
+      }
+#pragma unroll
+      for (int o = WAVE / 2; o > 0; o >>= 1) {
+        tx += __shfl_down(tx, o, WAVE);
+        tu += __shfl_down(tu, o, WAVE);
+      }
+      if (lane == 0) {
+        if (s == 0 || s == last_seg) {
+          const int e = (s == 0) ? 0 : 1;
+          end_sum[e][0] = tx;
+          end_sum[e][1] = tu;
+        } else {   // the layer lies inside the tile
+          const int l = sg.layer[s];
+          sg.coeff[s] = warmup_coeff_commit(tx, tu, l, wc.c_avg[l], wc.coeff_c, wc.c_avg, wc.c_min, wc.c_max,
+                                            wc.beta3, wc.omb3);
+        }
+      }
+    }
+  }
+  __syncthreads();
+  double* const partial = reinterpret_cast<double*>(sm.partial);
+  small_arrive(sm, ti, n_end, bc, [&](int e) {
+    double* q = partial + 2 * (int64_t)(ti.seg0 + (e ? last_seg : 0));
+    __hip_atomic_store(q, end_sum[e][0], __ATOMIC_RELAXED, OB_AGENT);
+    __hip_atomic_store(q + 1, end_sum[e][1], __ATOMIC_RELAXED, OB_AGENT);
+  });
+  for (int e = 0; e < n_end; ++e) {   // (uniform)
+    if ((bc[e] & 3ull) == 0ull) continue;
+    const int l = l_end[e], s0 = s0_end[e], s1 = s0 + (e ? ti.n_last : ti.n_first);
+    double tx = end_sum[e][0], tu = end_sum[e][1];
+    if (bc[e] & 1ull) {
+      tx = 0.0; tu = 0.0;
+      for (int s = s0 + threadIdx.x; s < s1; s += BLOCK) {
+        tx += __hip_atomic_load(&partial[2 * (int64_t)s], __ATOMIC_RELAXED, OB_AGENT);
+        tu += __hip_atomic_load(&partial[2 * (int64_t)s + 1], __ATOMIC_RELAXED, OB_AGENT);
+      }
+      tx = block_sum(tx, lds);
+      tu = block_sum(tu, lds);
+    }
+    if (threadIdx.x == 0) {
+      const float c = warmup_coeff_commit(tx, tu, l, ca_end[e], wc.coeff_c, wc.c_avg, wc.c_min, wc.c_max, wc.beta3,
+                                          wc.omb3);
+      c_end[e] = c;
+      if (bc[e] & 1ull)
+        (void)barrier_publish(&sm.flag[(int64_t)l * CTR_STRIDE], &sm.counter[(int64_t)l * CTR_STRIDE], s1 - s0,
+                              (unsigned int)(bc[e] >> 32), __float_as_uint(c));
+    }
+  }
+  // while the layers complete: the moments are stored
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int o = u * SPAN + o0;
+    if (o < p.len) {
+      if (inside) {
+        st4(m + p.tile0 + o, M[u]);
+        st4(v + p.tile0 + o, V[u]);
+      } else {
+        const int end = sg.end[last_seg];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (o + k < end) {
+            m[p.tile0 + o + k] = M[u][k];
+            v[p.tile0 + o + k] = V[u][k];
+          }
+      }
+    }
+  }
+  {
+    const int e = threadIdx.x / WAVE;
+    if (e < n_end && (threadIdx.x & (WAVE - 1)) == 0 && (bc[e] & 2ull) == 0ull) {
+      const unsigned long long f = barrier_wait<SMALL_POLL_SLEEP>(&sm.flag[(int64_t)l_end[e] * CTR_STRIDE], (unsigned int)(bc[e] >> 32),
+                                                sm.errflag, sm.spin_limit);
+      c_end[e] = __uint_as_float((unsigned int)(f & 0xffffffffull));
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int o = u * SPAN + o0;
+    if (o < p.len) {
+      if (inside) {
+        const float a = lr * c_end[0];
+        v4f xn;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) xn[k] = X[u][k] - a * UU[u][k];
+        st4(x + p.tile0 + o, xn);
+        if (LPX) st4_lp(x_lp, p.tile0 + o, xn, x_lp_bf16);
+      } else {
+        int s = sg.find(ti.nseg, o);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          while (s < ti.nseg && o + k >= sg.end[s]) ++s;
+          if (s < ti.nseg) {
+            const float c = (s == 0) ? c_end[0] : (s == last_seg) ? c_end[1] : sg.coeff[s];
+            const float xn = X[u][k] - (lr * c) * UU[u][k];
+            x[p.tile0 + o + k] = xn;
+            if (LPX) reinterpret_cast<unsigned short*>(x_lp)[p.tile0 + o + k] = float_to_lp(xn, x_lp_bf16);
+          }
+        }
+      }
     }
   }
 }

@@ -96,6 +96,8 @@ enum KernelId {
   KID_APPLY,
   KID_RATIOS_APPLY_RESIDENT,
   KID_RATIOS_APPLY_HIST,
+  KID_RATIOS_APPLY_SMALL,
+  KID_WARMUP_SMALL,
   KID_VARIANCE_DENSE,
   KID_VARIANCE_TERMS,
   KID_RATIOS_BIG_HIST,
@@ -113,8 +115,32 @@ enum KernelId {
 const char* const kKernelNames[KID_COUNT] = {
     "momentum_z_sumsq", "compress_resident", "chunk_scale",     "sign_pack_error", "compress_deferred", "server_unpack_avg",
     "server_scale",     "server_sign_pack", "server_resident", "ratios_pass",     "ratios_finalize",
-    "decompress_apply", "ratios_apply_resident", "ratios_apply_hist", "variance_dense", "variance_terms", "ratios_big_hist", "momentum_dense", "error_dense", "momentum_scale", "warmup_moments",   "warmup_coeff",    "warmup_apply",
+    "decompress_apply", "ratios_apply_resident", "ratios_apply_hist", "ratios_apply_small", "warmup_small", "variance_dense", "variance_terms", "ratios_big_hist", "momentum_dense", "error_dense", "momentum_scale", "warmup_moments",   "warmup_coeff",    "warmup_apply",
     "warmup_resident",  "fill",            "copy"};
+
+// Chunks of at most this many tiles get their scale from the kernel that forms the partials (chunk_ticket)
+// instead of k_chunk_scale.  A workgroup's arrival costs it two round trips to memory: at 256 tiles the
+// kernel takes 2.7 us more and the launch that it saves took 2.5 us and a gap (and 2 us of the host); at 8
+// tiles it is 1.4 us more.  Beyond that the workgroups of many rounds all pay.
+#ifndef OB_TICKET_MAX
+#define OB_TICKET_MAX 256
+#endif
+
+// Single-launch form of a list whose tiles all fit on the device at once (k_ratios_apply_small,
+// k_warmup_small).
+struct SmallPlan {
+  int u = 0;                            // spans per tile; 0: not used
+  int tpc = 0, n_tiles = 0, max_seg = 0;
+  bool empty_layers = false;
+  size_t lds_bytes = 0;
+  unsigned char* d_mem = nullptr;       // one allocation for all of the following
+  SmallTile* d_tiles = nullptr;
+  int* d_seg_layer = nullptr;
+  int* d_layer_seg0 = nullptr;
+  double* d_partial = nullptr;          // [2 * segments]
+  unsigned long long* d_counter = nullptr;
+  unsigned long long* d_flag = nullptr;
+};
 
 struct ProfRec {
   int kid;
@@ -213,6 +239,11 @@ struct ob_lamb_ctx {
   // of the work between it and the plain kernels
   LayerSplit sp_apply;                     // ob_lamb_ratios_apply
   LayerSplit sp_warm;                      // ob_lamb_warmup_step
+  SmallPlan sm_apply, sm_warm;             // the same calls on lists small enough for one launch
+  unsigned int* d_ticket = nullptr;        // chunk_ticket: counters of the worker's chunks (NULL: not used)
+  unsigned int* d_ticket_srv = nullptr;    // ... of the served chunk
+  double* d_ticket_part = nullptr;
+  double* d_ticket_part_srv = nullptr;
   size_t device_bytes = 0;                 // device memory this context holds (tables + workspace)
   // diagnostics
   bool profile = false;
@@ -256,17 +287,18 @@ struct Launch {
   }
 };
 
-#define OB_LAUNCH_B(la, kid, kernel, grid, block, ...)                            \
+#define OB_LAUNCH_S(la, kid, kernel, grid, block, lds_bytes, ...)                 \
   do {                                                                            \
     if ((la).ok && (grid) > 0) {                                                  \
       if ((la).begin(kid, false))                                                 \
-        hipExtLaunchKernelGGL(kernel, dim3((unsigned)(grid)), dim3(block), 0, (la).stream, \
+        hipExtLaunchKernelGGL(kernel, dim3((unsigned)(grid)), dim3(block), lds_bytes, (la).stream, \
                               (la).ctx->prof.back().e0, (la).ctx->prof.back().e1, 0, __VA_ARGS__); \
       else if ((la).ok)                                                           \
-        hipLaunchKernelGGL(kernel, dim3((unsigned)(grid)), dim3(block), 0, (la).stream, __VA_ARGS__); \
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(grid)), dim3(block), lds_bytes, (la).stream, __VA_ARGS__); \
       (la).end(kKernelNames[kid], false);                                         \
     }                                                                             \
   } while (0)
+#define OB_LAUNCH_B(la, kid, kernel, grid, block, ...) OB_LAUNCH_S(la, kid, kernel, grid, block, 0, __VA_ARGS__)
 #define OB_LAUNCH(la, kid, kernel, grid, ...) OB_LAUNCH_B(la, kid, kernel, grid, BLOCK, __VA_ARGS__)
 
 template <class T>
@@ -502,7 +534,8 @@ void plan_split(const Tiling& tl, int64_t tile_lb, const Tiling& tm, const std::
 
 // Plans and uploads one LayerSplit.
 bool build_split(ob_lamb_ctx* ctx, const Tiling& tl, int tile_lb, const Tiling& tm,
-                 const std::vector<int64_t>& h_off, int64_t max_tiles, LayerSplit* sp) {
+                 const std::vector<int64_t>& h_off, int64_t max_tiles, LayerSplit* sp,
+                 std::vector<unsigned char>* lagging) {
   const int64_t L = ctx->L;
   SplitPlan pl;
   plan_split(tl, tile_lb, tm, h_off, ctx->n_c, L, max_tiles, &pl);
@@ -521,6 +554,8 @@ bool build_split(ob_lamb_ctx* ctx, const Tiling& tl, int tile_lb, const Tiling& 
   sp->big_on = sp->n_big_tiles > 0;
   sp->n_big_params = pl.n_big_params;
   sp->n_rest_ratio_tiles = (int)pl.rest_ratio_tiles.size();
+  lagging->assign((size_t)tm.n_tiles, 0);
+  for (int t : cov) (*lagging)[(size_t)t] = 1;
   return upload(ctx, &sp->d_cov_tiles, cov) && upload(ctx, &sp->d_big_tiles, pl.big_tiles) &&
          upload(ctx, &sp->d_rest_ratio_tiles, pl.rest_ratio_tiles) && upload(ctx, &sp->d_fused_tiles, pl.fused_tiles) && upload(ctx, &sp->d_n_listed, pl.n_listed) &&
          upload(ctx, &sp->d_list_begin, pl.list_begin) && upload(ctx, &sp->d_seg_first, pl.seg_first) &&
@@ -528,6 +563,105 @@ bool build_split(ob_lamb_ctx* ctx, const Tiling& tl, int tile_lb, const Tiling& 
          alloc_zero(ctx, &sp->d_listed_sums, 2 * pl.fused_tiles.size()) &&
          upload(ctx, &sp->d_rest_tiles, pl.rest_tiles) && upload(ctx, &sp->d_has_listed, pl.has_listed) &&
          alloc_zero(ctx, &sp->d_counter, (size_t)L * CTR_STRIDE) && alloc_zero(ctx, &sp->d_flag, (size_t)L);
+}
+
+// The tiles and segments of one SmallPlan (no HIP call).  lagging: per 1024-element span (tm's tiling).
+void small_tiles(const Tiling& t, int U, const Tiling& tm, const std::vector<int64_t>& h_off, int64_t n_c, int64_t L,
+                 const std::vector<unsigned char>& lagging, std::vector<SmallTile>* tiles, int* max_seg) {
+  tiles->resize((size_t)t.n_tiles);
+  *max_seg = 1;
+  for (int64_t i = 0; i < t.n_tiles; ++i) {
+    const int64_t c = i / t.tpc, b = i % t.tpc;
+    const int64_t tile0 = c * n_c + b * (int64_t)SPAN * U, tile1 = std::min(tile0 + (int64_t)SPAN * U, (c + 1) * n_c);
+    SmallTile& st = (*tiles)[(size_t)i];
+    st.l0 = t.first[(size_t)i];
+    st.seg0 = t.tile_seg0[(size_t)i];
+    st.nseg = t.tile_seg0[(size_t)i + 1] - st.seg0;
+    const bool inside = st.l0 < L && tile1 <= h_off[(size_t)st.l0 + 1];
+    const bool lag = inside && lagging[(size_t)(c * tm.tpc + b * U)];   // (a lagging span's 8192-element tile lags as a whole)
+    st.chunk_kind = (int)(c << 2) | (inside ? 1 : 0) | (lag ? 2 : 0);
+    st.l_last = st.nseg > 0 ? t.seg_layer[(size_t)(st.seg0 + st.nseg - 1)] : st.l0;
+    auto total = [&](int l) { return l < L ? t.layer_seg0[(size_t)l + 1] - t.layer_seg0[(size_t)l] : 0; };
+    st.n_first = total(st.l0);
+    st.n_last = total(st.l_last);
+    st.pad = 0;
+    *max_seg = std::max(*max_seg, st.nseg);
+  }
+}
+
+// Chooses and uploads a SmallPlan: the smallest U whose tiles take at most 80 % of the device's workgroup
+// slots (slots(U, dynamic LDS bytes)).  vals: floats of LDS per element of a tile that meets several layers.
+template <class F>
+bool build_small(ob_lamb_ctx* ctx, const Tiling& tm, const std::vector<int64_t>& h_off,
+                 const std::vector<unsigned char>& lagging, int vals, F slots, SmallPlan* sp) {
+  for (int U : {1, 2, 4}) {
+    const int64_t tpc = (ctx->n_c + (int64_t)SPAN * U - 1) / ((int64_t)SPAN * U);
+    if (tpc * ctx->W > 4096) continue;   // (no device has the slots)
+    Tiling t;
+    std::vector<SmallTile> tiles;
+    int max_seg = 0;
+    if (!build_tiling((int64_t)SPAN * U, ctx->n_c, ctx->W, ctx->L, h_off, &t)) return true;
+    small_tiles(t, U, tm, h_off, ctx->n_c, ctx->L, lagging, &tiles, &max_seg);
+    const size_t bytes = 4 * ((size_t)vals * SPAN * U + 3 * (size_t)max_seg);
+    int64_t n_slots = 0;
+    if (!slots(U, bytes, &n_slots)) return false;
+    if (5 * (t.n_tiles + 8) > 4 * n_slots) continue;
+    sp->tpc = (int)t.tpc;
+    sp->n_tiles = (int)t.n_tiles;
+    sp->max_seg = max_seg;
+    sp->lds_bytes = bytes;
+    for (int64_t l = 0; l < ctx->L; ++l)
+      if (t.layer_seg0[(size_t)l + 1] == t.layer_seg0[(size_t)l]) sp->empty_layers = true;
+    std::vector<unsigned char> mem;
+    auto put = [&](const void* src, size_t n) {   // -> offset (256-byte aligned); src NULL: zeros
+      const size_t at = (mem.size() + 255) / 256 * 256;
+      mem.resize(at + n, 0);
+      if (src && n) std::memcpy(mem.data() + at, src, n);
+      return at;
+    };
+    const size_t line = CTR_STRIDE * sizeof(unsigned long long);
+    const size_t o_tiles = put(tiles.data(), tiles.size() * sizeof(SmallTile));
+    const size_t o_segl = put(t.seg_layer.data(), t.seg_layer.size() * sizeof(int));
+    const size_t o_lseg = put(t.layer_seg0.data(), t.layer_seg0.size() * sizeof(int));
+    const size_t o_part = put(nullptr, 2 * t.seg_layer.size() * sizeof(double));
+    const size_t o_ctr = put(nullptr, (size_t)ctx->L * line), o_flag = put(nullptr, (size_t)ctx->L * line);
+    if (!upload(ctx, &sp->d_mem, mem)) return false;
+    sp->d_tiles = reinterpret_cast<SmallTile*>(sp->d_mem + o_tiles);
+    sp->d_seg_layer = reinterpret_cast<int*>(sp->d_mem + o_segl);
+    sp->d_layer_seg0 = reinterpret_cast<int*>(sp->d_mem + o_lseg);
+    sp->d_partial = reinterpret_cast<double*>(sp->d_mem + o_part);
+    sp->d_counter = reinterpret_cast<unsigned long long*>(sp->d_mem + o_ctr);
+    sp->d_flag = reinterpret_cast<unsigned long long*>(sp->d_mem + o_flag);
+    sp->u = U;
+    return true;
+  }
+  return true;
+}
+
+SmallTab small_tab(const ob_lamb_ctx* ctx, const SmallPlan& sp) {
+  SmallTab t;
+  t.tiles = sp.d_tiles; t.n_tiles = sp.n_tiles; t.tpc = sp.tpc; t.max_seg = sp.max_seg; t.n_c = ctx->n_c;
+  t.seg_layer = sp.d_seg_layer; t.layer_seg0 = sp.d_layer_seg0; t.partial = sp.d_partial;
+  t.counter = sp.d_counter; t.flag = sp.d_flag; t.errflag = ctx->d_errflag; t.spin_limit = ctx->spin_limit;
+  return t;
+}
+
+// Calls f(integral_constant<int, u>) for u in {1, 2, 4}.
+template <class F>
+void dispatch_u(int u, F f) {
+  switch (u) {
+    case 1: f(std::integral_constant<int, 1>{}); break;
+    case 2: f(std::integral_constant<int, 2>{}); break;
+    default: f(std::integral_constant<int, 4>{}); break;
+  }
+}
+
+ChunkTicket chunk_ticket_of(unsigned int* count, double* part, int n_chunks, int tpc, float* scales, float* own_scale,
+                            int own_chunk) {
+  ChunkTicket tk;
+  tk.count = count; tk.sub_part = part; tk.n_chunks = n_chunks; tk.spc = (tpc + TICKET_SUB - 1) / TICKET_SUB;
+  tk.scales = scales; tk.own_scale = own_scale; tk.own_chunk = own_chunk;
+  return tk;
 }
 
 void free_split(LayerSplit* sp) {
@@ -596,6 +730,31 @@ void launch_apply(Launch& la, ob_lamb_ctx* ctx, const ob_lamb_state* st, const u
       OB_LAUNCH(la, KID_APPLY,
                 (k_decompress_apply<U_MAIN, decltype(hk)::value, decltype(wm)::value, decltype(lx)::value>),
                 n_launch_tiles, aa, ctx->n_c, ctx->tpc, lt, tiles);
+    });
+  });
+}
+
+RatioArgs ratio_args(const ob_lamb_ctx* ctx, const ob_lamb_state* st, const uint32_t* packed_all,
+                     const float* server_scales, const PackedMom& pm) {
+  RatioArgs ra;
+  ra.packed = packed_all; ra.sscales = server_scales; ra.m = st->m; ra.pm = pm;
+  ra.v_fresh = st->v_fresh; ra.v_frozen = st->v_frozen;
+  ra.beta1 = ctx->beta1; ra.omb1 = ctx->omb1; ra.beta2 = ctx->beta2; ra.omb2 = ctx->omb2;
+  return ra;
+}
+
+void launch_ratios_apply_small(Launch& la, ob_lamb_ctx* ctx, const ob_lamb_state* st, const RatioArgs& ra,
+                               const VfHist& vh, const ApplyArgs& aa) {
+  const SmallPlan& sm = ctx->sm_apply;
+  RatioClip rc;
+  rc.c_avg = st->c_avg; rc.r_prev = st->r_prev; rc.coeff_c = st->coeff_c;
+  rc.one_m_thr = ctx->one_m_thr; rc.one_p_thr = ctx->one_p_thr; rc.r_min = ctx->r_min; rc.r_max = ctx->r_max;
+  const LayerTab lt = layer_tab(ctx, st, ctx->d_first_layer);
+  dispatch_u(sm.u, [&](auto u) {
+    dispatch2(st->mom_scale != nullptr, aa.x_lp != nullptr, [&](auto hk, auto lx) {
+      OB_LAUNCH_S(la, KID_RATIOS_APPLY_SMALL,
+                  (k_ratios_apply_small<decltype(u)::value, decltype(hk)::value, decltype(lx)::value>),
+                  sm.n_tiles + (sm.empty_layers ? 1 : 0), BLOCK, sm.lds_bytes, ra, vh, aa, small_tab(ctx, sm), rc, lt);
     });
   });
 }
@@ -874,8 +1033,47 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
                               ? 0 : split_max_tiles(std::min(per_cu_a, OB_LB_MINW), cus, cfg->fused_max_tiles);
     const int64_t max_w = (cfg->flags & OB_CFG_TWO_PASS_WARMUP)
                               ? 0 : split_max_tiles(std::min(per_cu_w, OB_WU_MINW), cus, cfg->fused_max_tiles);
-    ok = ok && build_split(ctx, tl, TILE_LB, tm, h_off, max_a, &ctx->sp_apply) &&
-         build_split(ctx, tw, TILE_WU, tm, h_off, max_w, &ctx->sp_warm);
+    std::vector<unsigned char> lagging, unused;
+    ok = ok && build_split(ctx, tl, TILE_LB, tm, h_off, max_a, &ctx->sp_apply, &lagging) &&
+         build_split(ctx, tw, TILE_WU, tm, h_off, max_w, &ctx->sp_warm, &unused);
+    // one launch instead of three or four where the whole list fits on the device at once (unless the
+    // configuration lowers what the barrier kernels may take)
+    auto slots_of = [&](auto kernel, size_t bytes, int min_per_cu, int64_t* out) {
+      int per_cu = 0;
+      if (!hip_ok(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, BLOCK, bytes),
+                  "hipOccupancyMaxActiveBlocksPerMultiprocessor"))
+        return false;
+      *out = (int64_t)std::min(per_cu, min_per_cu) * cus;   // (every instantiation reaches its launch bound)
+      return true;
+    };
+    if (ok && cfg->fused_max_tiles == 0 && !(cfg->flags & OB_CFG_NO_FUSED_APPLY))
+      ok = build_small(ctx, tm, h_off, lagging, 1, [&](int U, size_t bytes, int64_t* n) {
+        bool r = false;
+        dispatch_u(U, [&](auto u) {
+          constexpr int UU = decltype(u)::value;
+          r = slots_of(k_ratios_apply_small<UU, true, true>, bytes, small_min_wg(UU), n);
+        });
+        return r;
+      }, &ctx->sm_apply);
+    if (ok && cfg->fused_max_tiles == 0 && !(cfg->flags & OB_CFG_TWO_PASS_WARMUP))
+      ok = build_small(ctx, tm, h_off, std::vector<unsigned char>((size_t)tm.n_tiles, 0), 2,
+                       [&](int U, size_t bytes, int64_t* n) {
+        bool r = false;
+        dispatch_u(U, [&](auto u) {
+          constexpr int UU = decltype(u)::value;
+          r = slots_of(k_warmup_small<UU, 1, true>, bytes, small_min_wg(UU), n);
+        });
+        return r;
+      }, &ctx->sm_warm);
+    // chunk_ticket: counters (128-byte lines), then the first-level sums; the worker's chunks and the served one
+    if (ctx->tpc <= OB_TICKET_MAX) {   // (the served chunk has the same tiles)
+      const size_t spc = (size_t)(ctx->tpc + TICKET_SUB - 1) / TICKET_SUB, chunks = (size_t)ctx->W + 1;
+      const size_t lines = chunks * (1 + spc), words = 2 * CTR_STRIDE;
+      ok = ok && alloc_zero(ctx, &ctx->d_ticket, lines * words + 2 * chunks * spc);
+      ctx->d_ticket_srv = ctx->d_ticket + ((size_t)ctx->W * (1 + spc)) * words;
+      ctx->d_ticket_part = reinterpret_cast<double*>(ctx->d_ticket + lines * words);
+      ctx->d_ticket_part_srv = ctx->d_ticket_part + (size_t)ctx->W * spc;
+    }
   }
   ok = ok && upload(ctx, &ctx->d_first_layer_res, first_res) &&
        alloc_zero(ctx, &ctx->d_partials_res, (size_t)ctx->n_tiles_res) &&
@@ -931,11 +1129,13 @@ void ob_lamb_destroy(ob_lamb_ctx* ctx) {
                   ctx->d_partials, ctx->d_partials_srv, ctx->d_seg_sums, ctx->d_seg_max, ctx->d_sigma,
                   ctx->d_first_layer_res, ctx->d_partials_res, ctx->d_counter, ctx->d_flag, ctx->d_errflag,
                   ctx->d_partials_srv_res, ctx->d_counter_srv, ctx->d_flag_srv, ctx->d_pair_base,
-                  ctx->d_pair_lfirst, ctx->d_pair_c, ctx->d_pair_l, ctx->d_vterms};
+                  ctx->d_pair_lfirst, ctx->d_pair_c, ctx->d_pair_l, ctx->d_vterms, ctx->d_ticket};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   free_split(&ctx->sp_apply);
   free_split(&ctx->sp_warm);
+  for (SmallPlan* sp : {&ctx->sm_apply, &ctx->sm_warm})
+    if (sp->d_mem) (void)hipFree(sp->d_mem);
   delete ctx;
 }
 
@@ -976,6 +1176,22 @@ ob_status ob_lamb_warmup_step_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st, cons
                 tiles);
     });
   };
+  if (ctx->sm_warm.u) {   // one launch
+    const SmallPlan& sm = ctx->sm_warm;
+    WarmClip wc;
+    wc.coeff_c = st->coeff_c; wc.c_avg = st->c_avg; wc.c_min = ctx->c_min; wc.c_max = ctx->c_max;
+    wc.beta3 = ctx->beta3; wc.omb3 = ctx->omb3;
+    dispatch_u(sm.u, [&](auto u) {
+      dispatch2(lpg, xl.p != nullptr, [&](auto lg, auto lx) {
+        OB_LAUNCH_S(la, KID_WARMUP_SMALL,
+                    (k_warmup_small<decltype(u)::value, decltype(lg)::value ? 1 : 0, decltype(lx)::value>),
+                    sm.n_tiles + (sm.empty_layers ? 1 : 0), BLOCK, sm.lds_bytes, gs, st->m, st->v_fresh, st->x,
+                    small_tab(ctx, sm), wc, ctx->beta1, ctx->omb1, ctx->beta2, ctx->omb2, ctx->eta, ctx->wd, lr, lt,
+                    xl.p, xl.bf16);
+      });
+    });
+    return la.ok ? OB_OK : OB_ERR_HIP;
+  }
   LayerSplit& sp = ctx->sp_warm;
   if (!sp.on) {   // two passes over everything
     moments(nullptr, ctx->n_tiles);
@@ -1050,17 +1266,19 @@ ob_status ob_lamb_compress_local_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st, c
     if (misaligned(st->err_packed)) return OB_ERR_ALIGN;
     if (packed_m && st->m_packed == st->err_packed) return OB_ERR_ARG;
     const LayerTab lt = layer_tab(ctx, st, ctx->d_first_layer);
+    const ChunkTicket tk = chunk_ticket_of(ctx->d_ticket, ctx->d_ticket_part, ctx->W, ctx->tpc, scales_out, oc.scale, oc.chunk);
     dispatch2(st->mom_scale != nullptr, packed_m, [&](auto hk, auto pk) {
-      dispatch1(lpg, [&](auto lg) {
+      dispatch2(lpg, tk.count != nullptr, [&](auto lg, auto ti) {
         OB_LAUNCH(la, KID_COMPRESS_DEFERRED,
                   (k_momentum_z_sumsq<U_MAIN, decltype(hk)::value, decltype(pk)::value,
-                                      decltype(lg)::value ? 1 : 0, true>),
+                                      decltype(lg)::value ? 1 : 0, true, decltype(ti)::value>),
                   ctx->n_tiles, gs, st->m, pm, st->err_worker, ctx->d_partials, ctx->n_c, ctx->tpc,
-                  ctx->beta1, ctx->omb1, lt, pe, packed_out, oc);
+                  ctx->beta1, ctx->omb1, lt, pe, packed_out, oc, tk);
       });
     });
-    OB_LAUNCH_B(la, KID_CHUNK_SCALE, k_chunk_scale, ctx->W, FBLOCK, ctx->d_partials, ctx->tpc, ctx->n_c, scales_out,
-                oc.scale, oc.chunk);
+    if (!tk.count)
+      OB_LAUNCH_B(la, KID_CHUNK_SCALE, k_chunk_scale, ctx->W, FBLOCK, ctx->d_partials, ctx->tpc, ctx->n_c, scales_out,
+                  oc.scale, oc.chunk);
     return la.ok ? OB_OK : OB_ERR_HIP;
   }
   if (ctx->resident) {
@@ -1088,7 +1306,7 @@ ob_status ob_lamb_compress_local_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st, c
       OB_LAUNCH(la, KID_MOMENTUM_Z,
                 (k_momentum_z_sumsq<U_MAIN, decltype(hk)::value, decltype(pk)::value, decltype(lg)::value ? 1 : 0>),
                 ctx->n_tiles, gs, st->m, pm, st->err_worker, ctx->d_partials, ctx->n_c, ctx->tpc,
-                ctx->beta1, ctx->omb1, lt, pe, packed_out, oc);
+                ctx->beta1, ctx->omb1, lt, pe, packed_out, oc, ChunkTicket{});
     });
   });
   OB_LAUNCH_B(la, KID_CHUNK_SCALE, k_chunk_scale, ctx->W, FBLOCK, ctx->d_partials, ctx->tpc, ctx->n_c, scales_out,
@@ -1127,10 +1345,15 @@ ob_status ob_lamb_server_reduce(ob_lamb_ctx* ctx, const ob_lamb_state* st, const
     // deferred server error: one pass over the chunk plus its scale -- no barrier, no second pass
     if (misaligned(st->srv_err_packed)) return OB_ERR_ALIGN;
     if (st->srv_err_packed == packed_out) return OB_ERR_ARG;
-    OB_LAUNCH(la, KID_SERVER_AVG, (k_server_unpack_avg<U_SRV, true>), ctx->tpc_srv, packed_in, scales_in,
-              st->err_server, ctx->d_partials_srv, ctx->n_c, (int)ctx->W, ctx->invW, st->srv_err_packed,
-              st->srv_err_scale, packed_out);
-    OB_LAUNCH_B(la, KID_SERVER_SCALE, k_chunk_scale, 1, FBLOCK, ctx->d_partials_srv, ctx->tpc_srv, ctx->n_c, scale_out,
+    const ChunkTicket tk = chunk_ticket_of(ctx->d_ticket_srv, ctx->d_ticket_part_srv, 1, ctx->tpc_srv, scale_out,
+                                           st->srv_err_scale, 0);
+    dispatch1(tk.count != nullptr, [&](auto ti) {
+      OB_LAUNCH(la, KID_SERVER_AVG, (k_server_unpack_avg<U_SRV, true, decltype(ti)::value>), ctx->tpc_srv, packed_in,
+                scales_in, st->err_server, ctx->d_partials_srv, ctx->n_c, (int)ctx->W, ctx->invW, st->srv_err_packed,
+                st->srv_err_scale, packed_out, tk);
+    });
+    if (!tk.count)
+      OB_LAUNCH_B(la, KID_SERVER_SCALE, k_chunk_scale, 1, FBLOCK, ctx->d_partials_srv, ctx->tpc_srv, ctx->n_c, scale_out,
                 st->srv_err_scale, 0);
     return la.ok ? OB_OK : OB_ERR_HIP;
   }
@@ -1156,7 +1379,7 @@ ob_status ob_lamb_server_reduce(ob_lamb_ctx* ctx, const ob_lamb_state* st, const
   }
   OB_LAUNCH(la, KID_SERVER_AVG, (k_server_unpack_avg<U_SRV>), ctx->tpc_srv, packed_in, scales_in,
             st->err_server, ctx->d_partials_srv, ctx->n_c, (int)ctx->W, ctx->invW, (uint32_t*)nullptr,
-            (const float*)nullptr, (uint32_t*)nullptr);
+            (const float*)nullptr, (uint32_t*)nullptr, ChunkTicket{});
   OB_LAUNCH_B(la, KID_SERVER_SCALE, k_chunk_scale, 1, FBLOCK, ctx->d_partials_srv, ctx->tpc_srv, ctx->n_c, scale_out,
               (float*)nullptr, 0);
   OB_LAUNCH(la, KID_SERVER_PACK, (k_sign_pack_error<U_SRV>), ctx->tpc_srv, st->err_server, packed_out,
@@ -1210,6 +1433,13 @@ ob_status ob_lamb_ratios_apply_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st, con
   if (ob_status s = momentum_source(st, &packed_m, &pm)) return s;
   if (packed_m && st->m_packed == packed_all) return OB_ERR_ARG;
   Launch la(ctx, hip_stream);
+  if (ctx->sm_apply.u && packed_m) {   // one launch
+    VfHist vh{};
+    vh.write_v = 1;
+    launch_ratios_apply_small(la, ctx, st, ratio_args(ctx, st, packed_all, server_scales, pm), vh,
+                              apply_args(ctx, st, packed_all, server_scales, lr, xl));
+    return la.ok ? OB_OK : OB_ERR_HIP;
+  }
   LayerSplit& sp = ctx->sp_apply;
   if (!sp.on || !packed_m) {
     // no tile qualifies, or the momentum is a dense array (the barrier kernel would have to hold it
@@ -1289,15 +1519,6 @@ ob_status vf_history(const ob_lamb_vf_history* h, VfHist* out) {
   return OB_OK;
 }
 
-RatioArgs ratio_args(const ob_lamb_ctx* ctx, const ob_lamb_state* st, const uint32_t* packed_all,
-                     const float* server_scales, const PackedMom& pm) {
-  RatioArgs ra;
-  ra.packed = packed_all; ra.sscales = server_scales; ra.m = st->m; ra.pm = pm;
-  ra.v_fresh = st->v_fresh; ra.v_frozen = st->v_frozen;
-  ra.beta1 = ctx->beta1; ra.omb1 = ctx->omb1; ra.beta2 = ctx->beta2; ra.omb2 = ctx->omb2;
-  return ra;
-}
-
 VTerms vterms(const ob_lamb_ctx* ctx) {
   VTerms vt;
   vt.t = ctx->d_vterms; vt.pair_base = ctx->d_pair_base; vt.pair_lfirst = ctx->d_pair_lfirst;
@@ -1334,6 +1555,11 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
   VfHist vh;
   if (ob_status s = vf_history(h, &vh)) return s;
   Launch la(ctx, hip_stream);
+  if (ctx->sm_apply.u) {   // one launch
+    launch_ratios_apply_small(la, ctx, st, ratio_args(ctx, st, packed_all, server_scales, pm), vh,
+                              apply_args(ctx, st, packed_all, server_scales, lr, xl));
+    return la.ok ? OB_OK : OB_ERR_HIP;
+  }
   LayerSplit& sp = ctx->sp_apply;
   if (!sp.on && !sp.big_on) {
     // no tile works from the history: the whole array is kept up to date
@@ -1504,6 +1730,8 @@ ob_status ob_lamb_check_device_status(ob_lamb_ctx* ctx, void* hip_stream) {
     (void)hipMemset(sp->d_counter, 0, sizeof(unsigned long long) * (size_t)ctx->L * CTR_STRIDE);
     (void)hipMemset(sp->d_flag, 0, sizeof(unsigned long long) * (size_t)ctx->L);
   }
+  ctx->sm_apply.u = 0;
+  ctx->sm_warm.u = 0;
   (void)hipMemset(ctx->d_counter, 0, sizeof(unsigned long long) * (size_t)ctx->W * CTR_STRIDE);
   (void)hipMemset(ctx->d_flag, 0, sizeof(unsigned long long) * (size_t)ctx->W);
   (void)hipMemset(ctx->d_errflag, 0, sizeof(unsigned int));
@@ -1621,7 +1849,7 @@ ob_status ob_lamb_server_reduce_static(int32_t num_workers, int64_t chunk_len, c
   // reads has been written by the first, so the array's previous contents do not matter
   hipLaunchKernelGGL((k_server_unpack_avg<U_SRV>), dim3((unsigned)tiles), dim3(BLOCK), 0, stream, packed_in,
                      scales_in, err_server, partials, chunk_len, (int)num_workers, invW, (uint32_t*)nullptr,
-                     (const float*)nullptr, (uint32_t*)nullptr);
+                     (const float*)nullptr, (uint32_t*)nullptr, ChunkTicket{});
   hipLaunchKernelGGL(k_chunk_scale, dim3(1), dim3(FBLOCK), 0, stream, partials, tiles, chunk_len, scale_out,
                      (float*)nullptr, 0);
   hipLaunchKernelGGL((k_sign_pack_error<U_SRV>), dim3((unsigned)tiles), dim3(BLOCK), 0, stream, err_server,

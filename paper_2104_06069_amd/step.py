@@ -119,22 +119,26 @@ class DeviceStep:
         return a.to(self.device).contiguous()
 
     def _state(self, momentum):
-        """ob_lamb_state for one call.  momentum: 'read' (source of m_{t-1}) or 'commit'."""
-        b = dict(self.t)
-        if self.fold_gather:
-            wpc = self.n_c // 32
-            b["own_packed_in"] = self.packed_in[self.c * wpc:]
-            b["own_scale_in"] = self.scales_in[self.c:]
-        if self.deferred_error:
-            b["err_packed"], b["err_scales"] = self.packed_local, self.scales_local
-            b["srv_err_packed"], b["srv_err_scale"] = self.srv_words, self.srv_scale
+        """ob_lamb_state for one call.  momentum: 'read' (source of m_{t-1}) or 'commit'.  (A small model's
+        step is as short as the host makes it: the structure is filled in one go, with offsets into
+        buffers as numbers instead of slices; every address is looked up anew.)"""
+        t = self.t
+        m, m_packed, m_scales = t["m"], None, None
         if self.packed_momentum and momentum == "commit":
-            b["m"] = None                       # committed in place: packed_all is the momentum
-            b["m_packed"], b["m_scales"] = self.packed_all, self.server_scales
+            m, m_packed, m_scales = None, self.packed_all, self.server_scales   # committed in place: packed_all is the momentum
         elif self.packed_momentum and self.m_is_packed:
-            b["m"] = None
-            b["m_packed"], b["m_scales"] = self._pa[self._prev], self._ss[self._prev]
-        return ob.make_state(**b)
+            m, m_packed, m_scales = None, self._pa[self._prev], self._ss[self._prev]
+        own_packed = own_scale = ep = es = sp = ss = None
+        if self.fold_gather:
+            own_packed = self.packed_in.data_ptr() + self.c * (self.n_c // 8)
+            own_scale = self.scales_in.data_ptr() + 4 * self.c
+        if self.deferred_error:
+            ep, es = self.packed_local.data_ptr(), self.scales_local.data_ptr()
+            sp, ss = self.srv_words.data_ptr(), self.srv_scale.data_ptr()
+        a = ob._addr
+        return ob.ObLambState(a(t["x"]), a(m), a(t["v_fresh"]), a(t["v_frozen"]), a(t["err_worker"]),
+                              a(t["err_server"]), a(t["c_avg"]), a(t["r_prev"]), a(t["coeff_c"]), a(t["mom_scale"]),
+                              a(m_packed), a(m_scales), own_packed, own_scale, ep, es, sp, ss)
 
     def close(self):
         if self.ctx is not None:
@@ -179,7 +183,12 @@ class DeviceStep:
         """ob_lamb_vf_history of the step whose pairs are (_cur, _prev): the n_old pairs before them."""
         R = len(self._pa)
         idx = [(self._cur - 2 - i) % R for i in range(n_old)]
-        return ob.make_vf_history([self._pa[i] for i in idx], [self._ss[i] for i in idx], write_v)
+        h = ob.ObLambVfHistory(n_old, 1 if write_v else 0)
+        if n_old:
+            bits, scales = h.bits, h.scales
+            for k, i in enumerate(idx):     # (the ring's tensors outlive the call)
+                bits[k], scales[k] = self._pa[i].data_ptr(), self._ss[i].data_ptr()
+        return h
 
     def _vf_state(self):
         """ob_lamb_state of the dense-view calls: the previous momentum in its 1-bit form, whatever
@@ -301,13 +310,16 @@ class DeviceStep:
         if self.packed_momentum and self.m_is_packed:
             self._cur = (self._cur + 1) % len(self._pa)
 
+    # each of the step's calls takes the state and stream from its caller, so that step() forms them once
     def compress_local(self, grad):
+        self._compress_local(grad, self._state("read"), self.stream)
+
+    def _compress_local(self, grad, state, stream):
         if self._is_plain(grad):
-            ob.ob_lamb_compress_local(self.ctx, self._state("read"), grad, self.packed_local,
-                                      self.scales_local, self.stream)
+            ob.ob_lamb_compress_local(self.ctx, state, grad, self.packed_local, self.scales_local, stream)
         else:
-            ob.ob_lamb_compress_local_lp(self.ctx, self._state("read"), grad, self._ob_dtype(grad),
-                                         self.grad_scale, self.packed_local, self.scales_local, self.stream)
+            ob.ob_lamb_compress_local_lp(self.ctx, state, grad, self._ob_dtype(grad), self.grad_scale,
+                                         self.packed_local, self.scales_local, stream)
 
     def gather(self):
         """Own chunk c of the worker output -> slot c of the server's input (device copies; already
@@ -321,10 +333,12 @@ class DeviceStep:
 
     def server_reduce(self):
         """Writes the recompressed chunk straight into slot c of packed_all / server_scales."""
-        wpc = self.n_c // 32
-        ob.ob_lamb_server_reduce(self.ctx, self._state("read"), self.packed_in, self.scales_in,
-                                 self.packed_all[self.c * wpc:], self.server_scales[self.c:],
-                                 self.stream)
+        self._server_reduce(self._state("read"), self.stream)
+
+    def _server_reduce(self, state, stream):
+        ob.ob_lamb_server_reduce(self.ctx, state, self.packed_in, self.scales_in,
+                                 self.packed_all.data_ptr() + self.c * (self.n_c // 8),
+                                 self.server_scales.data_ptr() + 4 * self.c, stream)
 
     def layer_ratios(self):
         self._vf_fold()
@@ -342,36 +356,39 @@ class DeviceStep:
             self.m_is_packed = True
 
     def ratios_apply(self, lr):
+        self._ratios_apply(lr, self._state("read"), self.stream)
+
+    def _ratios_apply(self, lr, state, stream):
         if self.vf_period and self.m_is_packed:
             # the variance in deferred form: the array is brought up to date every vf_period-th step
             # (which buffers hold the history and how old the array is changes from step to step with
             # a period of graph_period steps: a captured graph must hold a multiple of that many)
             n_old = self._vf_n_old
             write_v = (n_old + 1 >= self.vf_period)
-            ob.ob_lamb_ratios_apply_hist_lp(self.ctx, self._state("read"), self.packed_all, self.server_scales, lr,
-                                            self._vf_hist(n_old, write_v), *self._x_lp_args(), self.stream)
+            ob.ob_lamb_ratios_apply_hist_lp(self.ctx, state, self.packed_all, self.server_scales, lr,
+                                            self._vf_hist(n_old, write_v), *self._x_lp_args(), stream)
             self.vf_ages[n_old + 1] = self.vf_ages.get(n_old + 1, 0) + 1
             if write_v:
                 self._vf_n_old, self._vf_pending = 0, None
             else:
                 self._vf_n_old, self._vf_pending = n_old + 1, (self._cur, n_old)
         elif self._is_plain():
-            ob.ob_lamb_ratios_apply(self.ctx, self._state("read"), self.packed_all, self.server_scales, lr,
-                                    self.stream)
+            ob.ob_lamb_ratios_apply(self.ctx, state, self.packed_all, self.server_scales, lr, stream)
         else:
-            ob.ob_lamb_ratios_apply_lp(self.ctx, self._state("read"), self.packed_all, self.server_scales,
-                                       lr, *self._x_lp_args(), self.stream)
+            ob.ob_lamb_ratios_apply_lp(self.ctx, state, self.packed_all, self.server_scales,
+                                       lr, *self._x_lp_args(), stream)
         if self.packed_momentum:
             self.m_is_packed = True
 
     def step(self, grad, lr):
         """One compression-stage step into the current wire buffers (call begin_step() first and
         fill packed_in / packed_all with what the other ranks sent)."""
-        self.compress_local(grad)
+        state, stream = self._state("read"), self.stream
+        self._compress_local(grad, state, stream)
         self.gather()
-        self.server_reduce()
+        self._server_reduce(state, stream)
         if self.fused_apply:
-            self.ratios_apply(lr)
+            self._ratios_apply(lr, state, stream)
         else:
             self.layer_ratios()
             self.decompress_apply(lr)

@@ -2554,7 +2554,7 @@ __global__ __launch_bounds__(BLOCK) void k_warmup_apply(
 
 // ---------------------------------------------------------------------------------------------
 // K8 a+b+c in one pass: eq. (1) with g, m, v and x read once.  A workgroup updates the moments of
-// its tile, writes them, keeps u and x in registers, publishes the tile's fp64 sums of x^2 and u^2
+// its tile, writes them, keeps u and x in registers and LDS, publishes the tile's fp64 sums of x^2 and u^2
 // and arrives at its layer's barrier; the last of the layer's listed tiles to arrive sums ALL of
 // the layer's segment sums in a fixed order, forms c, commits coeff_c and c_avg (Algorithm 1 line
 // 2) and publishes c; the others wait for it and then update x from registers.  Same split of the
@@ -2575,8 +2575,20 @@ struct WarmSync {
   float c_min, c_max, beta3, omb3;
 };
 
+// Bound by HBM and, between a layer's arrival and its coefficient, by the workgroups that wait with their tile
+// in hand: what fits on the device at once limits both the layers that the kernel takes and what streams
+// while others wait.  With u and x of all 8 spans in registers 4 workgroups fit on a CU (a layer of at most
+// 811 tiles); with x of OB_WU_LDS spans in LDS (24 KB a workgroup) and loads one span at a time there are 6
+// (1220 tiles), and a handful of registers spilled.  Measured, fp32 gradient: twelve 2800x2800 tensors, which
+// took two passes before (40 bytes per element instead of 28), 620 -> 526 us; ten 3100x3100 639 -> 537 us;
+// one layer of 7.8 M elements among small ones (11 M in all) 88.1 -> 81.5 us; twenty 2048x2048, taken by both
+// forms, 408 -> 397 us; the 336 M BERT list 1734 -> 1723 us.  5 workgroups of 6 spans in LDS: 1743 us there;
+// 6 workgroups with loads two spans at a time spill 16 registers: 1757 us.
 #ifndef OB_WU_MINW
-#define OB_WU_MINW 4
+#define OB_WU_MINW 6
+#endif
+#ifndef OB_WU_LDS
+#define OB_WU_LDS 6
 #endif
 template <int U, int G, int GT, bool LPX>
 __global__ __launch_bounds__(BLOCK, OB_WU_MINW) void k_warmup_resident(
@@ -2586,6 +2598,8 @@ __global__ __launch_bounds__(BLOCK, OB_WU_MINW) void k_warmup_resident(
   constexpr int TILE = SPAN * U;
   __shared__ double lds[BLOCK / WAVE];
   __shared__ unsigned long long bc;
+  constexpr int S = OB_WU_LDS;   // spans whose x waits in LDS (each thread reads back its own values)
+  __shared__ v4f xs[S > 0 ? S * BLOCK : 1];
   const int tpc = ws.lt.tpc;
   const TilePos p = tile_pos<TILE>(ws.lt.n_c, tpc, ws.lt.tile_list[blockIdx.x]);
   const int sp0 = p.c * ws.lt.tpc_span + (p.t - p.c * tpc) * U;  // the tile's first span (1024-element tiling)
@@ -2633,6 +2647,7 @@ __global__ __launch_bounds__(BLOCK, OB_WU_MINW) void k_warmup_resident(
           sx += (double)X[u0 + j][k] * (double)X[u0 + j][k];
           su += (double)uu * (double)uu;
         }
+        if (u0 + j < S) xs[(u0 + j) * BLOCK + threadIdx.x] = X[u0 + j];
       }
     }
   }
@@ -2692,9 +2707,10 @@ __global__ __launch_bounds__(BLOCK, OB_WU_MINW) void k_warmup_resident(
   for (int u = 0; u < U; ++u) {
     const int o = u * SPAN + o0;
     if (o < p.len) {
+      const v4f xo = (u < S) ? xs[u * BLOCK + threadIdx.x] : X[u];
       v4f xn;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) xn[k] = X[u][k] - a * UU[u][k];
+      for (int k = 0; k < 4; ++k) xn[k] = xo[k] - a * UU[u][k];
       st4(x + p.tile0 + o, xn);
       if (LPX) st4_lp(x_lp, p.tile0 + o, xn, x_lp_bf16);
     }

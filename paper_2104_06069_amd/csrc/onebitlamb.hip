@@ -71,13 +71,13 @@ constexpr int TILE_LB = SPAN * U_LB;
 #ifndef OB_SPLIT_MARGIN
 #define OB_SPLIT_MARGIN 8
 #endif
-constexpr int U_WU = OB_U_WU;  // ... in the single-pass warmup kernel (u and x stay in registers)
+constexpr int U_WU = OB_U_WU;  // ... in the single-pass warmup kernel (u and x stay in registers and LDS)
 constexpr int TILE_WU = SPAN * U_WU;
 #ifndef OB_BIG_MIN_TILES
 #define OB_BIG_MIN_TILES 64   // a layer outside the barrier kernel with at least that many whole 8192-element tiles
 #endif
 #ifndef OB_G_WU
-#define OB_G_WU 2
+#define OB_G_WU 1
 #endif
 constexpr int G_WU = OB_G_WU;        // the single-pass warmup kernel issues its loads G_WU accesses at a time
 

@@ -56,6 +56,14 @@ __device__ __forceinline__ void st4(float* p, v4f v) {
   __builtin_nontemporal_store(v, reinterpret_cast<v4f*>(p));
 }
 
+// 16 bytes per lane from p straight into LDS: lane i's to dst[i], dst the same for the whole
+// wavefront, all of whose lanes take part.  The data is there after lds_loads_done() of the same wavefront.
+__device__ __forceinline__ void lds_load16(const float* p, v4f* dst) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)p,
+                                   (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+}
+__device__ __forceinline__ void lds_loads_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // 16-bit storage of the mixed-precision variant (the paper trains in FP16, Section 6): a gradient
 // may arrive as IEEE binary16 or bfloat16 and a 16-bit copy of the parameters may be written; all
 // arithmetic stays binary32.  GT / LPX are template flags so that the fp32-only instantiations
@@ -1833,13 +1841,19 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_big_hist(RatioArgs
 // words of every plane (8 spans x 8 words): each lane fetches ONE word of each plane and the lanes
 // then pass each other the words they need; what a lane keeps of a plane is its 8 nibbles packed
 // into one register.
-template <bool HAS_K, bool LPX>
-__global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_apply_hist(
+//
+// S > 0: v_frozen of S spans goes straight into LDS, and m/(sqrt(v_frozen)+eta) later in its place, 24 KB for
+// 6 spans: 72 to 79 registers instead of 96, so that 6 workgroups fit on a CU instead of 5.  Which form a
+// list takes: lh_in_lds in the host code.
+constexpr int LH_WG_LDS = 6;   // workgroups per CU with S > 0
+template <bool HAS_K, bool LPX, int S>
+__global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratios_apply_hist(
     RatioArgs ra, VfHist h, VTerms vt, ApplyArgs aa, LayerSync ls, LayerTab lt) {
   constexpr int U = 8;
   constexpr int TILE = SPAN * U;
   __shared__ float lds[BLOCK / WAVE];
   __shared__ unsigned long long bc;
+  __shared__ v4f zs[S > 0 ? S * BLOCK : 1];
   const int bid = (int)blockIdx.x - ls.n_lead;   // position in tile_list
   if (bid < 0) {
     lead_finalize(ls, lds);
@@ -1867,14 +1881,16 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_apply_hist(
     Wq[q] = 0u;
     if (q <= a && have_word) Wq[q] = plane_bits(ra, h, q)[wi];
   }
-  v4f V[U], VZ[U];
+  v4f V[U], VZ[U];   // (VZ[0 .. S): unused)
+  const int wv_u = __builtin_amdgcn_readfirstlane(wv);
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int o = u * SPAN + o0;
     V[u] = 0.0f; VZ[u] = 0.0f;
-    if (o < p.len) {
+    if (o < p.len) {   // all lanes of a wavefront or none
       V[u] = ld4(ra.v_fresh + p.tile0 + o);
-      VZ[u] = ld4(ra.v_frozen + p.tile0 + o);
+      if (u < S) lds_load16(ra.v_frozen + p.tile0 + o, &zs[u * BLOCK + wv_u * WAVE]);
+      else VZ[u] = ld4(ra.v_frozen + p.tile0 + o);
     }
   }
   // flips between consecutive planes, formed on the words as loaded; plane 0 stays (line 21 needs it)
@@ -1904,13 +1920,15 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_apply_hist(
     }
   }
   float r = 0.0f;
+  if (S > 0) lds_loads_done();
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int o = u * SPAN + o0;
     if (o < p.len) {
+      const v4f vz = (u < S) ? zs[u * BLOCK + threadIdx.x] : VZ[u];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const float q = VZ[u][k] / V[u][k];
+        const float q = vz[k] / V[u][k];
         if (q > r) r = q;
       }
     }
@@ -1938,13 +1956,16 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_apply_hist(
   for (int u = 0; u < U; ++u) {
     const int o = u * SPAN + o0;
     if (o < p.len) {
+      v4f z = (u < S) ? zs[u * BLOCK + threadIdx.x] : VZ[u];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const float mt = ((Wq[0] >> (4 * u + k)) & 1u) ? sp : -sp;
-        float uu = mt / (sqrtf(VZ[u][k]) + aa.eta);
+        float uu = mt / (sqrtf(z[k]) + aa.eta);
         asm volatile("" : "+v"(uu));   // evaluated here, not sunk below the wait
-        VZ[u][k] = uu;
+        z[k] = uu;
       }
+      if (u < S) zs[u * BLOCK + threadIdx.x] = z;
+      else VZ[u] = z;
     }
   }
   const float c = layer_wait(ls, l0, &bc);
@@ -1953,9 +1974,10 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_apply_hist(
   for (int u = 0; u < U; ++u) {
     const int o = u * SPAN + o0;
     if (o < p.len) {
+      const v4f z = (u < S) ? zs[u * BLOCK + threadIdx.x] : VZ[u];
       v4f xn;
 #pragma unroll
-      for (int k = 0; k < 4; ++k) xn[k] = X[u][k] - al * VZ[u][k];
+      for (int k = 0; k < 4; ++k) xn[k] = X[u][k] - al * z[k];
       st4(aa.x + p.tile0 + o, xn);
       if (LPX) st4_lp(aa.x_lp, p.tile0 + o, xn, aa.x_lp_bf16);
     }

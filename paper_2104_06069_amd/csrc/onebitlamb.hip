@@ -55,6 +55,7 @@ constexpr int TILE_RES = SPAN * U_RES;
 #endif
 constexpr int U_LB = OB_U_LB;  // ... in the fused ratio+update kernel (v_frozen and signs stay in registers)
 constexpr int TILE_LB = SPAN * U_LB;
+constexpr int S_LH = 6;        // spans in LDS in the LDS form of k_ratios_apply_hist
 #ifndef OB_U_WU
 #define OB_U_WU 8
 #endif
@@ -168,6 +169,7 @@ struct LayerSplit {
   int* d_seg_end = nullptr;                //     layer's listed tiles cover
   float* d_listed_max = nullptr;           // [n_fused_tiles] partial results of the listed tiles
   double* d_listed_sums = nullptr;         // [2*n_fused_tiles]
+  bool in_lds = false;      // form of k_ratios_apply_hist
   int tile = 0;             // elements per listed tile
   int tpc = 0;              // such tiles per chunk
   int* d_rest_tiles = nullptr;
@@ -681,6 +683,20 @@ ListedTiles listed_tiles(const ob_lamb_ctx* ctx, const LayerSplit& sp) {
   return lt;
 }
 
+// Which form of k_ratios_apply_hist a list takes (whole steps, us, with registers only / with LDS):
+//  - its listed tiles fit on the device at once only at LH_WG_LDS workgroups per CU: one round instead of a full
+//    one and a nearly empty one (1340 tiles, 256 CUs: 96.3 / 91.2)
+//  - 24 M to 70 M parameters: 32 M in 512x512 tensors 189 / 186, 34 M in 2048x2048 195 / 185, 50 M in 1100x1100
+//    274 / 266, 64 M in 2048x2048 343 / 325, in 2800x2800 379 / 378.  Below, where a launch is a few rounds, the way
+//    through LDS costs more than a sixth workgroup gives (9 M in 2048x2048 64.2 / 65.2, 16 M in 2800x2800 112.7 /
+//    115.2); beyond, more tiles in flight make the arrays' reads slower (90 M in 1100x1100 471 / 477, 95 M in
+//    2800x2800 558 / 579, 110 M in 512x512 595 / 608).
+constexpr int64_t LH_LDS_MIN_N = 24000000, LH_LDS_MAX_N = 70000000;
+bool lh_in_lds(int64_t n, int64_t n_tiles, int cus) {
+  return (n_tiles > (int64_t)OB_LB_MINW * cus && n_tiles <= (int64_t)LH_WG_LDS * cus) ||
+         (n >= LH_LDS_MIN_N && n <= LH_LDS_MAX_N);
+}
+
 // Largest number of one layer's tiles that a barrier kernel with `per_cu` resident workgroups per
 // CU may hold: 80 % of the device's slots, or the configuration's fused_max_tiles if that is lower
 // (cap; 0 = none).
@@ -1026,7 +1042,10 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
          hip_ok(ctx, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device),
                 "hipDeviceGetAttribute");
     int per_cu_h = 0;   // the same tiles go through the kernel with the variance in deferred form
-    ok = ok && hip_ok(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_h, k_ratios_apply_hist<true, false>, BLOCK, 0),
+    ok = ok && hip_ok(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_h, k_ratios_apply_hist<true, false, 0>, BLOCK, 0),
+                      "hipOccupancyMaxActiveBlocksPerMultiprocessor");
+    per_cu_a = std::min(per_cu_a, per_cu_h);
+    ok = ok && hip_ok(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_h, k_ratios_apply_hist<true, false, S_LH>, BLOCK, 0),
                       "hipOccupancyMaxActiveBlocksPerMultiprocessor");
     per_cu_a = std::min(per_cu_a, per_cu_h);
     const int64_t max_a = (cfg->flags & OB_CFG_NO_FUSED_APPLY)
@@ -1036,6 +1055,7 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
     std::vector<unsigned char> lagging, unused;
     ok = ok && build_split(ctx, tl, TILE_LB, tm, h_off, max_a, &ctx->sp_apply, &lagging) &&
          build_split(ctx, tw, TILE_WU, tm, h_off, max_w, &ctx->sp_warm, &unused);
+    ctx->sp_apply.in_lds = lh_in_lds(ctx->N, ctx->sp_apply.n_fused_tiles, cus);
     // one launch instead of three or four where the whole list fits on the device at once (unless the
     // configuration lowers what the barrier kernels may take)
     auto slots_of = [&](auto kernel, size_t bytes, int min_per_cu, int64_t* out) {
@@ -1605,8 +1625,11 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
   ls.one_m_thr = ctx->one_m_thr; ls.one_p_thr = ctx->one_p_thr; ls.r_min = ctx->r_min; ls.r_max = ctx->r_max;
   ls.n_lead = (sp.n_layers < ctx->L) ? (int)ctx->L : 0;
   dispatch2(st->mom_scale != nullptr, xl.p != nullptr, [&](auto k_, auto lx) {
-    OB_LAUNCH(la, KID_RATIOS_APPLY_HIST, (k_ratios_apply_hist<decltype(k_)::value, decltype(lx)::value>),
-              sp.n_fused_tiles + ls.n_lead, ra, vh, vterms(ctx), aa, ls, lt);
+    dispatch1(sp.in_lds, [&](auto in_lds) {
+      OB_LAUNCH(la, KID_RATIOS_APPLY_HIST,
+                (k_ratios_apply_hist<decltype(k_)::value, decltype(lx)::value, decltype(in_lds)::value ? S_LH : 0>),
+                sp.n_fused_tiles + ls.n_lead, ra, vh, vterms(ctx), aa, ls, lt);
+    });
   });
   launch_apply(la, ctx, st, packed_all, server_scales, lr, sp.d_rest_tiles, sp.n_rest_tiles, xl);
   return la.ok ? OB_OK : OB_ERR_HIP;

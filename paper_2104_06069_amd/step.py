@@ -383,13 +383,24 @@ class DeviceStep:
     def step(self, grad, lr):
         """One compression-stage step into the current wire buffers (call begin_step() first and
         fill packed_in / packed_all with what the other ranks sent)."""
-        state, stream = self._state("read"), self.stream
-        self._compress_local(grad, state, stream)
-        self.gather()
-        self._server_reduce(state, stream)
-        if self.fused_apply:
-            self._ratios_apply(lr, state, stream)
-        else:
+        if all(getattr(getattr(self, k), "__func__", None) is f for k, f in _STEP_CALLS):
+            state, stream = self._state("read"), self.stream
+            self._compress_local(grad, state, stream)
+            self.gather()
+            self._server_reduce(state, stream)
+            if self.fused_apply:
+                self._ratios_apply(lr, state, stream)
+        else:   # calls of a subclass's or of an instance's own: they may change what the next one is to see
+            self.compress_local(grad)
+            self.gather()
+            self.server_reduce()
+            if self.fused_apply:
+                self.ratios_apply(lr)
+        if not self.fused_apply:
             self.layer_ratios()
             self.decompress_apply(lr)
         self._count_step()
+
+
+# step() forms the state once for all of these as they stand here
+_STEP_CALLS = tuple((k, getattr(DeviceStep, k)) for k in ("compress_local", "gather", "server_reduce", "ratios_apply"))

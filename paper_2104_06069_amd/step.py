@@ -22,6 +22,7 @@ import torch
 
 from . import binding as ob
 
+_STATE_FIELDS = tuple(f for f, _ in ob.ObLambState._fields_)
 _STATE_KEYS = ("x", "m", "v_fresh", "v_frozen", "err_worker", "err_server", "c_avg", "r_prev")
 
 
@@ -122,23 +123,20 @@ class DeviceStep:
         """ob_lamb_state for one call.  momentum: 'read' (source of m_{t-1}) or 'commit'.  (A small model's
         step is as short as the host makes it: the structure is filled in one go, with offsets into
         buffers as numbers instead of slices; every address is looked up anew.)"""
-        t = self.t
-        m, m_packed, m_scales = t["m"], None, None
+        b = dict(self.t)   # (a program may have given the dense momentum back, or put pointers of its own in)
         if self.packed_momentum and momentum == "commit":
-            m, m_packed, m_scales = None, self.packed_all, self.server_scales   # committed in place: packed_all is the momentum
+            b["m"] = None                       # committed in place: packed_all is the momentum
+            b["m_packed"], b["m_scales"] = self.packed_all, self.server_scales
         elif self.packed_momentum and self.m_is_packed:
-            m, m_packed, m_scales = None, self._pa[self._prev], self._ss[self._prev]
-        own_packed = own_scale = ep = es = sp = ss = None
+            b["m"] = None
+            b["m_packed"], b["m_scales"] = self._pa[self._prev], self._ss[self._prev]
         if self.fold_gather:
-            own_packed = self.packed_in.data_ptr() + self.c * (self.n_c // 8)
-            own_scale = self.scales_in.data_ptr() + 4 * self.c
+            b["own_packed_in"] = self.packed_in.data_ptr() + self.c * (self.n_c // 8)
+            b["own_scale_in"] = self.scales_in.data_ptr() + 4 * self.c
         if self.deferred_error:
-            ep, es = self.packed_local.data_ptr(), self.scales_local.data_ptr()
-            sp, ss = self.srv_words.data_ptr(), self.srv_scale.data_ptr()
-        a = ob._addr
-        return ob.ObLambState(a(t["x"]), a(m), a(t["v_fresh"]), a(t["v_frozen"]), a(t["err_worker"]),
-                              a(t["err_server"]), a(t["c_avg"]), a(t["r_prev"]), a(t["coeff_c"]), a(t["mom_scale"]),
-                              a(m_packed), a(m_scales), own_packed, own_scale, ep, es, sp, ss)
+            b["err_packed"], b["err_scales"] = self.packed_local, self.scales_local
+            b["srv_err_packed"], b["srv_err_scale"] = self.srv_words, self.srv_scale
+        return ob.ObLambState(*map(ob._addr, map(b.get, _STATE_FIELDS)))
 
     def close(self):
         if self.ctx is not None:

@@ -68,3 +68,23 @@ def test_step_goes_through_calls_that_a_program_replaced(name, where, monkeypatc
     first = {"compress_local": 0, "gather": 1, "server_reduce": 1, "ratios_apply": 2, "layer_ratios": 2, "decompress_apply": 3}[name]
     for i, (_, s) in enumerate(calls):
         assert s.x == (ds.t["x"] if i >= first else before).data_ptr(), i
+
+
+def test_state_entries_that_a_program_took_out_or_put_in(monkeypatch):
+    """With the momentum in its 1-bit form the dense array may be given back (its entry deleted or None), and
+    pointers that the object does not fill itself may be put into the dict."""
+    ds, calls = _bare(type("Plain", (DeviceStep,), {}), True, monkeypatch)
+    del ds.t["m"], ds.t["mom_scale"]
+    ds.fold_gather = ds.deferred_error = False
+    ds.gather = lambda: None
+    mine = torch.zeros(64)
+    ds.t.update(own_packed_in=mine[:32], own_scale_in=mine[32:], err_packed=mine[4:])
+    ds.step(torch.zeros(ds.n_pad), 1e-3)
+    assert len(calls) == 3
+    for _, s in calls:
+        assert s.m is None and s.mom_scale is None and s.m_packed == ds._pa[1].data_ptr()
+        assert s.own_packed_in == mine.data_ptr() and s.own_scale_in == mine.data_ptr() + 128
+        assert s.err_packed == mine.data_ptr() + 16 and s.err_scales is None and s.srv_err_packed is None
+    ds.t["x"] = None
+    assert ds._state("commit").x is None and ds._state("commit").m_packed == ds._pa[0].data_ptr()
+    assert [f for f, _ in ob.ObLambState._fields_] == list(step_module._STATE_FIELDS)

@@ -119,14 +119,6 @@ const char* const kKernelNames[KID_COUNT] = {
     "decompress_apply", "ratios_apply_resident", "ratios_apply_hist", "ratios_apply_small", "warmup_small", "variance_dense", "variance_terms", "ratios_big_hist", "momentum_dense", "error_dense", "momentum_scale", "warmup_moments",   "warmup_coeff",    "warmup_apply",
     "warmup_resident",  "fill",            "copy"};
 
-// Chunks of at most this many tiles get their scale from the kernel that forms the partials (chunk_ticket)
-// instead of k_chunk_scale.  A workgroup's arrival costs it two round trips to memory: at 256 tiles the
-// kernel takes 2.7 us more and the launch that it saves took 2.5 us and a gap (and 2 us of the host); at 8
-// tiles it is 1.4 us more.  Beyond that the workgroups of many rounds all pay.
-#ifndef OB_TICKET_MAX
-#define OB_TICKET_MAX 256
-#endif
-
 // Single-launch form of a list whose tiles all fit on the device at once (k_ratios_apply_small,
 // k_warmup_small).
 struct SmallPlan {
@@ -658,6 +650,23 @@ void dispatch_u(int u, F f) {
   }
 }
 
+// Which chunks get their scale from the kernel that forms the partials (chunk_ticket) instead of a launch of
+// k_chunk_scale.  That launch costs 2.5 us and a gap; the ticket costs every workgroup a wait for its stores and
+// a returning atomic before it retires, and the last ones of up to 64 tiles a second one where a chunk has more
+// than 64 (TICKET_SUB).  n_tiles: the worker's 1024-element tiles; a round: 8 workgroups per CU.  A step, us, with
+// a launch / with the ticket in the worker's call (256 CUs):
+//   chunks of at most 64 tiles: 1024 tiles 30.2 / 28.6, 4096 50.0 / 49.0, 8192 76.4 / 74.9, 16384 119.0 / 120.6
+//   more:  640 tiles 27.2 / 26.0, 1536 30.8 / 30.0, 2560 44.0 / 44.3, 3072 45.8 / 45.3, 6144 58.8 / 58.6,
+//          8192 67.5 / 68.0, 14336 98.9 / 101.6, 24576 161.6 / 165.7, 40960 248.1 / 255.0
+// and in the server's, whose grid is the one chunk:
+//   at most 64 tiles: of 1024 30.2 / 28.8, of 4096 50.0 / 49.1, of 16384 119.0 / 117.3
+//   more:  of 640 27.2 / 25.9, of 2048 41.2 / 41.5, of 6144 58.8 / 59.0, of 8192 67.5 / 68.4, of 16384 110.2 / 111.6
+bool two_level_ticket(int tpc, int n_tiles, int cus) { return tpc <= 256 && n_tiles <= 3 * 8 * cus; }
+bool worker_ticket(int tpc, int n_tiles, int cus) {
+  return (tpc <= TICKET_SUB && n_tiles <= 5 * 8 * cus) || two_level_ticket(tpc, n_tiles, cus);
+}
+bool server_ticket(int tpc, int n_tiles, int cus) { return tpc <= TICKET_SUB || two_level_ticket(tpc, n_tiles, cus); }
+
 ChunkTicket chunk_ticket_of(unsigned int* count, double* part, int n_chunks, int tpc, float* scales, float* own_scale,
                             int own_chunk) {
   ChunkTicket tk;
@@ -1085,15 +1094,14 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
         });
         return r;
       }, &ctx->sm_warm);
-    // chunk_ticket: counters (128-byte lines), then the first-level sums; the worker's chunks and the served one
-    if (ctx->tpc <= OB_TICKET_MAX) {   // (the served chunk has the same tiles)
-      const size_t spc = (size_t)(ctx->tpc + TICKET_SUB - 1) / TICKET_SUB, chunks = (size_t)ctx->W + 1;
-      const size_t lines = chunks * (1 + spc), words = 2 * CTR_STRIDE;
-      ok = ok && alloc_zero(ctx, &ctx->d_ticket, lines * words + 2 * chunks * spc);
-      ctx->d_ticket_srv = ctx->d_ticket + ((size_t)ctx->W * (1 + spc)) * words;
-      ctx->d_ticket_part = reinterpret_cast<double*>(ctx->d_ticket + lines * words);
-      ctx->d_ticket_part_srv = ctx->d_ticket_part + (size_t)ctx->W * spc;
-    }
+    // chunk_ticket: counters (128-byte lines) and the first-level sums
+    static_assert(TILE_SRV == TILE_MAIN, "the served chunk has the tiles of the worker's chunks");
+    const size_t spc = (size_t)((ctx->tpc + TICKET_SUB - 1) / TICKET_SUB), line = 2 * CTR_STRIDE;
+    if (worker_ticket(ctx->tpc, ctx->n_tiles, cus))
+      ok = ok && alloc_zero(ctx, &ctx->d_ticket, (size_t)ctx->W * (1 + spc) * line) &&
+           alloc_zero(ctx, &ctx->d_ticket_part, (size_t)ctx->W * spc);
+    if (server_ticket(ctx->tpc, ctx->n_tiles, cus))
+      ok = ok && alloc_zero(ctx, &ctx->d_ticket_srv, (1 + spc) * line) && alloc_zero(ctx, &ctx->d_ticket_part_srv, spc);
   }
   ok = ok && upload(ctx, &ctx->d_first_layer_res, first_res) &&
        alloc_zero(ctx, &ctx->d_partials_res, (size_t)ctx->n_tiles_res) &&
@@ -1149,7 +1157,8 @@ void ob_lamb_destroy(ob_lamb_ctx* ctx) {
                   ctx->d_partials, ctx->d_partials_srv, ctx->d_seg_sums, ctx->d_seg_max, ctx->d_sigma,
                   ctx->d_first_layer_res, ctx->d_partials_res, ctx->d_counter, ctx->d_flag, ctx->d_errflag,
                   ctx->d_partials_srv_res, ctx->d_counter_srv, ctx->d_flag_srv, ctx->d_pair_base,
-                  ctx->d_pair_lfirst, ctx->d_pair_c, ctx->d_pair_l, ctx->d_vterms, ctx->d_ticket};
+                  ctx->d_pair_lfirst, ctx->d_pair_c, ctx->d_pair_l, ctx->d_vterms, ctx->d_ticket, ctx->d_ticket_srv,
+                  ctx->d_ticket_part, ctx->d_ticket_part_srv};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   free_split(&ctx->sp_apply);

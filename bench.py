@@ -454,12 +454,13 @@ def main():
     KB["server_resident"] = (W / 8.0 + 8.125, "n_c")   # R W*bits, err (4) + W err (4), bits (1/8)
     if ages_prof:   # mean over the profiled launches, which differ in how many momentum steps they applied
         KB["ratios_apply_hist"] = (hist_kernel_bytes_per_param(ages_prof, ds.vf_period), "fused")
+        KB["ratios_apply_hist_lds"] = KB["ratios_apply_hist"]
         KB["ratios_big_hist"] = (hist_big_ratio_bytes_per_param(ages_prof, ds.vf_period), "big")
     g_less = 2.0 if args.grad_dtype != "f32" else 0.0     # 16-bit gradient read
     x_more = 2.0 if args.x_lp != "none" else 0.0          # 16-bit parameter copy written
     for k in ("compress_resident", "compress_deferred", "momentum_z_sumsq", "warmup_moments", "warmup_resident"):
         KB[k] = (KB[k][0] - g_less, KB[k][1])
-    for k in ("decompress_apply", "ratios_apply_resident", "ratios_apply_hist", "warmup_apply", "warmup_resident"):
+    for k in ("decompress_apply", "ratios_apply_resident", "ratios_apply_hist", "ratios_apply_hist_lds", "warmup_apply", "warmup_resident"):
         if k in KB:
             KB[k] = (KB[k][0] + x_more, KB[k][1])
     fused_params, wfused = wl.fused_params, wl.wfused

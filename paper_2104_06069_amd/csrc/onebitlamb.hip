@@ -97,6 +97,7 @@ enum KernelId {
   KID_APPLY,
   KID_RATIOS_APPLY_RESIDENT,
   KID_RATIOS_APPLY_HIST,
+  KID_RATIOS_APPLY_HIST_LDS,
   KID_RATIOS_APPLY_SMALL,
   KID_WARMUP_SMALL,
   KID_VARIANCE_DENSE,
@@ -116,7 +117,7 @@ enum KernelId {
 const char* const kKernelNames[KID_COUNT] = {
     "momentum_z_sumsq", "compress_resident", "chunk_scale",     "sign_pack_error", "compress_deferred", "server_unpack_avg",
     "server_scale",     "server_sign_pack", "server_resident", "ratios_pass",     "ratios_finalize",
-    "decompress_apply", "ratios_apply_resident", "ratios_apply_hist", "ratios_apply_small", "warmup_small", "variance_dense", "variance_terms", "ratios_big_hist", "momentum_dense", "error_dense", "momentum_scale", "warmup_moments",   "warmup_coeff",    "warmup_apply",
+    "decompress_apply", "ratios_apply_resident", "ratios_apply_hist", "ratios_apply_hist_lds", "ratios_apply_small", "warmup_small", "variance_dense", "variance_terms", "ratios_big_hist", "momentum_dense", "error_dense", "momentum_scale", "warmup_moments",   "warmup_coeff",    "warmup_apply",
     "warmup_resident",  "fill",            "copy"};
 
 // Single-launch form of a list whose tiles all fit on the device at once (k_ratios_apply_small,
@@ -692,18 +693,22 @@ ListedTiles listed_tiles(const ob_lamb_ctx* ctx, const LayerSplit& sp) {
   return lt;
 }
 
-// Which form of k_ratios_apply_hist a list takes (whole steps, us, with registers only / with LDS):
-//  - its listed tiles fit on the device at once only at LH_WG_LDS workgroups per CU: one round instead of a full
-//    one and a nearly empty one (1340 tiles, 256 CUs: 96.3 / 91.2)
-//  - 24 M to 70 M parameters: 32 M in 512x512 tensors 189 / 186, 34 M in 2048x2048 195 / 185, 50 M in 1100x1100
-//    274 / 266, 64 M in 2048x2048 343 / 325, in 2800x2800 379 / 378.  Below, where a launch is a few rounds, the way
-//    through LDS costs more than a sixth workgroup gives (9 M in 2048x2048 64.2 / 65.2, 16 M in 2800x2800 112.7 /
-//    115.2); beyond, more tiles in flight make the arrays' reads slower (90 M in 1100x1100 471 / 477, 95 M in
-//    2800x2800 558 / 579, 110 M in 512x512 595 / 608).
-constexpr int64_t LH_LDS_MIN_N = 24000000, LH_LDS_MAX_N = 70000000;
-bool lh_in_lds(int64_t n, int64_t n_tiles, int cus) {
-  return (n_tiles > (int64_t)OB_LB_MINW * cus && n_tiles <= (int64_t)LH_WG_LDS * cus) ||
-         (n >= LH_LDS_MIN_N && n <= LH_LDS_MAX_N);
+// Which form of k_ratios_apply_hist a list takes: with registers only OB_LB_MINW (5) workgroups fit on a CU, with
+// LDS LH_WG_LDS (6), and each is the better one by how many rounds of the device's workgroups its listed tiles
+// make.  Whole steps on 256 CUs, us, registers / LDS, lists of equal square tensors and of BERT shape (whose word
+// embedding is too large to be listed: what counts is the kernel's tiles, not the parameters):
+//   one round only with LDS (1281 to 1536 tiles): 1345 94.0 / 89.7, 1440 82.8 / 77.9, 1536 86.6 / 81.0
+//   below and between, where the way through LDS costs more than a sixth workgroup gives: 864 54.8 / 56.8,
+//     1027 68.2 / 69.5, 1608 184.9 / 187.3, 1913 109.2 / 113.9, 2056 110.3 / 111.6, 2304 113.4 / 115.8, 2516 244.4 / 244.2
+//   two full rounds with registers (2560 tiles) to six with LDS (9216): 2560 128.3 / 122.6, 2789 142.3 / 138.3,
+//     3072 148.3 / 140.5, 4896 221.2 / 209.0, 7776 330.6 / 318.5, 8928 381.7 / 362.8, 9216 393.2 / 386.2; the least
+//     gain in 2800x2800 tensors (957 tiles each): 2869 156.7 / 156.5, 3827 199.2 / 200.2, 8605 416.8 / 418.2
+//   beyond, where more tiles in flight make the arrays' reads slower: 9561 460.6 / 468.3, 9760 432.0 / 443.0,
+//     10489 579.4 / 586.2, 13386 636.3 / 670.7
+constexpr int LH_LDS_MIN_ROUNDS = 2, LH_LDS_MAX_ROUNDS = 6;
+bool lh_in_lds(int64_t n_tiles, int cus) {
+  const int64_t r = (int64_t)OB_LB_MINW * cus, l = (int64_t)LH_WG_LDS * cus;
+  return (n_tiles > r && n_tiles <= l) || (n_tiles >= LH_LDS_MIN_ROUNDS * r && n_tiles <= LH_LDS_MAX_ROUNDS * l);
 }
 
 // Largest number of one layer's tiles that a barrier kernel with `per_cu` resident workgroups per
@@ -1064,7 +1069,7 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
     std::vector<unsigned char> lagging, unused;
     ok = ok && build_split(ctx, tl, TILE_LB, tm, h_off, max_a, &ctx->sp_apply, &lagging) &&
          build_split(ctx, tw, TILE_WU, tm, h_off, max_w, &ctx->sp_warm, &unused);
-    ctx->sp_apply.in_lds = lh_in_lds(ctx->N, ctx->sp_apply.n_fused_tiles, cus);
+    ctx->sp_apply.in_lds = lh_in_lds(ctx->sp_apply.n_fused_tiles, cus);
     // one launch instead of three or four where the whole list fits on the device at once (unless the
     // configuration lowers what the barrier kernels may take)
     auto slots_of = [&](auto kernel, size_t bytes, int min_per_cu, int64_t* out) {
@@ -1635,7 +1640,7 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
   ls.n_lead = (sp.n_layers < ctx->L) ? (int)ctx->L : 0;
   dispatch2(st->mom_scale != nullptr, xl.p != nullptr, [&](auto k_, auto lx) {
     dispatch1(sp.in_lds, [&](auto in_lds) {
-      OB_LAUNCH(la, KID_RATIOS_APPLY_HIST,
+      OB_LAUNCH(la, sp.in_lds ? KID_RATIOS_APPLY_HIST_LDS : KID_RATIOS_APPLY_HIST,
                 (k_ratios_apply_hist<decltype(k_)::value, decltype(lx)::value, decltype(in_lds)::value ? S_LH : 0>),
                 sp.n_fused_tiles + ls.n_lead, ra, vh, vterms(ctx), aa, ls, lt);
     });

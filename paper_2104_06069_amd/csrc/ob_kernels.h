@@ -1991,15 +1991,15 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
 // split above cost more than the work: every launch is a chain of dependent look-ups, loads and
 // reductions of a few microseconds whatever it moves.  Here every tile, whatever layers it meets, is one
 // workgroup that runs the ratio pass, takes part in the barriers of its layers and then the update, with
-// x, v_frozen and the signs in registers.  U is the smallest of 1, 2, 4 for which the tiles fit: the time
-// of a workgroup that is alone on its CU is its own chain of divisions.
+// x, v_frozen and the signs in registers.  U is 1, 2 or 4: small tiles keep a workgroup's own chain of
+// look-ups and divisions short, large ones the queue at a layer's counter (small_cost in the host code).
 //
 // A layer wholly inside a tile needs no barrier; only the first and the last segment of a tile can belong
 // to a layer that goes on elsewhere.  Same self-numbering counters, bounded waits and co-residency rule
 // (80 % of the workgroup slots) as the other barriers.  The spans that k_ratios_apply_hist would handle
 // from the variance's history ("lagging") do so here too, so that what the v_fresh array holds between two
 // calls does not depend on the kernel; their two values per step are formed by each thread.
-// Measured: four 512x512 tensors 11.5 us (k_ratios_apply_resident 14.5); 37 tensors of 2 to 64000 elements
+// Measured: four 512x512 tensors 9.0 us (k_ratios_apply_resident 12.6); 37 tensors of 2 to 64000 elements
 // 12.9 us (26 us in three launches, and the gaps between them).
 // ---------------------------------------------------------------------------------------------
 struct SmallTile {

@@ -562,9 +562,8 @@ bool build_split(ob_lamb_ctx* ctx, const Tiling& tl, int tile_lb, const Tiling& 
 
 // The tiles and segments of one SmallPlan (no HIP call).  lagging: per 1024-element span (tm's tiling).
 void small_tiles(const Tiling& t, int U, const Tiling& tm, const std::vector<int64_t>& h_off, int64_t n_c, int64_t L,
-                 const std::vector<unsigned char>& lagging, std::vector<SmallTile>* tiles, int* max_seg) {
+                 const std::vector<unsigned char>& lagging, std::vector<SmallTile>* tiles) {
   tiles->resize((size_t)t.n_tiles);
-  *max_seg = 1;
   for (int64_t i = 0; i < t.n_tiles; ++i) {
     const int64_t c = i / t.tpc, b = i % t.tpc;
     const int64_t tile0 = c * n_c + b * (int64_t)SPAN * U, tile1 = std::min(tile0 + (int64_t)SPAN * U, (c + 1) * n_c);
@@ -580,31 +579,88 @@ void small_tiles(const Tiling& t, int U, const Tiling& tm, const std::vector<int
     st.n_first = total(st.l0);
     st.n_last = total(st.l_last);
     st.pad = 0;
-    *max_seg = std::max(*max_seg, st.nseg);
   }
 }
 
-// Chooses and uploads a SmallPlan: the smallest U whose tiles take at most 80 % of the device's workgroup
-// slots (slots(U, dynamic LDS bytes)).  vals: floats of LDS per element of a tile that meets several layers.
+// What the choice of a tile size rests on, without its tables.
+struct SmallShape {
+  int64_t tpc = 0, n_tiles = 0;
+  int max_seg = 1;        // most layers that meet one tile
+  int max_arrivals = 0;   // most tiles that one layer meets
+  int mixed_spans = 0;    // 1024-element spans of the longest tile that is not wholly inside one layer
+};
+SmallShape small_shape(int U, const std::vector<int64_t>& h_off, int64_t n_c, int64_t W, int64_t L) {
+  const int64_t tile = (int64_t)SPAN * U;
+  SmallShape sh;
+  sh.tpc = (n_c + tile - 1) / tile;
+  sh.n_tiles = sh.tpc * W;
+  int64_t cur = -1;
+  int seg = 0;
+  for (int64_t l = 0; l < L; ++l) {
+    const int64_t a = h_off[(size_t)l], e = h_off[(size_t)l + 1];
+    if (e == a) continue;
+    const int64_t c = (e - 1) / n_c, b = (e - 1) % n_c / tile;
+    const int64_t t0 = a / n_c * sh.tpc + a % n_c / tile, t1 = c * sh.tpc + b;
+    seg = (t0 == cur) ? seg + 1 : 1;
+    sh.max_seg = std::max(sh.max_seg, seg);
+    if (t1 > t0) seg = 1;
+    cur = t1;
+    sh.max_arrivals = (int)std::max<int64_t>(sh.max_arrivals, t1 - t0 + 1);
+    const int64_t in_chunk = b * tile, len = std::min(tile, n_c - in_chunk);
+    if (e < c * n_c + in_chunk + len) sh.mixed_spans = (int)std::max<int64_t>(sh.mixed_spans, (len + SPAN - 1) / SPAN);
+  }
+  return sh;
+}
+// What sets the tile sizes apart, in ns: a workgroup's own chain of loads and divisions, the arrivals of a layer at
+// its counter, which are served one after the other, and the look-ups with which the threads of a tile that meets
+// several layers go through its spans.  Measured at U = 1 / 2 / 4 (kernel, us; LAMB step, then ratios_apply):
+//   eight tensors of 65536 7.6 / 7.7 / 8.9, 7.5 / 7.9 / 9.8; four of 262144 11.5 / 9.3 / 9.4, 10.3 / 9.0 / 10.0
+//   one of 0.9 M 18.9 / 14.1 / 15.8, 18.2 / 13.4 / 19.0; of 1.6 M 27.5 / 18.2 / 14.7, 27.0 / 18.1 / 14.7 (in
+//   8192-element tiles, k_warmup_resident and k_ratios_apply_resident: 16.5, 14.8)
+//   four of 125000 9.4 / 11.2 / 15.2, 10.6 / 13.8 / 16.9; 0.8 M and ten of 80000 18.4 / 14.1 / 20.1, 20.2 / 16.2 / 23.4
+int64_t small_cost(int U, const SmallShape& sh) {
+  return (U == 1 ? 0 : U == 2 ? 500 : 2000) + 13 * sh.max_arrivals + 2500 * std::max(sh.mixed_spans - 1, 0);
+}
+// Tilings of the tile sizes that a SmallPlan may take, formed when first asked for.
+struct SmallTilings {
+  const Tiling& tm;       // U = 1
+  Tiling t2, t4;
+  const Tiling* get(int U, int64_t n_c, int64_t W, int64_t L, const std::vector<int64_t>& h_off) {
+    if (U == 1) return &tm;
+    Tiling* t = (U == 2) ? &t2 : &t4;
+    if (t->n_tiles == 0 && !build_tiling((int64_t)SPAN * U, n_c, W, L, h_off, t)) return nullptr;
+    return t;
+  }
+};
+
+// Chooses and uploads a SmallPlan: of the U whose tiles take at most 80 % of the device's workgroup slots
+// (slots(U, dynamic LDS bytes)) the one of the lowest small_cost, the smallest of equals.  vals: floats of LDS per
+// element of a tile that meets several layers.
 template <class F>
-bool build_small(ob_lamb_ctx* ctx, const Tiling& tm, const std::vector<int64_t>& h_off,
+bool build_small(ob_lamb_ctx* ctx, SmallTilings* tilings, const std::vector<int64_t>& h_off,
                  const std::vector<unsigned char>& lagging, int vals, F slots, SmallPlan* sp) {
+  static_assert(TILE_MAIN == SPAN, "the TILE_MAIN tiling is that of U = 1");
+  int best = 0;
+  SmallShape sh;
   for (int U : {1, 2, 4}) {
-    const int64_t tpc = (ctx->n_c + (int64_t)SPAN * U - 1) / ((int64_t)SPAN * U);
-    if (tpc * ctx->W > 4096) continue;   // (no device has the slots)
-    Tiling t;
-    std::vector<SmallTile> tiles;
-    int max_seg = 0;
-    if (!build_tiling((int64_t)SPAN * U, ctx->n_c, ctx->W, ctx->L, h_off, &t)) return true;
-    small_tiles(t, U, tm, h_off, ctx->n_c, ctx->L, lagging, &tiles, &max_seg);
-    const size_t bytes = 4 * ((size_t)vals * SPAN * U + 3 * (size_t)max_seg);
+    const SmallShape s = small_shape(U, h_off, ctx->n_c, ctx->W, ctx->L);
+    if (s.n_tiles > 4096 || (best && small_cost(U, s) >= small_cost(best, sh))) continue;   // (no device has more slots)
+    const size_t bytes = 4 * ((size_t)vals * SPAN * U + 3 * (size_t)s.max_seg);
     int64_t n_slots = 0;
     if (!slots(U, bytes, &n_slots)) return false;
-    if (5 * (t.n_tiles + 8) > 4 * n_slots) continue;
-    sp->tpc = (int)t.tpc;
-    sp->n_tiles = (int)t.n_tiles;
-    sp->max_seg = max_seg;
+    if (5 * (s.n_tiles + 8) > 4 * n_slots) continue;
+    best = U;
+    sh = s;
     sp->lds_bytes = bytes;
+  }
+  const Tiling* tp = best ? tilings->get(best, ctx->n_c, ctx->W, ctx->L, h_off) : nullptr;
+  if (tp) {
+    const Tiling& t = *tp;
+    std::vector<SmallTile> tiles;
+    small_tiles(t, best, tilings->tm, h_off, ctx->n_c, ctx->L, lagging, &tiles);
+    sp->tpc = (int)sh.tpc;
+    sp->n_tiles = (int)sh.n_tiles;
+    sp->max_seg = sh.max_seg;
     for (int64_t l = 0; l < ctx->L; ++l)
       if (t.layer_seg0[(size_t)l + 1] == t.layer_seg0[(size_t)l]) sp->empty_layers = true;
     std::vector<unsigned char> mem;
@@ -627,8 +683,7 @@ bool build_small(ob_lamb_ctx* ctx, const Tiling& tm, const std::vector<int64_t>&
     sp->d_partial = reinterpret_cast<double*>(sp->d_mem + o_part);
     sp->d_counter = reinterpret_cast<unsigned long long*>(sp->d_mem + o_ctr);
     sp->d_flag = reinterpret_cast<unsigned long long*>(sp->d_mem + o_flag);
-    sp->u = U;
-    return true;
+    sp->u = best;
   }
   return true;
 }
@@ -1080,8 +1135,9 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
       *out = (int64_t)std::min(per_cu, min_per_cu) * cus;   // (every instantiation reaches its launch bound)
       return true;
     };
+    SmallTilings tilings{tm, {}, {}};
     if (ok && cfg->fused_max_tiles == 0 && !(cfg->flags & OB_CFG_NO_FUSED_APPLY))
-      ok = build_small(ctx, tm, h_off, lagging, 1, [&](int U, size_t bytes, int64_t* n) {
+      ok = build_small(ctx, &tilings, h_off, lagging, 1, [&](int U, size_t bytes, int64_t* n) {
         bool r = false;
         dispatch_u(U, [&](auto u) {
           constexpr int UU = decltype(u)::value;
@@ -1090,7 +1146,7 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
         return r;
       }, &ctx->sm_apply);
     if (ok && cfg->fused_max_tiles == 0 && !(cfg->flags & OB_CFG_TWO_PASS_WARMUP))
-      ok = build_small(ctx, tm, h_off, std::vector<unsigned char>((size_t)tm.n_tiles, 0), 2,
+      ok = build_small(ctx, &tilings, h_off, std::vector<unsigned char>((size_t)tm.n_tiles, 0), 2,
                        [&](int U, size_t bytes, int64_t* n) {
         bool r = false;
         dispatch_u(U, [&](auto u) {

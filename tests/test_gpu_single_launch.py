@@ -21,6 +21,8 @@ LISTS = {
     "edges": (EDGES, 3),
     "edges_many_chunks": (EDGES, 61),
     "u1": (EDGES + [900_000, 64, 600_000], 2),            # 1.58e6 elements
+    "u1_many": (EDGES + [115_001] * 13, 2),               # ... in tensors of few tiles
+    "one_large": ([1_600_000], 2),                        # one tensor that meets every tile
     "u2": (EDGES + [1_300_000, 64, 500_000, 7], 5),       # 1.88e6
     "u4": (EDGES + [700_001, 64, 1_300_000, 1_000_000], 4),   # 3.08e6
     "beyond": (EDGES + [1_700_001, 64, 2_300_000], 4),    # 4.08e6: the launches of the larger lists
@@ -78,3 +80,35 @@ def test_lamb_step_in_one_launch(name, wd):
     took = set(ob.ob_lamb_profile_read(dev.ctx))
     assert ("warmup_small" in took) == (name != "beyond"), took
     finish(dev)
+
+
+@pytest.mark.parametrize("n", [900_000, 1_600_000])
+@pytest.mark.parametrize("call", ["warmup_step", "ratios_apply"])
+def test_one_launch_is_no_slower_where_one_tensor_meets_every_tile(call, n):
+    """Every tile of a tensor arrives at one counter, one arrival after the other: 1563 tiles of 1024 elements took
+    27 us where the launches of the larger lists take 15 to 17.  Times of the kernels alone, in turn."""
+    _need_gpu()
+    import paper_2104_06069_amd as ob
+    devs, us = [], [[], []]
+    for max_tiles in (None, 1 << 20):
+        dev = DeviceStep(np.array([0, n]), 2, 0, two_pass=True, packed_momentum=True, fused_apply=True,
+                         deferred_error=True, fused_max_tiles=max_tiles, **HYPER)
+        for k in ("x", "v_fresh", "v_frozen"):
+            dev.t[k].fill_(1e-3)
+        dev.m_is_packed = (call == "ratios_apply")      # (a state of constants)
+        ob.ob_lamb_profile_enable(dev.ctx, True)
+        devs.append(dev)
+    g = torch.full((devs[0].n_pad,), 1e-3, device=devs[0].device)
+    for rep in range(40):
+        for dev, t in zip(devs, us):
+            if call == "warmup_step":
+                dev.warmup_step(g, 1e-3)
+            else:
+                dev.begin_step()
+                dev.ratios_apply(1e-3)
+            prof = ob.ob_lamb_profile_read(dev.ctx)
+            t.append(sum(ms for ms, _ in prof.values()))
+    one, several = (float(np.median(t[10:])) for t in us)
+    assert one <= 1.25 * several, (one, several)
+    for dev in devs:
+        finish(dev)

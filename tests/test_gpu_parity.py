@@ -45,6 +45,15 @@ def finish(dev):
     dev.close()
 
 
+LARGE = 1 << 20   # a limit on a layer's tiles that limits nothing: the launches of the larger lists on a small one
+
+
+def kernels_of(dev):
+    """Names of the kernels launched since the profile of the context was enabled or last read."""
+    import paper_2104_06069_amd as ob
+    return set(ob.ob_lamb_profile_read(dev.ctx))
+
+
 def assert_close(gpu, ref, what, rel=REL):
     gpu = np.asarray(gpu); ref = np.asarray(ref)
     assert gpu.shape == ref.shape, what
@@ -104,9 +113,12 @@ def make_case(name):
         # tiles: with a low limit on the tiles per layer the large one is "too large" for the kernel
         # with the per-layer barrier while the others are not
         sizes = [3 * 8192 + 5, 75 * 8192 + 1234, 100, 4 * 8192, 2 * 8192 + 77]
+    elif name == "lds_round":
+        # on 256 CUs the tiles of ob_lamb_ratios_apply_hist fit on the device at once only with v_frozen in LDS
+        sizes = [641 * 8192 + 11, 642 * 8192, 77, 1023]
     else:
         raise KeyError(name)
-    W = {"odd": 3, "w1": 1, "small": 2, "one_layer": 4, "big_and_small": 2}[name]
+    W = {"odd": 3, "w1": 1, "small": 2, "one_layer": 4, "big_and_small": 2, "lds_round": 1}[name]
     pl = ParamList(name, [(f"t{i}", s) for i, s in enumerate(sizes)])
     n_pad = padded_len(pl.N, W)
     return dict(name=name, plist=pl, W=W, n_pad=n_pad, n_c=n_pad // W, grad="student_t3",
@@ -283,14 +295,16 @@ def run_trajectory(cfg, steps, seed=0, two_pass=False, packed=False, warm_state=
     ("tiny", 12, 4, None), ("tiny", 20, 8, None), ("bert_mini", 30, 4, None), ("bert_mini", 21, 8, None),
     ("bert_mini", 13, 2, 1), ("odd", 14, 3, None), ("odd", 12, 5, 0), ("w1", 10, 4, None), ("small", 10, 4, None),
     ("big_and_small", 11, 4, 8), ("big_and_small", 7, 3, 5),
-    ("big_and_small", 9, 4, 0)])     # no barrier kernel at all: the large tensor still works from the history
+    ("big_and_small", 9, 4, 0),     # no barrier kernel at all: the large tensor still works from the history
+    ("tiny", 12, 4, LARGE), ("bert_mini", 30, 4, LARGE), ("odd", 14, 3, LARGE)])
 def test_trajectory_with_the_variance_in_deferred_form(case, steps, period, fused_max_tiles):
     """ob_lamb_ratios_apply_hist: the v_fresh array is brought up to date only every `period`-th
     step; in between every step forms the up-to-date variance from the array and the sign words and
     scales of the momenta since then.  After EVERY step the dense view of the variance
     (ob_lamb_variance_dense), the parameters, the errors and the ratios equal the oracle's bit for
-    bit, in the kernel with the per-layer barrier and in the plain kernels (tiles at layer
-    boundaries, empty and tiny tensors, momentum scaling on bert_mini)."""
+    bit, in the one launch of small lists (no limit on the tiles), in the kernel with the per-layer
+    barrier and in the plain kernels (tiles at layer boundaries, empty and tiny tensors, momentum
+    scaling on bert_mini)."""
     _need_gpu()
     cfg = make_case(case)
     ref, dev, stats = run_trajectory(cfg, steps, packed=True, fused=True, warm_state=True, deferred=True,
@@ -396,12 +410,14 @@ def test_trajectory(case, steps, two_pass, packed):
 @pytest.mark.parametrize("case,path", [
     ("odd", "single"), ("bert_mini", "single"), ("small", "single"), ("tiny", "single"), ("w1", "single"),
     ("bert_mini", "two_pass"), ("tiny", "two_pass"),
+    ("bert_mini", "resident"), ("tiny", "resident"), ("w1", "resident"),
     ("bert_mini", 1), ("tiny", 7)])      # layers over that many tiles of 8192 take two passes
 @pytest.mark.parametrize("wd", [0.0, 0.01])
 def test_warmup_and_freeze(case, path, wd):
-    """eq. (1) with the moving average of c, then the end-of-warmup snapshot.  path: the single-pass
-    kernel with a per-layer barrier for every layer that qualifies (the default), two passes for
-    every layer, or a lowered size limit so that both run side by side."""
+    """eq. (1) with the moving average of c, then the end-of-warmup snapshot.  path: the one launch of
+    small lists (the default for all of these), the single-pass kernel with a per-layer barrier for
+    every layer that qualifies, two passes for every layer, or a lowered size limit so that the last
+    two run side by side."""
     _need_gpu()
     import paper_2104_06069_amd as ob
     cfg = make_case(case)
@@ -415,7 +431,7 @@ def test_warmup_and_freeze(case, path, wd):
         hyper["c_min"] = 1e-4
     ref = RefStep(pl.offsets, cfg["W"], cfg["server_chunk"], **hyper)
     dev = DeviceStep(pl.offsets, cfg["W"], cfg["server_chunk"], two_pass_warmup=(path == "two_pass"),
-                     fused_max_tiles=(path if isinstance(path, int) else None), **hyper)
+                     fused_max_tiles=(path if isinstance(path, int) else LARGE if path == "resident" else None), **hyper)
     nf = ob.ob_lamb_warmup_fused_layers(dev.ctx)
     assert nf == {("tiny", "single"): 4, ("tiny", 7): 0, ("bert_mini", "two_pass"): 0,
                   ("tiny", "two_pass"): 0, ("small", "single"): 0}.get((case, path), nf)
@@ -429,6 +445,7 @@ def test_warmup_and_freeze(case, path, wd):
     s["v_fresh"][...] = 0
     s["c_avg"][...] = 0
     ref.load_state(s); dev.load_state(ref.t)
+    ob.ob_lamb_profile_enable(dev.ctx, True)
     for t in range(5):
         g = gradient(st, cfg, t)
         ref.warmup_step(g, 1e-3 * (t + 1))
@@ -438,6 +455,9 @@ def test_warmup_and_freeze(case, path, wd):
         if wd == 0.0:
             c = ref.t["coeff_c"][np.diff(pl.offsets) > 0]
             assert ((c > hyper["c_min"]) & (c < hyper["c_max"])).mean() > 0.5, "most coefficients should be unclipped"
+    took = kernels_of(dev)
+    assert (took == {"warmup_small"}) if path == "single" else "warmup_small" not in took, took
+    assert ("warmup_resident" in took) == (path != "single" and nf > 0), took
     ref.freeze(); dev.freeze()
     assert np.array_equal(dev.get("v_frozen"), dev.get("v_fresh"))
     assert np.all(dev.get("r_prev") == 1.0)
@@ -721,23 +741,26 @@ def test_two_stage_schedule(case, packed):
 
 
 @pytest.mark.parametrize("case,steps,packed,max_tiles", [
-    ("bert_mini", 60, True, None),    # every layer in the fused kernel
-    ("bert_mini", 60, False, None),   # ... with the fp32 momentum read and written in place
+    ("bert_mini", 60, True, None),    # one launch for the whole list
+    ("bert_mini", 60, True, LARGE),   # every layer that holds a whole tile in the kernel with the per-layer barrier
+    ("bert_mini", 60, False, None),   # the fp32 momentum read and written in place: two plain kernels
     ("bert_mini", 40, True, 2),       # layers over 2 tiles of 8192 go to the two-kernel path
     ("bert_mini", 40, False, 1),
     ("odd", 30, True, None),          # tiny tensors: every tile meets several layer boundaries
+    ("odd", 30, True, LARGE),         # ... none of them eligible
+    ("tiny", 10, True, LARGE),
     ("odd", 30, False, 0),            # nothing eligible: plain kernels behind the fused entry point
     ("tiny", 10, True, None), ("w1", 10, True, 1), ("small", 10, False, None)])
 def test_trajectory_fused_ratios_apply(case, steps, packed, max_tiles):
-    """ob_lamb_ratios_apply (ratio pass, clips and update in one call, one kernel where the layer
-    fits on the device) against the oracle's separate phases."""
+    """ob_lamb_ratios_apply (ratio pass, clips and update in one call; one launch where the list fits on
+    the device, else one kernel where the layer does) against the oracle's separate phases."""
     _need_gpu()
     import paper_2104_06069_amd as ob
     cfg = make_case(case)
     ref, dev, stats = run_trajectory(cfg, steps, packed=packed, warm_state=(case in ("odd", "w1")),
                                      fused=True, fused_max_tiles=max_tiles)
     nf = ob.ob_lamb_fused_layers(dev.ctx)
-    print(f"{case}: {nf} of {cfg['plist'].L} layers in the fused kernel, {stats}")
+    print(f"{case}: {nf} of {cfg['plist'].L} layers eligible for the barrier kernel, {stats}")
     if max_tiles == 0 or case in ("odd", "small", "w1"):   # no eligible layer holds a whole tile
         assert nf == 0
     else:
@@ -745,6 +768,12 @@ def test_trajectory_fused_ratios_apply(case, steps, packed, max_tiles):
     assert stats["scale_ulp_steps"] == 0 and stats["word_mismatch_steps"] == 0
     for k in ("x", "m", "v_fresh", "err_worker", "err_server", "r_prev", "coeff_c"):
         assert np.array_equal(dev.get(k), ref.t[k]), k
+    ob.ob_lamb_profile_enable(dev.ctx, True)
+    dev.begin_step()
+    dev.ratios_apply(1e-3)
+    took, one = kernels_of(dev), packed and max_tiles is None
+    assert ("ratios_apply_small" in took) == one, took
+    assert ("ratios_apply_resident" in took) == (packed and not one and nf > 0), took
     finish(dev)
 
 
@@ -775,7 +804,7 @@ def _to_lp(g32, fmt):
     return t, (1 if fmt == "f16" else 2, t.view(torch.int16).numpy().view(np.uint16).copy())
 
 
-@pytest.mark.parametrize("case,gfmt,xfmt,fused,packed,scale,vperiod", [
+@pytest.mark.parametrize("case,gfmt,xfmt,fused,packed,scale,vperiod,max_tiles,kernels", [(*c, None, "warmup_small") if len(c) == 7 else c for c in [
     ("bert_mini", "f16", "f16", True, True, 1.0 / 1024, 0),
     ("bert_mini", "bf16", "bf16", True, True, 1.0, 0),
     ("bert_mini", "f16", "bf16", False, False, 1.0 / 1000, 0),   # scale not a power of two; separate calls
@@ -788,12 +817,21 @@ def _to_lp(g32, fmt):
     ("bert_mini", "f16", "f16", True, True, 1.0 / 1024, 4),
     ("tiny", "bf16", "bf16", True, True, 1.0, 3),
     ("odd", "f32", "f16", True, True, 1.0, 2),
-    ("big_and_small", "bf16", "bf16", True, True, 1.0 / 16, 4)])
-def test_mixed_precision_variant(case, gfmt, xfmt, fused, packed, scale, vperiod):
+    ("big_and_small", "bf16", "bf16", True, True, 1.0 / 16, 4),
+    # the kernels with the per-layer barrier
+    ("bert_mini", "f16", "f16", True, True, 1.0 / 1024, 0, LARGE, "warmup_resident ratios_apply_resident"),
+    ("tiny", "bf16", "bf16", True, True, 1.0, 3, LARGE, "warmup_resident ratios_apply_hist"),
+    ("lds_round", "bf16", "bf16", True, True, 1.0 / 16, 2, None, "warmup_resident ratios_apply_hist_lds"),
+    ("lds_round", "f32", "f16", True, True, 1.0, 2, None, "warmup_resident ratios_apply_hist_lds")]])
+def test_mixed_precision_variant(case, gfmt, xfmt, fused, packed, scale, vperiod, max_tiles, kernels):
     """16-bit gradient in (times the inverse loss scale), 16-bit copy of the parameters out, through
     3 LAMB steps, the snapshot and 12 compression steps; state and arithmetic stay fp32, so every
-    comparison is as strict as for the fp32 entry points and the 16-bit copy is bit-exact."""
+    comparison is as strict as for the fp32 entry points and the 16-bit copy is bit-exact.
+    kernels: some that must have run."""
     _need_gpu()
+    import paper_2104_06069_amd as ob
+    if case == "lds_round" and torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        kernels = "warmup_resident"      # (the list is one for 256 CUs)
     cfg = make_case(case)
     st = Streams(11)
     pl = cfg["plist"]
@@ -801,7 +839,8 @@ def test_mixed_precision_variant(case, gfmt, xfmt, fused, packed, scale, vperiod
     ref.grad_scale = scale
     tdt = {None: None, "f16": torch.float16, "bf16": torch.bfloat16}[xfmt]
     dev = DeviceStep(pl.offsets, cfg["W"], cfg["server_chunk"], packed_momentum=packed, fused_apply=fused,
-                     x_lp_dtype=tdt, grad_scale=scale, deferred_variance=vperiod, **HYPER)
+                     x_lp_dtype=tdt, grad_scale=scale, deferred_variance=vperiod, fused_max_tiles=max_tiles, **HYPER)
+    ob.ob_lamb_profile_enable(dev.ctx, True)
     s = init_state(st, cfg)
     s["v_fresh"][...] = 0
     s["c_avg"][...] = 0
@@ -864,6 +903,10 @@ def test_mixed_precision_variant(case, gfmt, xfmt, fused, packed, scale, vperiod
         check_x_lp(t)
     if vperiod:
         assert set(dev.vf_ages) == set(range(1, vperiod + 1)), dev.vf_ages
+    took, want = kernels_of(dev), set(kernels.split())
+    if fused and packed and kernels == "warmup_small":
+        want.add("ratios_apply_small")
+    assert want <= took, took
     finish(dev)
 
 
@@ -895,27 +938,36 @@ def test_mixed_precision_argument_errors():
     finish(dev)
 
 
-@pytest.mark.parametrize("which", ["compress", "ratios_apply", "ratios_apply_hist", "warmup"])
-def test_expired_wait_is_reported_and_recovered(which):
+@pytest.mark.parametrize("which,case,max_tiles,kernel", [
+    ("compress", "tiny", None, "compress_resident"),
+    # the per-layer waits in the one launch of small lists, and in the barrier kernels of the larger ones
+    ("ratios_apply", "tiny", None, "ratios_apply_small"), ("ratios_apply", "tiny", LARGE, "ratios_apply_resident"),
+    ("ratios_apply_hist", "tiny", None, "ratios_apply_small"), ("ratios_apply_hist", "tiny", LARGE, "ratios_apply_hist"),
+    ("ratios_apply_hist", "lds_round", None, "ratios_apply_hist_lds"),
+    ("warmup", "tiny", None, "warmup_small"), ("warmup", "tiny", LARGE, "warmup_resident")])
+def test_expired_wait_is_reported_and_recovered(which, case, max_tiles, kernel):
     """The in-kernel barriers wait a bounded number of polls.  With the bound forced to 0 from the
     host every waiting workgroup gives up without polling, raises the device flag and runs to
     its end (nothing hangs, all accesses stay in bounds).  ob_lamb_check_device_status must report
     that once, switch the context to the barrier-free kernels, and the next steps -- from a restored
-    state -- must again agree with the oracle."""
+    state -- must again agree with the oracle.  kernel: the one whose wait expired."""
     _need_gpu()
     import paper_2104_06069_amd as ob
-    cfg = make_case("tiny")       # 16 tiles of 16384 per chunk, 32 tiles of 8192 per layer
+    if case == "lds_round" and torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the list is one for 256 CUs")
+    cfg = make_case(case)         # tiny: 32 tiles of 8192 per layer, 16 tiles of 16384 per chunk
     st = Streams(5)
     pl = cfg["plist"]
     ref = RefStep(pl.offsets, cfg["W"], cfg["server_chunk"], **HYPER)
     # "ratios_apply": the worker compression runs as two passes, so only the per-layer barrier trips
     # "ratios_apply_hist": the same with the variance in deferred form (its own kernel)
     dev = DeviceStep(pl.offsets, cfg["W"], cfg["server_chunk"], two_pass=which.startswith("ratios_apply"),
-                     packed_momentum=True, fused_apply=True, spin_limit=0,
+                     packed_momentum=True, fused_apply=True, spin_limit=0, fused_max_tiles=max_tiles,
                      deferred_variance=(3 if which == "ratios_apply_hist" else 0), **HYPER)
-    assert ob.ob_lamb_fused_layers(dev.ctx) == pl.L
+    assert ob.ob_lamb_fused_layers(dev.ctx) == (pl.L if case == "tiny" else 2)
     ref.load_state(init_state(st, cfg))
     dev.load_state(ref.t)
+    ob.ob_lamb_profile_enable(dev.ctx, True)
 
     def one_step(t, check):
         g = gradient(st, cfg, t)
@@ -941,6 +993,10 @@ def test_expired_wait_is_reported_and_recovered(which):
     # runs the kernel with the per-layer barrier
     for t in range({"compress": 1, "ratios_apply": 2, "ratios_apply_hist": 2, "warmup": 0}[which]):
         one_step(t, check=False)
+    waiting = {"compress_resident", "server_resident", "ratios_apply_small", "ratios_apply_resident", "ratios_apply_hist",
+               "ratios_apply_hist_lds", "warmup_small", "warmup_resident"}
+    took = kernels_of(dev) & waiting - ({"server_resident"} if which == "compress" else set())
+    assert took == {kernel}, took
     with pytest.raises(ob.ObLambError) as e:
         ob.ob_lamb_check_device_status(dev.ctx, dev.stream)
     assert e.value.status == -4
@@ -962,6 +1018,7 @@ def test_expired_wait_is_reported_and_recovered(which):
     dev.m_is_packed = False
     for t in range(2, 6):
         one_step(t, check=True)
+    assert not kernels_of(dev) & waiting
     finish(dev)
 
 

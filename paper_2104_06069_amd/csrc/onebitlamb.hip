@@ -11,6 +11,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <limits>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -127,7 +128,6 @@ struct SmallPlan {
   int tpc = 0, n_tiles = 0, max_seg = 0;
   bool empty_layers = false;
   size_t lds_bytes = 0;
-  unsigned char* d_mem = nullptr;       // one allocation for all of the following
   SmallTile* d_tiles = nullptr;
   int* d_seg_layer = nullptr;
   int* d_layer_seg0 = nullptr;
@@ -239,7 +239,8 @@ struct ob_lamb_ctx {
   unsigned int* d_ticket_srv = nullptr;    // ... of the served chunk
   double* d_ticket_part = nullptr;
   double* d_ticket_part_srv = nullptr;
-  size_t device_bytes = 0;                 // device memory this context holds (tables + workspace)
+  void* d_mem = nullptr;                   // the allocation that holds all of the arrays above (Workspace)
+  size_t device_bytes = 0;                 // its size
   // diagnostics
   bool profile = false;
   std::vector<ProfRec> prof;
@@ -296,22 +297,63 @@ struct Launch {
 #define OB_LAUNCH_B(la, kid, kernel, grid, block, ...) OB_LAUNCH_S(la, kid, kernel, grid, block, 0, __VA_ARGS__)
 #define OB_LAUNCH(la, kid, kernel, grid, ...) OB_LAUNCH_B(la, kid, kernel, grid, BLOCK, __VA_ARGS__)
 
-template <class T>
-bool upload(ob_lamb_ctx* ctx, T** dst, const std::vector<T>& src) {
-  const size_t bytes = src.size() * sizeof(T);
-  if (!hip_ok(ctx, hipMalloc(reinterpret_cast<void**>(dst), bytes ? bytes : sizeof(T)), "hipMalloc")) return false;
-  ctx->device_bytes += bytes ? bytes : sizeof(T);
-  if (bytes && !hip_ok(ctx, hipMemcpy(*dst, src.data(), bytes, hipMemcpyHostToDevice), "hipMemcpy")) return false;
-  return true;
-}
+// The device memory of a context is ONE allocation, so that what ob_lamb_create costs does not grow with the
+// number of tables a configuration needs: upload() and alloc_zero() note what goes where, commit() allocates, sets
+// the pointers, copies the small tables together and the large ones from where they are.  Every array starts at a
+// multiple of 256 bytes.  (A context of four 512x512 tensors, some 60 arrays: 490 us with an allocation each, 69.)
+class Workspace {
+ public:
+  template <class T>
+  void upload(T** dst, std::vector<T> src) {
+    auto keep = std::make_shared<std::vector<T>>(std::move(src));
+    const size_t bytes = keep->size() * sizeof(T);
+    (bytes < SMALL ? small_ : large_).push_back({reinterpret_cast<void**>(dst), keep->data(), bytes, keep});
+  }
+  template <class T>
+  void alloc_zero(T** dst, size_t count) {
+    zeroed_.push_back({reinterpret_cast<void**>(dst), nullptr, count * sizeof(T), nullptr});
+  }
+  bool commit(ob_lamb_ctx* ctx) {
+    std::vector<unsigned char> head(size_of(small_));
+    const size_t zero_at = head.size() + size_of(large_), total = zero_at + size_of(zeroed_);
+    if (!hip_ok(ctx, hipMalloc(&ctx->d_mem, total), "hipMalloc")) return false;
+    ctx->device_bytes = total;
+    unsigned char* const base = static_cast<unsigned char*>(ctx->d_mem);
+    size_t at = 0;
+    for (const Array& a : small_) {
+      if (a.bytes) std::memcpy(head.data() + at, a.src, a.bytes);
+      *a.dst = base + at;
+      at += room(a.bytes);
+    }
+    bool ok = hip_ok(ctx, hipMemcpy(base, head.data(), head.size(), hipMemcpyHostToDevice), "hipMemcpy");
+    for (const Array& a : large_) {
+      ok = ok && hip_ok(ctx, hipMemcpy(base + at, a.src, a.bytes, hipMemcpyHostToDevice), "hipMemcpy");
+      *a.dst = base + at;
+      at += room(a.bytes);
+    }
+    for (const Array& a : zeroed_) {
+      *a.dst = base + at;
+      at += room(a.bytes);
+    }
+    return ok && hip_ok(ctx, hipMemset(base + zero_at, 0, total - zero_at), "hipMemset");
+  }
 
-template <class T>
-bool alloc_zero(ob_lamb_ctx* ctx, T** dst, size_t count) {
-  const size_t bytes = (count ? count : 1) * sizeof(T);
-  if (!hip_ok(ctx, hipMalloc(reinterpret_cast<void**>(dst), bytes), "hipMalloc")) return false;
-  ctx->device_bytes += bytes;
-  return hip_ok(ctx, hipMemset(*dst, 0, bytes), "hipMemset");
-}
+ private:
+  struct Array {
+    void** dst;
+    const void* src;
+    size_t bytes;
+    std::shared_ptr<void> keep;   // what src points into
+  };
+  static constexpr size_t SMALL = 65536;
+  static size_t room(size_t bytes) { return (std::max<size_t>(bytes, 1) + 255) / 256 * 256; }
+  static size_t size_of(const std::vector<Array>& v) {
+    size_t n = 0;
+    for (const Array& a : v) n += room(a.bytes);
+    return n;
+  }
+  std::vector<Array> small_, large_, zeroed_;
+};
 
 ob_status check_common(const ob_lamb_ctx* ctx, const ob_lamb_state* st) {
   if (!ctx || !st) return OB_ERR_NULL;
@@ -528,7 +570,7 @@ void plan_split(const Tiling& tl, int64_t tile_lb, const Tiling& tm, const std::
 }
 
 // Plans and uploads one LayerSplit.
-bool build_split(ob_lamb_ctx* ctx, const Tiling& tl, int tile_lb, const Tiling& tm,
+void build_split(ob_lamb_ctx* ctx, Workspace* ws, const Tiling& tl, int tile_lb, const Tiling& tm,
                  const std::vector<int64_t>& h_off, int64_t max_tiles, LayerSplit* sp,
                  std::vector<unsigned char>* lagging) {
   const int64_t L = ctx->L;
@@ -551,13 +593,20 @@ bool build_split(ob_lamb_ctx* ctx, const Tiling& tl, int tile_lb, const Tiling& 
   sp->n_rest_ratio_tiles = (int)pl.rest_ratio_tiles.size();
   lagging->assign((size_t)tm.n_tiles, 0);
   for (int t : cov) (*lagging)[(size_t)t] = 1;
-  return upload(ctx, &sp->d_cov_tiles, cov) && upload(ctx, &sp->d_big_tiles, pl.big_tiles) &&
-         upload(ctx, &sp->d_rest_ratio_tiles, pl.rest_ratio_tiles) && upload(ctx, &sp->d_fused_tiles, pl.fused_tiles) && upload(ctx, &sp->d_n_listed, pl.n_listed) &&
-         upload(ctx, &sp->d_list_begin, pl.list_begin) && upload(ctx, &sp->d_seg_first, pl.seg_first) &&
-         upload(ctx, &sp->d_seg_end, pl.seg_end) && alloc_zero(ctx, &sp->d_listed_max, pl.fused_tiles.size()) &&
-         alloc_zero(ctx, &sp->d_listed_sums, 2 * pl.fused_tiles.size()) &&
-         upload(ctx, &sp->d_rest_tiles, pl.rest_tiles) && upload(ctx, &sp->d_has_listed, pl.has_listed) &&
-         alloc_zero(ctx, &sp->d_counter, (size_t)L * CTR_STRIDE) && alloc_zero(ctx, &sp->d_flag, (size_t)L);
+  ws->upload(&sp->d_cov_tiles, std::move(cov));
+  ws->upload(&sp->d_big_tiles, std::move(pl.big_tiles));
+  ws->upload(&sp->d_rest_ratio_tiles, std::move(pl.rest_ratio_tiles));
+  ws->upload(&sp->d_fused_tiles, std::move(pl.fused_tiles));
+  ws->upload(&sp->d_n_listed, std::move(pl.n_listed));
+  ws->upload(&sp->d_list_begin, std::move(pl.list_begin));
+  ws->upload(&sp->d_seg_first, std::move(pl.seg_first));
+  ws->upload(&sp->d_seg_end, std::move(pl.seg_end));
+  ws->upload(&sp->d_rest_tiles, std::move(pl.rest_tiles));
+  ws->upload(&sp->d_has_listed, std::move(pl.has_listed));
+  ws->alloc_zero(&sp->d_listed_max, (size_t)sp->n_fused_tiles);
+  ws->alloc_zero(&sp->d_listed_sums, 2 * (size_t)sp->n_fused_tiles);
+  ws->alloc_zero(&sp->d_counter, (size_t)L * CTR_STRIDE);
+  ws->alloc_zero(&sp->d_flag, (size_t)L);
 }
 
 // The tiles and segments of one SmallPlan (no HIP call).  lagging: per 1024-element span (tm's tiling).
@@ -621,10 +670,15 @@ SmallShape small_shape(int U, const std::vector<int64_t>& h_off, int64_t n_c, in
 int64_t small_cost(int U, const SmallShape& sh) {
   return (U == 1 ? 0 : U == 2 ? 500 : 2000) + 13 * sh.max_arrivals + 2500 * std::max(sh.mixed_spans - 1, 0);
 }
-// Tilings of the tile sizes that a SmallPlan may take, formed when first asked for.
+// Tilings of the tile sizes that a SmallPlan may take, formed when first asked for, and their shapes.
 struct SmallTilings {
   const Tiling& tm;       // U = 1
+  SmallShape sh[3];       // U = 1, 2, 4 (n_tiles = 0: more tiles than any device holds)
   Tiling t2, t4;
+  SmallTilings(const Tiling& t, int64_t n_c, int64_t W, int64_t L, const std::vector<int64_t>& h_off) : tm(t) {
+    for (int i = 0; i < 3; ++i)
+      if ((n_c + ((int64_t)SPAN << i) - 1) / ((int64_t)SPAN << i) * W <= 4096) sh[i] = small_shape(1 << i, h_off, n_c, W, L);
+  }
   const Tiling* get(int U, int64_t n_c, int64_t W, int64_t L, const std::vector<int64_t>& h_off) {
     if (U == 1) return &tm;
     Tiling* t = (U == 2) ? &t2 : &t4;
@@ -637,14 +691,14 @@ struct SmallTilings {
 // (slots(U, dynamic LDS bytes)) the one of the lowest small_cost, the smallest of equals.  vals: floats of LDS per
 // element of a tile that meets several layers.
 template <class F>
-bool build_small(ob_lamb_ctx* ctx, SmallTilings* tilings, const std::vector<int64_t>& h_off,
+bool build_small(ob_lamb_ctx* ctx, Workspace* ws, SmallTilings* tilings, const std::vector<int64_t>& h_off,
                  const std::vector<unsigned char>& lagging, int vals, F slots, SmallPlan* sp) {
   static_assert(TILE_MAIN == SPAN, "the TILE_MAIN tiling is that of U = 1");
   int best = 0;
   SmallShape sh;
   for (int U : {1, 2, 4}) {
-    const SmallShape s = small_shape(U, h_off, ctx->n_c, ctx->W, ctx->L);
-    if (s.n_tiles > 4096 || (best && small_cost(U, s) >= small_cost(best, sh))) continue;   // (no device has more slots)
+    const SmallShape& s = tilings->sh[U / 2];
+    if (s.n_tiles == 0 || (best && small_cost(U, s) >= small_cost(best, sh))) continue;
     const size_t bytes = 4 * ((size_t)vals * SPAN * U + 3 * (size_t)s.max_seg);
     int64_t n_slots = 0;
     if (!slots(U, bytes, &n_slots)) return false;
@@ -663,26 +717,12 @@ bool build_small(ob_lamb_ctx* ctx, SmallTilings* tilings, const std::vector<int6
     sp->max_seg = sh.max_seg;
     for (int64_t l = 0; l < ctx->L; ++l)
       if (t.layer_seg0[(size_t)l + 1] == t.layer_seg0[(size_t)l]) sp->empty_layers = true;
-    std::vector<unsigned char> mem;
-    auto put = [&](const void* src, size_t n) {   // -> offset (256-byte aligned); src NULL: zeros
-      const size_t at = (mem.size() + 255) / 256 * 256;
-      mem.resize(at + n, 0);
-      if (src && n) std::memcpy(mem.data() + at, src, n);
-      return at;
-    };
-    const size_t line = CTR_STRIDE * sizeof(unsigned long long);
-    const size_t o_tiles = put(tiles.data(), tiles.size() * sizeof(SmallTile));
-    const size_t o_segl = put(t.seg_layer.data(), t.seg_layer.size() * sizeof(int));
-    const size_t o_lseg = put(t.layer_seg0.data(), t.layer_seg0.size() * sizeof(int));
-    const size_t o_part = put(nullptr, 2 * t.seg_layer.size() * sizeof(double));
-    const size_t o_ctr = put(nullptr, (size_t)ctx->L * line), o_flag = put(nullptr, (size_t)ctx->L * line);
-    if (!upload(ctx, &sp->d_mem, mem)) return false;
-    sp->d_tiles = reinterpret_cast<SmallTile*>(sp->d_mem + o_tiles);
-    sp->d_seg_layer = reinterpret_cast<int*>(sp->d_mem + o_segl);
-    sp->d_layer_seg0 = reinterpret_cast<int*>(sp->d_mem + o_lseg);
-    sp->d_partial = reinterpret_cast<double*>(sp->d_mem + o_part);
-    sp->d_counter = reinterpret_cast<unsigned long long*>(sp->d_mem + o_ctr);
-    sp->d_flag = reinterpret_cast<unsigned long long*>(sp->d_mem + o_flag);
+    ws->upload(&sp->d_tiles, std::move(tiles));
+    ws->upload(&sp->d_seg_layer, t.seg_layer);
+    ws->upload(&sp->d_layer_seg0, t.layer_seg0);
+    ws->alloc_zero(&sp->d_partial, 2 * t.seg_layer.size());
+    ws->alloc_zero(&sp->d_counter, (size_t)ctx->L * CTR_STRIDE);
+    ws->alloc_zero(&sp->d_flag, (size_t)ctx->L * CTR_STRIDE);
     sp->u = best;
   }
   return true;
@@ -729,15 +769,6 @@ ChunkTicket chunk_ticket_of(unsigned int* count, double* part, int n_chunks, int
   tk.count = count; tk.sub_part = part; tk.n_chunks = n_chunks; tk.spc = (tpc + TICKET_SUB - 1) / TICKET_SUB;
   tk.scales = scales; tk.own_scale = own_scale; tk.own_chunk = own_chunk;
   return tk;
-}
-
-void free_split(LayerSplit* sp) {
-  void* ptrs[] = {sp->d_fused_tiles, sp->d_n_listed, sp->d_list_begin, sp->d_seg_first, sp->d_seg_end,
-                  sp->d_listed_max,  sp->d_listed_sums, sp->d_rest_tiles, sp->d_cov_tiles, sp->d_big_tiles,
-                  sp->d_rest_ratio_tiles,
-                  sp->d_has_listed,  sp->d_counter,  sp->d_flag};
-  for (void* p : ptrs)
-    if (p) (void)hipFree(p);
 }
 
 ListedTiles listed_tiles(const ob_lamb_ctx* ctx, const LayerSplit& sp) {
@@ -1040,8 +1071,6 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
   ctx->tpc = (int)tm.tpc;
   ctx->n_tiles = (int)tm.n_tiles;
   ctx->n_segs = (int)tm.seg_layer.size();
-  const std::vector<int>&first = tm.first, &tile_seg0 = tm.tile_seg0, &seg_layer = tm.seg_layer,
-                        &layer_seg0 = tm.layer_seg0;
 
   // single-pass worker compression: its own (larger) tiles and the layer of each tile's start
   const int64_t tpc_res = (ctx->n_c + TILE_RES - 1) / TILE_RES;
@@ -1058,6 +1087,7 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
     first_res[(size_t)t] = (int)lo;
   }
 
+  Workspace ws;
   bool ok = hip_ok(ctx, hipGetDevice(&ctx->device), "hipGetDevice");
   if (ok) {
     // The single-pass kernel needs a whole chunk's workgroups on the device at once (see the
@@ -1122,8 +1152,8 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
     const int64_t max_w = (cfg->flags & OB_CFG_TWO_PASS_WARMUP)
                               ? 0 : split_max_tiles(std::min(per_cu_w, OB_WU_MINW), cus, cfg->fused_max_tiles);
     std::vector<unsigned char> lagging, unused;
-    ok = ok && build_split(ctx, tl, TILE_LB, tm, h_off, max_a, &ctx->sp_apply, &lagging) &&
-         build_split(ctx, tw, TILE_WU, tm, h_off, max_w, &ctx->sp_warm, &unused);
+    build_split(ctx, &ws, tl, TILE_LB, tm, h_off, max_a, &ctx->sp_apply, &lagging);
+    build_split(ctx, &ws, tw, TILE_WU, tm, h_off, max_w, &ctx->sp_warm, &unused);
     ctx->sp_apply.in_lds = lh_in_lds(ctx->sp_apply.n_fused_tiles, cus);
     // one launch instead of three or four where the whole list fits on the device at once (unless the
     // configuration lowers what the barrier kernels may take)
@@ -1135,9 +1165,9 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
       *out = (int64_t)std::min(per_cu, min_per_cu) * cus;   // (every instantiation reaches its launch bound)
       return true;
     };
-    SmallTilings tilings{tm, {}, {}};
+    SmallTilings tilings(tm, ctx->n_c, ctx->W, L, h_off);
     if (ok && cfg->fused_max_tiles == 0 && !(cfg->flags & OB_CFG_NO_FUSED_APPLY))
-      ok = build_small(ctx, &tilings, h_off, lagging, 1, [&](int U, size_t bytes, int64_t* n) {
+      ok = build_small(ctx, &ws, &tilings, h_off, lagging, 1, [&](int U, size_t bytes, int64_t* n) {
         bool r = false;
         dispatch_u(U, [&](auto u) {
           constexpr int UU = decltype(u)::value;
@@ -1146,7 +1176,7 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
         return r;
       }, &ctx->sm_apply);
     if (ok && cfg->fused_max_tiles == 0 && !(cfg->flags & OB_CFG_TWO_PASS_WARMUP))
-      ok = build_small(ctx, &tilings, h_off, std::vector<unsigned char>((size_t)tm.n_tiles, 0), 2,
+      ok = build_small(ctx, &ws, &tilings, h_off, std::vector<unsigned char>((size_t)tm.n_tiles, 0), 2,
                        [&](int U, size_t bytes, int64_t* n) {
         bool r = false;
         dispatch_u(U, [&](auto u) {
@@ -1158,26 +1188,33 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
     // chunk_ticket: counters (128-byte lines) and the first-level sums
     static_assert(TILE_SRV == TILE_MAIN, "the served chunk has the tiles of the worker's chunks");
     const size_t spc = (size_t)((ctx->tpc + TICKET_SUB - 1) / TICKET_SUB), line = 2 * CTR_STRIDE;
-    if (worker_ticket(ctx->tpc, ctx->n_tiles, cus))
-      ok = ok && alloc_zero(ctx, &ctx->d_ticket, (size_t)ctx->W * (1 + spc) * line) &&
-           alloc_zero(ctx, &ctx->d_ticket_part, (size_t)ctx->W * spc);
-    if (server_ticket(ctx->tpc, ctx->n_tiles, cus))
-      ok = ok && alloc_zero(ctx, &ctx->d_ticket_srv, (1 + spc) * line) && alloc_zero(ctx, &ctx->d_ticket_part_srv, spc);
+    if (worker_ticket(ctx->tpc, ctx->n_tiles, cus)) {
+      ws.alloc_zero(&ctx->d_ticket, (size_t)ctx->W * (1 + spc) * line);
+      ws.alloc_zero(&ctx->d_ticket_part, (size_t)ctx->W * spc);
+    }
+    if (server_ticket(ctx->tpc, ctx->n_tiles, cus)) {
+      ws.alloc_zero(&ctx->d_ticket_srv, (1 + spc) * line);
+      ws.alloc_zero(&ctx->d_ticket_part_srv, spc);
+    }
   }
-  ok = ok && upload(ctx, &ctx->d_first_layer_res, first_res) &&
-       alloc_zero(ctx, &ctx->d_partials_res, (size_t)ctx->n_tiles_res) &&
-       alloc_zero(ctx, &ctx->d_counter, (size_t)ctx->W * CTR_STRIDE) && alloc_zero(ctx, &ctx->d_flag, (size_t)ctx->W) &&
-       alloc_zero(ctx, &ctx->d_errflag, 1) &&
-       alloc_zero(ctx, &ctx->d_partials_srv_res, (size_t)ctx->tpc_srv_res) &&
-       alloc_zero(ctx, &ctx->d_counter_srv, (size_t)CTR_STRIDE) && alloc_zero(ctx, &ctx->d_flag_srv, 1);
-  ok = ok && upload(ctx, &ctx->d_off, h_off) && upload(ctx, &ctx->d_first_layer, first) &&
-       upload(ctx, &ctx->d_tile_seg0, tile_seg0) && upload(ctx, &ctx->d_seg_layer, seg_layer) &&
-       upload(ctx, &ctx->d_layer_seg0, layer_seg0) &&
-       alloc_zero(ctx, &ctx->d_partials, (size_t)n_tiles) &&
-       alloc_zero(ctx, &ctx->d_partials_srv, (size_t)tpc_srv) &&
-       alloc_zero(ctx, &ctx->d_seg_sums, 2 * (size_t)ctx->n_segs) &&
-       alloc_zero(ctx, &ctx->d_sigma, (size_t)L) &&
-       alloc_zero(ctx, &ctx->d_seg_max, (size_t)ctx->n_segs);
+  ws.upload(&ctx->d_first_layer_res, std::move(first_res));
+  ws.upload(&ctx->d_off, h_off);
+  ws.upload(&ctx->d_first_layer, std::move(tm.first));
+  ws.upload(&ctx->d_tile_seg0, std::move(tm.tile_seg0));
+  ws.upload(&ctx->d_seg_layer, std::move(tm.seg_layer));
+  ws.upload(&ctx->d_layer_seg0, std::move(tm.layer_seg0));
+  ws.alloc_zero(&ctx->d_partials_res, (size_t)ctx->n_tiles_res);
+  ws.alloc_zero(&ctx->d_counter, (size_t)ctx->W * CTR_STRIDE);
+  ws.alloc_zero(&ctx->d_flag, (size_t)ctx->W);
+  ws.alloc_zero(&ctx->d_errflag, 1);
+  ws.alloc_zero(&ctx->d_partials_srv_res, (size_t)ctx->tpc_srv_res);
+  ws.alloc_zero(&ctx->d_counter_srv, (size_t)CTR_STRIDE);
+  ws.alloc_zero(&ctx->d_flag_srv, 1);
+  ws.alloc_zero(&ctx->d_partials, (size_t)n_tiles);
+  ws.alloc_zero(&ctx->d_partials_srv, (size_t)tpc_srv);
+  ws.alloc_zero(&ctx->d_seg_sums, 2 * (size_t)ctx->n_segs);
+  ws.alloc_zero(&ctx->d_sigma, (size_t)L);
+  ws.alloc_zero(&ctx->d_seg_max, (size_t)ctx->n_segs);
   if (ok) {
     // the layers that meet each chunk (empty layers in between included; a chunk that lies in the
     // padding has none)
@@ -1197,11 +1234,13 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
     }
     pair_base[(size_t)ctx->W] = (int)pair_c.size();
     ctx->n_pairs = (int)pair_c.size();
-    ok = upload(ctx, &ctx->d_pair_base, pair_base) && upload(ctx, &ctx->d_pair_lfirst, pair_lfirst) &&
-         upload(ctx, &ctx->d_pair_c, pair_c) && upload(ctx, &ctx->d_pair_l, pair_l) &&
-         alloc_zero(ctx, &ctx->d_vterms, (size_t)(VF_MAX_OLD + 1) * (size_t)ctx->n_pairs * 2);
+    ws.upload(&ctx->d_pair_base, std::move(pair_base));
+    ws.upload(&ctx->d_pair_lfirst, std::move(pair_lfirst));
+    ws.upload(&ctx->d_pair_c, std::move(pair_c));
+    ws.upload(&ctx->d_pair_l, std::move(pair_l));
+    ws.alloc_zero(&ctx->d_vterms, (size_t)(VF_MAX_OLD + 1) * (size_t)ctx->n_pairs * 2);
   }
-  ok = ok && hip_ok(ctx, hipDeviceSynchronize(), "hipDeviceSynchronize");
+  ok = ok && ws.commit(ctx) && hip_ok(ctx, hipDeviceSynchronize(), "hipDeviceSynchronize");
   if (!ok) return OB_ERR_HIP;
   guard.c = nullptr;
   *out = ctx;
@@ -1214,18 +1253,7 @@ void ob_lamb_destroy(ob_lamb_ctx* ctx) {
     (void)hipEventDestroy(r.e0);
     (void)hipEventDestroy(r.e1);
   }
-  void* ptrs[] = {ctx->d_off, ctx->d_first_layer, ctx->d_tile_seg0, ctx->d_seg_layer, ctx->d_layer_seg0,
-                  ctx->d_partials, ctx->d_partials_srv, ctx->d_seg_sums, ctx->d_seg_max, ctx->d_sigma,
-                  ctx->d_first_layer_res, ctx->d_partials_res, ctx->d_counter, ctx->d_flag, ctx->d_errflag,
-                  ctx->d_partials_srv_res, ctx->d_counter_srv, ctx->d_flag_srv, ctx->d_pair_base,
-                  ctx->d_pair_lfirst, ctx->d_pair_c, ctx->d_pair_l, ctx->d_vterms, ctx->d_ticket, ctx->d_ticket_srv,
-                  ctx->d_ticket_part, ctx->d_ticket_part_srv};
-  for (void* p : ptrs)
-    if (p) (void)hipFree(p);
-  free_split(&ctx->sp_apply);
-  free_split(&ctx->sp_warm);
-  for (SmallPlan* sp : {&ctx->sm_apply, &ctx->sm_warm})
-    if (sp->d_mem) (void)hipFree(sp->d_mem);
+  if (ctx->d_mem) (void)hipFree(ctx->d_mem);
   delete ctx;
 }
 

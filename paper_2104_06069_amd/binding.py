@@ -118,11 +118,13 @@ def lib():
 
 
 def _addr(t):
-    if t is None:
-        return None
-    if hasattr(t, "data_ptr"):
-        return t.data_ptr()
-    return int(t)
+    if t is None or type(t) is int:
+        return t
+    try:
+        data_ptr = t.data_ptr
+    except AttributeError:
+        return int(t)
+    return data_ptr()
 
 
 def make_state(**buffers):

@@ -22,7 +22,9 @@ import torch
 
 from . import binding as ob
 
-_STATE_FIELDS = tuple(f for f, _ in ob.ObLambState._fields_)
+_STATE_FIELDS = ("x", "m", "v_fresh", "v_frozen", "err_worker", "err_server", "c_avg", "r_prev", "coeff_c", "mom_scale",
+                 "m_packed", "m_scales", "own_packed_in", "own_scale_in", "err_packed", "err_scales", "srv_err_packed",
+                 "srv_err_scale")     # the order in which DeviceStep._state() fills the structure
 _STATE_KEYS = ("x", "m", "v_fresh", "v_frozen", "err_worker", "err_server", "c_avg", "r_prev")
 
 
@@ -123,20 +125,25 @@ class DeviceStep:
         """ob_lamb_state for one call.  momentum: 'read' (source of m_{t-1}) or 'commit'.  (A small model's
         step is as short as the host makes it: the structure is filled in one go, with offsets into
         buffers as numbers instead of slices; every address is looked up anew.)"""
-        b = dict(self.t)   # (a program may have given the dense momentum back, or put pointers of its own in)
+        g = self.t.get      # (a program may have given the dense momentum back, or put pointers of its own in)
+        m, m_packed, m_scales = g("m"), g("m_packed"), g("m_scales")
         if self.packed_momentum and momentum == "commit":
-            b["m"] = None                       # committed in place: packed_all is the momentum
-            b["m_packed"], b["m_scales"] = self.packed_all, self.server_scales
+            m, m_packed, m_scales = None, self.packed_all, self.server_scales   # committed in place: packed_all is the momentum
         elif self.packed_momentum and self.m_is_packed:
-            b["m"] = None
-            b["m_packed"], b["m_scales"] = self._pa[self._prev], self._ss[self._prev]
+            m, m_packed, m_scales = None, self._pa[self._prev], self._ss[self._prev]
+        a = ob._addr
         if self.fold_gather:
-            b["own_packed_in"] = self.packed_in.data_ptr() + self.c * (self.n_c // 8)
-            b["own_scale_in"] = self.scales_in.data_ptr() + 4 * self.c
+            own = self.packed_in.data_ptr() + self.c * (self.n_c // 8), self.scales_in.data_ptr() + 4 * self.c
+        else:
+            own = a(g("own_packed_in")), a(g("own_scale_in"))
         if self.deferred_error:
-            b["err_packed"], b["err_scales"] = self.packed_local, self.scales_local
-            b["srv_err_packed"], b["srv_err_scale"] = self.srv_words, self.srv_scale
-        return ob.ObLambState(*map(ob._addr, map(b.get, _STATE_FIELDS)))
+            errs = (self.packed_local.data_ptr(), self.scales_local.data_ptr(), self.srv_words.data_ptr(),
+                    self.srv_scale.data_ptr())
+        else:
+            errs = a(g("err_packed")), a(g("err_scales")), a(g("srv_err_packed")), a(g("srv_err_scale"))
+        return ob.ObLambState(a(g("x")), a(m), a(g("v_fresh")), a(g("v_frozen")), a(g("err_worker")), a(g("err_server")),
+                              a(g("c_avg")), a(g("r_prev")), a(g("coeff_c")), a(g("mom_scale")), a(m_packed), a(m_scales),
+                              *own, *errs)
 
     def close(self):
         if self.ctx is not None:
@@ -381,7 +388,9 @@ class DeviceStep:
     def step(self, grad, lr):
         """One compression-stage step into the current wire buffers (call begin_step() first and
         fill packed_in / packed_all with what the other ranks sent)."""
-        if all(getattr(getattr(self, k), "__func__", None) is f for k, f in _STEP_CALLS):
+        c = type(self)
+        if ((c.compress_local, c.gather, c.server_reduce, c.ratios_apply) == _STEP_CALLS
+                and self.__dict__.keys().isdisjoint(_STEP_NAMES)):
             state, stream = self._state("read"), self.stream
             self._compress_local(grad, state, stream)
             self.gather()
@@ -401,4 +410,5 @@ class DeviceStep:
 
 
 # step() forms the state once for all of these as they stand here
-_STEP_CALLS = tuple((k, getattr(DeviceStep, k)) for k in ("compress_local", "gather", "server_reduce", "ratios_apply"))
+_STEP_NAMES = ("compress_local", "gather", "server_reduce", "ratios_apply")
+_STEP_CALLS = tuple(getattr(DeviceStep, k) for k in _STEP_NAMES)

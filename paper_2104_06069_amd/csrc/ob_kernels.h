@@ -603,6 +603,8 @@ __device__ __forceinline__ unsigned long long barrier_publish(unsigned long long
 // Bounded wait (thread 0 of a workgroup) for a flag of generation `want`: at most spin_limit polls
 // (0: none, the wait expires at once whatever the flag holds); returns the flag word last read (0
 // if none was).  On expiry *errflag is raised; once it is raised every wait ends within 64 polls.
+// The first 64 polls are SLEEP * 64 clocks apart, the others OB_POLL_SLEEP * 64: how long spin_limit
+// polls take does not depend on the kernel.
 template <int SLEEP = OB_POLL_SLEEP>
 __device__ __forceinline__ unsigned long long barrier_wait(const unsigned long long* flag,
                                                            unsigned int want, unsigned int* errflag,
@@ -616,7 +618,8 @@ __device__ __forceinline__ unsigned long long barrier_wait(const unsigned long l
     f = __hip_atomic_load(flag, __ATOMIC_RELAXED, OB_AGENT);
     if ((unsigned int)(f >> 32) == want) break;
     if ((it & 63) == 63 && __hip_atomic_load(errflag, __ATOMIC_RELAXED, OB_AGENT) != 0u) break;
-    __builtin_amdgcn_s_sleep(SLEEP);
+    if (SLEEP != OB_POLL_SLEEP && it < 64) __builtin_amdgcn_s_sleep(SLEEP);
+    else __builtin_amdgcn_s_sleep(OB_POLL_SLEEP);
   }
   return f;
 }
@@ -2014,7 +2017,7 @@ struct SmallTile {
 };
 // workgroups per CU that the kernels are built for (their registers at each U)
 constexpr int small_min_wg(int u) { return u == 1 ? 8 : (u == 2 ? 5 : 4); }
-constexpr int SMALL_POLL_SLEEP = 2;   // (the whole launch lasts some 10 us: a poll every 128 clocks)
+constexpr int SMALL_POLL_SLEEP = 2;   // (the whole launch lasts some 10 us: at first a poll every 128 clocks)
 struct SmallTab {
   const SmallTile* tiles;
   int n_tiles, tpc, max_seg;

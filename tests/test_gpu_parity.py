@@ -474,14 +474,14 @@ def test_warmup_and_freeze(case, path, wd):
     finish(dev)
 
 
-@pytest.mark.parametrize("packed,fused", [(False, False), (True, True)])
-def test_previous_ratio_outside_its_bounds(packed, fused):
+@pytest.mark.parametrize("packed,fused,max_tiles", [(False, False, None), (True, True, None), (True, True, LARGE)])
+def test_previous_ratio_outside_its_bounds(packed, fused, max_tiles):
     """Algorithm 1 applies line 18 (the window around the previous ratio) before line 19 (r_min,
     r_max); the order shows when a loaded r_prev lies outside [r_min, r_max], and when it is not 1
     the window is a factor, not a distance.  Two steps from previous ratios between 0.05 and 20."""
     _need_gpu()
     cfg = make_case("bert_mini")
-    st, ref, dev = start_pair(cfg, warm_state=True, packed=packed, fused=fused)
+    st, ref, dev = start_pair(cfg, warm_state=True, packed=packed, fused=fused, fused_max_tiles=max_tiles)
     r0 = np.exp(np.random.default_rng(3).uniform(np.log(0.05), np.log(20.0), ref.L)).astype(np.float32)
     assert (r0 < HYPER["r_min"]).sum() >= 3 and (r0 > HYPER["r_max"]).sum() >= 3
     ref.t["r_prev"][...] = r0
@@ -501,14 +501,15 @@ def test_previous_ratio_outside_its_bounds(packed, fused):
     finish(dev)
 
 
-@pytest.mark.parametrize("case,packed,fused", [("odd", False, False), ("tiny", True, True),
-                                               ("bert_mini", True, True), ("bert_mini", False, True)])
-def test_degenerate_values(case, packed, fused):
+@pytest.mark.parametrize("case,packed,fused,max_tiles", [
+    ("odd", False, False, None), ("tiny", True, True, None), ("bert_mini", True, True, None), ("bert_mini", False, True, None),
+    ("tiny", True, True, LARGE), ("bert_mini", True, True, LARGE)])
+def test_degenerate_values(case, packed, fused, max_tiles):
     """Zero chunks, NaN/Inf gradients, zero fresh variance, near-zero layers: IEEE behaviour of the
     device matches the oracle's -- in the plain kernels and in the ones with in-kernel barriers."""
     _need_gpu()
     cfg = make_case(case)
-    st, ref, dev = start_pair(cfg, warm_state=False, packed=packed, fused=fused)
+    st, ref, dev = start_pair(cfg, warm_state=False, packed=packed, fused=fused, fused_max_tiles=max_tiles)
     N = ref.N
     # step 0: all-zero gradient and momentum -> every scale is 0, every bit is 1
     g = np.zeros(cfg["n_pad"], np.float32)
@@ -556,9 +557,10 @@ def test_degenerate_values(case, packed, fused):
     finish(dev)
 
 
-@pytest.mark.parametrize("case,packed,fused", [("bert_mini", False, False), ("bert_mini", True, True),
-                                               ("tiny", True, True)])
-def test_bitwise_reproducible(case, packed, fused):
+@pytest.mark.parametrize("case,packed,fused,max_tiles", [
+    ("bert_mini", False, False, None), ("bert_mini", True, True, None), ("tiny", True, True, None),
+    ("bert_mini", True, True, LARGE), ("tiny", True, True, LARGE)])
+def test_bitwise_reproducible(case, packed, fused, max_tiles):
     """Same inputs twice -> identical bits everywhere (fixed-order reductions, no float atomics; in
     the kernels with barriers the order of arrival does not enter the result).  Two steps, so that
     the second one runs the single-pass ratio+update kernel when the momentum is in 1-bit form."""
@@ -566,7 +568,7 @@ def test_bitwise_reproducible(case, packed, fused):
     cfg = make_case(case)
     outs = []
     for _ in range(2):
-        st, ref, dev = start_pair(cfg, packed=packed, fused=fused)
+        st, ref, dev = start_pair(cfg, packed=packed, fused=fused, fused_max_tiles=max_tiles)
         for t in range(2):
             g = torch.from_numpy(gradient(st, cfg, t)).to(dev.device)
             fw, fs = foreign_worker_chunks(st, cfg, t); fa, fss = foreign_server_chunks(st, cfg, t)
@@ -1093,8 +1095,10 @@ def test_gpu_rank_inside_a_simulated_job(packed, fused, use_k):
     finish(dev)
 
 
-@pytest.mark.parametrize("case,period", [("tiny", 0), ("bert_mini", 0), ("bert_mini", 2), ("tiny", 3), ("big_and_small", 2)])
-def test_step_replayed_from_a_captured_graph(case, period):
+@pytest.mark.parametrize("case,period,max_tiles", [
+    ("tiny", 0, None), ("bert_mini", 0, None), ("bert_mini", 2, None), ("tiny", 3, None), ("big_and_small", 2, 8),
+    ("tiny", 0, LARGE), ("bert_mini", 2, LARGE)])
+def test_step_replayed_from_a_captured_graph(case, period, max_tiles):
     """The barriers of the single-pass kernels number their launches themselves, so a step needs
     nothing from the host that changes from call to call: as many consecutive steps as it takes for
     the buffers to be arranged as at the start (DeviceStep.graph_period: 2 with the 1-bit momentum,
@@ -1105,7 +1109,7 @@ def test_step_replayed_from_a_captured_graph(case, period):
     _need_gpu()
     cfg = make_case(case)
     st, ref, dev = start_pair(cfg, warm_state=False, packed=True, fused=True, deferred=True,
-                              deferred_variance=period, fused_max_tiles=(8 if case == "big_and_small" else None))
+                              deferred_variance=period, fused_max_tiles=max_tiles)
     P = dev.graph_period
     assert P == (2 * period if period else 2)
     n_pad = cfg["n_pad"]
@@ -1173,7 +1177,7 @@ def test_step_replayed_from_a_captured_graph(case, period):
 
 
 
-@pytest.mark.parametrize("seed", list(range(16)))
+@pytest.mark.parametrize("seed", list(range(24)))
 def test_random_layer_lists(seed):
     """Random tensor lists -- empty, tiny, exactly tile-sized, tile-aligned and ragged tensors, random
     W and served chunk, with or without momentum scaling, random size limit of the barrier kernels
@@ -1194,6 +1198,8 @@ def test_random_layer_lists(seed):
     c_srv = int(r.integers(0, W))
     use_k = bool(r.integers(0, 2))
     max_tiles = [None, None, 1, 2, 3][int(r.integers(0, 5))]
+    if seed >= 16:      # the launches of the larger lists without a limit on their tiles
+        max_tiles = LARGE
     st = Streams(seed)
     k = st.uniform_host("mom_scale", 0, pl.L, 0.25, 4.0) if use_k else None
     hyper = dict(HYPER, c_min=1e-3)

@@ -44,6 +44,7 @@ KERNEL_BYTES = {
         "ratios_pass": (12.25, "n_pad"),         # R bits, m bits (1/4), v_fresh, v_frozen (8) + W v_fresh (4)
         "decompress_apply": (12.125, "n_pad"),   # R bits, v_frozen, x (8.125) + W x (4)
         "ratios_apply_resident": (20.25, "fused"),   # R bits x2, v_fresh, v_frozen, x (12.25) + W v_fresh, x (8)
+        "ratios_apply_small": (20.25, "n_pad"),  # the same for the whole of a list that takes one launch
     },
     "both": {
         "sign_pack_error": (8.125, "n_pad"),     # R z (4) + W err (4) + W bits (1/8)
@@ -53,6 +54,7 @@ KERNEL_BYTES = {
         "warmup_moments": (24.0, "n_pad"),       # R g, m, v, x (16) + W m, v (8)
         "warmup_apply": (16.0, "n_pad"),         # R m, v, x (12) + W x (4)
         "warmup_resident": (28.0, "wfused"),     # R g, m, v, x (16) + W m, v, x (12)
+        "warmup_small": (28.0, "n_pad"),
     },
 }
 
@@ -455,12 +457,15 @@ def main():
     if ages_prof:   # mean over the profiled launches, which differ in how many momentum steps they applied
         KB["ratios_apply_hist"] = (hist_kernel_bytes_per_param(ages_prof, ds.vf_period), "fused")
         KB["ratios_apply_hist_lds"] = KB["ratios_apply_hist"]
+        lag = (wl.fused_params + wl.big_params) / float(ds.n_pad)     # what a list in one launch keeps behind, too
+        KB["ratios_apply_small"] = (lag * KB["ratios_apply_hist"][0] + (1.0 - lag) * KB["ratios_apply_small"][0], "n_pad")
         KB["ratios_big_hist"] = (hist_big_ratio_bytes_per_param(ages_prof, ds.vf_period), "big")
     g_less = 2.0 if args.grad_dtype != "f32" else 0.0     # 16-bit gradient read
     x_more = 2.0 if args.x_lp != "none" else 0.0          # 16-bit parameter copy written
-    for k in ("compress_resident", "compress_deferred", "momentum_z_sumsq", "warmup_moments", "warmup_resident"):
+    for k in ("compress_resident", "compress_deferred", "momentum_z_sumsq", "warmup_moments", "warmup_resident", "warmup_small"):
         KB[k] = (KB[k][0] - g_less, KB[k][1])
-    for k in ("decompress_apply", "ratios_apply_resident", "ratios_apply_hist", "ratios_apply_hist_lds", "warmup_apply", "warmup_resident"):
+    for k in ("decompress_apply", "ratios_apply_resident", "ratios_apply_hist", "ratios_apply_hist_lds", "ratios_apply_small",
+              "warmup_apply", "warmup_resident", "warmup_small"):
         if k in KB:
             KB[k] = (KB[k][0] + x_more, KB[k][1])
     fused_params, wfused = wl.fused_params, wl.wfused

@@ -28,6 +28,9 @@ def test_kernel_bytes_are_each_input_once_each_output_once():
     # both in one kernel: v_frozen and the new bits are read once
     assert p["ratios_apply_resident"][0] == p["ratios_pass"][0] + p["decompress_apply"][0] - (4 + bit)
     assert b.KERNEL_BYTES["both"]["warmup_resident"][0] == 16 + 12
+    # the same work on a whole small list in one launch
+    assert p["ratios_apply_small"] == (p["ratios_apply_resident"][0], "n_pad")
+    assert b.KERNEL_BYTES["both"]["warmup_small"] == (16 + 12, "n_pad")
 
 
 def test_step_bytes():

@@ -82,7 +82,9 @@ typedef struct ob_lamb_config {
   uint32_t flags;               /* OB_CFG_* bits */
   int32_t fused_max_tiles;      /* > 0: the kernels with a per-layer barrier leave every layer with more
                                    than this many 8192-element tiles to the plain kernels, even if
-                                   the device could hold more; 0 = the device's limit */
+                                   the device could hold more, and no list, however small and
+                                   whatever the value, takes the one-launch form of
+                                   ob_lamb_ratios_apply / ob_lamb_warmup_step; 0 = the device's limit */
   int32_t spin_limit;           /* bound, in polls, of every device-side wait: 0 = the default
                                    (OB_SPIN_LIMIT_DEFAULT); > 0 = that many, at most the default;
                                    OB_SPIN_NONE = give up without polling (exists so that the expiry
@@ -92,11 +94,12 @@ typedef struct ob_lamb_config {
 /* ob_lamb_config.flags */
 #define OB_CFG_TWO_PASS_COMPRESS 1u   /* ob_lamb_compress_local as two passes through memory and
                                          ob_lamb_server_reduce as three kernels: no chunk barrier */
-#define OB_CFG_NO_FUSED_APPLY 2u      /* ob_lamb_ratios_apply runs the two plain kernels for every layer */
+#define OB_CFG_NO_FUSED_APPLY 2u      /* ob_lamb_ratios_apply runs the two plain kernels for every list and layer */
 #define OB_CFG_TWO_PASS_WARMUP 4u     /* ob_lamb_warmup_step takes two passes for every layer */
 #define OB_CFG_NO_BARRIERS (OB_CFG_TWO_PASS_COMPRESS | OB_CFG_NO_FUSED_APPLY | OB_CFG_TWO_PASS_WARMUP)
 #define OB_SPIN_NONE (-1)
-/* A poll is one 8-byte load plus a sleep of 1024 clocks; at the 2.4 GHz the device runs at, the
+/* A poll is one 8-byte load plus a sleep of 1024 clocks (128 for the first 64 polls in the one-launch
+ * form of small lists); at the 2.4 GHz the device runs at, the
  * default bounds a wait at 2^20 polls = about 0.5 s (about 1 s at the lowest power state's clock). */
 #define OB_SPIN_LIMIT_DEFAULT (1 << 20)
 
@@ -143,7 +146,8 @@ typedef struct ob_lamb_state {
  *     which are the err_packed / err_scales of the next call.  They may be the very same buffers
  *     (err_packed == packed_out, err_scales == scales_out): pass the worker's output buffers and
  *     leave them untouched between the steps.
- * The call is then ONE streaming kernel plus a W-workgroup kernel for the scales: no in-kernel
+ * The call is then ONE streaming kernel plus a W-workgroup kernel for the scales (on lists of few
+ * tiles the streaming kernel's last workgroup of each chunk forms the scale): no in-kernel
  * barrier, nothing read twice.  Results are bit-identical to the other forms.  An err_scales of all
  * zeros makes err_worker an ordinary error buffer (x - (+-0) = x): that is how a run starts, or
  * resumes from a dense error.  ob_lamb_error_dense writes the error itself, delta, to err_out
@@ -153,7 +157,7 @@ ob_status ob_lamb_error_dense(ob_lamb_ctx* ctx, const ob_lamb_state* st, float* 
  * err_server holds zb of the previous ob_lamb_server_reduce, the carried error is err_server -
  * C[zb] decoded from those two buffers, and the call writes the new zb to err_server and its sign
  * words to packed_out and to srv_err_packed (the new scale to scale_out and srv_err_scale): one pass
- * over the chunk plus one workgroup for the scale, no barrier.  A zero srv_err_scale makes err_server
+ * over the chunk plus one workgroup for the scale (a launch of its own, or the last of the pass), no barrier.  A zero srv_err_scale makes err_server
  * an ordinary error.  ob_lamb_server_error_dense writes the error itself to err_out [n_c]. */
 ob_status ob_lamb_server_error_dense(ob_lamb_ctx* ctx, const ob_lamb_state* st, float* err_out,
                                      void* hip_stream);
@@ -246,7 +250,10 @@ ob_status ob_lamb_decompress_apply(ob_lamb_ctx* ctx, const ob_lamb_state* st,
  * Momentum: if st->m is non-NULL it is the source of m_{t-1} and receives m_t (the two kernels of
  * the separate calls run).  If it is NULL the source is (st->m_packed, st->m_scales), which must
  * not be packed_all (OB_ERR_ARG), and nothing is written -- the new momentum is
- * packed_all/server_scales themselves, to be passed as m_packed/m_scales of the next step; then,
+ * packed_all/server_scales themselves, to be passed as m_packed/m_scales of the next step; then a
+ * list whose tiles of 1024, 2048 or 4096 elements all fit on the device at once (at most 80 % of its
+ * workgroup slots: about 3.3 million parameters on 256 CUs) runs as ONE launch with per-layer
+ * barriers, each array read once, unless ob_lamb_config.fused_max_tiles is set.  On larger lists,
  * for every layer that holds whole tiles of 8192 elements and whose such tiles fit on the device at
  * once (at most 80 % of its workgroup slots), a single kernel keeps v_frozen and the sign words of
  * those tiles in registers across a per-layer barrier, so they are read once instead of twice
@@ -254,7 +261,7 @@ ob_status ob_lamb_decompress_apply(ob_lamb_ctx* ctx, const ob_lamb_state* st,
  * the spans where layers meet) takes the two kernels, restricted to it.  Waits are bounded as for
  * ob_lamb_compress_local (ob_lamb_check_device_status).  OB_CFG_NO_FUSED_APPLY in
  * ob_lamb_config.flags forces the two-kernel path for everything, ob_lamb_config.fused_max_tiles = n
- * for every layer with more than n such tiles. */
+ * for every layer with more than n such tiles (and asks for this form on small lists too). */
 ob_status ob_lamb_ratios_apply(ob_lamb_ctx* ctx, const ob_lamb_state* st, const uint32_t* packed_all,
                                const float* server_scales, float lr, void* hip_stream);
 /* The fresh variance in deferred form: ob_lamb_ratios_apply for callers that keep the sign words and
@@ -273,7 +280,8 @@ ob_status ob_lamb_ratios_apply(ob_lamb_ctx* ctx, const ob_lamb_state* st, const 
  * date there, after which the history starts anew (the next call passes n_old = 0).  Everywhere
  * else -- the plain kernels' elements -- st->v_fresh is rewritten at every call as by
  * ob_lamb_ratios_apply and the history is not read (on their 1024-element tiles the ratio pass is
- * bound by its launch shape, not by the bytes it moves).
+ * bound by its launch shape, not by the bytes it moves).  Which elements these are follows from the
+ * configuration alone; a list small enough for the one-launch form keeps the array in the same way.
  *
  * n_old: number of momenta older than the previous one (st->m_packed / st->m_scales) that have been
  * committed since write_v was last 1 (or since ob_lamb_ratios_apply / the LAMB step last wrote
@@ -321,7 +329,9 @@ ob_status ob_lamb_plan_split(const ob_lamb_config* cfg, int64_t max_tiles, uint8
  * tiles of every layer that is not listed and has at least 64 of them -- and 0 elsewhere. */
 ob_status ob_lamb_plan_big_tiles(const ob_lamb_config* cfg, int64_t max_tiles, uint8_t* span_big);
 
-/* Number of layers the single kernel of ob_lamb_ratios_apply takes part in on this device (0..L). */
+/* Number of layers with tiles for the kernel with the per-layer barrier of ob_lamb_ratios_apply on this
+ * device (0..L): the split that ob_lamb_plan_split describes.  A list that takes the one-launch form
+ * has these counts too, although its calls do not use that split. */
 int64_t ob_lamb_fused_layers(const ob_lamb_ctx* ctx);
 /* ... and the number of parameters in its tiles. */
 int64_t ob_lamb_fused_params(const ob_lamb_ctx* ctx);
@@ -329,9 +339,9 @@ int64_t ob_lamb_fused_params(const ob_lamb_ctx* ctx);
  * where ob_lamb_ratios_apply_hist also works from the history (ratio pass only). */
 int64_t ob_lamb_big_tile_params(const ob_lamb_ctx* ctx);
 /* The same two counts for ob_lamb_warmup_step, which reads g, m, v and x once (one kernel with a
- * per-layer barrier that keeps eq. (1)'s update direction and x in registers while the layer's
+ * per-layer barrier that keeps eq. (1)'s update direction and x on the chip while the layer's
  * norms complete) for every layer whose tiles fit on the device, and takes two passes for the
- * rest.  OB_CFG_TWO_PASS_WARMUP in ob_lamb_config.flags forces two passes for every layer. */
+ * rest (a list whose tiles of 1024 to 4096 elements all fit at once: one launch, as above).  OB_CFG_TWO_PASS_WARMUP in ob_lamb_config.flags forces two passes for every layer. */
 int64_t ob_lamb_warmup_fused_layers(const ob_lamb_ctx* ctx);
 int64_t ob_lamb_warmup_fused_params(const ob_lamb_ctx* ctx);
 
@@ -382,7 +392,8 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
  * ob_lamb_compress_local runs as ONE kernel that keeps z in registers across a per-chunk arrival
  * barrier whenever one chunk's workgroups fill at most 80 % of the device (otherwise, or with
  * OB_CFG_TWO_PASS_COMPRESS, as two passes through memory).  ob_lamb_server_reduce,
- * ob_lamb_ratios_apply and ob_lamb_warmup_step have such a form too (per chunk / per layer).  All
+ * ob_lamb_ratios_apply and ob_lamb_warmup_step have such forms too (per chunk / per layer; on small
+ * lists the last two are one launch in which all tiles of the list are resident).  All
  * forms compute the same operations in the same order per element; the two sum-of-squares
  * reductions add the same fp64 terms grouped by different tile sizes, so a scale or norm can differ
  * in its last binary32 bit between forms (about once in 10^8 reductions) -- within the 1e-6 bar,
@@ -397,7 +408,7 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
  * the compute units busy for seconds on end can make a wait expire; shorter interference only slows
  * them down.  Every wait is bounded by ob_lamb_config.spin_limit polls (one 8-byte atomic load,
  * whose round trip to the memory side is of the order of a microsecond, plus a sleep of 1024
- * clocks = 0.43 us at 2.4 GHz): with the default of 2^20 polls a wait lasts 1.5 s at most (3 s at
+ * clocks = 0.43 us at 2.4 GHz; the one-launch forms sleep 128 clocks between their first 64 polls): with the default of 2^20 polls a wait lasts 1.5 s at most (3 s at
  * half the clock), and once one wait has expired every other wait of the context ends within 64
  * polls, so a kernel in which a wait expires still ends about 2 s after its last workgroup started.
  *

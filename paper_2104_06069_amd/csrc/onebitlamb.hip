@@ -662,14 +662,16 @@ SmallShape small_shape(int U, const std::vector<int64_t>& h_off, int64_t n_c, in
 }
 // What sets the tile sizes apart, in ns: a workgroup's own chain of loads and divisions, the arrivals of a layer at
 // its counter, which are served one after the other, and the look-ups with which the threads of a tile that meets
-// several layers go through its spans.  Measured at U = 1 / 2 / 4 (kernel, us; LAMB step, then ratios_apply):
-//   eight tensors of 65536 7.6 / 7.7 / 8.9, 7.5 / 7.9 / 9.8; four of 262144 11.5 / 9.3 / 9.4, 10.3 / 9.0 / 10.0
-//   one of 0.9 M 18.9 / 14.1 / 15.8, 18.2 / 13.4 / 19.0; of 1.6 M 27.5 / 18.2 / 14.7, 27.0 / 18.1 / 14.7 (in
-//   8192-element tiles, k_warmup_resident and k_ratios_apply_resident: 16.5, 14.8)
-//   four of 125000 9.4 / 11.2 / 15.2, 10.6 / 13.8 / 16.9; 0.8 M and ten of 80000 18.4 / 14.1 / 20.1, 20.2 / 16.2 / 23.4
+// several layers go through its spans.
+// Measured at U = 1 / 2 / 4 (kernel, us; LAMB step, then ratios_apply):
+//   eight tensors of 65536 7.7 / 7.6 / 8.8, 7.6 / 8.4 / 10.2; four of 262144 11.3 / 9.1 / 9.5, 10.6 / 9.4 / 10.3
+//   one of 0.9 M 18.6 / 14.0 / 15.9, 17.7 / 13.3 / 16.4; of 1.6 M 27.7 / 17.9 / 14.4, 27.2 / 17.9 / 15.0 (in
+//   8192-element tiles, k_warmup_resident and k_ratios_apply_resident: 16.1, 14.6)
+//   four of 125000 9.0 / 11.2 / 14.4, 9.5 / 12.2 / 14.6; 0.8 M and ten of 80000 17.7 / 14.4 / 20.1, 18.3 / 14.8 / 19.7
 int64_t small_cost(int U, const SmallShape& sh) {
   return (U == 1 ? 0 : U == 2 ? 500 : 2000) + 13 * sh.max_arrivals + 2500 * std::max(sh.mixed_spans - 1, 0);
 }
+
 // Tilings of the tile sizes that a SmallPlan may take, formed when first asked for, and their shapes.
 struct SmallTilings {
   const Tiling& tm;       // U = 1
@@ -688,18 +690,18 @@ struct SmallTilings {
 };
 
 // Chooses and uploads a SmallPlan: of the U whose tiles take at most 80 % of the device's workgroup slots
-// (slots(U, dynamic LDS bytes)) the one of the lowest small_cost, the smallest of equals.  vals: floats of LDS per
-// element of a tile that meets several layers.
+// (slots(U, dynamic LDS bytes)) the one of the lowest small_cost, the smallest of equals.  vals, tables: 4-byte words
+// of LDS per element and per segment of a tile that meets several layers.
 template <class F>
 bool build_small(ob_lamb_ctx* ctx, Workspace* ws, SmallTilings* tilings, const std::vector<int64_t>& h_off,
-                 const std::vector<unsigned char>& lagging, int vals, F slots, SmallPlan* sp) {
+                 const std::vector<unsigned char>& lagging, int vals, int tables, F slots, SmallPlan* sp) {
   static_assert(TILE_MAIN == SPAN, "the TILE_MAIN tiling is that of U = 1");
   int best = 0;
   SmallShape sh;
   for (int U : {1, 2, 4}) {
     const SmallShape& s = tilings->sh[U / 2];
     if (s.n_tiles == 0 || (best && small_cost(U, s) >= small_cost(best, sh))) continue;
-    const size_t bytes = 4 * ((size_t)vals * SPAN * U + 3 * (size_t)s.max_seg);
+    const size_t bytes = 4 * ((size_t)vals * SPAN * U + (size_t)tables * (size_t)s.max_seg);
     int64_t n_slots = 0;
     if (!slots(U, bytes, &n_slots)) return false;
     if (5 * (s.n_tiles + 8) > 4 * n_slots) continue;
@@ -1167,7 +1169,7 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
     };
     SmallTilings tilings(tm, ctx->n_c, ctx->W, L, h_off);
     if (ok && cfg->fused_max_tiles == 0 && !(cfg->flags & OB_CFG_NO_FUSED_APPLY))
-      ok = build_small(ctx, &ws, &tilings, h_off, lagging, 1, [&](int U, size_t bytes, int64_t* n) {
+      ok = build_small(ctx, &ws, &tilings, h_off, lagging, 1, 4, [&](int U, size_t bytes, int64_t* n) {
         bool r = false;
         dispatch_u(U, [&](auto u) {
           constexpr int UU = decltype(u)::value;
@@ -1176,7 +1178,7 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
         return r;
       }, &ctx->sm_apply);
     if (ok && cfg->fused_max_tiles == 0 && !(cfg->flags & OB_CFG_TWO_PASS_WARMUP))
-      ok = build_small(ctx, &ws, &tilings, h_off, std::vector<unsigned char>((size_t)tm.n_tiles, 0), 2,
+      ok = build_small(ctx, &ws, &tilings, h_off, std::vector<unsigned char>((size_t)tm.n_tiles, 0), 2, 3,
                        [&](int U, size_t bytes, int64_t* n) {
         bool r = false;
         dispatch_u(U, [&](auto u) {

@@ -25,6 +25,7 @@ LISTS = {
     "one_large": ([1_600_000], 2),                        # one tensor that meets every tile
     "u2": (EDGES + [1_300_000, 64, 500_000, 7], 5),       # 1.88e6
     "u4": (EDGES + [700_001, 64, 1_300_000, 1_000_000], 4),   # 3.08e6
+    "u4_scaled": ([4097, 3, 8191, 1000] * 150 + [1_100_003], 3),   # 3.09e6: momentum scaling in tiles of several tensors
     "beyond": (EDGES + [1_700_001, 64, 2_300_000], 4),    # 4.08e6: the launches of the larger lists
 }
 
@@ -34,7 +35,7 @@ def _cfg(name):
     pl = ParamList(name, [(f"t{i}", s) for i, s in enumerate(sizes)])
     n_pad = padded_len(pl.N, W)
     return dict(name=name, plist=pl, W=W, n_pad=n_pad, n_c=n_pad // W, grad="student_t3", steps=3,
-                server_chunk=W - 1, use_k=(name in ("edges", "u2")))
+                server_chunk=W - 1, use_k=(name in ("edges", "u2", "u4_scaled")))
 
 
 @pytest.mark.parametrize("period", [0, 3])
@@ -82,17 +83,20 @@ def test_lamb_step_in_one_launch(name, wd):
     finish(dev)
 
 
-@pytest.mark.parametrize("n", [900_000, 1_600_000])
+# One tensor that meets every tile: its 1563 tiles of 1024 elements arrived at one counter, one after the other, in
+# 27 us where the launches of the larger lists take 15 to 17.  Tensors that share tiles, with momentum scaling: 29 us
+# against 24, most of it each element's own divisions by its tensor's coefficient.
 @pytest.mark.parametrize("call", ["warmup_step", "ratios_apply"])
-def test_one_launch_is_no_slower_where_one_tensor_meets_every_tile(call, n):
-    """Every tile of a tensor arrives at one counter, one arrival after the other: 1563 tiles of 1024 elements took
-    27 us where the launches of the larger lists take 15 to 17.  Times of the kernels alone, in turn."""
+@pytest.mark.parametrize("sizes,W", [([900_000], 2), ([1_600_000], 2), ([90_000] * 24, 8)])
+def test_one_launch_is_no_slower_than_those_of_larger_lists(sizes, W, call):
+    """Times of the kernels alone, in turn."""
     _need_gpu()
     import paper_2104_06069_amd as ob
     devs, us = [], [[], []]
     for max_tiles in (None, 1 << 20):
-        dev = DeviceStep(np.array([0, n]), 2, 0, two_pass=True, packed_momentum=True, fused_apply=True,
-                         deferred_error=True, fused_max_tiles=max_tiles, **HYPER)
+        dev = DeviceStep(np.concatenate([[0], np.cumsum(sizes)]), W, 0, two_pass=True, packed_momentum=True, fused_apply=True,
+                         deferred_error=True, fused_max_tiles=max_tiles,
+                         mom_scale=np.linspace(0.5, 2.0, len(sizes)).astype(np.float32), **HYPER)
         for k in ("x", "v_fresh", "v_frozen"):
             dev.t[k].fill_(1e-3)
         dev.m_is_packed = (call == "ratios_apply")      # (a state of constants)
@@ -109,6 +113,6 @@ def test_one_launch_is_no_slower_where_one_tensor_meets_every_tile(call, n):
             prof = ob.ob_lamb_profile_read(dev.ctx)
             t.append(sum(ms for ms, _ in prof.values()))
     one, several = (float(np.median(t[10:])) for t in us)
-    assert one <= 1.25 * several, (one, several)
+    assert one <= 1.1 * several, (one, several)
     for dev in devs:
         finish(dev)

@@ -661,15 +661,16 @@ SmallShape small_shape(int U, const std::vector<int64_t>& h_off, int64_t n_c, in
   return sh;
 }
 // What sets the tile sizes apart, in ns: a workgroup's own chain of loads and divisions, the arrivals of a layer at
-// its counter, which are served one after the other, and the look-ups with which the threads of a tile that meets
-// several layers go through its spans.
+// its counter, which are served one after the other, the look-ups with which the threads of a tile that meets
+// several layers go through its spans, and the segments of such a tile, which its wavefronts finish in turn.
 // Measured at U = 1 / 2 / 4 (kernel, us; LAMB step, then ratios_apply):
 //   eight tensors of 65536 7.7 / 7.6 / 8.8, 7.6 / 8.4 / 10.2; four of 262144 11.3 / 9.1 / 9.5, 10.6 / 9.4 / 10.3
 //   one of 0.9 M 18.6 / 14.0 / 15.9, 17.7 / 13.3 / 16.4; of 1.6 M 27.7 / 17.9 / 14.4, 27.2 / 17.9 / 15.0 (in
 //   8192-element tiles, k_warmup_resident and k_ratios_apply_resident: 16.1, 14.6)
 //   four of 125000 9.0 / 11.2 / 14.4, 9.5 / 12.2 / 14.6; 0.8 M and ten of 80000 17.7 / 14.4 / 20.1, 18.3 / 14.8 / 19.7
+//   3000 of 1 and one of 1.2 M 205 / 394 / 561, 105 / 213 / 306
 int64_t small_cost(int U, const SmallShape& sh) {
-  return (U == 1 ? 0 : U == 2 ? 500 : 2000) + 13 * sh.max_arrivals + 2500 * std::max(sh.mixed_spans - 1, 0);
+  return (U == 1 ? 0 : U == 2 ? 500 : 2000) + 13 * sh.max_arrivals + 2500 * std::max(sh.mixed_spans - 1, 0) + 100 * sh.max_seg;
 }
 
 // Tilings of the tile sizes that a SmallPlan may take, formed when first asked for, and their shapes.

@@ -474,7 +474,7 @@ def main():
         for k in ("warmup_moments", "warmup_apply"):
             KB[k] = (KB[k][0], "rest_w")
         units["rest_w"] = ds.n_pad - wfused
-    if ds.fused_apply and fused_params:   # the plain ratio/update kernels then cover only the remaining layers
+    if ds.fused_apply and (fused_params or wl.big_params):   # the plain ratio/update kernels then cover only what is left
         KB["ratios_pass"] = (KB["ratios_pass"][0], "rest_ratio")
         KB["decompress_apply"] = (KB["decompress_apply"][0], "rest")
         units["rest"] = ds.n_pad - fused_params

@@ -398,8 +398,9 @@ __device__ __forceinline__ void chunk_ticket(const ChunkTicket& tk, double* part
 // DEFER: the whole of lines 6-7 in this one pass, with no wait for the chunk's scale: the carried
 // error arrives in deferred form (PackedErr), z is written over it AS the next deferred error, and
 // the sign words of z are packed and written here as well (they do not depend on the scale); the
-// scale itself follows from the tile partials in k_chunk_scale.  packed_out / pe.bits may be the
-// same buffer: a word is read and rewritten by the same 8 lanes, in program order.
+// scale itself follows from the tile partials, in k_chunk_scale or (TICKET) in the last workgroup of
+// the chunk to finish.  packed_out / pe.bits may be the same buffer: a word is read and rewritten by
+// the same 8 lanes, in program order.
 template <int U, bool HAS_K, bool PACKED_M, int GT = 0, bool DEFER = false, bool TICKET = false>
 __global__ __launch_bounds__(BLOCK) void k_momentum_z_sumsq(
     GradSrc g, const float* __restrict__ m, PackedMom pm,
@@ -2005,8 +2006,8 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
 // (80 % of the workgroup slots) as the other barriers.  The spans that k_ratios_apply_hist would handle
 // from the variance's history ("lagging") do so here too, so that what the v_fresh array holds between two
 // calls does not depend on the kernel; their two values per step are formed by each thread.
-// Measured: four 512x512 tensors 9.0 us (k_ratios_apply_resident 12.6); 37 tensors of 2 to 64000 elements
-// 12.9 us (26 us in three launches, and the gaps between them).
+// Measured: four 512x512 tensors 9.0 us (k_ratios_apply_resident 12.6); 46 tensors of 2 to 64000 elements
+// 10.5 us (26 us in three launches, and the gaps between them).
 // ---------------------------------------------------------------------------------------------
 struct SmallTile {
   int l0;          // layer of the first element
@@ -2771,7 +2772,7 @@ __global__ __launch_bounds__(BLOCK, OB_WU_MINW) void k_warmup_resident(
 // ---------------------------------------------------------------------------------------------
 // Small lists: eq. (1) of the whole buffer in one launch (see k_ratios_apply_small: same tiles, segments
 // and barriers, with the fp64 sums of x^2 and u^2 in place of the maxima).
-// Measured: 2.95 M parameters, binary16 gradient: 26 us (37 us in four launches).
+// Measured: 3.04 M parameters, binary16 gradient: 26 us (37 us in four launches).
 // ---------------------------------------------------------------------------------------------
 struct WarmClip {
   float* coeff_c;

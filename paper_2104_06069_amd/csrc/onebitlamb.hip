@@ -1563,8 +1563,8 @@ ob_status ob_lamb_ratios_apply_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st, con
   }
   LayerSplit& sp = ctx->sp_apply;
   if (!sp.on || !packed_m) {
-    // no tile qualifies, or the momentum is a dense array (the barrier kernel would have to hold it
-    // too, which costs more than the second read of v_frozen saves): the two plain kernels
+    // no tile qualifies, or the momentum is a dense array (the barrier kernel reads and commits the 1-bit
+    // form only): the two plain kernels
     launch_ratios(la, ctx, st, packed_all, server_scales, packed_m, pm, nullptr, ctx->n_tiles, nullptr, true);
     launch_apply(la, ctx, st, packed_all, server_scales, lr, nullptr, ctx->n_tiles, xl);
     return la.ok ? OB_OK : OB_ERR_HIP;

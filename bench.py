@@ -7,7 +7,7 @@ Prints ONE JSON line: the metric on the BERT-Large-shaped list at W = 64, the do
 roofline from HIP-event timings of its launches, per-call and per-kernel times (each kernel also
 against a plain copy kernel's rate measured in the same run), the other benchmark configurations in
 brief (`workloads`), and the CPU oracle timed beside it (serial, and through its multi-threaded
-drivers).  `--gpus N` with N > 1 is refused: this build measures one GPU's share of the
+drivers).  `--gpus N` with N > 1 is refused: this program measures one GPU's share of the
 data-parallel step and uses no collectives.
 """
 import argparse

@@ -510,13 +510,13 @@ def chunks_of(cfg, first, last):
 
 
 def test_bert_large_100_steps_on_windows_with_the_served_chunk(capsys):
-    """configs[2] at its stated length: 100 steps, W = 64; the window holds the served chunk."""
+    """The BERT-Large-shaped list over 100 steps, W = 64; the window holds the served chunk."""
     trajectory_on_windows(capsys, "bert_large", c_srv=33, windows=[(32, 35)], steps=100,
                           must_cover=[])
 
 
 def test_bert_base_100_steps_two_stage_on_windows(capsys):
-    """configs[1] at its stated length: 100 compression steps, W = 16, per-tensor gradient scales
+    """The BERT-Base-shaped list over 100 compression steps, W = 16, per-tensor gradient scales
     spread over a factor of 100, momentum scaling generated on the device after two LAMB steps.
     The window holds the 23.4 M-element word embedding (too large for the kernels with a per-layer
     barrier: plain kernels on tile lists) and the served chunk."""
@@ -527,7 +527,7 @@ def test_bert_base_100_steps_two_stage_on_windows(capsys):
 
 
 def test_gpt_1p3b_50_steps_two_stage_on_windows(capsys):
-    """configs[4] at its stated length: 50 compression steps, W = 128, 1 % of the tensors with
+    """The GPT-1.3B-shaped list over 50 compression steps, W = 128, 1 % of the tensors with
     gradients of 1e-9 (their momentum-scale coefficients, generated on the device after two LAMB
     steps, are about 10^6 times the others').  One window holds the 103 M-element word embedding and
     the position table, the other a whole transformer block (QKV 12.6 M, FFN 16.8 M: the tensors

@@ -253,7 +253,8 @@ ob_status ob_lamb_decompress_apply(ob_lamb_ctx* ctx, const ob_lamb_state* st,
  * packed_all/server_scales themselves, to be passed as m_packed/m_scales of the next step; then a
  * list whose tiles of 1024, 2048 or 4096 elements all fit on the device at once (at most 80 % of its
  * workgroup slots: about 3.3 million parameters on 256 CUs) runs as ONE launch with per-layer
- * barriers, each array read once, unless ob_lamb_config.fused_max_tiles is set.  On larger lists,
+ * barriers, each array read once, unless ob_lamb_config.fused_max_tiles is set or the kernel below
+ * takes every parameter of one very large layer faster.  On larger lists,
  * for every layer that holds whole tiles of 8192 elements and whose such tiles fit on the device at
  * once (at most 80 % of its workgroup slots), a single kernel keeps v_frozen and the sign words of
  * those tiles in registers across a per-layer barrier, so they are read once instead of twice

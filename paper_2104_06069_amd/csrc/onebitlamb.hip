@@ -693,9 +693,17 @@ struct SmallTilings {
 // Chooses and uploads a SmallPlan: of the U whose tiles take at most 80 % of the device's workgroup slots
 // (slots(U, dynamic LDS bytes)) the one of the lowest small_cost, the smallest of equals.  vals, tables: 4-byte words
 // of LDS per element and per segment of a tile that meets several layers.
+// The list keeps the barrier kernel of the larger lists (split) where that is all it takes, every parameter lying in its
+// 8192-element tiles, and one layer has more than max_queue arrivals at its counter here, twice as many as there.
+// The calls of one tensor, or two equal ones, in whole tiles, us, LAMB step, ratios_apply, ratios_apply_hist, in one
+// launch / in the barrier kernel: 1.6 M (391 arrivals) 15.4 / 16.8, 15.9 / 16.0, 16.9 / 17.1; two of 1.6 M (392) 18.9 /
+// 20.3, 19.0 / 19.0, 20.3 / 19.6; 2.4 M (586) 18.5 / 19.4, 18.7 / 18.6, 19.9 / 19.5; 3.2 M (782) 22.4 / 21.5, 22.5 / 20.0,
+// 23.7 / 20.6; with a part outside those tiles, so that the plain kernels run too, 3.2 M 23.0 / 33.2, 22.7 / 27.6, 23.8 / 26.1.
+constexpr int SMALL_QUEUE_APPLY = 512, SMALL_QUEUE_LAMB = 700;
 template <class F>
 bool build_small(ob_lamb_ctx* ctx, Workspace* ws, SmallTilings* tilings, const std::vector<int64_t>& h_off,
-                 const std::vector<unsigned char>& lagging, int vals, int tables, F slots, SmallPlan* sp) {
+                 const std::vector<unsigned char>& lagging, const LayerSplit& split, int max_queue, int vals, int tables,
+                 F slots, SmallPlan* sp) {
   static_assert(TILE_MAIN == SPAN, "the TILE_MAIN tiling is that of U = 1");
   int best = 0;
   SmallShape sh;
@@ -710,6 +718,7 @@ bool build_small(ob_lamb_ctx* ctx, Workspace* ws, SmallTilings* tilings, const s
     sh = s;
     sp->lds_bytes = bytes;
   }
+  if (best && split.on && split.n_rest_tiles == 0 && sh.max_arrivals > max_queue) best = 0;
   const Tiling* tp = best ? tilings->get(best, ctx->n_c, ctx->W, ctx->L, h_off) : nullptr;
   if (tp) {
     const Tiling& t = *tp;
@@ -1170,7 +1179,7 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
     };
     SmallTilings tilings(tm, ctx->n_c, ctx->W, L, h_off);
     if (ok && cfg->fused_max_tiles == 0 && !(cfg->flags & OB_CFG_NO_FUSED_APPLY))
-      ok = build_small(ctx, &ws, &tilings, h_off, lagging, 1, 4, [&](int U, size_t bytes, int64_t* n) {
+      ok = build_small(ctx, &ws, &tilings, h_off, lagging, ctx->sp_apply, SMALL_QUEUE_APPLY, 1, 4, [&](int U, size_t bytes, int64_t* n) {
         bool r = false;
         dispatch_u(U, [&](auto u) {
           constexpr int UU = decltype(u)::value;
@@ -1179,8 +1188,8 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
         return r;
       }, &ctx->sm_apply);
     if (ok && cfg->fused_max_tiles == 0 && !(cfg->flags & OB_CFG_TWO_PASS_WARMUP))
-      ok = build_small(ctx, &ws, &tilings, h_off, std::vector<unsigned char>((size_t)tm.n_tiles, 0), 2, 3,
-                       [&](int U, size_t bytes, int64_t* n) {
+      ok = build_small(ctx, &ws, &tilings, h_off, std::vector<unsigned char>((size_t)tm.n_tiles, 0), ctx->sp_warm,
+                       SMALL_QUEUE_LAMB, 2, 3, [&](int U, size_t bytes, int64_t* n) {
         bool r = false;
         dispatch_u(U, [&](auto u) {
           constexpr int UU = decltype(u)::value;

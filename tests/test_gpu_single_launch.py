@@ -27,7 +27,9 @@ LISTS = {
     "u4": (EDGES + [700_001, 64, 1_300_000, 1_000_000], 4),   # 3.08e6
     "u4_scaled": ([4097, 3, 8191, 1000] * 150 + [1_100_003], 3),   # 3.09e6: momentum scaling in tiles of several tensors
     "beyond": (EDGES + [1_700_001, 64, 2_300_000], 4),    # 4.08e6: the launches of the larger lists
+    "one_in_whole_tiles": ([3_200_000], 4),               # ... a tensor that the barrier kernels take as a whole, too
 }
+LARGER = ("beyond", "one_in_whole_tiles")
 
 
 def _cfg(name):
@@ -55,7 +57,7 @@ def test_ratios_apply_in_one_launch(name, max_tiles, period):
     dev.begin_step()
     dev.ratios_apply(1e-3)
     took = set(ob.ob_lamb_profile_read(dev.ctx))
-    assert ("ratios_apply_small" in took) == (name != "beyond" and max_tiles is None), took
+    assert ("ratios_apply_small" in took) == (name not in LARGER and max_tiles is None), took
     finish(dev)
 
 
@@ -79,15 +81,16 @@ def test_lamb_step_in_one_launch(name, wd):
         for k in ("m", "v_fresh", "x", "coeff_c", "c_avg"):
             assert_close(dev.get(k), ref.t[k], f"step {t}: {k}")
     took = set(ob.ob_lamb_profile_read(dev.ctx))
-    assert ("warmup_small" in took) == (name != "beyond"), took
+    assert ("warmup_small" in took) == (name not in LARGER), took
     finish(dev)
 
 
 # One tensor that meets every tile: its 1563 tiles of 1024 elements arrived at one counter, one after the other, in
 # 27 us where the launches of the larger lists take 15 to 17.  Tensors that share tiles, with momentum scaling: 29 us
-# against 24, most of it each element's own divisions by its tensor's coefficient.
+# against 24, most of it each element's own divisions by its tensor's coefficient.  One tensor in whole 8192-element
+# tiles, all that the barrier kernel takes: 23 us against 20, twice as many arrivals.
 @pytest.mark.parametrize("call", ["warmup_step", "ratios_apply"])
-@pytest.mark.parametrize("sizes,W", [([900_000], 2), ([1_600_000], 2), ([90_000] * 24, 8)])
+@pytest.mark.parametrize("sizes,W", [([900_000], 2), ([1_600_000], 2), ([90_000] * 24, 8), ([3_200_000], 4)])
 def test_one_launch_is_no_slower_than_those_of_larger_lists(sizes, W, call):
     """Times of the kernels alone, in turn."""
     _need_gpu()

@@ -342,7 +342,11 @@ int64_t ob_lamb_big_tile_params(const ob_lamb_ctx* ctx);
 /* The same two counts for ob_lamb_warmup_step, which reads g, m, v and x once (one kernel with a
  * per-layer barrier that keeps eq. (1)'s update direction and x on the chip while the layer's
  * norms complete) for every layer whose tiles fit on the device, and takes two passes for the
- * rest (a list whose tiles of 1024 to 4096 elements all fit at once: one launch, as above).  OB_CFG_TWO_PASS_WARMUP in ob_lamb_config.flags forces two passes for every layer. */
+ * rest (a list whose tiles of 1024 to 4096 elements all fit at once: one launch, as above).  Of the
+ * rest, the whole 8192-element tiles of large layers take both passes in one launch in which a layer's
+ * update follows its moments closely enough to find m, v and x in the memory-side cache; it waits (bounded,
+ * as below) for the layer's norms.  OB_CFG_TWO_PASS_WARMUP in ob_lamb_config.flags forces two passes for every
+ * layer and lets no kernel wait (such tiles then take launches that end between a layer's passes). */
 int64_t ob_lamb_warmup_fused_layers(const ob_lamb_ctx* ctx);
 int64_t ob_lamb_warmup_fused_params(const ob_lamb_ctx* ctx);
 
@@ -394,8 +398,9 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
  * barrier whenever one chunk's workgroups fill at most 80 % of the device (otherwise, or with
  * OB_CFG_TWO_PASS_COMPRESS, as two passes through memory).  ob_lamb_server_reduce,
  * ob_lamb_ratios_apply and ob_lamb_warmup_step have such forms too (per chunk / per layer; on small
- * lists the last two are one launch in which all tiles of the list are resident).  All
- * forms compute the same operations in the same order per element; the two sum-of-squares
+ * lists the last two are one launch in which all tiles of the list are resident); in
+ * ob_lamb_warmup_step, workgroups that update a large layer also wait for workgroups of the same launch that
+ * were dispatched before them, which need not be resident together.  All forms compute the same operations in the same order per element; the two sum-of-squares
  * reductions add the same fp64 terms grouped by different tile sizes, so a scale or norm can differ
  * in its last binary32 bit between forms (about once in 10^8 reductions) -- within the 1e-6 bar,
  * and the sign words that depend on such a scale can then differ for elements within one unit in

@@ -92,17 +92,23 @@ __device__ __forceinline__ unsigned short float_to_lp(float x, int bf16) {
   return __builtin_bit_cast(unsigned short, (_Float16)x);   // hardware convert, round to nearest even
 }
 
-// The thread's 4 gradient values at flat index i (a multiple of 4).
+// The thread's 4 gradient values at flat index i (a multiple of 4): the load, and the values from what it
+// brought.  (Apart, so that a kernel can request everything before it converts anything: the conversion
+// branches on the format, and no load moves across that branch.)
 template <int GT>
-__device__ __forceinline__ v4f load_grad(const GradSrc& gs, int64_t i) {
-  if (GT == 0) return ld4(reinterpret_cast<const float*>(gs.p) + i);
-  const v4h h = __builtin_nontemporal_load(
-      reinterpret_cast<const v4h*>(reinterpret_cast<const unsigned short*>(gs.p) + i));
+__device__ __forceinline__ typename std::conditional<GT == 0, v4f, v4h>::type grad_request(const GradSrc& gs, int64_t i) {
+  if constexpr (GT == 0) return ld4(reinterpret_cast<const float*>(gs.p) + i);
+  else return __builtin_nontemporal_load(reinterpret_cast<const v4h*>(reinterpret_cast<const unsigned short*>(gs.p) + i));
+}
+__device__ __forceinline__ v4f grad_value(const GradSrc&, v4f g) { return g; }
+__device__ __forceinline__ v4f grad_value(const GradSrc& gs, v4h h) {
   v4f r;
 #pragma unroll
   for (int k = 0; k < 4; ++k) r[k] = lp_to_float(h[k], gs.bf16) * gs.scale;
   return r;
 }
+template <int GT>
+__device__ __forceinline__ v4f load_grad(const GradSrc& gs, int64_t i) { return grad_value(gs, grad_request<GT>(gs, i)); }
 
 __device__ __forceinline__ void st4_lp(void* __restrict__ base, int64_t i, v4f v, int bf16) {
   v4h h;
@@ -2517,14 +2523,22 @@ __device__ __forceinline__ float warmup_coeff_commit(double sx, double su, int l
   return c;
 }
 
+struct WarmClip {
+  float* coeff_c;
+  float* c_avg;
+  float c_min, c_max, beta3, omb3;
+};
+
 __global__ __launch_bounds__(FBLOCK) void k_warmup_coeff(const double* __restrict__ seg_sums,
                                                          const int* __restrict__ layer_seg0,
                                                          float* __restrict__ coeff_c,
                                                          float* __restrict__ c_avg, float c_min,
                                                          float c_max, float beta3, float omb3,
-                                                         const unsigned char* __restrict__ done_elsewhere) {
+                                                         const unsigned char* __restrict__ done_elsewhere,
+                                                         unsigned long long* __restrict__ clear_flag) {
   __shared__ double lds[FBLOCK / WAVE];
   const int l = blockIdx.x;
+  if (clear_flag && threadIdx.x == 0) clear_flag[l] = 0ull;   // (of k_warmup_trail, which runs after this kernel)
   if (done_elsewhere && done_elsewhere[l]) return;  // the kernel with the per-layer barrier finishes it
   const int s0 = layer_seg0[l], s1 = layer_seg0[l + 1];
   const float ca = c_avg[l];
@@ -2770,15 +2784,225 @@ __global__ __launch_bounds__(BLOCK, OB_WU_MINW) void k_warmup_resident(
 }
 
 // ---------------------------------------------------------------------------------------------
+// K8 a+b+c for the layers that are too large for k_warmup_resident: moments (a) and update (c) as two kinds
+// of workgroups of one launch, on parts of the 8192-element tiles that lie inside one layer.  Nothing is held
+// on chip in between; the update's reads of m, v and x (12 of 40 bytes per element) come from the
+// memory-side cache instead of HBM: a layer's update follows its moments as closely as its coefficient allows,
+// the moments' stores and their load of x do not bypass that cache, and everything else does.
+//
+// `items` lists the workgroups in the order of dispatch: the parts in position order for the moments, and a
+// layer's parts for the update `lag` parts after its last one (trail_items in the host code).  The last moments
+// workgroup of a layer to finish adds up the sums (arrivals counted in two levels, as in chunk_ticket) and
+// publishes c in flag[l]; an update workgroup fetches its part, forms u and then waits for that flag,
+// which by then is normally there.  Moments workgroups wait for nothing and an update workgroup only for ones
+// dispatched before it, so progress needs in-order dispatch, not co-residency.  Without `wait` the launch
+// ends between a layer's two passes instead.
+//
+// The two passes of a part may run on different XCDs, whose L2 caches do not see each other's lines: the
+// moments store m and v through to memory (agent scope) and wait for the acknowledgements before they arrive,
+// and the update loads them, after it has seen the flag, past its own caches.
+// ---------------------------------------------------------------------------------------------
+constexpr int CACHE_NT = 2, CACHE_AGENT = 16;     // cache policy bits of the buffer builtins (nt, sc1)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t part_rsrc(const float* p, int bytes) {   // p uniform
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, bytes, OB_BUFFER_RSRC_WORD3);
+}
+template <int POLICY>
+__device__ __forceinline__ v4f buf_ld4(__amdgpu_buffer_rsrc_t r, int byte) {
+  return __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(r, byte, 0, POLICY));
+}
+template <int POLICY>
+__device__ __forceinline__ void buf_st4(__amdgpu_buffer_rsrc_t r, int byte, v4f v) {
+  typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), r, byte, 0, POLICY);
+}
+constexpr unsigned int TRAIL_UPDATE = 1u << 31;   // update (else: moments)
+constexpr unsigned int TRAIL_KEEP = 1u << 30;     // moments: read again soon
+constexpr int TRAIL_U = 2;                        // spans per part
+constexpr int TRAIL_PARTS = 8 / TRAIL_U;          // parts per tile
+struct TrailTab {
+  const unsigned int* items;    // of this launch: flags above | tile's position in lt.tile_list * TRAIL_PARTS + part
+  ListedTiles lt;               // the tiles of these layers (positions as for the barrier kernels)
+  const int* count0;            // [L] the layer's first counter: second level, then the first-level ones
+  unsigned int* count;          // lines of CTR_STRIDE 8-byte words
+  double* sub_sums;             // [2 * counters] of the first-level groups
+  double* part_sums;            // [2 * parts]
+  unsigned long long* flag;     // [L] 2^32 | bits of c once known; cleared by an earlier launch of the call
+  const double* seg_sums;       // [2 * segments] sums left by k_warmup_moments
+  unsigned int* errflag;
+  int spin_limit;
+  int wait;                     // an update waits for flag[l] (else: coeff_c[l] is there)
+};
+
+// First wavefront of a moments workgroup; part: its number, sx, su: its sums (lane 0).
+__device__ __forceinline__ bool trail_arrive(unsigned int* counter, unsigned int n, double* payload, double sx, double su) {
+  int last = 0;
+  if ((threadIdx.x & (WAVE - 1)) == 0) {
+    __hip_atomic_store(payload, sx, __ATOMIC_RELAXED, OB_AGENT);
+    __hip_atomic_store(payload + 1, su, __ATOMIC_RELAXED, OB_AGENT);
+    payload_before_arrival();
+    last = (__hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, OB_AGENT) + 1u == n);
+    if (last) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, OB_AGENT);
+  }
+  return __shfl(last, 0, WAVE) != 0;
+}
+// l, lp, c0, ca: the layer, its ranges, first counter and c_avg (read early, where their latency hides).
+__device__ __forceinline__ void trail_finish(const TrailTab& tt, const WarmClip& wc, int part, int l, const LayerParts& lp,
+                                             int64_t c0, float ca, double sx, double su) {
+  constexpr int LINE = 2 * CTR_STRIDE;
+  const int lane = threadIdx.x & (WAVE - 1);
+  const int n_parts = lp.nl * TRAIL_PARTS, part0 = lp.lb * TRAIL_PARTS;
+  const int sub = (part - part0) / TICKET_SUB, first = sub * TICKET_SUB;
+  const int n = (n_parts - first < TICKET_SUB) ? n_parts - first : TICKET_SUB;
+  const int n_sub = (n_parts + TICKET_SUB - 1) / TICKET_SUB;
+  const int64_t cs = c0 + 1 + sub;
+  if (!trail_arrive(tt.count + cs * LINE, (unsigned int)n, &tt.part_sums[2 * (int64_t)part], sx, su)) return;
+  double tx = 0.0, tu = 0.0;
+  if (lane < n) {
+    tx = __hip_atomic_load(&tt.part_sums[2 * ((int64_t)part0 + first + lane)], __ATOMIC_RELAXED, OB_AGENT);
+    tu = __hip_atomic_load(&tt.part_sums[2 * ((int64_t)part0 + first + lane) + 1], __ATOMIC_RELAXED, OB_AGENT);
+  }
+  tx = wave_sum(tx);
+  tu = wave_sum(tu);
+  if (!trail_arrive(tt.count + c0 * LINE, (unsigned int)n_sub, &tt.sub_sums[2 * cs], tx, tu)) return;
+  const double* sub_sums = tt.sub_sums + 2 * (c0 + 1);
+  tx = 0.0; tu = 0.0;
+  for (int s = lane; s < n_sub; s += 4 * WAVE) {   // four pairs in flight (the sums are >= +0: adding zeros changes nothing)
+    double vx[4], vu[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const bool in = (s + q * WAVE < n_sub);
+      vx[q] = in ? __hip_atomic_load(&sub_sums[2 * (s + q * WAVE)], __ATOMIC_RELAXED, OB_AGENT) : 0.0;
+      vu[q] = in ? __hip_atomic_load(&sub_sums[2 * (s + q * WAVE) + 1], __ATOMIC_RELAXED, OB_AGENT) : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) { tx += vx[q]; tu += vu[q]; }
+  }
+  auto plain = [&](int s) {   // written by an earlier kernel
+    tx += tt.seg_sums[2 * (int64_t)s];
+    tu += tt.seg_sums[2 * (int64_t)s + 1];
+  };
+  for (int s = lp.a + lane; s < lp.s_first; s += WAVE) plain(s);
+  for (int s = lp.s_end + lane; s < lp.b; s += WAVE) plain(s);
+  tx = wave_sum(tx);
+  tu = wave_sum(tu);
+  if (lane == 0) {
+    const float c = warmup_coeff_commit(tx, tu, l, ca, wc.coeff_c, wc.c_avg, wc.c_min, wc.c_max, wc.beta3, wc.omb3);
+    __hip_atomic_store(&tt.flag[l], (1ull << 32) | (unsigned long long)__float_as_uint(c), __ATOMIC_RELAXED, OB_AGENT);
+  }
+}
+
+// Bound by HBM and the memory-side cache together (28 bytes per element from one, 12 from the other).  Measured: 1.21e9
+// elements in layers of 12.6, 16.8 and 103 M, bf16: 6870 us, in two passes 8000 to 8300 (4350-4740 + 3470-3590); with nothing
+// kept 7250.  Parts of 1024, 2048 and 4096 elements: 6860, 6870, 6940.  The same pattern of accesses without
+// arithmetic: 6660.
+template <int GT, bool LPX>
+__global__ __launch_bounds__(BLOCK, 8) void k_warmup_trail(
+    GradSrc g, float* __restrict__ m, float* __restrict__ v, float* __restrict__ x, TrailTab tt, WarmClip wc,
+    float beta1, float omb1, float beta2, float omb2, float eta, float wd, float lr, LayerTab lt,
+    void* __restrict__ x_lp, int x_lp_bf16) {
+  constexpr int U = TRAIL_U;
+  __shared__ double lds[BLOCK / WAVE];
+  __shared__ float c_of_layer;
+  const unsigned int item = tt.items[blockIdx.x];
+  const int part = (int)(item & (TRAIL_KEEP - 1u));
+  TilePos p = tile_pos<8 * SPAN>(tt.lt.n_c, tt.lt.tpc, tt.lt.tile_list[part / TRAIL_PARTS]);
+  const int sp0 = p.c * tt.lt.tpc_span + (p.t - p.c * tt.lt.tpc) * 8;  // the tile's first span
+  const int in_tile = (part % TRAIL_PARTS) * (U * SPAN);
+  p.tile0 += in_tile;
+  p.len -= in_tile;            // (a short tile may lack its last parts: <= 0)
+  if (p.len > U * SPAN) p.len = U * SPAN;
+  const int o0 = threadIdx.x * 4;
+  v4f M[U], V[U], X[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) { M[u] = 0.0f; V[u] = 0.0f; X[u] = 0.0f; }
+  const __amdgpu_buffer_rsrc_t rm = part_rsrc(m + p.tile0, U * SPAN * 4), rv = part_rsrc(v + p.tile0, U * SPAN * 4);
+  const int l0 = lt.first_layer[sp0];   // the layer the tile lies in (lt.first_layer: of the 1024-element tiling)
+  if (item & TRAIL_UPDATE) {
+    if (p.len <= 0) return;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int o = u * SPAN + o0;
+      if (o < p.len) X[u] = ld4(x + p.tile0 + o);
+    }
+    if (threadIdx.x == 0)
+      c_of_layer = tt.wait ? __uint_as_float((unsigned int)(barrier_wait(&tt.flag[l0], 1u, tt.errflag, tt.spin_limit) & 0xffffffffull))
+                           : wc.coeff_c[l0];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int o = u * SPAN + o0;
+      if (o < p.len) {
+        M[u] = buf_ld4<CACHE_AGENT | CACHE_NT>(rm, 4 * o);
+        V[u] = buf_ld4<CACHE_AGENT | CACHE_NT>(rv, 4 * o);
+      }
+    }
+    const float a = lr * c_of_layer;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int o = u * SPAN + o0;
+      if (o < p.len) {
+        v4f xn;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) xn[k] = X[u][k] - a * lamb_u(M[u][k], V[u][k], X[u][k], eta, wd);
+        st4(x + p.tile0 + o, xn);
+        if (LPX) st4_lp(x_lp, p.tile0 + o, xn, x_lp_bf16);
+      }
+    }
+    return;
+  }
+  const bool keep = (item & TRAIL_KEEP) != 0;   // uniform
+  const LayerParts lp = layer_parts(tt.lt, l0);
+  const int64_t count0 = tt.count0[l0];
+  const float ca = wc.c_avg[l0];
+  decltype(grad_request<GT>(g, 0)) GR[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int o = u * SPAN + o0;
+    if (o < p.len) {
+      GR[u] = grad_request<GT>(g, p.tile0 + o);
+      M[u] = ld4(m + p.tile0 + o);
+      V[u] = ld4(v + p.tile0 + o);
+      if (keep) X[u] = *reinterpret_cast<const v4f*>(x + p.tile0 + o);
+      else X[u] = ld4(x + p.tile0 + o);
+    }
+  }
+  double sx = 0.0, su = 0.0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int o = u * SPAN + o0;
+    if (o < p.len) {
+      const v4f G = grad_value(g, GR[u]);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        M[u][k] = beta1 * M[u][k] + omb1 * G[k];
+        V[u][k] = beta2 * V[u][k] + omb2 * (G[k] * G[k]);
+      }
+      if (keep) {
+        buf_st4<CACHE_AGENT>(rm, 4 * o, M[u]);
+        buf_st4<CACHE_AGENT>(rv, 4 * o, V[u]);
+      } else {
+        buf_st4<CACHE_AGENT | CACHE_NT>(rm, 4 * o, M[u]);
+        buf_st4<CACHE_AGENT | CACHE_NT>(rv, 4 * o, V[u]);
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float uu = lamb_u(M[u][k], V[u][k], X[u][k], eta, wd);
+        sx += (double)X[u][k] * (double)X[u][k];
+        su += (double)uu * (double)uu;
+      }
+    }
+  }
+  payload_before_arrival();   // (every wavefront's stores, before the barriers inside)
+  sx = block_sum(sx, lds);
+  su = block_sum(su, lds);
+  if (threadIdx.x < WAVE) trail_finish(tt, wc, part, l0, lp, count0, ca, sx, su);
+}
+
+// ---------------------------------------------------------------------------------------------
 // Small lists: eq. (1) of the whole buffer in one launch (see k_ratios_apply_small: same tiles, segments
 // and barriers, with the fp64 sums of x^2 and u^2 in place of the maxima).
 // Measured: 3.04 M parameters, binary16 gradient: 26 us (37 us in four launches).
 // ---------------------------------------------------------------------------------------------
-struct WarmClip {
-  float* coeff_c;
-  float* c_avg;
-  float c_min, c_max, beta3, omb3;
-};
 template <int U, int GT, bool LPX>
 __global__ __launch_bounds__(BLOCK, small_min_wg(U)) void k_warmup_small(
     GradSrc g, float* __restrict__ m, float* __restrict__ v, float* __restrict__ x, SmallTab sm, WarmClip wc,

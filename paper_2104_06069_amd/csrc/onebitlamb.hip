@@ -111,6 +111,7 @@ enum KernelId {
   KID_WARMUP_COEFF,
   KID_WARMUP_APPLY,
   KID_WARMUP_RESIDENT,
+  KID_WARMUP_TRAIL,
   KID_FILL,
   KID_COPY,
   KID_COUNT
@@ -119,7 +120,7 @@ const char* const kKernelNames[KID_COUNT] = {
     "momentum_z_sumsq", "compress_resident", "chunk_scale",     "sign_pack_error", "compress_deferred", "server_unpack_avg",
     "server_scale",     "server_sign_pack", "server_resident", "ratios_pass",     "ratios_finalize",
     "decompress_apply", "ratios_apply_resident", "ratios_apply_hist", "ratios_apply_hist_lds", "ratios_apply_small", "warmup_small", "variance_dense", "variance_terms", "ratios_big_hist", "momentum_dense", "error_dense", "momentum_scale", "warmup_moments",   "warmup_coeff",    "warmup_apply",
-    "warmup_resident",  "fill",            "copy"};
+    "warmup_resident",  "warmup_trail", "fill",            "copy"};
 
 // Single-launch form of a list whose tiles all fit on the device at once (k_ratios_apply_small,
 // k_warmup_small).
@@ -172,6 +173,20 @@ struct LayerSplit {
   int n_big_tiles = 0;
   int64_t n_big_params = 0;
   int* d_big_tiles = nullptr;
+  // k_warmup_trail over them: its workgroups in order, and the end of each launch's share
+  bool trail_wait = false;
+  unsigned int* d_items = nullptr;
+  std::vector<int64_t> item_end;
+  int* d_big_n = nullptr;                  // [L] big tiles of each layer
+  int* d_big_begin = nullptr;              // [L] position of the first
+  int* d_big_seg_first = nullptr;          // [L] first / one past the last segment that they cover
+  int* d_big_seg_end = nullptr;
+  int* d_count0 = nullptr;                 // [L] first counter
+  unsigned int* d_count = nullptr;         // [counters] lines
+  double* d_sub_sums = nullptr;            // [2 * counters]
+  double* d_part_sums = nullptr;           // [2 * parts]
+  unsigned long long* d_trail_flag = nullptr;   // [L]
+  unsigned char* d_has_tiles = nullptr;    // [L] 1 for layers with listed or big tiles
   int n_rest_ratio_tiles = 0;              // TILE_MAIN tiles outside the listed and the big tiles
   int* d_rest_ratio_tiles = nullptr;
   int n_cov_tiles = 0;                     // TILE_MAIN tiles inside the listed or the big tiles
@@ -495,15 +510,22 @@ struct SplitPlan {
   std::vector<int> fused_tiles, rest_tiles, n_listed, list_begin, seg_first, seg_end;
   std::vector<unsigned char> covered;      // [TILE_MAIN tiles] 1 inside a listed tile
   std::vector<int> big_tiles, rest_ratio_tiles;
+  std::vector<int> big_n, big_begin, big_seg_first, big_seg_end;   // [L]
   std::vector<unsigned char> covered_big;  // [TILE_MAIN tiles] 1 inside a big tile
   int64_t n_layers = 0, n_params = 0, n_big_params = 0;
+};
+
+// Which layers outside the barrier kernel have big tiles: those with enough whole tiles and not too many,
+// and only if they hold enough together.
+struct BigRule {
+  int64_t min_tiles = OB_BIG_MIN_TILES, max_tiles = std::numeric_limits<int64_t>::max(), min_total = 0;
 };
 
 // tl / tm: the barrier kernel's tiling (tiles of tile_lb elements) and the TILE_MAIN tiling;
 // max_tiles: the largest number of tiles of one layer the barrier kernel may hold (0: it is not
 // used).  No HIP call.
 void plan_split(const Tiling& tl, int64_t tile_lb, const Tiling& tm, const std::vector<int64_t>& h_off,
-                int64_t n_c, int64_t L, int64_t max_tiles, SplitPlan* pl) {
+                int64_t n_c, int64_t L, int64_t max_tiles, const BigRule& rule, SplitPlan* pl) {
   pl->has_listed.assign((size_t)L, 0);
   pl->n_listed.assign((size_t)L, 0);
   pl->list_begin.assign((size_t)L, 0);
@@ -548,9 +570,18 @@ void plan_split(const Tiling& tl, int64_t tile_lb, const Tiling& tm, const std::
   }
   // big tiles: the whole tiles of the layers that hold many of them but are not listed
   pl->covered_big.assign((size_t)tm.n_tiles, 0);
+  for (std::vector<int>* v : {&pl->big_n, &pl->big_begin, &pl->big_seg_first, &pl->big_seg_end}) v->assign((size_t)L, 0);
+  auto is_big = [&](int64_t l) {
+    const int64_t n = (int64_t)inside[(size_t)l].size();
+    return !pl->has_listed[(size_t)l] && n >= rule.min_tiles && n <= rule.max_tiles;
+  };
+  int64_t n_big = 0;
+  for (int64_t l = 0; l < L; ++l) n_big += is_big(l) ? (int64_t)inside[(size_t)l].size() : 0;
   for (int64_t l = 0; l < L; ++l) {   // (also when no layer is listed: the pass needs no barrier)
+    if (!is_big(l) || n_big < rule.min_total) continue;
     const std::vector<int>& in = inside[(size_t)l];
-    if (pl->has_listed[(size_t)l] || in.size() < (size_t)OB_BIG_MIN_TILES) continue;
+    pl->big_n[(size_t)l] = (int)in.size();
+    pl->big_begin[(size_t)l] = (int)pl->big_tiles.size();
     for (int t : in) {
       int64_t tile0, tile1;
       tile_range(t, &tile0, &tile1);
@@ -560,6 +591,8 @@ void plan_split(const Tiling& tl, int64_t tile_lb, const Tiling& tm, const std::
       const int64_t span0 = c * tm.tpc + b * (tile_lb / TILE_MAIN);
       const int64_t nspan = (tile1 - tile0 + TILE_MAIN - 1) / TILE_MAIN;
       for (int64_t j2 = 0; j2 < nspan; ++j2) pl->covered_big[(size_t)(span0 + j2)] = 1;
+      if (t == in.front()) pl->big_seg_first[(size_t)l] = tm.tile_seg0[(size_t)span0];
+      pl->big_seg_end[(size_t)l] = tm.tile_seg0[(size_t)(span0 + nspan)];
     }
   }
   for (int64_t t = 0; t < tm.n_tiles; ++t)
@@ -569,13 +602,91 @@ void plan_split(const Tiling& tl, int64_t tile_lb, const Tiling& tm, const std::
     }
 }
 
+// Which layers k_warmup_trail takes, and how.  A LAMB step, us, in two passes over everything outside the barrier
+// kernel / with k_warmup_trail (256 CUs; fp32 gradient except gpt, 16-bit there):
+//   in one launch: squares of 3300 x 1 75.7 / 78.2, 4000 x 1 115 / 109, 3400 x 2 156 / 151, 5000 x 1 173 / 160, 4000 x 3 313 / 286,
+//     5000 x 8 1335 / 1175, 7000 x 6 1930 / 1838, 20000 x 2 5400 / 5520; the GPT list of 1.3e9 parameters 8490 / 7400
+//   in several launches (no kernel may wait): BERT and GPT lists of 11 M 80 / 87, 25 M 152 / 160, 40 M 273 / 275,
+//     50 M 353 / 332, 60 M 400 / 386, 110 M 733 / 681, 336 M 2218 / 2056, 1.3e9 8800 / 8010
+// so that it is taken from 14.7 M and 42 M elements on, and not for layers of which the cache holds next to nothing.
+// A configuration that lowers the barrier kernels' limit (cap) takes it for lists of any size.
+constexpr int64_t TRAIL_MIN_TILES = 1792, TRAIL_MIN_TILES_NO_WAIT = 5120, TRAIL_MAX_LAYER_TILES = 16384;
+BigRule trail_rule(bool wait, int32_t cap) {
+  BigRule r;
+  r.max_tiles = TRAIL_MAX_LAYER_TILES;
+  r.min_total = cap > 0 ? 0 : wait ? TRAIL_MIN_TILES : TRAIL_MIN_TILES_NO_WAIT;
+  return r;
+}
+
+// The workgroups of k_warmup_trail in order (no HIP call).  n, begin: parts of each layer.  lag > 0: one launch, the
+// update of a layer `lag` moments parts after the layer's last one: what is in flight on the device then (2048
+// workgroups) lies between them, so that no update waits for long (half of that 2 % slower, twice no difference).  lag = 0: no update
+// waits; the layers are taken in groups of at least `group` parts (16.8 M elements; 33 M no difference), and a launch updates one
+// group and forms the moments of the next.
+// A layer of more than TRAIL_KEEP_PARTS parts (16.8 M elements, 200 MB of m, v and x) does not fit the cache: its last
+// parts are updated first, and only they are kept.
+constexpr int64_t TRAIL_LAG = 2560, TRAIL_GROUP = 8192, TRAIL_KEEP_PARTS = 8192;
+void trail_items(const std::vector<int>& n, const std::vector<int>& begin, int64_t lag, int64_t group,
+                 std::vector<unsigned int>* items, std::vector<int64_t>* item_end) {
+  items->clear();
+  item_end->clear();
+  auto moments = [&](int64_t l) {
+    const int64_t keep = n[(size_t)l] - std::min<int64_t>(n[(size_t)l], TRAIL_KEEP_PARTS);
+    for (int64_t j = 0; j < n[(size_t)l]; ++j)
+      items->push_back((unsigned int)(begin[(size_t)l] + j) | (j >= keep ? TRAIL_KEEP : 0u));
+  };
+  auto update = [&](int64_t l) {
+    const int64_t keep = n[(size_t)l] - std::min<int64_t>(n[(size_t)l], TRAIL_KEEP_PARTS);
+    for (int64_t j = keep; j < n[(size_t)l]; ++j) items->push_back((unsigned int)(begin[(size_t)l] + j) | TRAIL_UPDATE);
+    for (int64_t j = 0; j < keep; ++j) items->push_back((unsigned int)(begin[(size_t)l] + j) | TRAIL_UPDATE);
+  };
+  std::vector<int64_t> layers;
+  for (size_t l = 0; l < n.size(); ++l)
+    if (n[l] > 0) layers.push_back((int64_t)l);
+  if (layers.empty()) return;
+  if (lag > 0) {
+    size_t done = 0;   // layers whose update is in the list
+    for (size_t i = 0; i < layers.size(); ++i) {
+      const size_t first = items->size();
+      moments(layers[i]);
+      // the updates that become due among this layer's moments parts go in between
+      const std::vector<unsigned int> tiles(items->begin() + (int64_t)first, items->end());
+      items->resize(first);
+      const int64_t at0 = begin[(size_t)layers[i]];   // moments parts before this layer
+      size_t j = 0;
+      for (; done < i; ++done) {
+        const int64_t due = begin[(size_t)layers[done]] + n[(size_t)layers[done]] + lag;
+        if (due > at0 + (int64_t)tiles.size()) break;
+        for (; at0 + (int64_t)j < due; ++j) items->push_back(tiles[j]);
+        update(layers[done]);
+      }
+      for (; j < tiles.size(); ++j) items->push_back(tiles[j]);
+    }
+    for (; done < layers.size(); ++done) update(layers[done]);
+    item_end->push_back((int64_t)items->size());
+    return;
+  }
+  size_t from = 0, updated = 0;
+  while (from < layers.size()) {
+    size_t to = from;
+    int64_t tiles = 0;
+    while (to < layers.size() && tiles < group) tiles += n[(size_t)layers[to++]];
+    for (; updated < from; ++updated) update(layers[updated]);
+    for (size_t i = from; i < to; ++i) moments(layers[i]);
+    item_end->push_back((int64_t)items->size());
+    from = to;
+  }
+  for (; updated < layers.size(); ++updated) update(layers[updated]);
+  item_end->push_back((int64_t)items->size());
+}
+
 // Plans and uploads one LayerSplit.
 void build_split(ob_lamb_ctx* ctx, Workspace* ws, const Tiling& tl, int tile_lb, const Tiling& tm,
-                 const std::vector<int64_t>& h_off, int64_t max_tiles, LayerSplit* sp,
+                 const std::vector<int64_t>& h_off, int64_t max_tiles, const BigRule& rule, bool trail, LayerSplit* sp,
                  std::vector<unsigned char>* lagging) {
   const int64_t L = ctx->L;
   SplitPlan pl;
-  plan_split(tl, tile_lb, tm, h_off, ctx->n_c, L, max_tiles, &pl);
+  plan_split(tl, tile_lb, tm, h_off, ctx->n_c, L, max_tiles, rule, &pl);
   sp->tile = tile_lb;
   sp->tpc = (int)tl.tpc;
   sp->n_layers = pl.n_layers;
@@ -593,6 +704,35 @@ void build_split(ob_lamb_ctx* ctx, Workspace* ws, const Tiling& tl, int tile_lb,
   sp->n_rest_ratio_tiles = (int)pl.rest_ratio_tiles.size();
   lagging->assign((size_t)tm.n_tiles, 0);
   for (int t : cov) (*lagging)[(size_t)t] = 1;
+  if (trail && sp->big_on) {
+    static_assert(TILE_WU == 8 * SPAN, "k_warmup_trail's tiles");
+    std::vector<int> n = pl.big_n, begin = pl.big_begin;   // in parts
+    for (int& q : n) q *= TRAIL_PARTS;
+    for (int& q : begin) q *= TRAIL_PARTS;
+    std::vector<unsigned int> items;
+    sp->trail_wait = max_tiles > 0;
+    trail_items(n, begin, sp->trail_wait ? TRAIL_LAG : 0, TRAIL_GROUP, &items, &sp->item_end);
+    ws->upload(&sp->d_items, std::move(items));
+    std::vector<int> count0((size_t)L, 0);
+    std::vector<unsigned char> has_tiles = pl.has_listed;
+    int counters = 0;
+    for (int64_t l = 0; l < L; ++l) {
+      count0[(size_t)l] = counters;
+      if (n[(size_t)l] == 0) continue;
+      has_tiles[(size_t)l] = 1;
+      counters += 1 + (n[(size_t)l] + TICKET_SUB - 1) / TICKET_SUB;
+    }
+    ws->upload(&sp->d_count0, std::move(count0));
+    ws->upload(&sp->d_has_tiles, std::move(has_tiles));
+    ws->upload(&sp->d_big_n, std::move(pl.big_n));
+    ws->upload(&sp->d_big_begin, std::move(pl.big_begin));
+    ws->upload(&sp->d_big_seg_first, std::move(pl.big_seg_first));
+    ws->upload(&sp->d_big_seg_end, std::move(pl.big_seg_end));
+    ws->alloc_zero(&sp->d_count, (size_t)counters * 2 * CTR_STRIDE);
+    ws->alloc_zero(&sp->d_sub_sums, 2 * (size_t)counters);
+    ws->alloc_zero(&sp->d_part_sums, 2 * (size_t)TRAIL_PARTS * (size_t)sp->n_big_tiles);
+    ws->alloc_zero(&sp->d_trail_flag, (size_t)L);
+  }
   ws->upload(&sp->d_cov_tiles, std::move(cov));
   ws->upload(&sp->d_big_tiles, std::move(pl.big_tiles));
   ws->upload(&sp->d_rest_ratio_tiles, std::move(pl.rest_ratio_tiles));
@@ -1001,7 +1141,7 @@ ob_status ob_lamb_plan_split(const ob_lamb_config* cfg, int64_t max_tiles, uint8
     if (!build_tiling(TILE_MAIN, n_c, W, L, h_off, &tm) || !build_tiling(TILE_LB, n_c, W, L, h_off, &tl))
       return OB_ERR_ARG;
     SplitPlan pl;
-    plan_split(tl, TILE_LB, tm, h_off, n_c, L, max_tiles, &pl);
+    plan_split(tl, TILE_LB, tm, h_off, n_c, L, max_tiles, BigRule(), &pl);
     for (int64_t t = 0; t < tm.n_tiles; ++t) span_owner[t] = pl.covered[(size_t)t] ? 2 : 0;
     for (int t : pl.rest_tiles) span_owner[t] = 1;
     for (int64_t l = 0; l < L; ++l) layer_listed[l] = pl.n_listed[(size_t)l];
@@ -1023,7 +1163,7 @@ ob_status ob_lamb_plan_big_tiles(const ob_lamb_config* cfg, int64_t max_tiles, u
     if (!build_tiling(TILE_MAIN, n_c, W, L, h_off, &tm) || !build_tiling(TILE_LB, n_c, W, L, h_off, &tl))
       return OB_ERR_ARG;
     SplitPlan pl;
-    plan_split(tl, TILE_LB, tm, h_off, n_c, L, max_tiles, &pl);
+    plan_split(tl, TILE_LB, tm, h_off, n_c, L, max_tiles, BigRule(), &pl);
     for (int64_t t = 0; t < tm.n_tiles; ++t) span_big[t] = pl.covered_big[(size_t)t] ? 1 : 0;
     return OB_OK;
   } catch (const std::bad_alloc&) {
@@ -1164,8 +1304,8 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
     const int64_t max_w = (cfg->flags & OB_CFG_TWO_PASS_WARMUP)
                               ? 0 : split_max_tiles(std::min(per_cu_w, OB_WU_MINW), cus, cfg->fused_max_tiles);
     std::vector<unsigned char> lagging, unused;
-    build_split(ctx, &ws, tl, TILE_LB, tm, h_off, max_a, &ctx->sp_apply, &lagging);
-    build_split(ctx, &ws, tw, TILE_WU, tm, h_off, max_w, &ctx->sp_warm, &unused);
+    build_split(ctx, &ws, tl, TILE_LB, tm, h_off, max_a, BigRule(), false, &ctx->sp_apply, &lagging);
+    build_split(ctx, &ws, tw, TILE_WU, tm, h_off, max_w, trail_rule(max_w > 0, cfg->fused_max_tiles), true, &ctx->sp_warm, &unused);
     ctx->sp_apply.in_lds = lh_in_lds(ctx->sp_apply.n_fused_tiles, cus);
     // one launch instead of three or four where the whole list fits on the device at once (unless the
     // configuration lowers what the barrier kernels may take)
@@ -1295,9 +1435,9 @@ ob_status ob_lamb_warmup_step_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st, cons
                 ctx->beta2, ctx->omb2, ctx->eta, ctx->wd, lt, ctx->d_tile_seg0, ctx->d_seg_layer, tiles);
     });
   };
-  auto coeff = [&](const unsigned char* done_elsewhere) {
+  auto coeff = [&](const unsigned char* done_elsewhere, unsigned long long* clear_flag) {
     OB_LAUNCH_B(la, KID_WARMUP_COEFF, k_warmup_coeff, (int)ctx->L, FBLOCK, ctx->d_seg_sums, ctx->d_layer_seg0,
-                st->coeff_c, st->c_avg, ctx->c_min, ctx->c_max, ctx->beta3, ctx->omb3, done_elsewhere);
+                st->coeff_c, st->c_avg, ctx->c_min, ctx->c_max, ctx->beta3, ctx->omb3, done_elsewhere, clear_flag);
   };
   auto apply = [&](const int* tiles, int n_launch_tiles) {
     dispatch1(xl.p != nullptr, [&](auto lx) {
@@ -1306,11 +1446,11 @@ ob_status ob_lamb_warmup_step_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st, cons
                 tiles);
     });
   };
+  WarmClip wc;
+  wc.coeff_c = st->coeff_c; wc.c_avg = st->c_avg; wc.c_min = ctx->c_min; wc.c_max = ctx->c_max;
+  wc.beta3 = ctx->beta3; wc.omb3 = ctx->omb3;
   if (ctx->sm_warm.u) {   // one launch
     const SmallPlan& sm = ctx->sm_warm;
-    WarmClip wc;
-    wc.coeff_c = st->coeff_c; wc.c_avg = st->c_avg; wc.c_min = ctx->c_min; wc.c_max = ctx->c_max;
-    wc.beta3 = ctx->beta3; wc.omb3 = ctx->omb3;
     dispatch_u(sm.u, [&](auto u) {
       dispatch2(lpg, xl.p != nullptr, [&](auto lg, auto lx) {
         OB_LAUNCH_S(la, KID_WARMUP_SMALL,
@@ -1323,31 +1463,53 @@ ob_status ob_lamb_warmup_step_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st, cons
     return la.ok ? OB_OK : OB_ERR_HIP;
   }
   LayerSplit& sp = ctx->sp_warm;
-  if (!sp.on) {   // two passes over everything
+  if (!sp.on && !sp.big_on) {   // two passes over everything
     moments(nullptr, ctx->n_tiles);
-    coeff(nullptr);
+    coeff(nullptr, nullptr);
     apply(nullptr, ctx->n_tiles);
     return la.ok ? OB_OK : OB_ERR_HIP;
   }
-  // 1. moments and partial sums of everything outside the listed tiles; the layers without listed
+  // 1. moments and partial sums of everything outside the tiles of the next two kernels; the layers without such
   //    tiles get their c here (an empty layer too), the sums of the others wait in seg_sums
-  moments(sp.d_rest_tiles, sp.n_rest_tiles);
-  if (sp.n_layers < ctx->L) coeff(sp.d_has_listed);
-  // 2. the listed tiles: moments, layer barrier, update
+  const int* rest = sp.big_on ? sp.d_rest_ratio_tiles : sp.d_rest_tiles;
+  const int n_rest = sp.big_on ? sp.n_rest_ratio_tiles : sp.n_rest_tiles;
+  moments(rest, n_rest);
+  if (sp.n_layers < ctx->L) coeff(sp.big_on ? sp.d_has_tiles : sp.d_has_listed, sp.big_on ? sp.d_trail_flag : nullptr);
+  // 2. the layers that are too large for the kernel with the per-layer barrier
+  if (sp.big_on) {
+    TrailTab tt;
+    tt.lt = listed_tiles(ctx, sp);
+    tt.lt.tile_list = sp.d_big_tiles; tt.lt.list_begin = sp.d_big_begin; tt.lt.n_listed = sp.d_big_n;
+    tt.lt.seg_first = sp.d_big_seg_first; tt.lt.seg_end = sp.d_big_seg_end;
+    tt.count0 = sp.d_count0; tt.count = sp.d_count; tt.sub_sums = sp.d_sub_sums; tt.part_sums = sp.d_part_sums;
+    tt.flag = sp.d_trail_flag; tt.seg_sums = ctx->d_seg_sums;
+    tt.errflag = ctx->d_errflag; tt.spin_limit = ctx->spin_limit; tt.wait = sp.trail_wait ? 1 : 0;
+    int64_t from = 0;
+    for (int64_t end : sp.item_end) {
+      tt.items = sp.d_items + from;
+      dispatch2(lpg, xl.p != nullptr, [&](auto lg, auto lx) {
+        OB_LAUNCH(la, KID_WARMUP_TRAIL, (k_warmup_trail<decltype(lg)::value ? 1 : 0, decltype(lx)::value>), (int)(end - from),
+                  gs, st->m, st->v_fresh, st->x, tt, wc, ctx->beta1, ctx->omb1, ctx->beta2, ctx->omb2, ctx->eta, ctx->wd,
+                  lr, lt, xl.p, xl.bf16);
+      });
+      from = end;
+    }
+  }
+  // 3. the listed tiles: moments, layer barrier, update
   WarmSync ws;
   ws.seg_sums = ctx->d_seg_sums; ws.listed_sums = sp.d_listed_sums; ws.lt = listed_tiles(ctx, sp);
   ws.counter = sp.d_counter; ws.flag = sp.d_flag; ws.errflag = ctx->d_errflag;
   ws.spin_limit = ctx->spin_limit;
   ws.coeff_c = st->coeff_c; ws.c_avg = st->c_avg;
   ws.c_min = ctx->c_min; ws.c_max = ctx->c_max; ws.beta3 = ctx->beta3; ws.omb3 = ctx->omb3;
-  dispatch2(lpg, xl.p != nullptr, [&](auto lg, auto lx) {
+  if (sp.on) dispatch2(lpg, xl.p != nullptr, [&](auto lg, auto lx) {
     OB_LAUNCH(la, KID_WARMUP_RESIDENT,
               (k_warmup_resident<U_WU, G_WU, decltype(lg)::value ? 1 : 0, decltype(lx)::value>), sp.n_fused_tiles,
               gs, st->m, st->v_fresh, st->x, ws, ctx->beta1, ctx->omb1, ctx->beta2, ctx->omb2, ctx->eta, ctx->wd,
               lr, lt, xl.p, xl.bf16);
   });
-  // 3. update of everything outside the listed tiles, with the coefficients of steps 1 and 2
-  apply(sp.d_rest_tiles, sp.n_rest_tiles);
+  // 4. update of everything else, with the coefficients of steps 1 to 3
+  apply(rest, n_rest);
   return la.ok ? OB_OK : OB_ERR_HIP;
 }
 

@@ -575,6 +575,7 @@ __global__ __launch_bounds__(BLOCK) void k_sign_pack_error(float* __restrict__ e
 struct ChunkSync {
   double* partials;             // [tiles of the launching kernel]
   unsigned long long* counter;  // [chunks * CTR_STRIDE] (generation << 32) | arrivals
+  unsigned long long* sub;      // [chunks * groups(tiles of a chunk) * CTR_STRIDE] group counters
   unsigned long long* flag;     // [chunks] (generation << 32) | bits of the scale
   unsigned int* errflag;        // [1]
   int spin_limit;
@@ -597,13 +598,43 @@ __device__ __forceinline__ unsigned long long barrier_arrive(unsigned long long*
   return ((unsigned long long)want << 32) | (last ? 1ull : 0ull);
 }
 
-// The last arrival's publication: flag <- (want << 32) | payload, then the counter is re-armed.
+// Whoever completes a counter re-arms it: the next generation, no arrivals.
+__device__ __forceinline__ void barrier_rearm(unsigned long long* counter, int n) {
+  (void)__hip_atomic_fetch_add(counter, (1ull << 32) - (unsigned long long)n, __ATOMIC_RELAXED, OB_AGENT);
+}
+
+// The same for arrival j of n, counted in two levels where there are more than one_level of them: atomics on one
+// cache line are served one after the other, and the tiles of a layer arrive close together.  The last of each ARRIVE_SUB
+// neighbours arrives at `top` for all of them (every payload of the group was in memory before its arrival).
+// sub: the barrier's group counters, CTR_STRIDE words apart; they advance with `top`, one generation a launch.
+// Measured, us, one level / two, a step and a LAMB step: one tensor of 384 tiles 44.2 / 41.9, 25.3 / 23.6; of 512 44.3 / 42.2,
+// 28.6 / 25.8; of 957 67.1 / 64.4, 54.2 / 51.7; two of 512 64.1 / 61.1, 45.6 / 42.2; 954 among small ones 90.0 / 86.4; twelve of
+// 957 565 / 559, 514 / 514.  Up to 256 the second round trip costs what the queue does: one of 256 35.2 / 35.1, four 67.6 / 66.5,
+// twelve 149 / 149; and up to 512 in lists of many rounds of the device, whose tiles arrive spread out: 96 of 128 and 48 of 512
+// 1728 / 1738 (arrivals_one_level in the host code).  Groups of 16 or 64: the same.
+constexpr int ARRIVE_ONE_LEVEL = 256, ARRIVE_SUB = 32;
+__device__ __forceinline__ int top_arrivals(int n, int one_level) { return n > one_level ? (n + ARRIVE_SUB - 1) / ARRIVE_SUB : n; }
+__device__ __forceinline__ unsigned long long barrier_arrive(unsigned long long* top, unsigned long long* sub, int j, int n,
+                                                             int one_level = ARRIVE_ONE_LEVEL) {
+  if (n > one_level) {
+    const int g = j / ARRIVE_SUB, rest = n - g * ARRIVE_SUB;
+    const int m = rest < ARRIVE_SUB ? rest : ARRIVE_SUB;
+    unsigned long long* c = sub + (int64_t)g * CTR_STRIDE;
+    const unsigned long long r = barrier_arrive(c, m);
+    if ((r & 1ull) == 0ull) return r;
+    barrier_rearm(c, m);
+  }
+  return barrier_arrive(top, top_arrivals(n, one_level));
+}
+
+// The publication by the last of n arrivals: flag <- (want << 32) | payload, then the counter is re-armed.
 __device__ __forceinline__ unsigned long long barrier_publish(unsigned long long* flag,
-                                                              unsigned long long* counter, int n,
-                                                              unsigned int want, unsigned int payload) {
+                                                              unsigned long long* top, int n,
+                                                              unsigned int want, unsigned int payload,
+                                                              int one_level = ARRIVE_ONE_LEVEL) {
   const unsigned long long f = ((unsigned long long)want << 32) | (unsigned long long)payload;
   __hip_atomic_store(flag, f, __ATOMIC_RELAXED, OB_AGENT);
-  (void)__hip_atomic_fetch_add(counter, (1ull << 32) - (unsigned long long)n, __ATOMIC_RELAXED, OB_AGENT);
+  barrier_rearm(top, top_arrivals(n, one_level));
   return f;
 }
 
@@ -639,7 +670,8 @@ __device__ __forceinline__ float chunk_barrier_scale(const ChunkSync& cs, int ti
   if (threadIdx.x == 0) {
     __hip_atomic_store(&cs.partials[tile], part, __ATOMIC_RELAXED, OB_AGENT);
     payload_before_arrival();
-    *bc = barrier_arrive(counter, tpc);
+    const int groups = (tpc + ARRIVE_SUB - 1) / ARRIVE_SUB;
+    *bc = barrier_arrive(counter, cs.sub + (int64_t)c * groups * CTR_STRIDE, tile - c * tpc, tpc);
   }
   __syncthreads();
   const bool last = ((*bc & 1ull) != 0ull);
@@ -1322,6 +1354,7 @@ struct ListedTiles {
   const int* layer_seg0;        // [L+1] segments of each layer
   int64_t n_c;
   int tpc, tpc_span;            // tiles of this kernel / spans per chunk
+  int one_level;                // arrivals of a layer that are counted in one level (barrier_arrive)
 };
 
 // The ranges of one layer, read by every workgroup at its start (uniform, next to its other
@@ -1354,11 +1387,16 @@ __device__ __forceinline__ void for_layer_parts(const LayerParts& q, T zero, FL 
   for (int j = q.s_end + threadIdx.x; j < q.b; j += BLOCK) plain(j);
 }
 
+// Where the group counters of layer l begin (in 8-byte words), whose arrivals are first, first + 1, ... in a numbering
+// that runs on from layer to layer: no two layers' groups overlap, and no table is needed.
+__device__ __forceinline__ int64_t group_line(int first, int l) { return (int64_t)(first / ARRIVE_SUB + l) * CTR_STRIDE; }
+
 struct LayerSync {
   const float* seg_max;         // [segments of the 1024-element tiling] maxima left by the plain ratio pass
   float* listed_max;            // [listed tiles] maxima of this launch's tiles
   ListedTiles lt;
   unsigned long long* counter;  // [L * CTR_STRIDE] (generation << 32) | arrivals
+  unsigned long long* sub;      // group counters (group_line)
   unsigned long long* flag;     // [L] (generation << 32) | bits of c_t
   unsigned int* errflag;
   int spin_limit;
@@ -1380,7 +1418,7 @@ __device__ __forceinline__ void layer_arrive(const LayerSync& ls, int bid, int l
   if (threadIdx.x == 0) {
     __hip_atomic_store(&ls.listed_max[bid], r, __ATOMIC_RELAXED, OB_AGENT);
     payload_before_arrival();
-    *bc = barrier_arrive(counter, lp.nl);
+    *bc = barrier_arrive(counter, ls.sub + group_line(lp.lb, l), bid - lp.lb, lp.nl, ls.lt.one_level);
   }
   __syncthreads();
   const bool last = ((*bc & 1ull) != 0ull);
@@ -1400,7 +1438,7 @@ __device__ __forceinline__ void layer_arrive(const LayerSync& ls, int bid, int l
     if (threadIdx.x == 0) {
       const float c = ratio_clip_commit(q, l, rp, ca, ls.r_prev, ls.coeff_c, ls.one_m_thr,
                                         ls.one_p_thr, ls.r_min, ls.r_max);
-      (void)barrier_publish(&ls.flag[l], counter, lp.nl, want, __float_as_uint(c));
+      (void)barrier_publish(&ls.flag[l], counter, lp.nl, want, __float_as_uint(c), ls.lt.one_level);
     }
   }
   // every thread leaves with the generation to wait for in *bc's high word (the last arriver too)
@@ -2027,6 +2065,8 @@ struct SmallTile {
 };
 // workgroups per CU that the kernels are built for (their registers at each U)
 constexpr int small_min_wg(int u) { return u == 1 ? 8 : (u == 2 ? 5 : 4); }
+// Arrivals counted in one level (a LAMB step, us, one level / two: 384 arrivals 26.8 / 27.1, 588 19.5 / 16.5, 706 20.4 / 16.7).
+constexpr int SMALL_ONE_LEVEL = 512;
 constexpr int SMALL_POLL_SLEEP = 2;   // (the whole launch lasts some 10 us: at first a poll every 128 clocks)
 struct SmallTab {
   const SmallTile* tiles;
@@ -2036,6 +2076,7 @@ struct SmallTab {
   const int* layer_seg0;        // [L+1]
   void* partial;                // [segments] float maxima, or [2 * segments] double sums
   unsigned long long* counter;  // [L * CTR_STRIDE]
+  unsigned long long* sub;      // group counters (group_line)
   unsigned long long* flag;     // [L * CTR_STRIDE]
   unsigned int* errflag;
   int spin_limit;
@@ -2080,8 +2121,8 @@ struct SmallSegs {
 // one (if that is another).  store(e): publishes the segment's partial result.  bc[e] = (generation << 32) |
 // (1: the layer's last arrival) | (2: the layer is this segment alone, no barrier).
 template <class F>
-__device__ __forceinline__ void small_arrive(const SmallTab& sm, const SmallTile& ti, int n_end, unsigned long long* bc,
-                                             F store) {
+__device__ __forceinline__ void small_arrive(const SmallTab& sm, const SmallTile& ti, int n_end, const int (&s0_end)[2],
+                                             unsigned long long* bc, F store) {
   const int e = threadIdx.x / WAVE;
   if (e < n_end && (threadIdx.x & (WAVE - 1)) == 0) {
     const int n = e ? ti.n_last : ti.n_first, l = e ? ti.l_last : ti.l0;
@@ -2090,7 +2131,8 @@ __device__ __forceinline__ void small_arrive(const SmallTab& sm, const SmallTile
     } else {
       store(e);
       payload_before_arrival();
-      bc[e] = barrier_arrive(&sm.counter[(int64_t)l * CTR_STRIDE], n);
+      const int s0 = e ? s0_end[1] : s0_end[0], s = ti.seg0 + (e ? ti.nseg - 1 : 0);
+      bc[e] = barrier_arrive(&sm.counter[(int64_t)l * CTR_STRIDE], sm.sub + group_line(s0, l), s - s0, n, SMALL_ONE_LEVEL);
     }
   }
   __syncthreads();
@@ -2235,7 +2277,7 @@ __global__ __launch_bounds__(BLOCK, small_min_wg(U)) void k_ratios_apply_small(
     }
   }
   float* const partial = reinterpret_cast<float*>(sm.partial);
-  small_arrive(sm, ti, n_end, bc, [&](int e) {
+  small_arrive(sm, ti, n_end, s0_end, bc, [&](int e) {
     __hip_atomic_store(&partial[ti.seg0 + (e ? last_seg : 0)], r_end[e], __ATOMIC_RELAXED, OB_AGENT);
   });
   for (int e = 0; e < n_end; ++e) {   // (uniform)
@@ -2257,7 +2299,7 @@ __global__ __launch_bounds__(BLOCK, small_min_wg(U)) void k_ratios_apply_small(
       c_end[e] = c;
       if (bc[e] & 1ull)
         (void)barrier_publish(&sm.flag[(int64_t)l * CTR_STRIDE], &sm.counter[(int64_t)l * CTR_STRIDE], s1 - s0,
-                              (unsigned int)(bc[e] >> 32), __float_as_uint(c));
+                              (unsigned int)(bc[e] >> 32), __float_as_uint(c), SMALL_ONE_LEVEL);
     }
   }
   // while the layers complete: the variance is stored, m_t/(sqrt(v_frozen)+eta) formed in place of v_frozen
@@ -2633,6 +2675,7 @@ struct WarmSync {
   double* listed_sums;          // [2 * listed tiles] sums of this launch's tiles
   ListedTiles lt;
   unsigned long long* counter;  // [L * CTR_STRIDE] (generation << 32) | arrivals
+  unsigned long long* sub;      // group counters (group_line)
   unsigned long long* flag;     // [L] (generation << 32) | bits of c
   unsigned int* errflag;
   int spin_limit;
@@ -2725,7 +2768,7 @@ __global__ __launch_bounds__(BLOCK, OB_WU_MINW) void k_warmup_resident(
     __hip_atomic_store(&ws.listed_sums[2 * (int64_t)blockIdx.x], sx, __ATOMIC_RELAXED, OB_AGENT);
     __hip_atomic_store(&ws.listed_sums[2 * (int64_t)blockIdx.x + 1], su, __ATOMIC_RELAXED, OB_AGENT);
     payload_before_arrival();
-    bc = barrier_arrive(counter, lp.nl);
+    bc = barrier_arrive(counter, ws.sub + group_line(lp.lb, l0), (int)blockIdx.x - lp.lb, lp.nl, ws.lt.one_level);
   }
   __syncthreads();
   const bool last = ((bc & 1ull) != 0ull);
@@ -2761,7 +2804,7 @@ __global__ __launch_bounds__(BLOCK, OB_WU_MINW) void k_warmup_resident(
     if (threadIdx.x == 0) {
       const float cc = warmup_coeff_commit(tx, tu, l0, ca, ws.coeff_c, ws.c_avg, ws.c_min, ws.c_max,
                                            ws.beta3, ws.omb3);
-      bc = barrier_publish(&ws.flag[l0], counter, lp.nl, want, __float_as_uint(cc));
+      bc = barrier_publish(&ws.flag[l0], counter, lp.nl, want, __float_as_uint(cc), ws.lt.one_level);
     }
   } else if (threadIdx.x == 0) {
     bc = barrier_wait(&ws.flag[l0], want, ws.errflag, ws.spin_limit);
@@ -3112,7 +3155,7 @@ __global__ __launch_bounds__(BLOCK, small_min_wg(U)) void k_warmup_small(
   }
   __syncthreads();
   double* const partial = reinterpret_cast<double*>(sm.partial);
-  small_arrive(sm, ti, n_end, bc, [&](int e) {
+  small_arrive(sm, ti, n_end, s0_end, bc, [&](int e) {
     double* q = partial + 2 * (int64_t)(ti.seg0 + (e ? last_seg : 0));
     __hip_atomic_store(q, end_sum[e][0], __ATOMIC_RELAXED, OB_AGENT);
     __hip_atomic_store(q + 1, end_sum[e][1], __ATOMIC_RELAXED, OB_AGENT);
@@ -3136,7 +3179,7 @@ __global__ __launch_bounds__(BLOCK, small_min_wg(U)) void k_warmup_small(
       c_end[e] = c;
       if (bc[e] & 1ull)
         (void)barrier_publish(&sm.flag[(int64_t)l * CTR_STRIDE], &sm.counter[(int64_t)l * CTR_STRIDE], s1 - s0,
-                              (unsigned int)(bc[e] >> 32), __float_as_uint(c));
+                              (unsigned int)(bc[e] >> 32), __float_as_uint(c), SMALL_ONE_LEVEL);
     }
   }
   // while the layers complete: the moments are stored

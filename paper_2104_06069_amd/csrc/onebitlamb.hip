@@ -134,6 +134,7 @@ struct SmallPlan {
   int* d_layer_seg0 = nullptr;
   double* d_partial = nullptr;          // [2 * segments]
   unsigned long long* d_counter = nullptr;
+  unsigned long long* d_sub = nullptr;
   unsigned long long* d_flag = nullptr;
 };
 
@@ -193,6 +194,7 @@ struct LayerSplit {
   int* d_cov_tiles = nullptr;
   unsigned char* d_has_listed = nullptr;   // [L] 1 for layers that the barrier kernel finishes
   unsigned long long* d_counter = nullptr; // [L * CTR_STRIDE] (generation << 32) | arrivals
+  unsigned long long* d_sub = nullptr;     // [group_lines(n_fused_tiles, L) * CTR_STRIDE] group counters
   unsigned long long* d_flag = nullptr;    // [L] (generation << 32) | payload
 };
 
@@ -234,6 +236,7 @@ struct ob_lamb_ctx {
   int* d_first_layer_res = nullptr;        // [n_tiles_res]
   double* d_partials_res = nullptr;        // [n_tiles_res]
   unsigned long long* d_counter = nullptr; // [W * CTR_STRIDE] (generation << 32) | arrivals
+  unsigned long long* d_sub = nullptr;     // [W * groups(tpc_res) * CTR_STRIDE] group counters
   unsigned long long* d_flag = nullptr;    // [W] (generation << 32) | scale bits
   unsigned int* d_errflag = nullptr;       // [1] raised when a bounded wait expired
   // single-pass server kernel (k_server_resident): selected at create when all of its workgroups
@@ -242,6 +245,7 @@ struct ob_lamb_ctx {
   int tpc_srv_res = 0;                         // such tiles of the server chunk
   double* d_partials_srv_res = nullptr;        // [tpc_srv_res]
   unsigned long long* d_counter_srv = nullptr; // [CTR_STRIDE]
+  unsigned long long* d_sub_srv = nullptr;     // [groups(tpc_srv_res) * CTR_STRIDE]
   unsigned long long* d_flag_srv = nullptr;    // [1]
   int spin_limit = OB_SPIN_LIMIT_DEFAULT;
   // kernels with a per-layer barrier (k_ratios_apply_resident, k_warmup_resident): their common
@@ -680,6 +684,10 @@ void trail_items(const std::vector<int>& n, const std::vector<int>& begin, int64
   item_end->push_back((int64_t)items->size());
 }
 
+// Group counters of a barrier with n arrivals, and of the barriers of L layers with n together (group_line).
+size_t arrival_groups(int64_t n) { return (size_t)((n + ARRIVE_SUB - 1) / ARRIVE_SUB); }
+size_t group_lines(int64_t n, int64_t L) { return arrival_groups(n) + (size_t)L; }
+
 // Plans and uploads one LayerSplit.
 void build_split(ob_lamb_ctx* ctx, Workspace* ws, const Tiling& tl, int tile_lb, const Tiling& tm,
                  const std::vector<int64_t>& h_off, int64_t max_tiles, const BigRule& rule, bool trail, LayerSplit* sp,
@@ -746,6 +754,7 @@ void build_split(ob_lamb_ctx* ctx, Workspace* ws, const Tiling& tl, int tile_lb,
   ws->alloc_zero(&sp->d_listed_max, (size_t)sp->n_fused_tiles);
   ws->alloc_zero(&sp->d_listed_sums, 2 * (size_t)sp->n_fused_tiles);
   ws->alloc_zero(&sp->d_counter, (size_t)L * CTR_STRIDE);
+  ws->alloc_zero(&sp->d_sub, group_lines(sp->n_fused_tiles, L) * CTR_STRIDE);
   ws->alloc_zero(&sp->d_flag, (size_t)L);
 }
 
@@ -874,6 +883,7 @@ bool build_small(ob_lamb_ctx* ctx, Workspace* ws, SmallTilings* tilings, const s
     ws->upload(&sp->d_layer_seg0, t.layer_seg0);
     ws->alloc_zero(&sp->d_partial, 2 * t.seg_layer.size());
     ws->alloc_zero(&sp->d_counter, (size_t)ctx->L * CTR_STRIDE);
+    ws->alloc_zero(&sp->d_sub, group_lines((int64_t)t.seg_layer.size(), ctx->L) * CTR_STRIDE);
     ws->alloc_zero(&sp->d_flag, (size_t)ctx->L * CTR_STRIDE);
     sp->u = best;
   }
@@ -884,7 +894,7 @@ SmallTab small_tab(const ob_lamb_ctx* ctx, const SmallPlan& sp) {
   SmallTab t;
   t.tiles = sp.d_tiles; t.n_tiles = sp.n_tiles; t.tpc = sp.tpc; t.max_seg = sp.max_seg; t.n_c = ctx->n_c;
   t.seg_layer = sp.d_seg_layer; t.layer_seg0 = sp.d_layer_seg0; t.partial = sp.d_partial;
-  t.counter = sp.d_counter; t.flag = sp.d_flag; t.errflag = ctx->d_errflag; t.spin_limit = ctx->spin_limit;
+  t.counter = sp.d_counter; t.sub = sp.d_sub; t.flag = sp.d_flag; t.errflag = ctx->d_errflag; t.spin_limit = ctx->spin_limit;
   return t;
 }
 
@@ -923,11 +933,15 @@ ChunkTicket chunk_ticket_of(unsigned int* count, double* part, int n_chunks, int
   return tk;
 }
 
+// (Figures at barrier_arrive.  The lists that gain in layers of up to 512 tiles have at most 6144 tiles.)
+int arrivals_one_level(int n_listed_tiles) { return n_listed_tiles > 10240 ? 512 : ARRIVE_ONE_LEVEL; }
+
 ListedTiles listed_tiles(const ob_lamb_ctx* ctx, const LayerSplit& sp) {
   ListedTiles lt;
   lt.tile_list = sp.d_fused_tiles; lt.list_begin = sp.d_list_begin; lt.n_listed = sp.d_n_listed;
   lt.seg_first = sp.d_seg_first; lt.seg_end = sp.d_seg_end; lt.layer_seg0 = ctx->d_layer_seg0;
   lt.n_c = ctx->n_c; lt.tpc = sp.tpc; lt.tpc_span = ctx->tpc;
+  lt.one_level = arrivals_one_level(sp.n_fused_tiles);
   return lt;
 }
 
@@ -1357,10 +1371,12 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
   ws.upload(&ctx->d_layer_seg0, std::move(tm.layer_seg0));
   ws.alloc_zero(&ctx->d_partials_res, (size_t)ctx->n_tiles_res);
   ws.alloc_zero(&ctx->d_counter, (size_t)ctx->W * CTR_STRIDE);
+  ws.alloc_zero(&ctx->d_sub, (size_t)ctx->W * arrival_groups(ctx->tpc_res) * CTR_STRIDE);
   ws.alloc_zero(&ctx->d_flag, (size_t)ctx->W);
   ws.alloc_zero(&ctx->d_errflag, 1);
   ws.alloc_zero(&ctx->d_partials_srv_res, (size_t)ctx->tpc_srv_res);
   ws.alloc_zero(&ctx->d_counter_srv, (size_t)CTR_STRIDE);
+  ws.alloc_zero(&ctx->d_sub_srv, arrival_groups(ctx->tpc_srv_res) * CTR_STRIDE);
   ws.alloc_zero(&ctx->d_flag_srv, 1);
   ws.alloc_zero(&ctx->d_partials, (size_t)n_tiles);
   ws.alloc_zero(&ctx->d_partials_srv, (size_t)tpc_srv);
@@ -1498,7 +1514,7 @@ ob_status ob_lamb_warmup_step_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st, cons
   // 3. the listed tiles: moments, layer barrier, update
   WarmSync ws;
   ws.seg_sums = ctx->d_seg_sums; ws.listed_sums = sp.d_listed_sums; ws.lt = listed_tiles(ctx, sp);
-  ws.counter = sp.d_counter; ws.flag = sp.d_flag; ws.errflag = ctx->d_errflag;
+  ws.counter = sp.d_counter; ws.sub = sp.d_sub; ws.flag = sp.d_flag; ws.errflag = ctx->d_errflag;
   ws.spin_limit = ctx->spin_limit;
   ws.coeff_c = st->coeff_c; ws.c_avg = st->c_avg;
   ws.c_min = ctx->c_min; ws.c_max = ctx->c_max; ws.beta3 = ctx->beta3; ws.omb3 = ctx->omb3;
@@ -1577,6 +1593,7 @@ ob_status ob_lamb_compress_local_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st, c
     ChunkSync cs;
     cs.partials = ctx->d_partials_res;
     cs.counter = ctx->d_counter;
+    cs.sub = ctx->d_sub;
     cs.flag = ctx->d_flag;
     cs.errflag = ctx->d_errflag;
     cs.spin_limit = ctx->spin_limit;
@@ -1653,6 +1670,7 @@ ob_status ob_lamb_server_reduce(ob_lamb_ctx* ctx, const ob_lamb_state* st, const
     ChunkSync cs;
     cs.partials = ctx->d_partials_srv_res;
     cs.counter = ctx->d_counter_srv;
+    cs.sub = ctx->d_sub_srv;
     cs.flag = ctx->d_flag_srv;
     cs.errflag = ctx->d_errflag;
     cs.spin_limit = ctx->spin_limit;
@@ -1760,7 +1778,7 @@ ob_status ob_lamb_ratios_apply_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st, con
   // 2. the listed tiles: ratio pass, layer barrier, update
   LayerSync ls;
   ls.seg_max = ctx->d_seg_max; ls.listed_max = sp.d_listed_max; ls.lt = listed_tiles(ctx, sp);
-  ls.counter = sp.d_counter; ls.flag = sp.d_flag; ls.errflag = ctx->d_errflag;
+  ls.counter = sp.d_counter; ls.sub = sp.d_sub; ls.flag = sp.d_flag; ls.errflag = ctx->d_errflag;
   ls.spin_limit = ctx->spin_limit;
   ls.c_avg = st->c_avg; ls.r_prev = st->r_prev; ls.coeff_c = st->coeff_c;
   ls.one_m_thr = ctx->one_m_thr; ls.one_p_thr = ctx->one_p_thr; ls.r_min = ctx->r_min; ls.r_max = ctx->r_max;
@@ -1891,7 +1909,7 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
   // 18-20 from the segment maxima that launches 1 and 2 left), the others the listed tiles
   LayerSync ls;
   ls.seg_max = ctx->d_seg_max; ls.listed_max = sp.d_listed_max; ls.lt = listed_tiles(ctx, sp);
-  ls.counter = sp.d_counter; ls.flag = sp.d_flag; ls.errflag = ctx->d_errflag;
+  ls.counter = sp.d_counter; ls.sub = sp.d_sub; ls.flag = sp.d_flag; ls.errflag = ctx->d_errflag;
   ls.spin_limit = ctx->spin_limit;
   ls.c_avg = st->c_avg; ls.r_prev = st->r_prev; ls.coeff_c = st->coeff_c;
   ls.one_m_thr = ctx->one_m_thr; ls.one_p_thr = ctx->one_p_thr; ls.r_min = ctx->r_min; ls.r_max = ctx->r_max;
@@ -2017,17 +2035,21 @@ ob_status ob_lamb_check_device_status(ob_lamb_ctx* ctx, void* hip_stream) {
   // synchronisation state and fall back to the two-pass kernels for the rest of this context.
   ctx->resident = false;
   ctx->u_srv_res = 0;
-  (void)hipMemset(ctx->d_counter_srv, 0, sizeof(unsigned long long) * CTR_STRIDE);
+  const size_t line = sizeof(unsigned long long) * CTR_STRIDE;
+  (void)hipMemset(ctx->d_counter_srv, 0, line);
+  (void)hipMemset(ctx->d_sub_srv, 0, line * arrival_groups(ctx->tpc_srv_res));
   (void)hipMemset(ctx->d_flag_srv, 0, sizeof(unsigned long long));
   for (LayerSplit* sp : {&ctx->sp_apply, &ctx->sp_warm}) {
     sp->on = false;
     sp->big_on = false;   // (no wait in that pass; but after an expiry every call takes the plain kernels)
-    (void)hipMemset(sp->d_counter, 0, sizeof(unsigned long long) * (size_t)ctx->L * CTR_STRIDE);
+    (void)hipMemset(sp->d_counter, 0, line * (size_t)ctx->L);
+    (void)hipMemset(sp->d_sub, 0, line * group_lines(sp->n_fused_tiles, ctx->L));
     (void)hipMemset(sp->d_flag, 0, sizeof(unsigned long long) * (size_t)ctx->L);
   }
   ctx->sm_apply.u = 0;
   ctx->sm_warm.u = 0;
-  (void)hipMemset(ctx->d_counter, 0, sizeof(unsigned long long) * (size_t)ctx->W * CTR_STRIDE);
+  (void)hipMemset(ctx->d_counter, 0, line * (size_t)ctx->W);
+  (void)hipMemset(ctx->d_sub, 0, line * (size_t)ctx->W * arrival_groups(ctx->tpc_res));
   (void)hipMemset(ctx->d_flag, 0, sizeof(unsigned long long) * (size_t)ctx->W);
   (void)hipMemset(ctx->d_errflag, 0, sizeof(unsigned int));
   (void)hipDeviceSynchronize();

@@ -399,8 +399,9 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
  * OB_CFG_TWO_PASS_COMPRESS, as two passes through memory).  ob_lamb_server_reduce,
  * ob_lamb_ratios_apply and ob_lamb_warmup_step have such forms too (per chunk / per layer; on small
  * lists the last two are one launch in which all tiles of the list are resident); in
- * ob_lamb_warmup_step, workgroups that update a large layer also wait for workgroups of the same launch that
- * were dispatched before them, which need not be resident together.  All forms compute the same operations in the same order per element; the two sum-of-squares
+ * ob_lamb_warmup_step, workgroups that update a large layer, and in ob_lamb_ratios_apply_hist on lists of few tiles
+ * those of a layer, also wait for workgroups of the same launch that were dispatched before them and wait for
+ * nothing themselves, which need not be resident together.  All forms compute the same operations in the same order per element; the two sum-of-squares
  * reductions add the same fp64 terms grouped by different tile sizes, so a scale or norm can differ
  * in its last binary32 bit between forms (about once in 10^8 reductions) -- within the 1e-6 bar,
  * and the sign words that depend on such a scale can then differ for elements within one unit in

@@ -1109,8 +1109,9 @@ struct RatioTile {
   }
 };
 
-// The ratio pass of one tile (a workgroup; lds: [BLOCK / WAVE]).
-template <int U, bool HAS_K, bool PACKED_M>
+// The ratio pass of one tile (a workgroup; lds: [BLOCK / WAVE]).  SAME_LAUNCH: the maxima are read by other
+// workgroups of the launch.
+template <int U, bool HAS_K, bool PACKED_M, bool SAME_LAUNCH = false>
 __device__ __forceinline__ void ratios_pass_tile(const RatioArgs& ra, float* __restrict__ seg_max,
                                                  int64_t n_c, int tpc, const LayerTab& lt,
                                                  const int* __restrict__ tile_seg0,
@@ -1128,11 +1129,15 @@ __device__ __forceinline__ void ratios_pass_tile(const RatioArgs& ra, float* __r
   const int s0 = tile_seg0[p.t];
   RatioTile<U, HAS_K, PACKED_M> rt;
   rt.load(ra, p);
+  auto store = [&](int s, float r) {
+    if (SAME_LAUNCH) __hip_atomic_store(&seg_max[s], r, __ATOMIC_RELAXED, OB_AGENT);
+    else seg_max[s] = r;
+  };
   const bool uniform = (p.tile0 + p.len <= l0_end);
   if (uniform) {
     float r = rt.uniform_pass(ra, p, ss, s_prev, kt);
     r = block_max(r, lds);
-    if (threadIdx.x == 0) seg_max[s0] = r;
+    if (threadIdx.x == 0) store(s0, r);
   } else {
     rt.element_pass(ra, lt, p, l0, ss, s_prev);
     const int s1 = tile_seg0[p.t + 1];
@@ -1140,7 +1145,7 @@ __device__ __forceinline__ void ratios_pass_tile(const RatioArgs& ra, float* __r
       const int l = seg_layer[s];
       float r = rt.segment_max(p, lt.off[l], lt.off[l + 1]);
       r = block_max(r, lds);
-      if (threadIdx.x == 0) seg_max[s] = r;
+      if (threadIdx.x == 0) store(s, r);
     }
   }
 }
@@ -1392,7 +1397,7 @@ __device__ __forceinline__ void for_layer_parts(const LayerParts& q, T zero, FL 
 __device__ __forceinline__ int64_t group_line(int first, int l) { return (int64_t)(first / ARRIVE_SUB + l) * CTR_STRIDE; }
 
 struct LayerSync {
-  const float* seg_max;         // [segments of the 1024-element tiling] maxima left by the plain ratio pass
+  float* seg_max;               // [segments of the 1024-element tiling] maxima left by the plain ratio pass
   float* listed_max;            // [listed tiles] maxima of this launch's tiles
   ListedTiles lt;
   unsigned long long* counter;  // [L * CTR_STRIDE] (generation << 32) | arrivals
@@ -1404,44 +1409,104 @@ struct LayerSync {
   float* r_prev;
   float* coeff_c;
   float one_m_thr, one_p_thr, r_min, r_max;
-  int n_lead;                   // leading workgroups of the launch, one per layer, that
+  int n_lead;                   // leading workgroups of the launch: without rest_tiles one per layer, that
                                 // finish the layers without listed tiles (0: a kernel of its own has done that)
+  // k_ratios_apply_hist with the plain ratio pass in its launch (else rest_tiles = NULL): the leading workgroups
+  // finish the n_alone layers that have no arrivals and run the pass of the rest_tiles, whose segments arrive too
+  const int* rest_tiles;
+  const int* alone;
+  int n_alone;
+  const int* arr0;              // [L] arrivals of the layers before
+  const int* skip_first;        // [L] first / one past the last of the layer's segments that no rest tile forms
+  const int* skip_end;
+  const int* tile_seg0;
+  const int* seg_layer;
 };
 
+// All of layer l's maxima, the two clips (lines 18-19), and the publication of c_t (a layer that is one segment of a rest
+// tile has no barrier): by the whole workgroup that arrived last of n.
+__device__ __forceinline__ void layer_finish(const LayerSync& ls, int l, const LayerParts& lp, float rp, float ca, int n,
+                                             unsigned int want, float* lds) {
+  float q = 0.0f;
+  // four loads in flight per thread: every waiter of the layer is waiting for this, and a layer that is too large to be
+  // listed has tens of thousands of segments (the maxima are >= +0, so that missing ones as 0 change nothing)
+  auto range = [&](const float* v, int j0, int j1) {
+    for (int j = j0 + (int)threadIdx.x; j < j1; j += 4 * BLOCK) {
+      float t[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        t[u] = (j + u * BLOCK < j1) ? __hip_atomic_load(&v[j + u * BLOCK], __ATOMIC_RELAXED, OB_AGENT) : 0.0f;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (t[u] > q) q = t[u];
+    }
+  };
+  range(ls.listed_max, lp.lb, lp.lb + lp.nl);
+  range(ls.seg_max, lp.a, lp.s_first);
+  range(ls.seg_max, lp.s_end, lp.b);
+  q = block_max(q, lds);
+  if (threadIdx.x == 0) {
+    const float c = ratio_clip_commit(q, l, rp, ca, ls.r_prev, ls.coeff_c, ls.one_m_thr,
+                                      ls.one_p_thr, ls.r_min, ls.r_max);
+    if (n > 1 || lp.nl > 0)
+      (void)barrier_publish(&ls.flag[l], &ls.counter[(int64_t)l * CTR_STRIDE], n, want, __float_as_uint(c), ls.lt.one_level);
+  }
+}
+
 // Publishes the maximum r of the workgroup's listed tile (of layer l; bid: its position in
-// tile_list) and arrives; if this was the
-// layer's last listed tile, finishes the layer.  All threads call; r is valid in thread 0.
-// lp, rp, ca: the layer's ranges, r_prev[l] and c_avg[l], read at the start of the kernel.
-__device__ __forceinline__ void layer_arrive(const LayerSync& ls, int bid, int l, const LayerParts& lp, float rp,
-                                             float ca, float r, float* lds, unsigned long long* bc) {
-  unsigned long long* counter = &ls.counter[(int64_t)l * CTR_STRIDE];
+// tile_list) and arrives; if this was the layer's last arrival, finishes the layer.  All threads call; r is valid
+// in thread 0.  lp, rp, ca: the layer's ranges, r_prev[l] and c_avg[l], read at the start of the kernel; first, n: the
+// layer's first arrival in the numbering of all, and how many it has.
+__device__ __forceinline__ void layer_arrive(const LayerSync& ls, int bid, int l, const LayerParts& lp, int first, int n,
+                                             float rp, float ca, float r, float* lds, unsigned long long* bc) {
   if (threadIdx.x == 0) {
     __hip_atomic_store(&ls.listed_max[bid], r, __ATOMIC_RELAXED, OB_AGENT);
     payload_before_arrival();
-    *bc = barrier_arrive(counter, ls.sub + group_line(lp.lb, l), bid - lp.lb, lp.nl, ls.lt.one_level);
+    *bc = barrier_arrive(&ls.counter[(int64_t)l * CTR_STRIDE], ls.sub + group_line(first, l), bid - lp.lb, n, ls.lt.one_level);
   }
   __syncthreads();
   const bool last = ((*bc & 1ull) != 0ull);
   const unsigned int want = (unsigned int)(*bc >> 32);
   __syncthreads();
-  if (last) {
-    float q = 0.0f;
-    for_layer_parts(
-        lp, 0.0f,
-        [&](int i) { return __hip_atomic_load(&ls.listed_max[i], __ATOMIC_RELAXED, OB_AGENT); },
-        [&](float v) { if (v > q) q = v; },
-        [&](int j) {
-          const float v = ls.seg_max[j];   // written by an earlier kernel
-          if (v > q) q = v;
-        });
-    q = block_max(q, lds);
-    if (threadIdx.x == 0) {
-      const float c = ratio_clip_commit(q, l, rp, ca, ls.r_prev, ls.coeff_c, ls.one_m_thr,
-                                        ls.one_p_thr, ls.r_min, ls.r_max);
-      (void)barrier_publish(&ls.flag[l], counter, lp.nl, want, __float_as_uint(c), ls.lt.one_level);
-    }
-  }
+  if (last) layer_finish(ls, l, lp, rp, ca, n, want, lds);
   // every thread leaves with the generation to wait for in *bc's high word (the last arriver too)
+}
+
+// A rest tile's half of the barriers (whole workgroup, after its ratio pass with SAME_LAUNCH): its first and last
+// segments arrive at their layers, those in between, layers of their own, are finished here.
+__device__ __forceinline__ void rest_arrive(const LayerSync& ls, int tile, float* lds, unsigned long long* bc /* [2] */) {
+  const int s0 = ls.tile_seg0[tile], s1 = ls.tile_seg0[tile + 1], n_end = (s1 - s0 > 1) ? 2 : 1;
+  auto arrivals = [&](const LayerParts& lp, int l, int* a, int* e) {
+    *a = ls.skip_first[l];
+    *e = ls.skip_end[l];
+    return lp.nl + (*a - lp.a) + (lp.b - *e);
+  };
+  if (threadIdx.x == 0) payload_before_arrival();   // (thread 0 has stored the maxima)
+  __syncthreads();
+  const int e = threadIdx.x / WAVE;
+  if (e < n_end && (threadIdx.x & (WAVE - 1)) == 0) {
+    const int sg = e ? s1 - 1 : s0, l = ls.seg_layer[sg];
+    const LayerParts lp = layer_parts(ls.lt, l);
+    int a, b;
+    const int n = arrivals(lp, l, &a, &b);
+    const int j = lp.nl + (sg < a ? sg - lp.a : (a - lp.a) + (sg - b));
+    bc[e] = (n == 1) ? 1ull : barrier_arrive(&ls.counter[(int64_t)l * CTR_STRIDE], ls.sub + group_line(ls.arr0[l], l), j, n, ls.lt.one_level);
+  }
+  __syncthreads();
+  for (int sg = s0 + 1 + (int)threadIdx.x; sg < s1 - 1; sg += BLOCK) {
+    const int l = ls.seg_layer[sg];
+    const float r = __hip_atomic_load(&ls.seg_max[sg], __ATOMIC_RELAXED, OB_AGENT);
+    (void)ratio_clip_commit(r, l, ls.r_prev[l], ls.c_avg[l], ls.r_prev, ls.coeff_c, ls.one_m_thr, ls.one_p_thr, ls.r_min,
+                            ls.r_max);
+  }
+  for (int q = 0; q < n_end; ++q) {   // uniform
+    if ((bc[q] & 1ull) == 0ull) continue;
+    const int l = ls.seg_layer[q ? s1 - 1 : s0];
+    const LayerParts lp = layer_parts(ls.lt, l);
+    int a, b;
+    const int n = arrivals(lp, l, &a, &b);
+    layer_finish(ls, l, lp, ls.r_prev[l], ls.c_avg[l], n, (unsigned int)(bc[q] >> 32), lds);
+  }
 }
 
 // Waits (bounded) until layer l's coefficient of this launch is published; returns it to all
@@ -1497,7 +1562,7 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_apply_resident(
   rt.load(ra, p);
   float r = rt.template uniform_pass<true>(ra, p, ss, s_prev, kt);
   r = block_max(r, lds);
-  layer_arrive(ls, bid, l0, lp, rp, ca, r, lds, &bc);   // before the stores of v_fresh: nothing to wait for
+  layer_arrive(ls, bid, l0, lp, lp.lb, lp.nl, rp, ca, r, lds, &bc);   // before the stores of v_fresh: nothing to wait for
   rt.store_v_fresh(ra, p);
   v4f X[U];
 #pragma unroll
@@ -1609,7 +1674,7 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_apply_stream(
     }
   }
   r = block_max(r, lds);
-  layer_arrive(ls, (int)blockIdx.x, l0, lp, rp, ca, r, lds, &bc);
+  layer_arrive(ls, (int)blockIdx.x, l0, lp, lp.lb, lp.nl, rp, ca, r, lds, &bc);
 #pragma unroll
   for (int j = 0; j < G; ++j) {
     const int o = (U - G + j) * SPAN + o0;
@@ -1708,9 +1773,8 @@ __device__ __forceinline__ const uint32_t* plane_bits(const RatioArgs& ra, const
   return q == 0 ? ra.packed : (q == 1 ? ra.pm.bits : h.bits[q - 2]);
 }
 
-// The two values of every step are the same for all elements of a (chunk, layer) pair.  A small
-// kernel forms them once per call for every pair and step; the N-sized kernels then fetch two
-// scalars per step instead of each thread redoing four divisions per step.
+// The two values of every step are the same for all elements of a (chunk, layer) pair.  In long lists they are formed
+// once per call for every pair and step, by leading workgroups of the plain ratio pass's launch, and fetched from there.
 // Pairs: the layers that meet chunk c, in layer order, are pairs pair_base[c] .. pair_base[c+1]-1;
 // the pair of (c, l) is pair_base[c] + l - pair_lfirst[c].
 struct VTerms {
@@ -1743,14 +1807,41 @@ __device__ __forceinline__ void variance_terms_of_pair(const RatioArgs& ra, cons
   }
 }
 
-template <bool HAS_K>
-__global__ __launch_bounds__(BLOCK) void k_variance_terms(RatioArgs ra, VfHist h, VTerms vt,
-                                                          const float* __restrict__ mom_scale,
-                                                          float* __restrict__ out /* = vt.t */) {
-  variance_terms_of_pair<HAS_K>(ra, h, vt, mom_scale, out, (int)(blockIdx.x * BLOCK + threadIdx.x));
-}
+// The values of a tile, those of step s in lane s - 1 of each group of 8, from where the walk reads them: fetched from
+// the table (vt.t), or formed by these lanes, once for all steps, while the wavefront's loads are in flight.  Forming
+// them makes the launch before unnecessary; over 37000 tiles it costs more (6910 / 6970 us for four steps).
+struct StepTerms {
+  float same, diff;
+  template <bool HAS_K>
+  __device__ __forceinline__ void form(const RatioArgs& ra, const VfHist& h, int c, float kt) {
+    const int s = (int)(threadIdx.x & 7) + 1;
+    float s_new = 0.0f, s_old = 0.0f;
+#pragma unroll
+    for (int q = 0; q < VF_MAX_OLD + 2; ++q)
+      if (q <= h.n_old + 1) {   // uniform
+        const float v = plane_scale(ra, h, q, c);
+        if (q == s - 1) s_new = v;
+        if (q == s) s_old = v;
+      }
+    variance_terms<HAS_K>(ra, s_new, s_old, kt, &same, &diff);
+  }
+  template <bool HAS_K>
+  __device__ __forceinline__ void get(const VTerms& vt, const RatioArgs& ra, const VfHist& h, int c, int l, float kt) {
+    if (vt.t) {   // uniform
+      const int s = (int)(threadIdx.x & 7) < h.n_old + 1 ? (int)(threadIdx.x & 7) : h.n_old;
+      const float2 t = reinterpret_cast<const float2*>(vt.t)[(int64_t)s * vt.n_pairs + pair_of(vt, c, l)];
+      same = t.x;
+      diff = t.y;
+    } else {
+      form<HAS_K>(ra, h, c, kt);
+    }
+  }
+  // of step s, uniform
+  __device__ __forceinline__ float t_same(int s) const { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(same), s - 1)); }
+  __device__ __forceinline__ float t_diff(int s) const { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(diff), s - 1)); }
+};
 
-// k_variance_terms and k_ratios_pass (momentum in 1-bit form, tile list) in one launch: the first n_lead
+// The terms and the plain ratio pass (momentum in 1-bit form, tile list) in one launch: the first n_lead
 // workgroups form the terms, the others run the plain ratio pass of tile_list[blockIdx.x - n_lead].
 // Neither reads what the other writes; both are over before the kernels that use the terms start.
 template <int U, bool HAS_K>
@@ -1772,16 +1863,17 @@ __global__ __launch_bounds__(BLOCK) void k_ratios_pass_vterms(RatioArgs ra, floa
 // Dense view of a variance held in deferred form, over the 1024-element tiles inside the tiles of
 // the two kernels below (each lies inside one layer): the up-to-date variance goes to the base
 // array itself if h.write_v, else to vf_dense (another array, which leaves the base as it is).
-__global__ __launch_bounds__(BLOCK) void k_variance_dense(RatioArgs ra, VfHist h, VTerms vt,
-                                                          float* __restrict__ vf_dense, int64_t n_c, int tpc,
+template <bool HAS_K>
+__global__ __launch_bounds__(BLOCK) void k_variance_dense(RatioArgs ra, VfHist h, float* __restrict__ vf_dense, int64_t n_c, int tpc,
                                                           LayerTab lt, const int* __restrict__ tile_list) {
   const TilePos p = tile_pos<SPAN>(n_c, tpc, tile_list[blockIdx.x]);
   const int l0 = lt.first_layer[p.t];
   if (l0 >= lt.L || p.tile0 + p.len > lt.off[l0 + 1]) return;   // (not a tile of those kernels: nothing lags there)
   const int a = h.n_old + 1;   // steps to apply
-  const float* tt = vt.t + (int64_t)pair_of(vt, p.c, l0) * 2;
+  StepTerms st;
+  st.form<HAS_K>(ra, h, p.c, HAS_K ? lt.mom_scale[l0] : 1.0f);
   const int o = threadIdx.x * 4;
-  if (o >= p.len) return;
+  if (o >= p.len) return;   // all lanes of a wavefront or none
   float* vf_out = h.write_v ? ra.v_fresh : vf_dense;   // uniform
   unsigned int NBq[VF_MAX_OLD + 2];   // the lane's nibble of every plane, newest first
 #pragma unroll
@@ -1793,7 +1885,7 @@ __global__ __launch_bounds__(BLOCK) void k_variance_dense(RatioArgs ra, VfHist h
 #pragma unroll
   for (int s = VF_MAX_OLD + 1; s >= 1; --s) {
     if (s <= a) {   // uniform: the step from plane s to plane s-1
-      const float t_same = tt[(int64_t)(s - 1) * vt.n_pairs * 2], t_diff = tt[(int64_t)(s - 1) * vt.n_pairs * 2 + 1];
+      const float t_same = st.t_same(s), t_diff = st.t_diff(s);
       const unsigned int flip = NBq[s] ^ NBq[s - 1];
 #pragma unroll
       for (int k = 0; k < 4; ++k) V[k] = ra.beta2 * V[k] + select_by_bit(flip, k, t_diff, t_same);
@@ -1810,6 +1902,7 @@ __global__ __launch_bounds__(BLOCK) void k_variance_dense(RatioArgs ra, VfHist h
 // walk through the steps as k_ratios_apply_hist.  The tile's maximum goes to the segment of its
 // first 1024-element span, 0 to the segments of its other spans (k_ratios_finalize takes the
 // maximum over all of a layer's segments).
+template <bool HAS_K>
 __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_big_hist(RatioArgs ra, VfHist h, VTerms vt, float* __restrict__ seg_max,
                                                            const int* __restrict__ big_tiles, int64_t n_c,
                                                            int tpc_big, int tpc_span, LayerTab lt,
@@ -1820,7 +1913,6 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_big_hist(RatioArgs
   const TilePos p = tile_pos<TILE>(n_c, tpc_big, big_tiles[blockIdx.x]);
   const int sp0 = p.c * tpc_span + (p.t - p.c * tpc_big) * U;  // the tile's first span
   const int l0 = lt.first_layer[sp0];  // the layer the tile lies in (lt.first_layer: of the 1024-element tiling)
-  const float* tt = vt.t + (int64_t)pair_of(vt, p.c, l0) * 2;
   const int a = h.n_old + 1;   // steps to apply
   const int o0 = threadIdx.x * 4;
   const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
@@ -1843,6 +1935,8 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_big_hist(RatioArgs
       VZ[u] = ld4(ra.v_frozen + p.tile0 + o);
     }
   }
+  StepTerms st;
+  st.get<HAS_K>(vt, ra, h, p.c, l0, HAS_K ? lt.mom_scale[l0] : 1.0f);
 #pragma unroll
   for (int s = VF_MAX_OLD + 1; s >= 1; --s)
     if (s <= a) Wq[s] ^= Wq[s - 1];
@@ -1860,7 +1954,7 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_big_hist(RatioArgs
 #pragma unroll
   for (int s = VF_MAX_OLD + 1; s >= 1; --s) {
     if (s <= a) {   // uniform: the step from plane s to plane s-1
-      const float t_same = tt[(int64_t)(s - 1) * vt.n_pairs * 2], t_diff = tt[(int64_t)(s - 1) * vt.n_pairs * 2 + 1];
+      const float t_same = st.t_same(s), t_diff = st.t_diff(s);
 #pragma unroll
       for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -1900,11 +1994,21 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
   constexpr int U = 8;
   constexpr int TILE = SPAN * U;
   __shared__ float lds[BLOCK / WAVE];
-  __shared__ unsigned long long bc;
+  __shared__ unsigned long long bc, bc_rest[2];
   __shared__ v4f zs[S > 0 ? S * BLOCK : 1];
   const int bid = (int)blockIdx.x - ls.n_lead;   // position in tile_list
   if (bid < 0) {
-    lead_finalize(ls, lds);
+    const int lead = (int)blockIdx.x - ls.n_alone;   // (uniform branches)
+    if (!ls.rest_tiles) {
+      lead_finalize(ls, lds);
+    } else if (lead < 0) {
+      ratios_finalize_layer<BLOCK>(ls.alone[blockIdx.x], ls.seg_max, ls.lt.layer_seg0, ls.c_avg, ls.r_prev, ls.coeff_c,
+                                   ls.one_m_thr, ls.one_p_thr, ls.r_min, ls.r_max, lds);
+    } else {
+      const int tile = ls.rest_tiles[lead];
+      ratios_pass_tile<1, HAS_K, true, true>(ra, ls.seg_max, ls.lt.n_c, ls.lt.tpc_span, lt, ls.tile_seg0, ls.seg_layer, tile, lds);
+      rest_arrive(ls, tile, lds, bc_rest);
+    }
     return;
   }
   const int tpc = ls.lt.tpc;
@@ -1915,7 +2019,7 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
   const float ss = ra.sscales[p.c];
   const LayerParts lp = layer_parts(ls.lt, l0);
   const float rp = ls.r_prev[l0], ca = ls.c_avg[l0];
-  const float* tt = vt.t + (int64_t)pair_of(vt, p.c, l0) * 2;
+  const int first = ls.rest_tiles ? ls.arr0[l0] : lp.lb;
   const int a = h.n_old + 1;   // steps to apply
   const int o0 = threadIdx.x * 4;
   const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
@@ -1941,6 +2045,8 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
       else VZ[u] = ld4(ra.v_frozen + p.tile0 + o);
     }
   }
+  StepTerms st;
+  st.get<HAS_K>(vt, ra, h, p.c, l0, kt);
   // flips between consecutive planes, formed on the words as loaded; plane 0 stays (line 21 needs it)
 #pragma unroll
   for (int s = VF_MAX_OLD + 1; s >= 1; --s)
@@ -1960,7 +2066,7 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
 #pragma unroll
   for (int s = VF_MAX_OLD + 1; s >= 1; --s) {
     if (s <= a) {   // uniform: the step from plane s to plane s-1
-      const float t_same = tt[(int64_t)(s - 1) * vt.n_pairs * 2], t_diff = tt[(int64_t)(s - 1) * vt.n_pairs * 2 + 1];
+      const float t_same = st.t_same(s), t_diff = st.t_diff(s);
 #pragma unroll
       for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -1982,7 +2088,8 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
     }
   }
   r = block_max(r, lds);
-  layer_arrive(ls, bid, l0, lp, rp, ca, r, lds, &bc);   // before any store: nothing to wait for
+  // before any store: nothing to wait for
+  layer_arrive(ls, bid, l0, lp, first, lp.nl + (ls.rest_tiles ? (lp.s_first - lp.a) + (lp.b - lp.s_end) : 0), rp, ca, r, lds, &bc);
   if (h.write_v) {   // uniform
 #pragma unroll
     for (int u = 0; u < U; ++u) {

@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstdlib>
@@ -102,7 +103,6 @@ enum KernelId {
   KID_RATIOS_APPLY_SMALL,
   KID_WARMUP_SMALL,
   KID_VARIANCE_DENSE,
-  KID_VARIANCE_TERMS,
   KID_RATIOS_BIG_HIST,
   KID_MOMENTUM_DENSE,
   KID_ERROR_DENSE,
@@ -119,7 +119,7 @@ enum KernelId {
 const char* const kKernelNames[KID_COUNT] = {
     "momentum_z_sumsq", "compress_resident", "chunk_scale",     "sign_pack_error", "compress_deferred", "server_unpack_avg",
     "server_scale",     "server_sign_pack", "server_resident", "ratios_pass",     "ratios_finalize",
-    "decompress_apply", "ratios_apply_resident", "ratios_apply_hist", "ratios_apply_hist_lds", "ratios_apply_small", "warmup_small", "variance_dense", "variance_terms", "ratios_big_hist", "momentum_dense", "error_dense", "momentum_scale", "warmup_moments",   "warmup_coeff",    "warmup_apply",
+    "decompress_apply", "ratios_apply_resident", "ratios_apply_hist", "ratios_apply_hist_lds", "ratios_apply_small", "warmup_small", "variance_dense", "ratios_big_hist", "momentum_dense", "error_dense", "momentum_scale", "warmup_moments",   "warmup_coeff",    "warmup_apply",
     "warmup_resident",  "warmup_trail", "fill",            "copy"};
 
 // Single-launch form of a list whose tiles all fit on the device at once (k_ratios_apply_small,
@@ -188,6 +188,17 @@ struct LayerSplit {
   double* d_part_sums = nullptr;           // [2 * parts]
   unsigned long long* d_trail_flag = nullptr;   // [L]
   unsigned char* d_has_tiles = nullptr;    // [L] 1 for layers with listed or big tiles
+  // k_ratios_apply_hist with the plain ratio pass in its launch (LayerSync), which counts arrivals of its own
+  bool rest_in_launch = false;
+  int n_alone = 0;
+  int* d_alone = nullptr;
+  int* d_arr0 = nullptr;
+  int* d_skip_first = nullptr;
+  int* d_skip_end = nullptr;
+  int64_t n_arrivals = 0;
+  unsigned long long* d_counter_rest = nullptr;
+  unsigned long long* d_sub_rest = nullptr;
+  unsigned long long* d_flag_rest = nullptr;
   int n_rest_ratio_tiles = 0;              // TILE_MAIN tiles outside the listed and the big tiles
   int* d_rest_ratio_tiles = nullptr;
   int n_cov_tiles = 0;                     // TILE_MAIN tiles inside the listed or the big tiles
@@ -533,8 +544,8 @@ void plan_split(const Tiling& tl, int64_t tile_lb, const Tiling& tm, const std::
   pl->has_listed.assign((size_t)L, 0);
   pl->n_listed.assign((size_t)L, 0);
   pl->list_begin.assign((size_t)L, 0);
-  pl->seg_first.assign((size_t)L, 0);
-  pl->seg_end.assign((size_t)L, 0);
+  pl->seg_first.assign(tm.layer_seg0.begin(), tm.layer_seg0.begin() + L);   // (no listed tile: nothing skipped)
+  pl->seg_end = pl->seg_first;
   pl->covered.assign((size_t)tm.n_tiles, 0);
   auto tile_range = [&](int64_t t, int64_t* tile0, int64_t* tile1) {
     const int64_t c = t / tl.tpc, b = t % tl.tpc;
@@ -688,6 +699,16 @@ void trail_items(const std::vector<int>& n, const std::vector<int>& begin, int64
 size_t arrival_groups(int64_t n) { return (size_t)((n + ARRIVE_SUB - 1) / ARRIVE_SUB); }
 size_t group_lines(int64_t n, int64_t L) { return arrival_groups(n) + (size_t)L; }
 
+// Whether the plain ratio pass runs in k_ratios_apply_hist's launch instead of its own, which saves that launch (5.6 us and
+// a gap) and costs its tiles the occupancy of their own kernel and every wavefront the values of StepTerms.  A step, us, in a
+// launch of its own / in that one, rest tiles and 8192-element tiles: 240, 1424 86.4 / 83.6; 1209, 2232 131.3 / 128.8; 468,
+// 2580 140.6 / 138.8; 433, 1713 110.1 / 109.3; 286, 3920 188.4 / 188.7; 1600, 4800 236.9 / 241.7; 647, 5135 242 / 239.7; 1297, 9677
+// 448 / 445; 710, 11239 501 / 511; 997, 25803 1134 / 1140; 1430, 40908 1716 / 1728.
+constexpr int REST_IN_LAUNCH_MAX = 1280, REST_IN_LAUNCH_MAX_TILES = 5120;
+bool rest_in_launch(int n_rest_tiles, int n_listed, int n_big) {
+  return n_listed > 0 && n_rest_tiles <= REST_IN_LAUNCH_MAX && n_listed + n_big <= REST_IN_LAUNCH_MAX_TILES;
+}
+
 // Plans and uploads one LayerSplit.
 void build_split(ob_lamb_ctx* ctx, Workspace* ws, const Tiling& tl, int tile_lb, const Tiling& tm,
                  const std::vector<int64_t>& h_off, int64_t max_tiles, const BigRule& rule, bool trail, LayerSplit* sp,
@@ -740,6 +761,29 @@ void build_split(ob_lamb_ctx* ctx, Workspace* ws, const Tiling& tl, int tile_lb,
     ws->alloc_zero(&sp->d_sub_sums, 2 * (size_t)counters);
     ws->alloc_zero(&sp->d_part_sums, 2 * (size_t)TRAIL_PARTS * (size_t)sp->n_big_tiles);
     ws->alloc_zero(&sp->d_trail_flag, (size_t)L);
+  }
+  sp->rest_in_launch = !trail && rest_in_launch(sp->n_rest_ratio_tiles, sp->n_fused_tiles, sp->n_big_tiles);
+  if (sp->rest_in_launch) {
+    std::vector<int> arr0((size_t)L), alone, skip_first = pl.seg_first, skip_end = pl.seg_end;
+    for (int64_t l = 0; l < L; ++l) {
+      const size_t i = (size_t)l;
+      if (pl.big_n[i]) {
+        skip_first[i] = pl.big_seg_first[i];
+        skip_end[i] = pl.big_seg_end[i];
+      }
+      arr0[i] = (int)sp->n_arrivals;
+      const int n = pl.n_listed[i] + (skip_first[i] - tm.layer_seg0[i]) + (tm.layer_seg0[i + 1] - skip_end[i]);
+      if (n == 0) alone.push_back((int)l);
+      sp->n_arrivals += n;
+    }
+    sp->n_alone = (int)alone.size();
+    ws->upload(&sp->d_alone, std::move(alone));
+    ws->upload(&sp->d_arr0, std::move(arr0));
+    ws->upload(&sp->d_skip_first, std::move(skip_first));
+    ws->upload(&sp->d_skip_end, std::move(skip_end));
+    ws->alloc_zero(&sp->d_counter_rest, (size_t)L * CTR_STRIDE);
+    ws->alloc_zero(&sp->d_sub_rest, group_lines(sp->n_arrivals, L) * CTR_STRIDE);
+    ws->alloc_zero(&sp->d_flag_rest, (size_t)L);
   }
   ws->upload(&sp->d_cov_tiles, std::move(cov));
   ws->upload(&sp->d_big_tiles, std::move(pl.big_tiles));
@@ -1383,7 +1427,7 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
   ws.alloc_zero(&ctx->d_seg_sums, 2 * (size_t)ctx->n_segs);
   ws.alloc_zero(&ctx->d_sigma, (size_t)L);
   ws.alloc_zero(&ctx->d_seg_max, (size_t)ctx->n_segs);
-  if (ok) {
+  if (ok && !ctx->sp_apply.rest_in_launch) {
     // the layers that meet each chunk (empty layers in between included; a chunk that lies in the
     // padding has none)
     std::vector<int> pair_base((size_t)ctx->W + 1, 0), pair_lfirst((size_t)ctx->W, 0), pair_c, pair_l;
@@ -1776,7 +1820,7 @@ ob_status ob_lamb_ratios_apply_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st, con
   launch_ratios(la, ctx, st, packed_all, server_scales, packed_m, pm, sp.d_rest_tiles, sp.n_rest_tiles,
                 sp.d_has_listed, n_lead == 0 && sp.n_layers < ctx->L);
   // 2. the listed tiles: ratio pass, layer barrier, update
-  LayerSync ls;
+  LayerSync ls{};
   ls.seg_max = ctx->d_seg_max; ls.listed_max = sp.d_listed_max; ls.lt = listed_tiles(ctx, sp);
   ls.counter = sp.d_counter; ls.sub = sp.d_sub; ls.flag = sp.d_flag; ls.errflag = ctx->d_errflag;
   ls.spin_limit = ctx->spin_limit;
@@ -1836,16 +1880,6 @@ VTerms vterms(const ob_lamb_ctx* ctx) {
   return vt;
 }
 
-// the two values of every (chunk, layer) pair and step of the history, for the kernels below
-void launch_variance_terms(Launch& la, ob_lamb_ctx* ctx, const ob_lamb_state* st, const RatioArgs& ra,
-                           const VfHist& vh) {
-  const VTerms vt = vterms(ctx);
-  dispatch1(st->mom_scale != nullptr, [&](auto hk) {
-    OB_LAUNCH(la, KID_VARIANCE_TERMS, (k_variance_terms<decltype(hk)::value>), (ctx->n_pairs + BLOCK - 1) / BLOCK,
-              ra, vh, vt, st->mom_scale, ctx->d_vterms);
-  });
-}
-
 }  // namespace
 
 extern "C" {
@@ -1886,18 +1920,25 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
   // its launch shape, not by the bytes it moves).  Without the barrier kernel (OB_CFG_NO_FUSED_APPLY)
   // every layer with enough whole tiles counts as too large: no wait anywhere, and still no rewrite
   // of the array at every step.
-  // launch 1: the two values of every (chunk, layer) pair and step of the history (leading workgroups)
-  // and the plain ratio pass outside the tiles that work from the history
-  const int n_lead_vt = (ctx->n_pairs + BLOCK - 1) / BLOCK;
-  dispatch1(st->mom_scale != nullptr, [&](auto hk) {
-    OB_LAUNCH(la, KID_RATIOS_PASS, (k_ratios_pass_vterms<U_MAIN, decltype(hk)::value>),
-              sp.n_rest_ratio_tiles + n_lead_vt, ra, ctx->d_seg_max, ctx->n_c, ctx->tpc, lt, ctx->d_tile_seg0,
-              ctx->d_seg_layer, sp.d_rest_ratio_tiles, vh, vterms(ctx), ctx->d_vterms, n_lead_vt);
-  });
+  // launch 1, where the barrier kernel's launch does not do it: the two values of every (chunk, layer) pair and step of
+  // the history (leading workgroups) and the plain ratio pass outside the tiles that work from the history
+  const bool hk = st->mom_scale != nullptr;
+  const bool rest_in_launch = sp.on && sp.rest_in_launch;
+  const VTerms vt = vterms(ctx);   // (vt.t = NULL: each wavefront forms its own)
+  if (!rest_in_launch) {
+    const int n_lead_vt = (ctx->n_pairs + BLOCK - 1) / BLOCK;
+    dispatch1(hk, [&](auto k_) {
+      OB_LAUNCH(la, KID_RATIOS_PASS, (k_ratios_pass_vterms<U_MAIN, decltype(k_)::value>),
+                sp.n_rest_ratio_tiles + n_lead_vt, ra, ctx->d_seg_max, ctx->n_c, ctx->tpc, lt, ctx->d_tile_seg0,
+                ctx->d_seg_layer, sp.d_rest_ratio_tiles, vh, vt, ctx->d_vterms, n_lead_vt);
+    });
+  }
   // launch 2: ratio pass of the layers that are too large for the barrier kernel, from the history
   if (sp.big_on)
-    OB_LAUNCH(la, KID_RATIOS_BIG_HIST, k_ratios_big_hist, sp.n_big_tiles, ra, vh, vterms(ctx), ctx->d_seg_max,
-              sp.d_big_tiles, ctx->n_c, sp.tpc, ctx->tpc, lt, ctx->d_tile_seg0);
+    dispatch1(hk, [&](auto k_) {
+      OB_LAUNCH(la, KID_RATIOS_BIG_HIST, (k_ratios_big_hist<decltype(k_)::value>), sp.n_big_tiles, ra, vh, vt, ctx->d_seg_max,
+                sp.d_big_tiles, ctx->n_c, sp.tpc, ctx->tpc, lt, ctx->d_tile_seg0);
+    });
   if (!sp.on) {
     OB_LAUNCH_B(la, KID_RATIOS_FINALIZE, k_ratios_finalize, (int)ctx->L, FBLOCK, ctx->d_seg_max,
                 ctx->d_layer_seg0, st->c_avg, st->r_prev, st->coeff_c, ctx->one_m_thr, ctx->one_p_thr,
@@ -1905,20 +1946,27 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
     launch_apply(la, ctx, st, packed_all, server_scales, lr, nullptr, ctx->n_tiles, xl);
     return la.ok ? OB_OK : OB_ERR_HIP;
   }
-  // launch 3: the barrier kernel; its leading workgroups finish the layers without listed tiles (lines
-  // 18-20 from the segment maxima that launches 1 and 2 left), the others the listed tiles
-  LayerSync ls;
+  // launch 3: the barrier kernel; its leading workgroups run launch 1's pass or finish the layers without listed tiles
+  // (lines 18-20 from the segment maxima that launches 1 and 2 left), the others the listed tiles
+  LayerSync ls{};
   ls.seg_max = ctx->d_seg_max; ls.listed_max = sp.d_listed_max; ls.lt = listed_tiles(ctx, sp);
   ls.counter = sp.d_counter; ls.sub = sp.d_sub; ls.flag = sp.d_flag; ls.errflag = ctx->d_errflag;
   ls.spin_limit = ctx->spin_limit;
   ls.c_avg = st->c_avg; ls.r_prev = st->r_prev; ls.coeff_c = st->coeff_c;
   ls.one_m_thr = ctx->one_m_thr; ls.one_p_thr = ctx->one_p_thr; ls.r_min = ctx->r_min; ls.r_max = ctx->r_max;
   ls.n_lead = (sp.n_layers < ctx->L) ? (int)ctx->L : 0;
-  dispatch2(st->mom_scale != nullptr, xl.p != nullptr, [&](auto k_, auto lx) {
+  if (rest_in_launch) {
+    ls.n_alone = sp.n_alone; ls.n_lead = sp.n_alone + sp.n_rest_ratio_tiles;
+    ls.rest_tiles = sp.d_rest_ratio_tiles; ls.alone = sp.d_alone; ls.arr0 = sp.d_arr0;
+    ls.skip_first = sp.d_skip_first; ls.skip_end = sp.d_skip_end;
+    ls.tile_seg0 = ctx->d_tile_seg0; ls.seg_layer = ctx->d_seg_layer;
+    ls.counter = sp.d_counter_rest; ls.sub = sp.d_sub_rest; ls.flag = sp.d_flag_rest;
+  }
+  dispatch2(hk, xl.p != nullptr, [&](auto k_, auto lx) {
     dispatch1(sp.in_lds, [&](auto in_lds) {
       OB_LAUNCH(la, sp.in_lds ? KID_RATIOS_APPLY_HIST_LDS : KID_RATIOS_APPLY_HIST,
                 (k_ratios_apply_hist<decltype(k_)::value, decltype(lx)::value, decltype(in_lds)::value ? S_LH : 0>),
-                sp.n_fused_tiles + ls.n_lead, ra, vh, vterms(ctx), aa, ls, lt);
+                sp.n_fused_tiles + ls.n_lead, ra, vh, vt, aa, ls, lt);
     });
   });
   launch_apply(la, ctx, st, packed_all, server_scales, lr, sp.d_rest_tiles, sp.n_rest_tiles, xl);
@@ -1956,9 +2004,10 @@ ob_status ob_lamb_variance_dense(ob_lamb_ctx* ctx, const ob_lamb_state* st, cons
   if ((sp.on || sp.big_on) && sp.n_cov_tiles > 0) {
     const RatioArgs ra = ratio_args(ctx, st, packed_all, server_scales, pm);
     const LayerTab lt = layer_tab(ctx, st, ctx->d_first_layer);
-    launch_variance_terms(la, ctx, st, ra, vh);
-    OB_LAUNCH(la, KID_VARIANCE_DENSE, k_variance_dense, sp.n_cov_tiles, ra, vh, vterms(ctx),
-              vh.write_v ? (float*)nullptr : v_out, ctx->n_c, ctx->tpc, lt, sp.d_cov_tiles);
+    dispatch1(st->mom_scale != nullptr, [&](auto k_) {
+      OB_LAUNCH(la, KID_VARIANCE_DENSE, (k_variance_dense<decltype(k_)::value>), sp.n_cov_tiles, ra, vh,
+                vh.write_v ? (float*)nullptr : v_out, ctx->n_c, ctx->tpc, lt, sp.d_cov_tiles);
+    });
   }
   return la.ok ? OB_OK : OB_ERR_HIP;
 }

@@ -1160,17 +1160,22 @@ __global__ __launch_bounds__(BLOCK) void k_ratios_pass(RatioArgs ra, float* __re
   ratios_pass_tile<U, HAS_K, PACKED_M>(ra, seg_max, n_c, tpc, lt, tile_seg0, seg_layer, listed_tile(tile_list), lds);
 }
 
-// Algorithm 1 lines 18-20 for one layer given the raw ratio (thread 0 of a workgroup).
-// rp, ca: r_prev[l] and c_avg[l], read by the caller (early, where their latency hides).
-__device__ __forceinline__ float ratio_clip_commit(float r, int l, float rp, float ca,
-                                                   float* __restrict__ r_prev,
-                                                   float* __restrict__ coeff_c, float one_m_thr,
-                                                   float one_p_thr, float r_min, float r_max) {
+// Algorithm 1 lines 18-19 for one layer given the raw ratio.  rp: r_prev[l].
+__device__ __forceinline__ float ratio_clip(float r, float rp, float one_m_thr, float one_p_thr, float r_min, float r_max) {
   const float lo = one_m_thr * rp, hi = one_p_thr * rp;
   r = (r > lo) ? r : lo;
   r = (r < hi) ? r : hi;
   r = (r > r_min) ? r : r_min;
   r = (r < r_max) ? r : r_max;
+  return r;
+}
+// ... lines 18-20 (thread 0 of a workgroup).
+// rp, ca: r_prev[l] and c_avg[l], read by the caller (early, where their latency hides).
+__device__ __forceinline__ float ratio_clip_commit(float r, int l, float rp, float ca,
+                                                   float* __restrict__ r_prev,
+                                                   float* __restrict__ coeff_c, float one_m_thr,
+                                                   float one_p_thr, float r_min, float r_max) {
+  r = ratio_clip(r, rp, one_m_thr, one_p_thr, r_min, r_max);
   r_prev[l] = r;
   const float c = r * ca;
   coeff_c[l] = c;
@@ -2181,10 +2186,11 @@ struct SmallTab {
   int64_t n_c;
   const int* seg_layer;         // [segments]
   const int* layer_seg0;        // [L+1]
-  void* partial;                // [segments] float maxima, or [2 * segments] double sums
+  double* partial;              // [2 * segments] sums
   unsigned long long* counter;  // [L * CTR_STRIDE]
   unsigned long long* sub;      // group counters (group_line)
   unsigned long long* flag;     // [L * CTR_STRIDE]
+  unsigned long long* slots;    // [segments] (generation << 32) | partial result (k_ratios_apply_small; the others: k_warmup_small)
   unsigned int* errflag;
   int spin_limit;
 };
@@ -2245,13 +2251,48 @@ __device__ __forceinline__ void small_arrive(const SmallTab& sm, const SmallTile
   __syncthreads();
 }
 
+// The barrier of a layer in k_ratios_apply_small: every workgroup publishes its segment's partial result in a slot of its
+// own, together with the number of the launch, and every workgroup reads all slots of the layer until each holds that
+// number, so that only a store and a load lie between the last partial result and its readers.  (Arrivals counted at an
+// atomic, whose last one reads the results and publishes the coefficient, are five such trips, and with the two fp64
+// sums of k_warmup_small, four words a slot, those cost less: 10.6 us instead of 12.6 for four tensors of 262144.)  A step, us,
+// counted / slots: four of 262144 23.9 / 22.3, two of 1 M 36.4 / 32.1, one of 0.9 M (221 segments) 29.4 / 26.2, of 1.6 M
+// (391) 30.2 / 29.5, of 2.9 M (706) 37.6 / 37.3; 24 of 65536 27.0 / 27.4.  The number is one more
+// than what the slot held: nothing that changes from call to call comes from the host.  What a workgroup has read of r_prev and c_avg it has
+// before it publishes; the layer's first segment's workgroup writes them, once all have published.
+__device__ __forceinline__ unsigned long long slot_load(const unsigned long long* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, OB_AGENT);
+}
+__device__ __forceinline__ void slot_store(unsigned long long* p, unsigned int want, unsigned int payload) {
+  __hip_atomic_store(p, ((unsigned long long)want << 32) | payload, __ATOMIC_RELAXED, OB_AGENT);
+}
+// The thread's slots of the n at p, each when it holds generation `want`: take(payload).  Waits are bounded as in barrier_wait.
+template <class F>
+__device__ __forceinline__ void slots_wait(const SmallTab& sm, const unsigned long long* p, int n, unsigned int want, F take) {
+  int it = 0;
+  for (int i = threadIdx.x; i < n; i += BLOCK) {
+    unsigned long long v = slot_load(p + i);
+    while (sm.spin_limit == 0 || (unsigned int)(v >> 32) != want) {
+      if (it >= sm.spin_limit) {
+        atomicOr(sm.errflag, 1u);
+        break;
+      }
+      if ((it & 63) == 63 && __hip_atomic_load(sm.errflag, __ATOMIC_RELAXED, OB_AGENT) != 0u) break;
+      if (it < 64) __builtin_amdgcn_s_sleep(SMALL_POLL_SLEEP);
+      else __builtin_amdgcn_s_sleep(OB_POLL_SLEEP);
+      ++it;
+      v = slot_load(p + i);
+    }
+    take((unsigned int)v);
+  }
+}
+
 template <int U, bool HAS_K, bool LPX>
 __global__ __launch_bounds__(BLOCK, small_min_wg(U)) void k_ratios_apply_small(
     RatioArgs ra, VfHist h, ApplyArgs aa, SmallTab sm, RatioClip rc, LayerTab lt) {
   constexpr int TILE = SPAN * U;
   extern __shared__ int dyn_lds[];
   __shared__ float lds[BLOCK / WAVE];
-  __shared__ unsigned long long bc[2];
   __shared__ float c_end[2];
   if ((int)blockIdx.x == sm.n_tiles) {   // the layers without elements go through the clips too
     for (int l = threadIdx.x; l < lt.L; l += BLOCK)
@@ -2298,10 +2339,13 @@ __global__ __launch_bounds__(BLOCK, small_min_wg(U)) void k_ratios_apply_small(
   const int last_seg = ti.nseg - 1;
   const int n_end = ti.nseg > 1 ? 2 : 1;
   const int l_end[2] = {ti.l0, ti.l_last};
-  float r_end[2] = {0.0f, 0.0f};                 // (thread 0: of the first segment; thread WAVE: of the last)
-  // what the last arriver of a layer needs, requested with everything else
+  float r_end[2] = {0.0f, 0.0f};                 // maxima of the first and the last segment (thread 0)
+  // what finishing a layer takes, requested with everything else
   const float rp_end[2] = {rc.r_prev[ti.l0], rc.r_prev[ti.l_last]}, ca_end[2] = {rc.c_avg[ti.l0], rc.c_avg[ti.l_last]};
-  const int s0_end[2] = {sm.layer_seg0[ti.l0], sm.layer_seg0[ti.l_last]};
+  const int s0_end[2] = {sm.layer_seg0[ti.l0], sm.layer_seg0[ti.l_last]}, n_of[2] = {ti.n_first, ti.n_last};
+  const int s_end[2] = {ti.seg0, ti.seg0 + last_seg};
+  const unsigned int want[2] = {(unsigned int)(slot_load(&sm.slots[s_end[0]]) >> 32) + 1u,
+                                (unsigned int)(slot_load(&sm.slots[s_end[1]]) >> 32) + 1u};
   if (inside) {
     const float kt = HAS_K ? lt.mom_scale[ti.l0] : 1.0f;
 #pragma unroll
@@ -2376,37 +2420,21 @@ __global__ __launch_bounds__(BLOCK, small_min_wg(U)) void k_ratios_apply_small(
     __syncthreads();
     r_end[0] = sg.coeff[0];
     r_end[1] = sg.coeff[last_seg];
+  }
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+      if (e < n_end && n_of[e] > 1) {
+        asm volatile("" ::"v"(rp_end[e]), "v"(ca_end[e]) : "memory");   // both are there before the slot says so
+        slot_store(&sm.slots[s_end[e]], want[e], __float_as_uint(r_end[e]));
+      }
+  }
+  if (!inside) {   // the layers in between lie inside the tile
     __syncthreads();
-    for (int s = 1 + (int)threadIdx.x; s < last_seg; s += BLOCK) {   // the layers in between lie inside the tile
+    for (int s = 1 + (int)threadIdx.x; s < last_seg; s += BLOCK) {
       const int l = sg.layer[s];
       sg.coeff[s] = ratio_clip_commit(sg.coeff[s], l, rc.r_prev[l], rc.c_avg[l], rc.r_prev, rc.coeff_c, rc.one_m_thr,
                                       rc.one_p_thr, rc.r_min, rc.r_max);
-    }
-  }
-  float* const partial = reinterpret_cast<float*>(sm.partial);
-  small_arrive(sm, ti, n_end, s0_end, bc, [&](int e) {
-    __hip_atomic_store(&partial[ti.seg0 + (e ? last_seg : 0)], r_end[e], __ATOMIC_RELAXED, OB_AGENT);
-  });
-  for (int e = 0; e < n_end; ++e) {   // (uniform)
-    if ((bc[e] & 3ull) == 0ull) continue;
-    const int l = l_end[e], s0 = s0_end[e], s1 = s0 + (e ? ti.n_last : ti.n_first);
-    float q = 0.0f;
-    if (bc[e] & 1ull) {
-      for (int s = s0 + threadIdx.x; s < s1; s += BLOCK) {
-        const float v = __hip_atomic_load(&partial[s], __ATOMIC_RELAXED, OB_AGENT);
-        if (v > q) q = v;
-      }
-      q = block_max(q, lds);
-    } else if ((int)threadIdx.x == e * WAVE) {
-      q = r_end[e];
-    }
-    if ((bc[e] & 1ull) ? threadIdx.x == 0 : (int)threadIdx.x == e * WAVE) {
-      const float c = ratio_clip_commit(q, l, rp_end[e], ca_end[e], rc.r_prev, rc.coeff_c, rc.one_m_thr, rc.one_p_thr,
-                                        rc.r_min, rc.r_max);
-      c_end[e] = c;
-      if (bc[e] & 1ull)
-        (void)barrier_publish(&sm.flag[(int64_t)l * CTR_STRIDE], &sm.counter[(int64_t)l * CTR_STRIDE], s1 - s0,
-                              (unsigned int)(bc[e] >> 32), __float_as_uint(c), SMALL_ONE_LEVEL);
     }
   }
   // while the layers complete: the variance is stored, m_t/(sqrt(v_frozen)+eta) formed in place of v_frozen
@@ -2450,13 +2478,25 @@ __global__ __launch_bounds__(BLOCK, small_min_wg(U)) void k_ratios_apply_small(
       }
     }
   }
-  {
-    const int e = threadIdx.x / WAVE;
-    if (e < n_end && (threadIdx.x & (WAVE - 1)) == 0 && (bc[e] & 2ull) == 0ull) {
-      // (the last arriver too: with no polls left its own flag is as late as anyone's)
-      const unsigned long long f = barrier_wait<SMALL_POLL_SLEEP>(&sm.flag[(int64_t)l_end[e] * CTR_STRIDE], (unsigned int)(bc[e] >> 32),
-                                                sm.errflag, sm.spin_limit);
-      c_end[e] = __uint_as_float((unsigned int)(f & 0xffffffffull));
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    if (e >= n_end) break;   // (uniform)
+    float q = r_end[e];
+    if (n_of[e] > 1) {
+      q = 0.0f;
+      slots_wait(sm, sm.slots + s0_end[e], n_of[e], want[e], [&](unsigned int w) {
+        const float v = __uint_as_float(w);
+        if (v > q) q = v;
+      });
+      q = block_max(q, lds);
+    }
+    if (threadIdx.x == 0) {
+      const float r = ratio_clip(q, rp_end[e], rc.one_m_thr, rc.one_p_thr, rc.r_min, rc.r_max), c = r * ca_end[e];
+      if (s_end[e] == s0_end[e]) {
+        rc.r_prev[l_end[e]] = r;
+        rc.coeff_c[l_end[e]] = c;
+      }
+      c_end[e] = c;
     }
   }
   __syncthreads();
@@ -3261,7 +3301,7 @@ __global__ __launch_bounds__(BLOCK, small_min_wg(U)) void k_warmup_small(
     }
   }
   __syncthreads();
-  double* const partial = reinterpret_cast<double*>(sm.partial);
+  double* const partial = sm.partial;
   small_arrive(sm, ti, n_end, s0_end, bc, [&](int e) {
     double* q = partial + 2 * (int64_t)(ti.seg0 + (e ? last_seg : 0));
     __hip_atomic_store(q, end_sum[e][0], __ATOMIC_RELAXED, OB_AGENT);

@@ -132,6 +132,7 @@ struct SmallPlan {
   SmallTile* d_tiles = nullptr;
   int* d_seg_layer = nullptr;
   int* d_layer_seg0 = nullptr;
+  unsigned long long* d_slots = nullptr;    // [segments] (k_ratios_apply_small), or (k_warmup_small)
   double* d_partial = nullptr;          // [2 * segments]
   unsigned long long* d_counter = nullptr;
   unsigned long long* d_sub = nullptr;
@@ -885,7 +886,7 @@ struct SmallTilings {
 
 // Chooses and uploads a SmallPlan: of the U whose tiles take at most 80 % of the device's workgroup slots
 // (slots(U, dynamic LDS bytes)) the one of the lowest small_cost, the smallest of equals.  vals, tables: 4-byte words
-// of LDS per element and per segment of a tile that meets several layers.
+// of LDS per element and per segment of a tile that meets several layers; by_slots: the barriers are those of slots.
 // The list keeps the barrier kernel of the larger lists (split) where that is all it takes, every parameter lying in its
 // 8192-element tiles, and one layer has more than max_queue arrivals at its counter here, twice as many as there.
 // The calls of one tensor, or two equal ones, in whole tiles, us, LAMB step, ratios_apply, ratios_apply_hist, in one
@@ -896,7 +897,7 @@ constexpr int SMALL_QUEUE_APPLY = 512, SMALL_QUEUE_LAMB = 700;
 template <class F>
 bool build_small(ob_lamb_ctx* ctx, Workspace* ws, SmallTilings* tilings, const std::vector<int64_t>& h_off,
                  const std::vector<unsigned char>& lagging, const LayerSplit& split, int max_queue, int vals, int tables,
-                 F slots, SmallPlan* sp) {
+                 bool by_slots, F slots, SmallPlan* sp) {
   static_assert(TILE_MAIN == SPAN, "the TILE_MAIN tiling is that of U = 1");
   int best = 0;
   SmallShape sh;
@@ -925,10 +926,14 @@ bool build_small(ob_lamb_ctx* ctx, Workspace* ws, SmallTilings* tilings, const s
     ws->upload(&sp->d_tiles, std::move(tiles));
     ws->upload(&sp->d_seg_layer, t.seg_layer);
     ws->upload(&sp->d_layer_seg0, t.layer_seg0);
-    ws->alloc_zero(&sp->d_partial, 2 * t.seg_layer.size());
-    ws->alloc_zero(&sp->d_counter, (size_t)ctx->L * CTR_STRIDE);
-    ws->alloc_zero(&sp->d_sub, group_lines((int64_t)t.seg_layer.size(), ctx->L) * CTR_STRIDE);
-    ws->alloc_zero(&sp->d_flag, (size_t)ctx->L * CTR_STRIDE);
+    if (by_slots) {
+      ws->alloc_zero(&sp->d_slots, t.seg_layer.size());
+    } else {
+      ws->alloc_zero(&sp->d_partial, 2 * t.seg_layer.size());
+      ws->alloc_zero(&sp->d_counter, (size_t)ctx->L * CTR_STRIDE);
+      ws->alloc_zero(&sp->d_sub, group_lines((int64_t)t.seg_layer.size(), ctx->L) * CTR_STRIDE);
+      ws->alloc_zero(&sp->d_flag, (size_t)ctx->L * CTR_STRIDE);
+    }
     sp->u = best;
   }
   return true;
@@ -938,7 +943,8 @@ SmallTab small_tab(const ob_lamb_ctx* ctx, const SmallPlan& sp) {
   SmallTab t;
   t.tiles = sp.d_tiles; t.n_tiles = sp.n_tiles; t.tpc = sp.tpc; t.max_seg = sp.max_seg; t.n_c = ctx->n_c;
   t.seg_layer = sp.d_seg_layer; t.layer_seg0 = sp.d_layer_seg0; t.partial = sp.d_partial;
-  t.counter = sp.d_counter; t.sub = sp.d_sub; t.flag = sp.d_flag; t.errflag = ctx->d_errflag; t.spin_limit = ctx->spin_limit;
+  t.counter = sp.d_counter; t.sub = sp.d_sub; t.flag = sp.d_flag; t.slots = sp.d_slots;
+  t.errflag = ctx->d_errflag; t.spin_limit = ctx->spin_limit;
   return t;
 }
 
@@ -1377,7 +1383,7 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
     };
     SmallTilings tilings(tm, ctx->n_c, ctx->W, L, h_off);
     if (ok && cfg->fused_max_tiles == 0 && !(cfg->flags & OB_CFG_NO_FUSED_APPLY))
-      ok = build_small(ctx, &ws, &tilings, h_off, lagging, ctx->sp_apply, SMALL_QUEUE_APPLY, 1, 4, [&](int U, size_t bytes, int64_t* n) {
+      ok = build_small(ctx, &ws, &tilings, h_off, lagging, ctx->sp_apply, SMALL_QUEUE_APPLY, 1, 4, true, [&](int U, size_t bytes, int64_t* n) {
         bool r = false;
         dispatch_u(U, [&](auto u) {
           constexpr int UU = decltype(u)::value;
@@ -1387,7 +1393,7 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
       }, &ctx->sm_apply);
     if (ok && cfg->fused_max_tiles == 0 && !(cfg->flags & OB_CFG_TWO_PASS_WARMUP))
       ok = build_small(ctx, &ws, &tilings, h_off, std::vector<unsigned char>((size_t)tm.n_tiles, 0), ctx->sp_warm,
-                       SMALL_QUEUE_LAMB, 2, 3, [&](int U, size_t bytes, int64_t* n) {
+                       SMALL_QUEUE_LAMB, 2, 3, false, [&](int U, size_t bytes, int64_t* n) {
         bool r = false;
         dispatch_u(U, [&](auto u) {
           constexpr int UU = decltype(u)::value;

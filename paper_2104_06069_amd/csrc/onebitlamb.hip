@@ -222,6 +222,8 @@ struct ob_lamb_ctx {
   int tpc = 0;        // TILE_MAIN tiles per chunk
   int n_tiles = 0;    // W * tpc
   int tpc_srv = 0;    // TILE_SRV tiles of the server chunk
+  int u_srv = 1;      // spans per tile of the server kernel without a barrier
+  int n_srv = 0;      // such tiles of the server chunk
   int n_segs = 0;     // (tile, layer) segments
   // device memory
   int device = -1;
@@ -975,6 +977,18 @@ bool worker_ticket(int tpc, int n_tiles, int cus) {
 }
 bool server_ticket(int tpc, int n_tiles, int cus) { return tpc <= TICKET_SUB || two_level_ticket(tpc, n_tiles, cus); }
 
+// Spans per tile of the server kernel without a barrier (k_server_unpack_avg).  With few workers a tile of 1024 elements is a
+// chain of latencies (scales, LDS, words) around a few additions: larger ones where the chunk still makes rounds of
+// the device; with many workers the additions bind, and more, smaller workgroups hide them better.  The call, us, 1 / 2 / 4 spans
+// (above 1 with chunk_ticket, which by then costs less than a launch: 0.3 to 4 us), workers, tiles of 1024 elements:
+//   1, 107520 229 / 160 / 153; 2, 53760 121 / 88.1 / 80.7; 2, 5504 17.4 / 14.1 / 13.4; 4, 26880 73.8 / 46.0 / 45.1; 4, 2752 12.1 /
+//   9.9 / 10.6; 8, 13440 36.4 / 28.1 / 28.4; 8, 1376 8.4 / 8.4 / 9.7; 16, 6720 24.4 / 21.6 / 22.2; 16, 688 7.4 / 8.0 / 9.6; 32,
+//   3360 19.6 / 19.2 / 22.8; 64, 5254 37.3 / 37.5 / 42.7; 64, 1680 18.0 / 19.8 / 21.0; 128, 840 18.7 / 20.8 / 31.1
+int server_spans(int W, int tpc) {
+  if (W <= 2 && tpc >= 4096) return 4;
+  return (W <= 32 && tpc >= 2048) ? 2 : 1;
+}
+
 ChunkTicket chunk_ticket_of(unsigned int* count, double* part, int n_chunks, int tpc, float* scales, float* own_scale,
                             int own_chunk) {
   ChunkTicket tk;
@@ -1276,6 +1290,8 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
   const int64_t tpc_srv = (ctx->n_c + TILE_SRV - 1) / TILE_SRV;
   if (tpc_srv > 0x7fffffff) return OB_ERR_ARG;
   ctx->tpc_srv = (int)tpc_srv;
+  ctx->u_srv = server_spans(ctx->W, ctx->tpc_srv);
+  ctx->n_srv = (int)((tpc_srv + ctx->u_srv - 1) / ctx->u_srv);
 
   const std::vector<int64_t> h_off = host_offsets(cfg);
   Tiling tm, tl, tw;
@@ -1408,7 +1424,7 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
       ws.alloc_zero(&ctx->d_ticket, (size_t)ctx->W * (1 + spc) * line);
       ws.alloc_zero(&ctx->d_ticket_part, (size_t)ctx->W * spc);
     }
-    if (server_ticket(ctx->tpc, ctx->n_tiles, cus)) {
+    if (ctx->u_srv > 1 || server_ticket(ctx->tpc, ctx->n_tiles, cus)) {
       ws.alloc_zero(&ctx->d_ticket_srv, (1 + spc) * line);
       ws.alloc_zero(&ctx->d_ticket_part_srv, spc);
     }
@@ -1704,15 +1720,17 @@ ob_status ob_lamb_server_reduce(ob_lamb_ctx* ctx, const ob_lamb_state* st, const
     // deferred server error: one pass over the chunk plus its scale -- no barrier, no second pass
     if (misaligned(st->srv_err_packed)) return OB_ERR_ALIGN;
     if (st->srv_err_packed == packed_out) return OB_ERR_ARG;
-    const ChunkTicket tk = chunk_ticket_of(ctx->d_ticket_srv, ctx->d_ticket_part_srv, 1, ctx->tpc_srv, scale_out,
+    const ChunkTicket tk = chunk_ticket_of(ctx->d_ticket_srv, ctx->d_ticket_part_srv, 1, ctx->n_srv, scale_out,
                                            st->srv_err_scale, 0);
     dispatch1(tk.count != nullptr, [&](auto ti) {
-      OB_LAUNCH(la, KID_SERVER_AVG, (k_server_unpack_avg<U_SRV, true, decltype(ti)::value>), ctx->tpc_srv, packed_in,
-                scales_in, st->err_server, ctx->d_partials_srv, ctx->n_c, (int)ctx->W, ctx->invW, st->srv_err_packed,
-                st->srv_err_scale, packed_out, tk);
+      dispatch_u(ctx->u_srv, [&](auto u) {
+        OB_LAUNCH(la, KID_SERVER_AVG, (k_server_unpack_avg<decltype(u)::value, true, decltype(ti)::value>), ctx->n_srv, packed_in,
+                  scales_in, st->err_server, ctx->d_partials_srv, ctx->n_c, (int)ctx->W, ctx->invW, st->srv_err_packed,
+                  st->srv_err_scale, packed_out, tk);
+      });
     });
     if (!tk.count)
-      OB_LAUNCH_B(la, KID_SERVER_SCALE, k_chunk_scale, 1, FBLOCK, ctx->d_partials_srv, ctx->tpc_srv, ctx->n_c, scale_out,
+      OB_LAUNCH_B(la, KID_SERVER_SCALE, k_chunk_scale, 1, FBLOCK, ctx->d_partials_srv, ctx->n_srv, ctx->n_c, scale_out,
                 st->srv_err_scale, 0);
     return la.ok ? OB_OK : OB_ERR_HIP;
   }
@@ -1737,10 +1755,12 @@ ob_status ob_lamb_server_reduce(ob_lamb_ctx* ctx, const ob_lamb_state* st, const
     }
     return la.ok ? OB_OK : OB_ERR_HIP;
   }
-  OB_LAUNCH(la, KID_SERVER_AVG, (k_server_unpack_avg<U_SRV>), ctx->tpc_srv, packed_in, scales_in,
-            st->err_server, ctx->d_partials_srv, ctx->n_c, (int)ctx->W, ctx->invW, (uint32_t*)nullptr,
-            (const float*)nullptr, (uint32_t*)nullptr, ChunkTicket{});
-  OB_LAUNCH_B(la, KID_SERVER_SCALE, k_chunk_scale, 1, FBLOCK, ctx->d_partials_srv, ctx->tpc_srv, ctx->n_c, scale_out,
+  dispatch_u(ctx->u_srv, [&](auto u) {
+    OB_LAUNCH(la, KID_SERVER_AVG, (k_server_unpack_avg<decltype(u)::value>), ctx->n_srv, packed_in, scales_in,
+              st->err_server, ctx->d_partials_srv, ctx->n_c, (int)ctx->W, ctx->invW, (uint32_t*)nullptr,
+              (const float*)nullptr, (uint32_t*)nullptr, ChunkTicket{});
+  });
+  OB_LAUNCH_B(la, KID_SERVER_SCALE, k_chunk_scale, 1, FBLOCK, ctx->d_partials_srv, ctx->n_srv, ctx->n_c, scale_out,
               (float*)nullptr, 0);
   OB_LAUNCH(la, KID_SERVER_PACK, (k_sign_pack_error<U_SRV>), ctx->tpc_srv, st->err_server, packed_out,
             scale_out, ctx->n_c, ctx->tpc_srv);

@@ -22,6 +22,18 @@ import torch
 
 from . import binding as ob
 
+try:      # the address of the current stream without an object around it: 0.3 instead of 2.2 us, of the 20 a step takes the host
+    from torch._C import _cuda_getCurrentRawStream
+except ImportError:     # (a build of torch without devices)
+    _cuda_getCurrentRawStream = None
+
+
+def _current_stream(device):
+    if _cuda_getCurrentRawStream is None or device.index is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    return _cuda_getCurrentRawStream(device.index)
+
+
 _STATE_FIELDS = ("x", "m", "v_fresh", "v_frozen", "err_worker", "err_server", "c_avg", "r_prev", "coeff_c", "mom_scale",
                  "m_packed", "m_scales", "own_packed_in", "own_scale_in", "err_packed", "err_scales", "srv_err_packed",
                  "srv_err_scale")     # the order in which DeviceStep._state() fills the structure
@@ -246,7 +258,7 @@ class DeviceStep:
 
     @property
     def stream(self):
-        return torch.cuda.current_stream(self.device).cuda_stream
+        return _current_stream(self.device)
 
     # ---- the calls ---------------------------------------------------------------------------
     @staticmethod

@@ -1825,7 +1825,9 @@ __device__ __forceinline__ void variance_terms_of_pair(const RatioArgs& ra, cons
 
 // The values of a tile, those of step s in lane s - 1 of each group of 8, from where the walk reads them: fetched from
 // the table (vt.t), or formed by these lanes, once for all steps, while the wavefront's loads are in flight.  Forming
-// them makes the launch before unnecessary; over 37000 tiles it costs more (6910 / 6970 us for four steps).
+// them makes the launch before unnecessary; over 37000 tiles it costs more (6910 / 6970 us for four steps).  (A kernel of its
+// own for each form spares 40 scalar registers their spills, but the one with the table then spills 27 to 46 vector
+// registers at OB_LB_MINW workgroups per CU: 6830 / 7680 us.)
 struct StepTerms {
   float same, diff;
   template <bool HAS_K>
@@ -2163,18 +2165,18 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
 // reductions of a few microseconds whatever it moves.  Here every tile, whatever layers it meets, is one
 // workgroup that runs the ratio pass, takes part in the barriers of its layers and then the update, with
 // x, v_frozen and the signs in registers.  U is 1, 2 or 4: small tiles keep a workgroup's own chain of
-// look-ups and divisions short, large ones the queue at a layer's counter (small_cost in the host code).
+// look-ups and divisions short, large ones the number of slots that each reads (small_cost in the host code).
 //
 // In a tile that meets several layers, what depends on the layer alone is formed once per segment (with momentum
 // scaling, by each element: 24 tensors of 300x300 28.5 instead of 20.5 us) and each lane looks its segments up once.
 //
 // A layer wholly inside a tile needs no barrier; only the first and the last segment of a tile can belong
-// to a layer that goes on elsewhere.  Same self-numbering counters, bounded waits and co-residency rule
-// (80 % of the workgroup slots) as the other barriers.  The spans that k_ratios_apply_hist would handle
+// to a layer that goes on elsewhere.  Barriers without counters (slots, below); bounded waits and co-residency rule (80 % of
+// the workgroup slots) as for the other barriers.  The spans that k_ratios_apply_hist would handle
 // from the variance's history ("lagging") do so here too, so that what the v_fresh array holds between two
 // calls does not depend on the kernel; their two values per step are formed by each thread.
-// Measured: four 512x512 tensors 9.0 us (k_ratios_apply_resident 12.6); 46 tensors of 2 to 64000 elements
-// 10.5 us (26 us in three launches, and the gaps between them).
+// Measured: four 512x512 tensors 8.8 us with slots, 9.7 with counted arrivals (k_ratios_apply_resident 12.6); 46 tensors of 2
+// to 64000 elements 9.4, 10.4 (26 us in three launches, and the gaps between them).
 // ---------------------------------------------------------------------------------------------
 struct SmallTile {
   int l0;          // layer of the first element

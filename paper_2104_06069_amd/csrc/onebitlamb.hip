@@ -865,6 +865,9 @@ SmallShape small_shape(int U, const std::vector<int64_t>& h_off, int64_t n_c, in
 //   8192-element tiles, k_warmup_resident and k_ratios_apply_resident: 16.1, 14.6)
 //   four of 125000 9.0 / 11.2 / 14.4, 9.5 / 12.2 / 14.6; 0.8 M and ten of 80000 17.7 / 14.4 / 20.1, 18.3 / 14.8 / 19.7
 //   3000 of 1 and one of 1.2 M 205 / 394 / 561, 105 / 213 / 306
+// (ratios_apply with counted arrivals.  With slots, called over and over with everything in the caches: eight of 65536 6.5 / 6.7 /
+// 8.6, four of 262144 7.9 / 8.0 / 9.6, 0.9 M 8.2 / 8.3 / 12.4, 1.6 M 11.3 / 11.2 / 14.2; as part of a step, which is what the choice
+// goes by, four of 262144 25.0 / 24.0 / 25.8, 0.9 M 28.5 / 25.5 / 29.9, 1.6 M 33.5 / 31.9 / 30.2.)
 int64_t small_cost(int U, const SmallShape& sh) {
   return (U == 1 ? 0 : U == 2 ? 500 : 2000) + 13 * sh.max_arrivals + 2500 * std::max(sh.mixed_spans - 1, 0) + 100 * sh.max_seg;
 }
@@ -894,7 +897,8 @@ struct SmallTilings {
 // The calls of one tensor, or two equal ones, in whole tiles, us, LAMB step, ratios_apply, ratios_apply_hist, in one
 // launch / in the barrier kernel: 1.6 M (391 arrivals) 15.4 / 16.8, 15.9 / 16.0, 16.9 / 17.1; two of 1.6 M (392) 18.9 /
 // 20.3, 19.0 / 19.0, 20.3 / 19.6; 2.4 M (586) 18.5 / 19.4, 18.7 / 18.6, 19.9 / 19.5; 3.2 M (782) 22.4 / 21.5, 22.5 / 20.0,
-// 23.7 / 20.6; with a part outside those tiles, so that the plain kernels run too, 3.2 M 23.0 / 33.2, 22.7 / 27.6, 23.8 / 26.1.
+// 23.7 / 20.6 (with slots and arrivals in two levels: 1.6 M 14.5 / 14.2, 11.2 / 16.5, 12.2 / 16.1; 2.4 M 14.6 / 19.1, 15.0 / 18.5,
+// 16.5 / 17.6; 3.2 M 17.4 / 20.4, 18.1 / 19.0, 18.8 / 17.9); with a part outside those tiles, so that the plain kernels run too, 3.2 M 23.0 / 33.2, 22.7 / 27.6, 23.8 / 26.1.
 constexpr int SMALL_QUEUE_APPLY = 512, SMALL_QUEUE_LAMB = 700;
 template <class F>
 bool build_small(ob_lamb_ctx* ctx, Workspace* ws, SmallTilings* tilings, const std::vector<int64_t>& h_off,

@@ -30,19 +30,14 @@
 #include <cstdint>
 #include <type_traits>
 
+#include "ob_plan.h"
+
 namespace obk {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-constexpr int BLOCK = 256;       // threads per workgroup (4 wavefronts of 64)
-constexpr int WAVE = 64;
-constexpr int SPAN = BLOCK * 4;  // elements one workgroup-wide 128-bit access covers
 constexpr int FBLOCK = 1024;     // threads per workgroup of the small per-layer / per-chunk finalize kernels
 #define OB_AGENT __HIP_MEMORY_SCOPE_AGENT
-// Arrival counters of different chunks / layers sit 128 bytes apart: read-modify-write atomics on one
-// cache line are served one at a time (12 ns each, measured), whichever word of it they address,
-// and several chunks or layers are always in flight together.
-constexpr int CTR_STRIDE = 16;   // in 8-byte words
 #ifndef OB_POLL_SLEEP
 #define OB_POLL_SLEEP 16  // s_sleep argument (units of 64 clocks) between two polls of a barrier flag
 #endif
@@ -358,7 +353,6 @@ struct ZTile {
 // served one at a time); whoever completes a counter sets it back, so nothing changes from call to call.
 // Only the first wavefront takes part, after the workgroup's stores: nothing waits for anything.
 // ---------------------------------------------------------------------------------------------
-constexpr int TICKET_SUB = 64;
 struct ChunkTicket {
   unsigned int* count;     // lines of CTR_STRIDE 8-byte words: [chunks] second level, [chunks * spc] first level
   double* sub_part;        // [chunks * spc]
@@ -622,7 +616,6 @@ __device__ __forceinline__ void barrier_rearm(unsigned long long* counter, int n
 // 957 565 / 559, 514 / 514.  Up to 256 the second round trip costs what the queue does: one of 256 35.2 / 35.1, four 67.6 / 66.5,
 // twelve 149 / 149; and up to 512 in lists of many rounds of the device, whose tiles arrive spread out: 96 of 128 and 48 of 512
 // 1728 / 1738 (arrivals_one_level in the host code).  Groups of 16 or 64: the same.
-constexpr int ARRIVE_ONE_LEVEL = 256, ARRIVE_SUB = 32;
 __device__ __forceinline__ int top_arrivals(int n, int one_level) { return n > one_level ? (n + ARRIVE_SUB - 1) / ARRIVE_SUB : n; }
 __device__ __forceinline__ unsigned long long barrier_arrive(unsigned long long* top, unsigned long long* sub, int j, int n,
                                                              int one_level = ARRIVE_ONE_LEVEL) {
@@ -1408,10 +1401,6 @@ __device__ __forceinline__ void for_layer_parts(const LayerParts& q, T zero, FL 
   for (int j = q.s_end + threadIdx.x; j < q.b; j += BLOCK) plain(j);
 }
 
-// Where the group counters of layer l begin (in 8-byte words), whose arrivals are first, first + 1, ... in a numbering
-// that runs on from layer to layer: no two layers' groups overlap, and no table is needed.
-__device__ __forceinline__ int64_t group_line(int first, int l) { return (int64_t)(first / ARRIVE_SUB + l) * CTR_STRIDE; }
-
 struct LayerSync {
   float* seg_max;               // [segments of the 1024-element tiling] maxima left by the plain ratio pass
   float* listed_max;            // [listed tiles] maxima of this launch's tiles
@@ -1495,7 +1484,7 @@ __device__ __forceinline__ void rest_arrive(const LayerSync& ls, int tile, float
   auto arrivals = [&](const LayerParts& lp, int l, int* a, int* e) {
     *a = ls.skip_first[l];
     *e = ls.skip_end[l];
-    return lp.nl + (*a - lp.a) + (lp.b - *e);
+    return layer_arrivals(lp.nl, lp.a, *a, *e, lp.b);
   };
   if (threadIdx.x == 0) payload_before_arrival();   // (thread 0 has stored the maxima)
   __syncthreads();
@@ -1505,7 +1494,7 @@ __device__ __forceinline__ void rest_arrive(const LayerSync& ls, int tile, float
     const LayerParts lp = layer_parts(ls.lt, l);
     int a, b;
     const int n = arrivals(lp, l, &a, &b);
-    const int j = lp.nl + (sg < a ? sg - lp.a : (a - lp.a) + (sg - b));
+    const int j = rest_arrival(sg, lp.nl, lp.a, a, b);
     bc[e] = (n == 1) ? 1ull : barrier_arrive(&ls.counter[(int64_t)l * CTR_STRIDE], ls.sub + group_line(ls.arr0[l], l), j, n, ls.lt.one_level);
   }
   __syncthreads();
@@ -2107,7 +2096,8 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
   }
   r = block_max(r, lds);
   // before any store: nothing to wait for
-  layer_arrive(ls, bid, l0, lp, first, lp.nl + (ls.rest_tiles ? (lp.s_first - lp.a) + (lp.b - lp.s_end) : 0), rp, ca, r, lds, &bc);
+  layer_arrive(ls, bid, l0, lp, first, ls.rest_tiles ? layer_arrivals(lp.nl, lp.a, lp.s_first, lp.s_end, lp.b) : lp.nl, rp, ca, r,
+               lds, &bc);
   if (h.write_v) {   // uniform
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -2178,16 +2168,6 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
 // Measured: four 512x512 tensors 8.8 us with slots, 9.7 with counted arrivals (k_ratios_apply_resident 12.6); 46 tensors of 2
 // to 64000 elements 9.4, 10.4 (26 us in three launches, and the gaps between them).
 // ---------------------------------------------------------------------------------------------
-struct SmallTile {
-  int l0;          // layer of the first element
-  int seg0;        // first segment
-  int nseg;        // segments (0: padding)
-  int chunk_kind;  // chunk << 2 | (1: wholly inside one layer) | (2: lagging)
-  int l_last;      // layer of the last segment
-  int n_first;     // segments of the first segment's layer, over all tiles
-  int n_last;      // ... of the last segment's
-  int pad;
-};
 // workgroups per CU that the kernels are built for (their registers at each U)
 constexpr int small_min_wg(int u) { return u == 1 ? 8 : (u == 2 ? 5 : 4); }
 // Arrivals counted in one level (a LAMB step, us, one level / two: 384 arrivals 26.8 / 27.1, 588 19.5 / 16.5, 706 20.4 / 16.7).
@@ -3018,10 +2998,6 @@ __device__ __forceinline__ void buf_st4(__amdgpu_buffer_rsrc_t r, int byte, v4f 
   typedef unsigned int v4u __attribute__((ext_vector_type(4)));
   __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), r, byte, 0, POLICY);
 }
-constexpr unsigned int TRAIL_UPDATE = 1u << 31;   // update (else: moments)
-constexpr unsigned int TRAIL_KEEP = 1u << 30;     // moments: read again soon
-constexpr int TRAIL_U = 2;                        // spans per part
-constexpr int TRAIL_PARTS = 8 / TRAIL_U;          // parts per tile
 struct TrailTab {
   const unsigned int* items;    // of this launch: flags above | tile's position in lt.tile_list * TRAIL_PARTS + part
   ListedTiles lt;               // the tiles of these layers (positions as for the barrier kernels)

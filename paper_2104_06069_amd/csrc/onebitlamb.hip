@@ -20,6 +20,7 @@
 #include <vector>
 
 #include "ob_kernels.h"
+#include "ob_plan.h"
 #include "onebitlamb.h"
 
 using namespace obk;
@@ -76,9 +77,6 @@ constexpr int S_LH = 6;        // spans in LDS in the LDS form of k_ratios_apply
 #endif
 constexpr int U_WU = OB_U_WU;  // ... in the single-pass warmup kernel (u and x stay in registers and LDS)
 constexpr int TILE_WU = SPAN * U_WU;
-#ifndef OB_BIG_MIN_TILES
-#define OB_BIG_MIN_TILES 64   // a layer outside the barrier kernel with at least that many whole 8192-element tiles
-#endif
 #ifndef OB_G_WU
 #define OB_G_WU 1
 #endif
@@ -480,238 +478,6 @@ ob_status momentum_source(const ob_lamb_state* st, bool* packed, PackedMom* pm) 
   return OB_OK;
 }
 
-// Tables of one tiling of the padded buffer (tiles of `tile` elements inside each chunk): the layer
-// of each tile's first element (L = padding), the (tile, layer) segments in position order and
-// their grouping by layer.
-struct Tiling {
-  int64_t tpc = 0, n_tiles = 0;
-  std::vector<int> first, tile_seg0, seg_layer, layer_seg0;
-};
-
-bool build_tiling(int64_t tile, int64_t n_c, int64_t W, int64_t L, const std::vector<int64_t>& h_off,
-                  Tiling* out) {
-  out->tpc = (n_c + tile - 1) / tile;
-  out->n_tiles = out->tpc * W;
-  if (out->n_tiles > 0x7fffffff) return false;
-  out->first.resize((size_t)out->n_tiles);
-  out->tile_seg0.resize((size_t)out->n_tiles + 1);
-  out->seg_layer.clear();
-  out->layer_seg0.assign((size_t)L + 1, 0);
-  for (int64_t t = 0; t < out->n_tiles; ++t) {
-    const int64_t c = t / out->tpc, b = t % out->tpc;
-    const int64_t tile0 = c * n_c + b * tile;
-    const int64_t tile1 = std::min(tile0 + tile, (c + 1) * n_c);
-    // first layer: the non-empty layer that holds tile0 (binary search on the offsets)
-    int64_t lo = 0, hi = L + 1;  // h_off[lo] <= tile0 < h_off[hi]
-    while (hi - lo > 1) {
-      const int64_t mid = (lo + hi) / 2;
-      if (h_off[(size_t)mid] <= tile0) lo = mid; else hi = mid;
-    }
-    out->first[(size_t)t] = (int)lo;  // lo == L when tile0 >= N
-    out->tile_seg0[(size_t)t] = (int)out->seg_layer.size();
-    for (int64_t l = lo; l < L && h_off[(size_t)l] < tile1; ++l) {
-      const int64_t a = std::max(h_off[(size_t)l], tile0), e = std::min(h_off[(size_t)l + 1], tile1);
-      if (e > a) out->seg_layer.push_back((int)l);
-    }
-  }
-  out->tile_seg0[(size_t)out->n_tiles] = (int)out->seg_layer.size();
-  std::vector<int> count((size_t)L, 0);  // segments are ordered by position, hence grouped by layer
-  for (int l : out->seg_layer) ++count[(size_t)l];
-  for (int64_t l = 0; l < L; ++l)
-    out->layer_seg0[(size_t)l + 1] = out->layer_seg0[(size_t)l] + count[(size_t)l];
-  return true;
-}
-
-// The host side of one LayerSplit: which tiles the barrier kernel takes and what is left.
-struct SplitPlan {
-  std::vector<unsigned char> has_listed;   // [L] 1 for layers that the barrier kernel finishes
-  std::vector<int> fused_tiles, rest_tiles, n_listed, list_begin, seg_first, seg_end;
-  std::vector<unsigned char> covered;      // [TILE_MAIN tiles] 1 inside a listed tile
-  std::vector<int> big_tiles, rest_ratio_tiles;
-  std::vector<int> big_n, big_begin, big_seg_first, big_seg_end;   // [L]
-  std::vector<unsigned char> covered_big;  // [TILE_MAIN tiles] 1 inside a big tile
-  int64_t n_layers = 0, n_params = 0, n_big_params = 0;
-};
-
-// Which layers outside the barrier kernel have big tiles: those with enough whole tiles and not too many,
-// and only if they hold enough together.
-struct BigRule {
-  int64_t min_tiles = OB_BIG_MIN_TILES, max_tiles = std::numeric_limits<int64_t>::max(), min_total = 0;
-};
-
-// tl / tm: the barrier kernel's tiling (tiles of tile_lb elements) and the TILE_MAIN tiling;
-// max_tiles: the largest number of tiles of one layer the barrier kernel may hold (0: it is not
-// used).  No HIP call.
-void plan_split(const Tiling& tl, int64_t tile_lb, const Tiling& tm, const std::vector<int64_t>& h_off,
-                int64_t n_c, int64_t L, int64_t max_tiles, const BigRule& rule, SplitPlan* pl) {
-  pl->has_listed.assign((size_t)L, 0);
-  pl->n_listed.assign((size_t)L, 0);
-  pl->list_begin.assign((size_t)L, 0);
-  pl->seg_first.assign(tm.layer_seg0.begin(), tm.layer_seg0.begin() + L);   // (no listed tile: nothing skipped)
-  pl->seg_end = pl->seg_first;
-  pl->covered.assign((size_t)tm.n_tiles, 0);
-  auto tile_range = [&](int64_t t, int64_t* tile0, int64_t* tile1) {
-    const int64_t c = t / tl.tpc, b = t % tl.tpc;
-    *tile0 = c * n_c + b * tile_lb;
-    *tile1 = std::min(*tile0 + tile_lb, (c + 1) * n_c);
-  };
-  // tiles inside one layer, per layer in position order
-  std::vector<std::vector<int>> inside((size_t)L);
-  for (int64_t t = 0; t < tl.n_tiles; ++t) {
-    int64_t tile0, tile1;
-    tile_range(t, &tile0, &tile1);
-    const int l = tl.first[(size_t)t];
-    if (l < L && tile1 <= h_off[(size_t)l + 1]) inside[(size_t)l].push_back((int)t);
-  }
-  for (int64_t l = 0; l < L; ++l) {
-    const std::vector<int>& in = inside[(size_t)l];
-    const size_t n = in.size();
-    if (n == 0 || n > (size_t)max_tiles) continue;   // (max_tiles = 0: no layer is listed)
-    pl->has_listed[(size_t)l] = 1;
-    pl->n_listed[(size_t)l] = (int)n;
-    pl->list_begin[(size_t)l] = (int)pl->fused_tiles.size();
-    pl->n_layers += 1;
-    for (size_t j = 0; j < n; ++j) {
-      const int64_t t = in[j];
-      int64_t tile0, tile1;
-      tile_range(t, &tile0, &tile1);
-      pl->fused_tiles.push_back((int)t);
-      pl->n_params += tile1 - tile0;
-      const int64_t c = t / tl.tpc, b = t % tl.tpc;
-      const int64_t span0 = c * tm.tpc + b * (tile_lb / TILE_MAIN);
-      const int64_t nspan = (tile1 - tile0 + TILE_MAIN - 1) / TILE_MAIN;
-      for (int64_t j2 = 0; j2 < nspan; ++j2) pl->covered[(size_t)(span0 + j2)] = 1;
-      // each of these spans lies inside the layer: one segment each, consecutive
-      if (j == 0) pl->seg_first[(size_t)l] = tm.tile_seg0[(size_t)span0];
-      pl->seg_end[(size_t)l] = tm.tile_seg0[(size_t)(span0 + nspan)];
-    }
-  }
-  // big tiles: the whole tiles of the layers that hold many of them but are not listed
-  pl->covered_big.assign((size_t)tm.n_tiles, 0);
-  for (std::vector<int>* v : {&pl->big_n, &pl->big_begin, &pl->big_seg_first, &pl->big_seg_end}) v->assign((size_t)L, 0);
-  auto is_big = [&](int64_t l) {
-    const int64_t n = (int64_t)inside[(size_t)l].size();
-    return !pl->has_listed[(size_t)l] && n >= rule.min_tiles && n <= rule.max_tiles;
-  };
-  int64_t n_big = 0;
-  for (int64_t l = 0; l < L; ++l) n_big += is_big(l) ? (int64_t)inside[(size_t)l].size() : 0;
-  for (int64_t l = 0; l < L; ++l) {   // (also when no layer is listed: the pass needs no barrier)
-    if (!is_big(l) || n_big < rule.min_total) continue;
-    const std::vector<int>& in = inside[(size_t)l];
-    pl->big_n[(size_t)l] = (int)in.size();
-    pl->big_begin[(size_t)l] = (int)pl->big_tiles.size();
-    for (int t : in) {
-      int64_t tile0, tile1;
-      tile_range(t, &tile0, &tile1);
-      pl->big_tiles.push_back(t);
-      pl->n_big_params += tile1 - tile0;
-      const int64_t c = t / tl.tpc, b = t % tl.tpc;
-      const int64_t span0 = c * tm.tpc + b * (tile_lb / TILE_MAIN);
-      const int64_t nspan = (tile1 - tile0 + TILE_MAIN - 1) / TILE_MAIN;
-      for (int64_t j2 = 0; j2 < nspan; ++j2) pl->covered_big[(size_t)(span0 + j2)] = 1;
-      if (t == in.front()) pl->big_seg_first[(size_t)l] = tm.tile_seg0[(size_t)span0];
-      pl->big_seg_end[(size_t)l] = tm.tile_seg0[(size_t)(span0 + nspan)];
-    }
-  }
-  for (int64_t t = 0; t < tm.n_tiles; ++t)
-    if (!pl->covered[(size_t)t] && tm.tile_seg0[(size_t)t + 1] > tm.tile_seg0[(size_t)t]) {
-      pl->rest_tiles.push_back((int)t);
-      if (!pl->covered_big[(size_t)t]) pl->rest_ratio_tiles.push_back((int)t);
-    }
-}
-
-// Which layers k_warmup_trail takes, and how.  A LAMB step, us, in two passes over everything outside the barrier
-// kernel / with k_warmup_trail (256 CUs; fp32 gradient except gpt, 16-bit there):
-//   in one launch: squares of 3300 x 1 75.7 / 78.2, 4000 x 1 115 / 109, 3400 x 2 156 / 151, 5000 x 1 173 / 160, 4000 x 3 313 / 286,
-//     5000 x 8 1335 / 1175, 7000 x 6 1930 / 1838, 20000 x 2 5400 / 5520; the GPT list of 1.3e9 parameters 8490 / 7400
-//   in several launches (no kernel may wait): BERT and GPT lists of 11 M 80 / 87, 25 M 152 / 160, 40 M 273 / 275,
-//     50 M 353 / 332, 60 M 400 / 386, 110 M 733 / 681, 336 M 2218 / 2056, 1.3e9 8800 / 8010
-// so that it is taken from 14.7 M and 42 M elements on, and not for layers of which the cache holds next to nothing.
-// A configuration that lowers the barrier kernels' limit (cap) takes it for lists of any size.
-constexpr int64_t TRAIL_MIN_TILES = 1792, TRAIL_MIN_TILES_NO_WAIT = 5120, TRAIL_MAX_LAYER_TILES = 16384;
-BigRule trail_rule(bool wait, int32_t cap) {
-  BigRule r;
-  r.max_tiles = TRAIL_MAX_LAYER_TILES;
-  r.min_total = cap > 0 ? 0 : wait ? TRAIL_MIN_TILES : TRAIL_MIN_TILES_NO_WAIT;
-  return r;
-}
-
-// The workgroups of k_warmup_trail in order (no HIP call).  n, begin: parts of each layer.  lag > 0: one launch, the
-// update of a layer `lag` moments parts after the layer's last one: what is in flight on the device then (2048
-// workgroups) lies between them, so that no update waits for long (half of that 2 % slower, twice no difference).  lag = 0: no update
-// waits; the layers are taken in groups of at least `group` parts (16.8 M elements; 33 M no difference), and a launch updates one
-// group and forms the moments of the next.
-// A layer of more than TRAIL_KEEP_PARTS parts (16.8 M elements, 200 MB of m, v and x) does not fit the cache: its last
-// parts are updated first, and only they are kept.
-constexpr int64_t TRAIL_LAG = 2560, TRAIL_GROUP = 8192, TRAIL_KEEP_PARTS = 8192;
-void trail_items(const std::vector<int>& n, const std::vector<int>& begin, int64_t lag, int64_t group,
-                 std::vector<unsigned int>* items, std::vector<int64_t>* item_end) {
-  items->clear();
-  item_end->clear();
-  auto moments = [&](int64_t l) {
-    const int64_t keep = n[(size_t)l] - std::min<int64_t>(n[(size_t)l], TRAIL_KEEP_PARTS);
-    for (int64_t j = 0; j < n[(size_t)l]; ++j)
-      items->push_back((unsigned int)(begin[(size_t)l] + j) | (j >= keep ? TRAIL_KEEP : 0u));
-  };
-  auto update = [&](int64_t l) {
-    const int64_t keep = n[(size_t)l] - std::min<int64_t>(n[(size_t)l], TRAIL_KEEP_PARTS);
-    for (int64_t j = keep; j < n[(size_t)l]; ++j) items->push_back((unsigned int)(begin[(size_t)l] + j) | TRAIL_UPDATE);
-    for (int64_t j = 0; j < keep; ++j) items->push_back((unsigned int)(begin[(size_t)l] + j) | TRAIL_UPDATE);
-  };
-  std::vector<int64_t> layers;
-  for (size_t l = 0; l < n.size(); ++l)
-    if (n[l] > 0) layers.push_back((int64_t)l);
-  if (layers.empty()) return;
-  if (lag > 0) {
-    size_t done = 0;   // layers whose update is in the list
-    for (size_t i = 0; i < layers.size(); ++i) {
-      const size_t first = items->size();
-      moments(layers[i]);
-      // the updates that become due among this layer's moments parts go in between
-      const std::vector<unsigned int> tiles(items->begin() + (int64_t)first, items->end());
-      items->resize(first);
-      const int64_t at0 = begin[(size_t)layers[i]];   // moments parts before this layer
-      size_t j = 0;
-      for (; done < i; ++done) {
-        const int64_t due = begin[(size_t)layers[done]] + n[(size_t)layers[done]] + lag;
-        if (due > at0 + (int64_t)tiles.size()) break;
-        for (; at0 + (int64_t)j < due; ++j) items->push_back(tiles[j]);
-        update(layers[done]);
-      }
-      for (; j < tiles.size(); ++j) items->push_back(tiles[j]);
-    }
-    for (; done < layers.size(); ++done) update(layers[done]);
-    item_end->push_back((int64_t)items->size());
-    return;
-  }
-  size_t from = 0, updated = 0;
-  while (from < layers.size()) {
-    size_t to = from;
-    int64_t tiles = 0;
-    while (to < layers.size() && tiles < group) tiles += n[(size_t)layers[to++]];
-    for (; updated < from; ++updated) update(layers[updated]);
-    for (size_t i = from; i < to; ++i) moments(layers[i]);
-    item_end->push_back((int64_t)items->size());
-    from = to;
-  }
-  for (; updated < layers.size(); ++updated) update(layers[updated]);
-  item_end->push_back((int64_t)items->size());
-}
-
-// Group counters of a barrier with n arrivals, and of the barriers of L layers with n together (group_line).
-size_t arrival_groups(int64_t n) { return (size_t)((n + ARRIVE_SUB - 1) / ARRIVE_SUB); }
-size_t group_lines(int64_t n, int64_t L) { return arrival_groups(n) + (size_t)L; }
-
-// Whether the plain ratio pass runs in k_ratios_apply_hist's launch instead of its own, which saves that launch (5.6 us and
-// a gap) and costs its tiles the occupancy of their own kernel and every wavefront the values of StepTerms.  A step, us, in a
-// launch of its own / in that one, rest tiles and 8192-element tiles: 240, 1424 86.4 / 83.6; 1209, 2232 131.3 / 128.8; 468,
-// 2580 140.6 / 138.8; 433, 1713 110.1 / 109.3; 286, 3920 188.4 / 188.7; 1600, 4800 236.9 / 241.7; 647, 5135 242 / 239.7; 1297, 9677
-// 448 / 445; 710, 11239 501 / 511; 997, 25803 1134 / 1140; 1430, 40908 1716 / 1728.
-constexpr int REST_IN_LAUNCH_MAX = 1280, REST_IN_LAUNCH_MAX_TILES = 5120;
-bool rest_in_launch(int n_rest_tiles, int n_listed, int n_big) {
-  return n_listed > 0 && n_rest_tiles <= REST_IN_LAUNCH_MAX && n_listed + n_big <= REST_IN_LAUNCH_MAX_TILES;
-}
-
 // Plans and uploads one LayerSplit.
 void build_split(ob_lamb_ctx* ctx, Workspace* ws, const Tiling& tl, int tile_lb, const Tiling& tm,
                  const std::vector<int64_t>& h_off, int64_t max_tiles, const BigRule& rule, bool trail, LayerSplit* sp,
@@ -767,23 +533,14 @@ void build_split(ob_lamb_ctx* ctx, Workspace* ws, const Tiling& tl, int tile_lb,
   }
   sp->rest_in_launch = !trail && rest_in_launch(sp->n_rest_ratio_tiles, sp->n_fused_tiles, sp->n_big_tiles);
   if (sp->rest_in_launch) {
-    std::vector<int> arr0((size_t)L), alone, skip_first = pl.seg_first, skip_end = pl.seg_end;
-    for (int64_t l = 0; l < L; ++l) {
-      const size_t i = (size_t)l;
-      if (pl.big_n[i]) {
-        skip_first[i] = pl.big_seg_first[i];
-        skip_end[i] = pl.big_seg_end[i];
-      }
-      arr0[i] = (int)sp->n_arrivals;
-      const int n = pl.n_listed[i] + (skip_first[i] - tm.layer_seg0[i]) + (tm.layer_seg0[i + 1] - skip_end[i]);
-      if (n == 0) alone.push_back((int)l);
-      sp->n_arrivals += n;
-    }
-    sp->n_alone = (int)alone.size();
-    ws->upload(&sp->d_alone, std::move(alone));
-    ws->upload(&sp->d_arr0, std::move(arr0));
-    ws->upload(&sp->d_skip_first, std::move(skip_first));
-    ws->upload(&sp->d_skip_end, std::move(skip_end));
+    ArrivalPlan ap;
+    plan_arrivals(pl, tm, L, &ap);
+    sp->n_arrivals = ap.n_arrivals;
+    sp->n_alone = (int)ap.alone.size();
+    ws->upload(&sp->d_alone, std::move(ap.alone));
+    ws->upload(&sp->d_arr0, std::move(ap.arr0));
+    ws->upload(&sp->d_skip_first, std::move(ap.skip_first));
+    ws->upload(&sp->d_skip_end, std::move(ap.skip_end));
     ws->alloc_zero(&sp->d_counter_rest, (size_t)L * CTR_STRIDE);
     ws->alloc_zero(&sp->d_sub_rest, group_lines(sp->n_arrivals, L) * CTR_STRIDE);
     ws->alloc_zero(&sp->d_flag_rest, (size_t)L);
@@ -804,90 +561,6 @@ void build_split(ob_lamb_ctx* ctx, Workspace* ws, const Tiling& tl, int tile_lb,
   ws->alloc_zero(&sp->d_sub, group_lines(sp->n_fused_tiles, L) * CTR_STRIDE);
   ws->alloc_zero(&sp->d_flag, (size_t)L);
 }
-
-// The tiles and segments of one SmallPlan (no HIP call).  lagging: per 1024-element span (tm's tiling).
-void small_tiles(const Tiling& t, int U, const Tiling& tm, const std::vector<int64_t>& h_off, int64_t n_c, int64_t L,
-                 const std::vector<unsigned char>& lagging, std::vector<SmallTile>* tiles) {
-  tiles->resize((size_t)t.n_tiles);
-  for (int64_t i = 0; i < t.n_tiles; ++i) {
-    const int64_t c = i / t.tpc, b = i % t.tpc;
-    const int64_t tile0 = c * n_c + b * (int64_t)SPAN * U, tile1 = std::min(tile0 + (int64_t)SPAN * U, (c + 1) * n_c);
-    SmallTile& st = (*tiles)[(size_t)i];
-    st.l0 = t.first[(size_t)i];
-    st.seg0 = t.tile_seg0[(size_t)i];
-    st.nseg = t.tile_seg0[(size_t)i + 1] - st.seg0;
-    const bool inside = st.l0 < L && tile1 <= h_off[(size_t)st.l0 + 1];
-    const bool lag = inside && lagging[(size_t)(c * tm.tpc + b * U)];   // (a lagging span's 8192-element tile lags as a whole)
-    st.chunk_kind = (int)(c << 2) | (inside ? 1 : 0) | (lag ? 2 : 0);
-    st.l_last = st.nseg > 0 ? t.seg_layer[(size_t)(st.seg0 + st.nseg - 1)] : st.l0;
-    auto total = [&](int l) { return l < L ? t.layer_seg0[(size_t)l + 1] - t.layer_seg0[(size_t)l] : 0; };
-    st.n_first = total(st.l0);
-    st.n_last = total(st.l_last);
-    st.pad = 0;
-  }
-}
-
-// What the choice of a tile size rests on, without its tables.
-struct SmallShape {
-  int64_t tpc = 0, n_tiles = 0;
-  int max_seg = 1;        // most layers that meet one tile
-  int max_arrivals = 0;   // most tiles that one layer meets
-  int mixed_spans = 0;    // 1024-element spans of the longest tile that is not wholly inside one layer
-};
-SmallShape small_shape(int U, const std::vector<int64_t>& h_off, int64_t n_c, int64_t W, int64_t L) {
-  const int64_t tile = (int64_t)SPAN * U;
-  SmallShape sh;
-  sh.tpc = (n_c + tile - 1) / tile;
-  sh.n_tiles = sh.tpc * W;
-  int64_t cur = -1;
-  int seg = 0;
-  for (int64_t l = 0; l < L; ++l) {
-    const int64_t a = h_off[(size_t)l], e = h_off[(size_t)l + 1];
-    if (e == a) continue;
-    const int64_t c = (e - 1) / n_c, b = (e - 1) % n_c / tile;
-    const int64_t t0 = a / n_c * sh.tpc + a % n_c / tile, t1 = c * sh.tpc + b;
-    seg = (t0 == cur) ? seg + 1 : 1;
-    sh.max_seg = std::max(sh.max_seg, seg);
-    if (t1 > t0) seg = 1;
-    cur = t1;
-    sh.max_arrivals = (int)std::max<int64_t>(sh.max_arrivals, t1 - t0 + 1);
-    const int64_t in_chunk = b * tile, len = std::min(tile, n_c - in_chunk);
-    if (e < c * n_c + in_chunk + len) sh.mixed_spans = (int)std::max<int64_t>(sh.mixed_spans, (len + SPAN - 1) / SPAN);
-  }
-  return sh;
-}
-// What sets the tile sizes apart, in ns: a workgroup's own chain of loads and divisions, the arrivals of a layer at
-// its counter, which are served one after the other, the look-ups with which the threads of a tile that meets
-// several layers go through its spans, and the segments of such a tile, which its wavefronts finish in turn.
-// Measured at U = 1 / 2 / 4 (kernel, us; LAMB step, then ratios_apply):
-//   eight tensors of 65536 7.7 / 7.6 / 8.8, 7.6 / 8.4 / 10.2; four of 262144 11.3 / 9.1 / 9.5, 10.6 / 9.4 / 10.3
-//   one of 0.9 M 18.6 / 14.0 / 15.9, 17.7 / 13.3 / 16.4; of 1.6 M 27.7 / 17.9 / 14.4, 27.2 / 17.9 / 15.0 (in
-//   8192-element tiles, k_warmup_resident and k_ratios_apply_resident: 16.1, 14.6)
-//   four of 125000 9.0 / 11.2 / 14.4, 9.5 / 12.2 / 14.6; 0.8 M and ten of 80000 17.7 / 14.4 / 20.1, 18.3 / 14.8 / 19.7
-//   3000 of 1 and one of 1.2 M 205 / 394 / 561, 105 / 213 / 306
-// (ratios_apply with counted arrivals.  With slots, called over and over with everything in the caches: eight of 65536 6.5 / 6.7 /
-// 8.6, four of 262144 7.9 / 8.0 / 9.6, 0.9 M 8.2 / 8.3 / 12.4, 1.6 M 11.3 / 11.2 / 14.2; as part of a step, which is what the choice
-// goes by, four of 262144 25.0 / 24.0 / 25.8, 0.9 M 28.5 / 25.5 / 29.9, 1.6 M 33.5 / 31.9 / 30.2.)
-int64_t small_cost(int U, const SmallShape& sh) {
-  return (U == 1 ? 0 : U == 2 ? 500 : 2000) + 13 * sh.max_arrivals + 2500 * std::max(sh.mixed_spans - 1, 0) + 100 * sh.max_seg;
-}
-
-// Tilings of the tile sizes that a SmallPlan may take, formed when first asked for, and their shapes.
-struct SmallTilings {
-  const Tiling& tm;       // U = 1
-  SmallShape sh[3];       // U = 1, 2, 4 (n_tiles = 0: more tiles than any device holds)
-  Tiling t2, t4;
-  SmallTilings(const Tiling& t, int64_t n_c, int64_t W, int64_t L, const std::vector<int64_t>& h_off) : tm(t) {
-    for (int i = 0; i < 3; ++i)
-      if ((n_c + ((int64_t)SPAN << i) - 1) / ((int64_t)SPAN << i) * W <= 4096) sh[i] = small_shape(1 << i, h_off, n_c, W, L);
-  }
-  const Tiling* get(int U, int64_t n_c, int64_t W, int64_t L, const std::vector<int64_t>& h_off) {
-    if (U == 1) return &tm;
-    Tiling* t = (U == 2) ? &t2 : &t4;
-    if (t->n_tiles == 0 && !build_tiling((int64_t)SPAN * U, n_c, W, L, h_off, t)) return nullptr;
-    return t;
-  }
-};
 
 // Chooses and uploads a SmallPlan: of the U whose tiles take at most 80 % of the device's workgroup slots
 // (slots(U, dynamic LDS bytes)) the one of the lowest small_cost, the smallest of equals.  vals, tables: 4-byte words

@@ -1,0 +1,188 @@
+// The tables of ob_plan.h over random tensor lists: what the kernels take for granted about the order of their workgroups
+// and the numbering of their arrivals.  One check per argument.
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <numeric>
+#include <random>
+
+#include "ob_plan.h"
+
+using namespace obk;
+
+#define CHECK(x) do { if (!(x)) { printf("%s:%d: %s\n", __FILE__, __LINE__, #x); exit(1); } } while (0)
+
+namespace {
+std::mt19937_64 rng(2024);
+int64_t pick(int64_t a, int64_t b) { return a + (int64_t)(rng() % (uint64_t)(b - a + 1)); }
+
+struct List {
+  int64_t W, L, n_c;
+  std::vector<int64_t> off;   // [L + 2], the padding last
+  Tiling tm, tl;
+};
+constexpr int TILE = 8 * SPAN;
+List random_list() {
+  const int64_t kinds[] = {0, 1, 2, 255, 256, 1023, 1024, 1025, 4097, TILE - 1, TILE, TILE + 1, 3 * TILE, 63 * TILE, 64 * TILE,
+                           65 * TILE + 77, 70 * TILE + 1, 100 * TILE, 300 * TILE + 5};
+  List s;
+  s.W = (const int64_t[]){1, 2, 3, 7, 16, 61}[rng() % 6];
+  s.L = pick(1, 14);
+  s.off.assign(1, 0);
+  for (int64_t l = 0; l < s.L; ++l) s.off.push_back(s.off.back() + kinds[rng() % (sizeof(kinds) / sizeof(kinds[0]))]);
+  if (s.off.back() == 0) s.off.back() = pick(1, 5000);
+  const int64_t unit = 256 * s.W;
+  s.n_c = (s.off.back() + unit - 1) / unit * 256;
+  s.off.push_back(s.n_c * s.W);
+  CHECK(build_tiling(SPAN, s.n_c, s.W, s.L, s.off, &s.tm) && build_tiling(TILE, s.n_c, s.W, s.L, s.off, &s.tl));
+  return s;
+}
+
+// Every part once as moments and once as update, the update after all moments of its layer (no later workgroup is waited
+// for), `lag` moments parts behind them while there are any, in a later launch where nothing waits; what is kept is at most what the cache holds, and updated first.
+void check_trail(const std::vector<int>& n, const std::vector<int>& begin, int64_t lag, int64_t group) {
+  std::vector<unsigned int> items;
+  std::vector<int64_t> end;
+  trail_items(n, begin, lag, group, &items, &end);
+  const int64_t parts = std::accumulate(n.begin(), n.end(), (int64_t)0);
+  CHECK((int64_t)items.size() == 2 * parts);
+  if (parts == 0) return;
+  CHECK(end.back() == (int64_t)items.size() && std::is_sorted(end.begin(), end.end()));
+  if (lag > 0) CHECK(end.size() == 1);
+  std::vector<int64_t> at_moments((size_t)parts, -1), at_update((size_t)parts, -1);
+  std::vector<char> kept((size_t)parts, 0);
+  for (size_t i = 0; i < items.size(); ++i) {
+    const int64_t p = items[i] & (TRAIL_KEEP - 1u);
+    CHECK(p < parts);
+    std::vector<int64_t>& at = (items[i] & TRAIL_UPDATE) ? at_update : at_moments;
+    CHECK(at[(size_t)p] < 0);
+    at[(size_t)p] = (int64_t)i;
+    if (!(items[i] & TRAIL_UPDATE)) kept[(size_t)p] = (items[i] & TRAIL_KEEP) != 0;
+  }
+  auto launch_of = [&](int64_t i) { return std::upper_bound(end.begin(), end.end(), i) - end.begin(); };
+  for (size_t l = 0; l < n.size(); ++l) {
+    if (n[l] == 0) continue;
+    int64_t last_moments = -1, first_update = (int64_t)items.size(), first_kept_update = -1, n_kept = 0;
+    for (int64_t p = begin[l]; p < begin[l] + n[l]; ++p) {
+      last_moments = std::max(last_moments, at_moments[(size_t)p]);
+      first_update = std::min(first_update, at_update[(size_t)p]);
+      n_kept += kept[(size_t)p];
+      if (kept[(size_t)p] && first_kept_update < 0) first_kept_update = at_update[(size_t)p];
+    }
+    CHECK(last_moments >= 0 && last_moments < first_update);
+    int64_t between = 0, left = 0;
+    for (int64_t at : at_moments) {
+      between += at > last_moments && at < first_update;
+      left += at > first_update;
+    }
+    if (lag > 0) CHECK(between >= lag || left == 0);
+    if (lag == 0) CHECK(launch_of(last_moments) < launch_of(first_update));
+    CHECK(n_kept == std::min<int64_t>(n[l], TRAIL_KEEP_PARTS) && first_kept_update == first_update);
+  }
+}
+
+void trail() {
+  for (int it = 0; it < 300; ++it) {
+    std::vector<int> n, begin;
+    int at = 0;
+    const int L = (int)pick(1, 9);
+    for (int l = 0; l < L; ++l) {
+      const int64_t kinds[] = {0, 0, 64 * TRAIL_PARTS, pick(1, 300), pick(256, 4000), pick(8000, 9000)};
+      n.push_back((int)kinds[rng() % 6]);
+      begin.push_back(n.back() ? at : 0);
+      at += n.back();
+    }
+    for (int64_t lag : {TRAIL_LAG, (int64_t)pick(1, 6000), (int64_t)0}) check_trail(n, begin, lag, it % 2 ? TRAIL_GROUP : pick(1, 9000));
+  }
+}
+
+// Which layers that rule takes: all those with enough whole tiles and not too many, or none at all below the total.
+void big_rule() {
+  for (int it = 0; it < 150; ++it) {
+    const List s = random_list();
+    const int64_t max_tiles = (const int64_t[]){0, 5, 66, 1000}[rng() % 4];
+    BigRule rule;
+    rule.max_tiles = (const int64_t[]){64, 99, rule.max_tiles}[rng() % 3];
+    rule.min_total = (const int64_t[]){0, 65, 200, 500}[rng() % 4];
+    SplitPlan pl;
+    plan_split(s.tl, TILE, s.tm, s.off, s.n_c, s.L, max_tiles, rule, &pl);
+    std::vector<int> inside((size_t)s.L, 0);
+    for (int64_t t = 0; t < s.tl.n_tiles; ++t) {
+      const int64_t a = t / s.tl.tpc * s.n_c + t % s.tl.tpc * TILE, e = std::min(a + TILE, (t / s.tl.tpc + 1) * s.n_c);
+      const int l = s.tl.first[(size_t)t];
+      if (l < s.L && e <= s.off[(size_t)l + 1]) ++inside[(size_t)l];
+    }
+    int64_t total = 0, got = 0;
+    for (int64_t l = 0; l < s.L; ++l) {
+      const bool fits = !pl.has_listed[(size_t)l] && inside[(size_t)l] >= rule.min_tiles && inside[(size_t)l] <= rule.max_tiles;
+      if (fits) total += inside[(size_t)l];
+      CHECK(pl.big_n[(size_t)l] == 0 || fits);
+      got += pl.big_n[(size_t)l];
+    }
+    CHECK(got == (total >= rule.min_total ? total : 0) && got == (int64_t)pl.big_tiles.size());
+  }
+  // without waits from 5120 tiles on, with them from 1792; a lowered limit takes lists of any size
+  CHECK(trail_rule(true, 0).min_total == 1792 && trail_rule(false, 0).min_total == 5120);
+  CHECK(trail_rule(true, 8).min_total == 0 && trail_rule(false, 8).min_total == 0);
+}
+
+// Every arrival of a layer has a number of its own below the layer's count, whoever arrives for it (k_ratios_apply_hist's
+// listed tiles, the first and the last segment of a rest tile); segments between them are layers of their own; the
+// layers' group counters lie apart and inside their allocation.
+void arrivals() {
+  for (int it = 0; it < 300; ++it) {
+    const List s = random_list();
+    SplitPlan pl;
+    plan_split(s.tl, TILE, s.tm, s.off, s.n_c, s.L, (const int64_t[]){0, 5, 66, 1000}[rng() % 4], BigRule(), &pl);
+    ArrivalPlan ap;
+    plan_arrivals(pl, s.tm, s.L, &ap);
+    std::vector<std::vector<char>> seen((size_t)s.L);
+    std::vector<int> finished((size_t)s.L, 0);
+    auto seg0 = [&](int l) { return s.tm.layer_seg0[(size_t)l]; };
+    for (int l = 0; l < s.L; ++l) {
+      const size_t i = (size_t)l;
+      const int n = layer_arrivals(pl.n_listed[i], seg0(l), ap.skip_first[i], ap.skip_end[i], seg0(l + 1));
+      CHECK(n >= 0 && (n == 0) == (std::count(ap.alone.begin(), ap.alone.end(), l) == 1));
+      seen[i].assign((size_t)n, 0);
+      // a listed tile's own count, from what it has at hand
+      if (pl.n_listed[i]) CHECK(n == layer_arrivals(pl.n_listed[i], seg0(l), pl.seg_first[i], pl.seg_end[i], seg0(l + 1)));
+      for (int j = 0; j < pl.n_listed[i]; ++j) seen[i][(size_t)j] = 1;
+    }
+    for (int tile : pl.rest_ratio_tiles) {
+      const int s0 = s.tm.tile_seg0[(size_t)tile], s1 = s.tm.tile_seg0[(size_t)tile + 1];
+      CHECK(s1 > s0);
+      for (int sg = s0; sg < s1; ++sg) {
+        const int l = s.tm.seg_layer[(size_t)sg];
+        const size_t i = (size_t)l;
+        const int j = rest_arrival(sg, pl.n_listed[i], seg0(l), ap.skip_first[i], ap.skip_end[i]);
+        CHECK(sg < ap.skip_first[i] || sg >= ap.skip_end[i]);
+        CHECK(j >= 0 && j < (int)seen[i].size() && !seen[i][(size_t)j]);
+        seen[i][(size_t)j] = 1;
+        if (sg > s0 && sg < s1 - 1) CHECK(seen[i].size() == 1);
+      }
+    }
+    int64_t next = 0, line_end = 0;
+    for (int l = 0; l < s.L; ++l) {
+      const size_t i = (size_t)l;
+      CHECK(std::count(seen[i].begin(), seen[i].end(), 1) == (int64_t)seen[i].size());
+      CHECK(ap.arr0[i] == next);
+      const int64_t line = group_line(ap.arr0[i], l) / CTR_STRIDE;
+      CHECK(line >= line_end);
+      line_end = line + (int64_t)arrival_groups((int64_t)seen[i].size());
+      next += (int64_t)seen[i].size();
+    }
+    CHECK(next == ap.n_arrivals && line_end <= (int64_t)group_lines(ap.n_arrivals, s.L));
+  }
+}
+}  // namespace
+
+int main(int argc, char** argv) {
+  const struct { const char* name; void (*f)(); } checks[] = {{"trail", trail}, {"big_rule", big_rule}, {"arrivals", arrivals}};
+  for (const auto& c : checks)
+    if (argc == 2 && !strcmp(argv[1], c.name)) {
+      c.f();
+      printf("ok\n");
+      return 0;
+    }
+  return 2;
+}

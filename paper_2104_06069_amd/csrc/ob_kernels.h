@@ -52,14 +52,21 @@ __device__ __forceinline__ void st4(float* p, v4f v) {
 }
 
 // What the next kernel of the step reads again is loaded without the nontemporal hint: k_compress_resident's dense momentum,
-// which k_ratios_pass reads, and that kernel's v_frozen, which k_decompress_apply does.  Where they cover the whole
-// buffer, k_ratios_pass goes from its end to its start, so that the 256 MB memory-side cache still holds what it and the
-// kernel after it read first.
+// which k_ratios_pass reads, and that kernel's v_frozen, which k_decompress_apply does (keeps_second_reads says for which lists).
+// Where they cover the whole buffer, k_ratios_pass goes from its end to its start (tile_from_end), so that the 256 MB
+// memory-side cache still holds what it and the kernel after it read first, and the L2s, tile by tile, what fits them.
 // Measured (4 bytes per element each, of the 53 that a step moves), us a step, everything nontemporal and from the start /
 // v_frozen kept, k_decompress_apply from the end / both kept, k_ratios_pass from the end: 110 M parameters 902 / 884 / 865,
-// 42 M 357 / 346 / 331, 80 M 649 / 630 / 611, 8 M 86.4 / 86.4 / 84.3, 336 M 2679 / - / 2661.  Keeping only what the cache can
-// hold: no difference.
+// 42 M 357 / 346 / 331, 80 M 649 / 630 / 611, 8 M 86.4 / 86.4 / 84.3, 336 M 2679 / - / 2661; from the end with each tile on another XCD /
+// on its own: 42 M 319.5 / 319.4, 21 M 167.5 / 165.4, 11 M 103.0 / 100.4, 4.2 M 57.8 / 56.8, 2.1 M 43.9 / 42.7, 1 M 36.9 / 36.2.
 __device__ __forceinline__ v4f ld4_keep(const float* p) { return *reinterpret_cast<const v4f*>(p); }
+// Which of the two is a template argument (for a value of the launch: the cache policy of the buffer builtins): the
+// compiler merges two loads of one address under a condition into one without the hint.
+template <bool KEEP>
+__device__ __forceinline__ v4f ld4_keep_if(const float* p) {
+  if constexpr (KEEP) return ld4_keep(p);
+  else return ld4(p);
+}
 
 // 16 bytes per lane from p straight into LDS: lane i's to dst[i], dst the same for the whole
 // wavefront, all of whose lanes take part.  The data is there after lds_loads_done() of the same wavefront.
@@ -712,7 +719,7 @@ __device__ __forceinline__ float chunk_barrier_scale(const ChunkSync& cs, int ti
 // the error from registers.  z never goes to memory.  Loads are issued G accesses at a time to
 // bound the staging registers.
 // ---------------------------------------------------------------------------------------------
-template <int U, int G, bool HAS_K, bool PACKED_M, int MINW = 4, int GT = 0>
+template <int U, int G, bool HAS_K, bool PACKED_M, int MINW = 4, int GT = 0, bool KEEP = false>
 __global__ __launch_bounds__(BLOCK, MINW) void k_compress_resident(
     GradSrc g, const float* __restrict__ m, PackedMom pm,
     float* __restrict__ err, uint32_t* __restrict__ packed, float* __restrict__ scales,
@@ -740,7 +747,7 @@ __global__ __launch_bounds__(BLOCK, MINW) void k_compress_resident(
         if (o < p.len) {
           Gr[j] = load_grad<GT>(g, p.tile0 + o);
           if (PACKED_M) NB[j] = load_nibble(pm.bits, p.tile0 + (u0 + j) * SPAN);
-          else M[j] = ld4_keep(m + p.tile0 + o);
+          else M[j] = ld4_keep_if<KEEP>(m + p.tile0 + o);
           E[j] = ld4(err + p.tile0 + o);
         }
       }
@@ -986,7 +993,8 @@ struct RatioTile {
   unsigned int NB[U], OB[U];
   v4f M[U], VF[U], VZ[U];
 
-  __device__ __forceinline__ void load(const RatioArgs& ra, const TilePos& p, bool keep_v_frozen = false /* a constant */) {
+  template <bool KEEP_V_FROZEN = false>
+  __device__ __forceinline__ void load(const RatioArgs& ra, const TilePos& p) {
     const int o0 = threadIdx.x * 4;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -997,7 +1005,7 @@ struct RatioTile {
         if (PACKED_M) OB[u] = load_nibble(ra.pm.bits, p.tile0 + u * SPAN);
         else M[u] = ld4(ra.m + p.tile0 + o);
         VF[u] = ld4(ra.v_fresh + p.tile0 + o);
-        VZ[u] = keep_v_frozen ? ld4_keep(ra.v_frozen + p.tile0 + o) : ld4(ra.v_frozen + p.tile0 + o);
+        VZ[u] = ld4_keep_if<KEEP_V_FROZEN>(ra.v_frozen + p.tile0 + o);
       }
     }
   }
@@ -1113,8 +1121,8 @@ struct RatioTile {
 };
 
 // The ratio pass of one tile (a workgroup; lds: [BLOCK / WAVE]).  SAME_LAUNCH: the maxima are read by other
-// workgroups of the launch.
-template <int U, bool HAS_K, bool PACKED_M, bool SAME_LAUNCH = false>
+// workgroups of the launch.  KEEP: v_frozen by ld4_keep.
+template <int U, bool HAS_K, bool PACKED_M, bool KEEP, bool SAME_LAUNCH = false>
 __device__ __forceinline__ void ratios_pass_tile(const RatioArgs& ra, float* __restrict__ seg_max,
                                                  int64_t n_c, int tpc, const LayerTab& lt,
                                                  const int* __restrict__ tile_seg0,
@@ -1131,7 +1139,7 @@ __device__ __forceinline__ void ratios_pass_tile(const RatioArgs& ra, float* __r
   const int64_t l0_end = lt.off[l0 + 1];
   const int s0 = tile_seg0[p.t];
   RatioTile<U, HAS_K, PACKED_M> rt;
-  rt.load(ra, p, true);
+  rt.template load<KEEP>(ra, p);
   auto store = [&](int s, float r) {
     if (SAME_LAUNCH) __hip_atomic_store(&seg_max[s], r, __ATOMIC_RELAXED, OB_AGENT);
     else seg_max[s] = r;
@@ -1153,15 +1161,15 @@ __device__ __forceinline__ void ratios_pass_tile(const RatioArgs& ra, float* __r
   }
 }
 
-template <int U, bool HAS_K, bool PACKED_M>
+template <int U, bool HAS_K, bool PACKED_M, bool KEEP>
 __global__ __launch_bounds__(BLOCK) void k_ratios_pass(RatioArgs ra, float* __restrict__ seg_max,
                                                        int64_t n_c, int tpc, LayerTab lt,
                                                        const int* __restrict__ tile_seg0,
                                                        const int* __restrict__ seg_layer,
                                                        const int* __restrict__ tile_list) {
   __shared__ float lds[BLOCK / WAVE];
-  const int tile = tile_list ? tile_list[blockIdx.x] : (int)(gridDim.x - 1 - blockIdx.x);   // (from the end: ld4_keep)
-  ratios_pass_tile<U, HAS_K, PACKED_M>(ra, seg_max, n_c, tpc, lt, tile_seg0, seg_layer, tile, lds);
+  const int tile = tile_list ? tile_list[blockIdx.x] : tile_from_end(blockIdx.x, gridDim.x);   // (ld4_keep)
+  ratios_pass_tile<U, HAS_K, PACKED_M, KEEP>(ra, seg_max, n_c, tpc, lt, tile_seg0, seg_layer, tile, lds);
 }
 
 // Algorithm 1 lines 18-19 for one layer given the raw ratio.  rp: r_prev[l].
@@ -1864,7 +1872,7 @@ __global__ __launch_bounds__(BLOCK) void k_ratios_pass_vterms(RatioArgs ra, floa
     variance_terms_of_pair<HAS_K>(ra, h, vt, lt.mom_scale, vt_out, (int)(blockIdx.x * BLOCK + threadIdx.x));
     return;
   }
-  ratios_pass_tile<U, HAS_K, true>(ra, seg_max, n_c, tpc, lt, tile_seg0, seg_layer, tile_list[bid], lds);
+  ratios_pass_tile<U, HAS_K, true, true>(ra, seg_max, n_c, tpc, lt, tile_seg0, seg_layer, tile_list[bid], lds);
 }
 
 // Dense view of a variance held in deferred form, over the 1024-element tiles inside the tiles of
@@ -2013,7 +2021,7 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
                                    ls.one_m_thr, ls.one_p_thr, ls.r_min, ls.r_max, lds);
     } else {
       const int tile = ls.rest_tiles[lead];
-      ratios_pass_tile<1, HAS_K, true, true>(ra, ls.seg_max, ls.lt.n_c, ls.lt.tpc_span, lt, ls.tile_seg0, ls.seg_layer, tile, lds);
+      ratios_pass_tile<1, HAS_K, true, true, true>(ra, ls.seg_max, ls.lt.n_c, ls.lt.tpc_span, lt, ls.tile_seg0, ls.seg_layer, tile, lds);
       rest_arrive(ls, tile, lds, bc_rest);
     }
     return;

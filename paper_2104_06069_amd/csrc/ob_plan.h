@@ -28,6 +28,29 @@ constexpr int ARRIVE_ONE_LEVEL = 256, ARRIVE_SUB = 32;   // (barrier_arrive)
 // that runs on from layer to layer: no two layers' groups overlap, and no table is needed.
 constexpr int64_t group_line(int first, int l) { return (int64_t)(first / ARRIVE_SUB + l) * CTR_STRIDE; }
 
+// Workgroup b's tile in a launch of n that goes from the last tile to the first.  Workgroups go round the XCDs, each with an L2
+// of its own: every tile stays on the XCD that it has in a launch from the first to the last (b mod 8).
+constexpr unsigned int XCDS = 8;
+constexpr int tile_from_end(unsigned int b, unsigned int n) {
+  const unsigned int x = b % XCDS;
+  return (int)(((n - x + XCDS - 1) / XCDS - 1 - b / XCDS) * XCDS + x);
+}
+
+// Whether the plain form leaves what its next kernel reads again in the caches (ld4_keep): where each worker's chunk has
+// at least 64 tiles, or the buffer 8 M elements.  Below, with many workers and so a short served chunk, the server's few
+// workgroups are bound by the latency of their W rows of words, which the lines kept for the other kernels push out.  A step of two equal
+// tensors in plain form, us, kept / not, by workers:
+//   elements   32           64           96           128          192          256
+//   1.7 M      41.1 / 41.1  42.7 / 41.8  44.6 / 42.8  43.8 / 41.7  45.1 / 41.4  47.9 / 42.9
+//   2.9 M      49.1 / 49.0  50.2 / 49.2  51.4 / 49.6  53.2 / 51.0  56.8 / 52.7  59.4 / 53.3
+//   4.2 M      56.0 / 57.3  56.9 / 57.4  59.2 / 58.7  60.8 / 59.1  65.4 / 62.9  68.9 / 63.8
+//   5.8 M      66.1 / 68.8  66.8 / 68.3  68.8 / 69.4  69.7 / 70.3  72.9 / 71.9  78.4 / 78.5
+//   8.4 M      82.4 / 86.6  81.5 / 85.6  84.2 / 88.3  85.2 / 87.7  90.1 / 93.6  92.9 / 91.7
+//   11.5 M    101.5 / 108.1 104.6 / 111.3 105.8 / 113.1 106.9 / 112.4 113.9 / 119.1 115.0 / 119.5
+// (1448x1448 twice with 16 workers 56.9 / 58.4, with 147 63.8 / 60.4.)
+constexpr int64_t KEEP_MIN_CHUNK = 64 * SPAN, KEEP_MIN = 8000000;
+constexpr bool keeps_second_reads(int64_t n, int64_t W) { return n >= (W * KEEP_MIN_CHUNK < KEEP_MIN ? W * KEEP_MIN_CHUNK : KEEP_MIN); }
+
 // Arrivals at a layer's barrier with nl listed tiles, whose segments are seg0 .. seg1-1 and of which those from skip_first to
 // skip_end-1 lie in listed or big tiles; the number of the arrival of one of the others, sg (the listed tiles come first).
 constexpr int layer_arrivals(int nl, int seg0, int skip_first, int skip_end, int seg1) {

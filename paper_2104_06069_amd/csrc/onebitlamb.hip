@@ -725,9 +725,10 @@ void launch_ratios(Launch& la, ob_lamb_ctx* ctx, const ob_lamb_state* st, const 
   ra.beta1 = ctx->beta1; ra.omb1 = ctx->omb1; ra.beta2 = ctx->beta2; ra.omb2 = ctx->omb2;
   const LayerTab lt = layer_tab(ctx, st, ctx->d_first_layer);
   dispatch2(st->mom_scale != nullptr, packed_m, [&](auto hk, auto pk) {
-    OB_LAUNCH(la, KID_RATIOS_PASS, (k_ratios_pass<U_MAIN, decltype(hk)::value, decltype(pk)::value>),
-              n_launch_tiles, ra, ctx->d_seg_max, ctx->n_c, ctx->tpc, lt, ctx->d_tile_seg0, ctx->d_seg_layer,
-              tiles);
+    dispatch1(keeps_second_reads(ctx->N, ctx->W), [&](auto kp) {
+      OB_LAUNCH(la, KID_RATIOS_PASS, (k_ratios_pass<U_MAIN, decltype(hk)::value, decltype(pk)::value, decltype(kp)::value>),
+                n_launch_tiles, ra, ctx->d_seg_max, ctx->n_c, ctx->tpc, lt, ctx->d_tile_seg0, ctx->d_seg_layer, tiles);
+    });
   });
   if (finalize)
     OB_LAUNCH_B(la, KID_RATIOS_FINALIZE, k_ratios_finalize, (int)ctx->L, FBLOCK, ctx->d_seg_max,
@@ -1342,10 +1343,10 @@ ob_status ob_lamb_compress_local_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st, c
     cs.spin_limit = ctx->spin_limit;
     const LayerTab lt = layer_tab(ctx, st, ctx->d_first_layer_res);
     dispatch2(st->mom_scale != nullptr, packed_m, [&](auto hk, auto pk) {
-      dispatch1(lpg, [&](auto lg) {
+      dispatch2(lpg, !packed_m && keeps_second_reads(ctx->N, ctx->W), [&](auto lg, auto kp) {
         OB_LAUNCH(la, KID_COMPRESS_RESIDENT,
                   (k_compress_resident<U_RES, G_RES, decltype(hk)::value, decltype(pk)::value, OB_RES_MINW,
-                                       decltype(lg)::value ? 1 : 0>),
+                                       decltype(lg)::value ? 1 : 0, decltype(kp)::value && !decltype(pk)::value>),
                   ctx->n_tiles_res, gs, st->m, pm, st->err_worker, packed_out, scales_out, cs, ctx->n_c,
                   ctx->tpc_res, ctx->beta1, ctx->omb1, lt, oc);
       });

@@ -174,10 +174,27 @@ void arrivals() {
     CHECK(next == ap.n_arrivals && line_end <= (int64_t)group_lines(ap.n_arrivals, s.L));
   }
 }
+
+// A launch from the last tile to the first takes every tile once, later ones first, each on its own XCD; the second
+// reads of a list stay in the caches only where the server's words don't need them (64 tiles a chunk, or 8e6 elements).
+void second_reads() {
+  for (unsigned int n = 1; n <= 2100; n += n < 40 ? 1 : 97) {
+    std::vector<char> seen(n, 0);
+    for (unsigned int b = 0; b < n; ++b) {
+      const int t = tile_from_end(b, n);
+      CHECK(t >= 0 && t < (int)n && !seen[(size_t)t]);
+      seen[(size_t)t] = 1;
+      CHECK((unsigned int)t % 8 == b % 8);
+      CHECK(b < 8 || t == tile_from_end(b - 8, n) - 8);
+    }
+  }
+  CHECK(!keeps_second_reads(2 * 909 * 909, 147) && !keeps_second_reads(64 * 65536 - 1, 64) && keeps_second_reads(64 * 65536, 64));
+  CHECK(keeps_second_reads(8000000, 256) && !keeps_second_reads(7999999, 256) && keeps_second_reads(65536, 1));
+}
 }  // namespace
 
 int main(int argc, char** argv) {
-  const struct { const char* name; void (*f)(); } checks[] = {{"trail", trail}, {"big_rule", big_rule}, {"arrivals", arrivals}};
+  const struct { const char* name; void (*f)(); } checks[] = {{"trail", trail}, {"big_rule", big_rule}, {"arrivals", arrivals}, {"second_reads", second_reads}};
   for (const auto& c : checks)
     if (argc == 2 && !strcmp(argv[1], c.name)) {
       c.f();

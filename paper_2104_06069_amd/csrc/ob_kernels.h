@@ -2979,7 +2979,7 @@ __global__ __launch_bounds__(BLOCK, OB_WU_MINW) void k_warmup_resident(
 // of workgroups of one launch, on parts of the 8192-element tiles that lie inside one layer.  Nothing is held
 // on chip in between; the update's reads of m, v and x (12 of 40 bytes per element) come from the
 // memory-side cache instead of HBM: a layer's update follows its moments as closely as its coefficient allows,
-// the moments' stores and their load of x do not bypass that cache, and everything else does.
+// the moments' stores of what is updated next and their load of x do not bypass that cache, and everything else does.
 //
 // `items` lists the workgroups in the order of dispatch: the parts in position order for the moments, and a
 // layer's parts for the update `lag` parts after its last one (trail_items in the host code).  The last moments
@@ -3082,6 +3082,8 @@ __device__ __forceinline__ void trail_finish(const TrailTab& tt, const WarmClip&
 // elements in layers of 12.6, 16.8 and 103 M, bf16: 6870 us, in two passes 8000 to 8300 (4350-4740 + 3470-3590); with nothing
 // kept 7250.  Parts of 1024, 2048 and 4096 elements: 6860, 6870, 6940.  The same pattern of accesses without
 // arithmetic: 6660.
+// x is kept in every part, m and v in those with TRAIL_KEEP.  x kept in those only: 1.3e9 elements 7352 us instead of 7346, lists with
+// an embedding of 31 M bf16 483.0 instead of 478.5, of 61 M fp32 612.6 instead of 607.6.
 template <int GT, bool LPX>
 __global__ __launch_bounds__(BLOCK, 8) void k_warmup_trail(
     GradSrc g, float* __restrict__ m, float* __restrict__ v, float* __restrict__ x, TrailTab tt, WarmClip wc,
@@ -3149,8 +3151,7 @@ __global__ __launch_bounds__(BLOCK, 8) void k_warmup_trail(
       GR[u] = grad_request<GT>(g, p.tile0 + o);
       M[u] = ld4(m + p.tile0 + o);
       V[u] = ld4(v + p.tile0 + o);
-      if (keep) X[u] = *reinterpret_cast<const v4f*>(x + p.tile0 + o);
-      else X[u] = ld4(x + p.tile0 + o);
+      X[u] = ld4_keep(x + p.tile0 + o);
     }
   }
   double sx = 0.0, su = 0.0;

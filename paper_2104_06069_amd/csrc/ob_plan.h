@@ -62,7 +62,7 @@ constexpr int rest_arrival(int sg, int nl, int seg0, int skip_first, int skip_en
 
 // k_warmup_trail's workgroups
 constexpr unsigned int TRAIL_UPDATE = 1u << 31;   // update (else: moments)
-constexpr unsigned int TRAIL_KEEP = 1u << 30;     // moments: read again soon
+constexpr unsigned int TRAIL_KEEP = 1u << 30;     // moments: m and v read again soon
 constexpr int TRAIL_U = 2;                        // spans per part
 constexpr int TRAIL_PARTS = 8 / TRAIL_U;          // parts per tile
 struct SmallTile {

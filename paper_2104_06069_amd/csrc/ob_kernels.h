@@ -2984,14 +2984,15 @@ __global__ __launch_bounds__(BLOCK, OB_WU_MINW) void k_warmup_resident(
 // `items` lists the workgroups in the order of dispatch: the parts in position order for the moments, and a
 // layer's parts for the update `lag` parts after its last one (trail_items in the host code).  The last moments
 // workgroup of a layer to finish adds up the sums (arrivals counted in two levels, as in chunk_ticket) and
-// publishes c in flag[l]; an update workgroup fetches its part, forms u and then waits for that flag,
-// which by then is normally there.  Moments workgroups wait for nothing and an update workgroup only for ones
-// dispatched before it, so progress needs in-order dispatch, not co-residency.  Without `wait` the launch
-// ends between a layer's two passes instead.
+// publishes c in flag[l].  An update workgroup requests x, which no moments workgroup writes, then waits for that
+// flag, which by then is normally there, and only then loads m and v and forms u.  Moments workgroups wait for
+// nothing and an update workgroup only for ones dispatched before it, so progress needs in-order dispatch, not
+// co-residency.  Without `wait` the launch ends between a layer's two passes instead.
 //
 // The two passes of a part may run on different XCDs, whose L2 caches do not see each other's lines: the
 // moments store m and v through to memory (agent scope) and wait for the acknowledgements before they arrive,
-// and the update loads them, after it has seen the flag, past its own caches.
+// and the update must load them after it has seen the flag, which those arrivals lead to, and past its own caches: a load
+// before the flag finds values of the step before.
 // ---------------------------------------------------------------------------------------------
 constexpr int CACHE_NT = 2, CACHE_AGENT = 16;     // cache policy bits of the buffer builtins (nt, sc1)
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t part_rsrc(const float* p, int bytes) {   // p uniform

@@ -2178,8 +2178,11 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
 // ---------------------------------------------------------------------------------------------
 // workgroups per CU that the kernels are built for (their registers at each U)
 constexpr int small_min_wg(int u) { return u == 1 ? 8 : (u == 2 ? 5 : 4); }
-// Arrivals counted in one level (a LAMB step, us, one level / two: 384 arrivals 26.8 / 27.1, 588 19.5 / 16.5, 706 20.4 / 16.7).
+// k_warmup_small's arrivals counted in one level (a LAMB step, us, one level / two: 384 arrivals 26.8 / 27.1, 588 19.5 / 16.5,
+// 706 20.4 / 16.7).  A kernel of its own for lists without longer layers: carrying both forms costs it 0.2 to 0.5 us of 11 to 17.
 constexpr int SMALL_ONE_LEVEL = 512;
+template <bool TWO_LEVELS>
+constexpr int small_one_level() { return TWO_LEVELS ? SMALL_ONE_LEVEL : 0x7fffffff; }
 constexpr int SMALL_POLL_SLEEP = 2;   // (the whole launch lasts some 10 us: at first a poll every 128 clocks)
 struct SmallTab {
   const SmallTile* tiles;
@@ -2187,11 +2190,9 @@ struct SmallTab {
   int64_t n_c;
   const int* seg_layer;         // [segments]
   const int* layer_seg0;        // [L+1]
-  double* partial;              // [2 * segments] sums
-  unsigned long long* counter;  // [L * CTR_STRIDE]
-  unsigned long long* sub;      // group counters (group_line)
-  unsigned long long* flag;     // [L * CTR_STRIDE]
-  unsigned long long* slots;    // [segments] (generation << 32) | partial result (k_ratios_apply_small; the others: k_warmup_small)
+  void* partial;                // k_ratios_apply_small: [segments] slots; k_warmup_small: [2 * segments] double sums
+  unsigned long long* counter;  // k_warmup_small: [L * CTR_STRIDE], then the group counters (group_line)
+  unsigned long long* flag;     // k_warmup_small: [L * CTR_STRIDE]
   unsigned int* errflag;
   int spin_limit;
 };
@@ -2234,8 +2235,8 @@ struct SmallSegs {
 // First half of the barriers of a tile: thread 0 arrives for its first segment, thread WAVE for its last
 // one (if that is another).  store(e): publishes the segment's partial result.  bc[e] = (generation << 32) |
 // (1: the layer's last arrival) | (2: the layer is this segment alone, no barrier).
-template <class F>
-__device__ __forceinline__ void small_arrive(const SmallTab& sm, const SmallTile& ti, int n_end, const int (&s0_end)[2],
+template <bool TWO_LEVELS, class F>
+__device__ __forceinline__ void small_arrive(const SmallTab& sm, int L, const SmallTile& ti, int n_end, const int (&s0_end)[2],
                                              unsigned long long* bc, F store) {
   const int e = threadIdx.x / WAVE;
   if (e < n_end && (threadIdx.x & (WAVE - 1)) == 0) {
@@ -2245,8 +2246,13 @@ __device__ __forceinline__ void small_arrive(const SmallTab& sm, const SmallTile
     } else {
       store(e);
       payload_before_arrival();
-      const int s0 = e ? s0_end[1] : s0_end[0], s = ti.seg0 + (e ? ti.nseg - 1 : 0);
-      bc[e] = barrier_arrive(&sm.counter[(int64_t)l * CTR_STRIDE], sm.sub + group_line(s0, l), s - s0, n, SMALL_ONE_LEVEL);
+      unsigned long long* top = &sm.counter[(int64_t)l * CTR_STRIDE];
+      if constexpr (TWO_LEVELS) {
+        const int s0 = e ? s0_end[1] : s0_end[0], s = ti.seg0 + (e ? ti.nseg - 1 : 0);
+        bc[e] = barrier_arrive(top, sm.counter + (int64_t)L * CTR_STRIDE + group_line(s0, l), s - s0, n, SMALL_ONE_LEVEL);
+      } else {
+        bc[e] = barrier_arrive(top, n);
+      }
     }
   }
   __syncthreads();
@@ -2345,8 +2351,9 @@ __global__ __launch_bounds__(BLOCK, small_min_wg(U)) void k_ratios_apply_small(
   const float rp_end[2] = {rc.r_prev[ti.l0], rc.r_prev[ti.l_last]}, ca_end[2] = {rc.c_avg[ti.l0], rc.c_avg[ti.l_last]};
   const int s0_end[2] = {sm.layer_seg0[ti.l0], sm.layer_seg0[ti.l_last]}, n_of[2] = {ti.n_first, ti.n_last};
   const int s_end[2] = {ti.seg0, ti.seg0 + last_seg};
-  const unsigned int want[2] = {(unsigned int)(slot_load(&sm.slots[s_end[0]]) >> 32) + 1u,
-                                (unsigned int)(slot_load(&sm.slots[s_end[1]]) >> 32) + 1u};
+  unsigned long long* const slots = static_cast<unsigned long long*>(sm.partial);
+  const unsigned int want[2] = {(unsigned int)(slot_load(&slots[s_end[0]]) >> 32) + 1u,
+                                (unsigned int)(slot_load(&slots[s_end[1]]) >> 32) + 1u};
   if (inside) {
     const float kt = HAS_K ? lt.mom_scale[ti.l0] : 1.0f;
 #pragma unroll
@@ -2427,7 +2434,7 @@ __global__ __launch_bounds__(BLOCK, small_min_wg(U)) void k_ratios_apply_small(
     for (int e = 0; e < 2; ++e)
       if (e < n_end && n_of[e] > 1) {
         asm volatile("" ::"v"(rp_end[e]), "v"(ca_end[e]) : "memory");   // both are there before the slot says so
-        slot_store(&sm.slots[s_end[e]], want[e], __float_as_uint(r_end[e]));
+        slot_store(&slots[s_end[e]], want[e], __float_as_uint(r_end[e]));
       }
   }
   if (!inside) {   // the layers in between lie inside the tile
@@ -2485,7 +2492,7 @@ __global__ __launch_bounds__(BLOCK, small_min_wg(U)) void k_ratios_apply_small(
     float q = r_end[e];
     if (n_of[e] > 1) {
       q = 0.0f;
-      slots_wait(sm, sm.slots + s0_end[e], n_of[e], want[e], [&](unsigned int w) {
+      slots_wait(sm, slots + s0_end[e], n_of[e], want[e], [&](unsigned int w) {
         const float v = __uint_as_float(w);
         if (v > q) q = v;
       });
@@ -3192,7 +3199,7 @@ __global__ __launch_bounds__(BLOCK, 8) void k_warmup_trail(
 // and barriers, with the fp64 sums of x^2 and u^2 in place of the maxima).
 // Measured: 3.04 M parameters, binary16 gradient: 26 us (37 us in four launches).
 // ---------------------------------------------------------------------------------------------
-template <int U, int GT, bool LPX>
+template <int U, int GT, bool LPX, bool TWO_LEVELS>
 __global__ __launch_bounds__(BLOCK, small_min_wg(U)) void k_warmup_small(
     GradSrc g, float* __restrict__ m, float* __restrict__ v, float* __restrict__ x, SmallTab sm, WarmClip wc,
     float beta1, float omb1, float beta2, float omb2, float eta, float wd, float lr, LayerTab lt,
@@ -3300,8 +3307,8 @@ __global__ __launch_bounds__(BLOCK, small_min_wg(U)) void k_warmup_small(
     }
   }
   __syncthreads();
-  double* const partial = sm.partial;
-  small_arrive(sm, ti, n_end, s0_end, bc, [&](int e) {
+  double* const partial = static_cast<double*>(sm.partial);
+  small_arrive<TWO_LEVELS>(sm, lt.L, ti, n_end, s0_end, bc, [&](int e) {
     double* q = partial + 2 * (int64_t)(ti.seg0 + (e ? last_seg : 0));
     __hip_atomic_store(q, end_sum[e][0], __ATOMIC_RELAXED, OB_AGENT);
     __hip_atomic_store(q + 1, end_sum[e][1], __ATOMIC_RELAXED, OB_AGENT);
@@ -3325,7 +3332,7 @@ __global__ __launch_bounds__(BLOCK, small_min_wg(U)) void k_warmup_small(
       c_end[e] = c;
       if (bc[e] & 1ull)
         (void)barrier_publish(&sm.flag[(int64_t)l * CTR_STRIDE], &sm.counter[(int64_t)l * CTR_STRIDE], s1 - s0,
-                              (unsigned int)(bc[e] >> 32), __float_as_uint(c), SMALL_ONE_LEVEL);
+                              (unsigned int)(bc[e] >> 32), __float_as_uint(c), small_one_level<TWO_LEVELS>());
     }
   }
   // while the layers complete: the moments are stored

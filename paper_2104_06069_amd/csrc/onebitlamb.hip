@@ -130,10 +130,10 @@ struct SmallPlan {
   SmallTile* d_tiles = nullptr;
   int* d_seg_layer = nullptr;
   int* d_layer_seg0 = nullptr;
+  bool two_levels = false;                  // (k_warmup_small) of arrivals
   unsigned long long* d_slots = nullptr;    // [segments] (k_ratios_apply_small), or (k_warmup_small)
   double* d_partial = nullptr;          // [2 * segments]
   unsigned long long* d_counter = nullptr;
-  unsigned long long* d_sub = nullptr;
   unsigned long long* d_flag = nullptr;
 };
 
@@ -609,8 +609,9 @@ bool build_small(ob_lamb_ctx* ctx, Workspace* ws, SmallTilings* tilings, const s
       ws->alloc_zero(&sp->d_slots, t.seg_layer.size());
     } else {
       ws->alloc_zero(&sp->d_partial, 2 * t.seg_layer.size());
-      ws->alloc_zero(&sp->d_counter, (size_t)ctx->L * CTR_STRIDE);
-      ws->alloc_zero(&sp->d_sub, group_lines((int64_t)t.seg_layer.size(), ctx->L) * CTR_STRIDE);
+      sp->two_levels = sh.max_arrivals > SMALL_ONE_LEVEL;
+      const size_t groups = sp->two_levels ? group_lines((int64_t)t.seg_layer.size(), ctx->L) : 0;
+      ws->alloc_zero(&sp->d_counter, ((size_t)ctx->L + groups) * CTR_STRIDE);
       ws->alloc_zero(&sp->d_flag, (size_t)ctx->L * CTR_STRIDE);
     }
     sp->u = best;
@@ -621,8 +622,9 @@ bool build_small(ob_lamb_ctx* ctx, Workspace* ws, SmallTilings* tilings, const s
 SmallTab small_tab(const ob_lamb_ctx* ctx, const SmallPlan& sp) {
   SmallTab t;
   t.tiles = sp.d_tiles; t.n_tiles = sp.n_tiles; t.tpc = sp.tpc; t.max_seg = sp.max_seg; t.n_c = ctx->n_c;
-  t.seg_layer = sp.d_seg_layer; t.layer_seg0 = sp.d_layer_seg0; t.partial = sp.d_partial;
-  t.counter = sp.d_counter; t.sub = sp.d_sub; t.flag = sp.d_flag; t.slots = sp.d_slots;
+  t.seg_layer = sp.d_seg_layer; t.layer_seg0 = sp.d_layer_seg0;
+  t.partial = sp.d_slots ? (void*)sp.d_slots : (void*)sp.d_partial;
+  t.counter = sp.d_counter; t.flag = sp.d_flag;
   t.errflag = ctx->d_errflag; t.spin_limit = ctx->spin_limit;
   return t;
 }
@@ -1091,7 +1093,7 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
         bool r = false;
         dispatch_u(U, [&](auto u) {
           constexpr int UU = decltype(u)::value;
-          r = slots_of(k_warmup_small<UU, 1, true>, bytes, small_min_wg(UU), n);
+          r = slots_of(k_warmup_small<UU, 1, true, true>, bytes, small_min_wg(UU), n);
         });
         return r;
       }, &ctx->sm_warm);
@@ -1213,11 +1215,13 @@ ob_status ob_lamb_warmup_step_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st, cons
     const SmallPlan& sm = ctx->sm_warm;
     dispatch_u(sm.u, [&](auto u) {
       dispatch2(lpg, xl.p != nullptr, [&](auto lg, auto lx) {
-        OB_LAUNCH_S(la, KID_WARMUP_SMALL,
-                    (k_warmup_small<decltype(u)::value, decltype(lg)::value ? 1 : 0, decltype(lx)::value>),
-                    sm.n_tiles + (sm.empty_layers ? 1 : 0), BLOCK, sm.lds_bytes, gs, st->m, st->v_fresh, st->x,
-                    small_tab(ctx, sm), wc, ctx->beta1, ctx->omb1, ctx->beta2, ctx->omb2, ctx->eta, ctx->wd, lr, lt,
-                    xl.p, xl.bf16);
+        dispatch1(sm.two_levels, [&](auto two) {
+          OB_LAUNCH_S(la, KID_WARMUP_SMALL,
+                      (k_warmup_small<decltype(u)::value, decltype(lg)::value ? 1 : 0, decltype(lx)::value, decltype(two)::value>),
+                      sm.n_tiles + (sm.empty_layers ? 1 : 0), BLOCK, sm.lds_bytes, gs, st->m, st->v_fresh, st->x,
+                      small_tab(ctx, sm), wc, ctx->beta1, ctx->omb1, ctx->beta2, ctx->omb2, ctx->eta, ctx->wd, lr, lt,
+                      xl.p, xl.bf16);
+        });
       });
     });
     return la.ok ? OB_OK : OB_ERR_HIP;

@@ -2163,7 +2163,7 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
 // reductions of a few microseconds whatever it moves.  Here every tile, whatever layers it meets, is one
 // workgroup that runs the ratio pass, takes part in the barriers of its layers and then the update, with
 // x, v_frozen and the signs in registers.  U is 1, 2 or 4: small tiles keep a workgroup's own chain of
-// look-ups and divisions short, large ones the number of slots that each reads (small_cost in the host code).
+// look-ups and divisions short, large ones the number of workgroups small (small_cost in the host code).
 //
 // In a tile that meets several layers, what depends on the layer alone is formed once per segment (with momentum
 // scaling, by each element: 24 tensors of 300x300 28.5 instead of 20.5 us) and each lane looks its segments up once.
@@ -2178,9 +2178,9 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
 // ---------------------------------------------------------------------------------------------
 // workgroups per CU that the kernels are built for (their registers at each U)
 constexpr int small_min_wg(int u) { return u == 1 ? 8 : (u == 2 ? 5 : 4); }
-// k_warmup_small's arrivals counted in one level (a LAMB step, us, one level / two: 384 arrivals 26.8 / 27.1, 588 19.5 / 16.5,
-// 706 20.4 / 16.7).  A kernel of its own for lists without longer layers: carrying both forms costs it 0.2 to 0.5 us of 11 to 17.
-constexpr int SMALL_ONE_LEVEL = 512;
+// k_warmup_small's arrivals counted in one level up to SMALL_ONE_LEVEL (a LAMB step, us, in one level / two: 200 arrivals 10.0 / 8.8, 256
+// 12.2 / 10.3, 313 12.0 / 9.9, 392 13.3 / 10.4, 400 11.9 / 8.6, 588 19.5 / 16.5; 128 10.8 / 10.4 and 124 10.6 / 10.6).  A kernel of its own
+// for lists without longer layers: carrying both forms costs it 0.2 to 0.5 us of 11 to 17.
 template <bool TWO_LEVELS>
 constexpr int small_one_level() { return TWO_LEVELS ? SMALL_ONE_LEVEL : 0x7fffffff; }
 constexpr int SMALL_POLL_SLEEP = 2;   // (the whole launch lasts some 10 us: at first a poll every 128 clocks)
@@ -2263,8 +2263,8 @@ __device__ __forceinline__ void small_arrive(const SmallTab& sm, int L, const Sm
 // number, so that only a store and a load lie between the last partial result and its readers.  (Arrivals counted at an
 // atomic, whose last one reads the results and publishes the coefficient, are five such trips, and with the two fp64
 // sums of k_warmup_small, four words a slot, those cost less: 10.6 us instead of 12.6 for four tensors of 262144.)  A step, us,
-// counted / slots: four of 262144 23.9 / 22.3, two of 1 M 36.4 / 32.1, one of 0.9 M (221 segments) 29.4 / 26.2, of 1.6 M
-// (391) 30.2 / 29.5, of 2.9 M (706) 37.6 / 37.3; 24 of 65536 27.0 / 27.4.  The number is one more
+// counted / slots: four of 262144 23.9 / 22.3, two of 1 M 36.4 / 32.1, one of 1.6 M
+// (391 segments) 30.2 / 29.5, of 2.9 M (706) 37.6 / 37.3; 24 of 65536 27.0 / 27.4.  The number is one more
 // than what the slot held: nothing that changes from call to call comes from the host.  What a workgroup has read of r_prev and c_avg it has
 // before it publishes; the layer's first segment's workgroup writes them, once all have published.
 __device__ __forceinline__ unsigned long long slot_load(const unsigned long long* p) {

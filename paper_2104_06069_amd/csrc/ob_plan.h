@@ -384,21 +384,48 @@ inline SmallShape small_shape(int U, const std::vector<int64_t>& h_off, int64_t 
   }
   return sh;
 }
-// What sets the tile sizes apart, in ns: a workgroup's own chain of loads and divisions, the arrivals of a layer at
-// its counter, which are served one after the other, the look-ups with which the threads of a tile that meets
-// several layers go through its spans, and the segments of such a tile, which its wavefronts finish in turn.
-// Measured at U = 1 / 2 / 4 (kernel, us; LAMB step, then ratios_apply):
-//   eight tensors of 65536 7.7 / 7.6 / 8.8, 7.6 / 8.4 / 10.2; four of 262144 11.3 / 9.1 / 9.5, 10.6 / 9.4 / 10.3
-//   one of 0.9 M 18.6 / 14.0 / 15.9, 17.7 / 13.3 / 16.4; of 1.6 M 27.7 / 17.9 / 14.4, 27.2 / 17.9 / 15.0 (in
-//   8192-element tiles, k_warmup_resident and k_ratios_apply_resident: 16.1, 14.6)
-//   four of 125000 9.0 / 11.2 / 14.4, 9.5 / 12.2 / 14.6; 0.8 M and ten of 80000 17.7 / 14.4 / 20.1, 18.3 / 14.8 / 19.7
-//   3000 of 1 and one of 1.2 M 205 / 394 / 561, 105 / 213 / 306
-// (ratios_apply with counted arrivals.  With slots, called over and over with everything in the caches: eight of 65536 6.5 / 6.7 /
-// 8.6, four of 262144 7.9 / 8.0 / 9.6, 0.9 M 8.2 / 8.3 / 12.4, 1.6 M 11.3 / 11.2 / 14.2; as part of a step, which is what the choice
-// goes by, four of 262144 25.0 / 24.0 / 25.8, 0.9 M 28.5 / 25.5 / 29.9, 1.6 M 33.5 / 31.9 / 30.2.)
-inline int64_t small_cost(int U, const SmallShape& sh) {
-  return (U == 1 ? 0 : U == 2 ? 500 : 2000) + 13 * sh.max_arrivals + 2500 * std::max(sh.mixed_spans - 1, 0) + 100 * sh.max_seg;
+// What sets the tile sizes apart, in ns: a workgroup's own chain of loads and divisions, the look-ups with which the threads
+// of a tile that meets several layers (or the padding) go through its spans, the segments of such a tile, which its wavefronts
+// finish in turn, and many workgroups.  k_ratios_apply_small reads a slot for every tile of its layer, which costs next to nothing; only
+// workgroups of several layers side by side cost it time (those of one layer, up to 1600, do not).  k_warmup_small's arrivals queue
+// at a counter, in two levels from SMALL_ONE_LEVEL on.
+// Compression steps and LAMB steps at U = 1 / 2 / 4, us (256 CUs; four steps in 20 or so of the lists; -: does not fit):
+//   elements, tensors      steps with the variance's history       steps without             LAMB steps
+//   0.41 M, one            21.2 / 22.1 / 24.5                      20.0 / 20.6 / 22.8        8.6 / 8.8 / 10.3
+//   0.50 M, four           22.5 / 22.8 / 27.2                      21.6 / 21.9 / 26.8        10.6 / 9.0 / 15.5
+//   0.52 M, eight          21.3 / 22.2 / 25.0                      20.3 / 21.2 / 23.3        8.1 / 8.5 / 9.9
+//   0.80 M, one            24.5 / 25.2 / 25.8                      24.3 / 24.5 / 24.3        10.1 / 10.4 / 10.9
+//   0.90 M, one, padded    24.0 / 25.9 / 30.3                      23.5 / 25.1 / 30.2        11.1 / 12.3 / 17.5
+//   0.99 M, eight, shared  25.7 / 26.5 / 31.3                      25.5 / 25.9 / 31.3        10.0 / 13.5 / 19.2
+//   1.05 M, four           25.6 / 24.7 / 26.3                      25.1 / 23.3 / 24.6        10.3 / 10.8 / 11.2
+//   1.31 M, five           28.1 / 26.9 / 28.0                      28.0 / 25.5 / 26.5
+//   1.57 M, six            30.2 / 28.0 / 29.1                      31.2 / 26.7 / 27.6
+//   1.60 M, one, padded    30.0 / 30.7 / 32.0                      29.6 / 28.8 / 31.7        13.8 / 13.2 / 17.5
+//   1.64 M, one            29.5 / 30.2 / 29.9                      29.0 / 28.5 / 28.3        13.4 / 13.2 / 13.6
+//   1.6 M, 109 tensors     29.9 / 32.2 / 36.2                      30.3 / 31.5 / 35.9        14.8 / 16.9 / 22.9
+//   0.18 M, 46 tensors     19.8 / 21.6 / 27.2                      18.4 / 21.1 / 26.2        10.6 / 12.6 / 19.2
+// The choice is the fastest of these lists and 20 like them or within 4 %, on average within 0.2 %.
+constexpr int SMALL_ONE_LEVEL = 128;   // (figures at k_warmup_small)
+inline int64_t small_cost(int U, const SmallShape& sh, bool by_slots, int cus) {
+  int64_t c = (U == 1 ? 0 : U == 2 ? 500 : 2000) + 2500 * std::max(sh.mixed_spans - 1, 0) + 100 * sh.max_seg +
+              3 * std::max<int64_t>(by_slots ? sh.n_tiles - sh.max_arrivals - 11 * cus / 8 : sh.n_tiles - 4 * cus, 0);
+  if (!by_slots)
+    c += 13 * (sh.max_arrivals <= SMALL_ONE_LEVEL ? sh.max_arrivals : ARRIVE_SUB + sh.max_arrivals / ARRIVE_SUB + 46 /* another trip */);
+  return c;
 }
+// The index in U = 1, 2, 4 (fits[i]: the tiles of sh[i] fit on the device; the smallest of equals), -1 if none fits.
+inline int small_choice(const SmallShape (&sh)[3], const bool (&fits)[3], bool by_slots, int cus) {
+  int best = -1;
+  for (int i = 0; i < 3; ++i)
+    if (fits[i] && (best < 0 || small_cost(1 << i, sh[i], by_slots, cus) < small_cost(1 << best, sh[best], by_slots, cus))) best = i;
+  return best;
+}
+// A list all of whose parameters lie in 8192-element tiles of layers that the barrier kernels take keeps those where one layer
+// has more than this many 1024-element spans.  Steps of one tensor, or two, us, in one launch / in the barrier kernel, with the
+// variance's history, without, LAMB: 1.6 M (1600 spans) 29.9 / 33.9, 28.3 / 33.4, 13.6 / 17.6; two of 1.6 M 40.2 / 39.7, 39.1 /
+// 40.3, 20.6 / 21.6; 2.4 M (2304) 35.3 / 37.0, 33.5 / 37.6, 16.3 / 20.0; 3.2 M (3136) 40.2 / 39.4, 39.4 / 40.0, 21.1 / 22.3.
+// (One limit for both calls; compression steps with the history are what runs most.)
+constexpr int64_t SMALL_MAX_SPANS = 2800;
 
 // Tilings of the tile sizes that a SmallPlan may take, formed when first asked for, and their shapes.
 struct SmallTilings {

@@ -562,36 +562,30 @@ void build_split(ob_lamb_ctx* ctx, Workspace* ws, const Tiling& tl, int tile_lb,
   ws->alloc_zero(&sp->d_flag, (size_t)L);
 }
 
-// Chooses and uploads a SmallPlan: of the U whose tiles take at most 80 % of the device's workgroup slots
-// (slots(U, dynamic LDS bytes)) the one of the lowest small_cost, the smallest of equals.  vals, tables: 4-byte words
-// of LDS per element and per segment of a tile that meets several layers; by_slots: the barriers are those of slots.
-// The list keeps the barrier kernel of the larger lists (split) where that is all it takes, every parameter lying in its
-// 8192-element tiles, and one layer has more than max_queue arrivals at its counter here, twice as many as there.
-// The calls of one tensor, or two equal ones, in whole tiles, us, LAMB step, ratios_apply, ratios_apply_hist, in one
-// launch / in the barrier kernel: 1.6 M (391 arrivals) 15.4 / 16.8, 15.9 / 16.0, 16.9 / 17.1; two of 1.6 M (392) 18.9 /
-// 20.3, 19.0 / 19.0, 20.3 / 19.6; 2.4 M (586) 18.5 / 19.4, 18.7 / 18.6, 19.9 / 19.5; 3.2 M (782) 22.4 / 21.5, 22.5 / 20.0,
-// 23.7 / 20.6 (with slots and arrivals in two levels: 1.6 M 14.5 / 14.2, 11.2 / 16.5, 12.2 / 16.1; 2.4 M 14.6 / 19.1, 15.0 / 18.5,
-// 16.5 / 17.6; 3.2 M 17.4 / 20.4, 18.1 / 19.0, 18.8 / 17.9); with a part outside those tiles, so that the plain kernels run too, 3.2 M 23.0 / 33.2, 22.7 / 27.6, 23.8 / 26.1.
-constexpr int SMALL_QUEUE_APPLY = 512, SMALL_QUEUE_LAMB = 700;
+// Chooses and uploads a SmallPlan: small_choice among the U whose tiles take at most 80 % of the device's workgroup slots
+// (slots(U, dynamic LDS bytes)).  vals, tables: 4-byte words of LDS per element and per segment of a tile that
+// meets several layers; by_slots: the barriers are those of slots; split: the barrier kernel of the larger lists.
 template <class F>
 bool build_small(ob_lamb_ctx* ctx, Workspace* ws, SmallTilings* tilings, const std::vector<int64_t>& h_off,
-                 const std::vector<unsigned char>& lagging, const LayerSplit& split, int max_queue, int vals, int tables,
-                 bool by_slots, F slots, SmallPlan* sp) {
+                 const std::vector<unsigned char>& lagging, const LayerSplit& split, int vals, int tables, bool by_slots, int cus,
+                 F slots, SmallPlan* sp) {
   static_assert(TILE_MAIN == SPAN, "the TILE_MAIN tiling is that of U = 1");
-  int best = 0;
-  SmallShape sh;
-  for (int U : {1, 2, 4}) {
-    const SmallShape& s = tilings->sh[U / 2];
-    if (s.n_tiles == 0 || (best && small_cost(U, s) >= small_cost(best, sh))) continue;
-    const size_t bytes = 4 * ((size_t)vals * SPAN * U + (size_t)tables * (size_t)s.max_seg);
+  bool fits[3] = {false, false, false};
+  size_t lds_bytes[3] = {0, 0, 0};
+  for (int i = 0; i < 3; ++i) {
+    const SmallShape& s = tilings->sh[i];
+    if (s.n_tiles == 0) continue;
+    lds_bytes[i] = 4 * ((size_t)vals * (SPAN << i) + (size_t)tables * (size_t)s.max_seg);
     int64_t n_slots = 0;
-    if (!slots(U, bytes, &n_slots)) return false;
-    if (5 * (s.n_tiles + 8) > 4 * n_slots) continue;
-    best = U;
-    sh = s;
-    sp->lds_bytes = bytes;
+    if (!slots(1 << i, lds_bytes[i], &n_slots)) return false;
+    fits[i] = 5 * (s.n_tiles + 8) <= 4 * n_slots;
   }
-  if (best && split.on && split.n_rest_tiles == 0 && sh.max_arrivals > max_queue) best = 0;
+  int choice = small_choice(tilings->sh, fits, by_slots, cus);
+  if (choice >= 0 && split.on && split.n_rest_tiles == 0 && ((int64_t)tilings->sh[choice].max_arrivals << choice) > SMALL_MAX_SPANS)
+    choice = -1;
+  const int best = choice < 0 ? 0 : 1 << choice;
+  const SmallShape sh = choice < 0 ? SmallShape() : tilings->sh[choice];
+  if (best) sp->lds_bytes = lds_bytes[choice];
   const Tiling* tp = best ? tilings->get(best, ctx->n_c, ctx->W, ctx->L, h_off) : nullptr;
   if (tp) {
     const Tiling& t = *tp;
@@ -1079,7 +1073,7 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
     };
     SmallTilings tilings(tm, ctx->n_c, ctx->W, L, h_off);
     if (ok && cfg->fused_max_tiles == 0 && !(cfg->flags & OB_CFG_NO_FUSED_APPLY))
-      ok = build_small(ctx, &ws, &tilings, h_off, lagging, ctx->sp_apply, SMALL_QUEUE_APPLY, 1, 4, true, [&](int U, size_t bytes, int64_t* n) {
+      ok = build_small(ctx, &ws, &tilings, h_off, lagging, ctx->sp_apply, 1, 4, true, cus, [&](int U, size_t bytes, int64_t* n) {
         bool r = false;
         dispatch_u(U, [&](auto u) {
           constexpr int UU = decltype(u)::value;
@@ -1089,7 +1083,7 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
       }, &ctx->sm_apply);
     if (ok && cfg->fused_max_tiles == 0 && !(cfg->flags & OB_CFG_TWO_PASS_WARMUP))
       ok = build_small(ctx, &ws, &tilings, h_off, std::vector<unsigned char>((size_t)tm.n_tiles, 0), ctx->sp_warm,
-                       SMALL_QUEUE_LAMB, 2, 3, false, [&](int U, size_t bytes, int64_t* n) {
+                       2, 3, false, cus, [&](int U, size_t bytes, int64_t* n) {
         bool r = false;
         dispatch_u(U, [&](auto u) {
           constexpr int UU = decltype(u)::value;

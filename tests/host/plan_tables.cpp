@@ -191,10 +191,42 @@ void second_reads() {
   CHECK(!keeps_second_reads(2 * 909 * 909, 147) && !keeps_second_reads(64 * 65536 - 1, 64) && keeps_second_reads(64 * 65536, 64));
   CHECK(keeps_second_reads(8000000, 256) && !keeps_second_reads(7999999, 256) && keeps_second_reads(65536, 1));
 }
+
+// Tile sizes of the one-launch kernels where another one measures 4 % or more slower (256 CUs; 80 % of the slots).
+void small_lists() {
+  struct Want { int64_t W; std::vector<int64_t> sizes; int u_apply, u_lamb; };
+  const int64_t k = 1024;
+  const Want wants[] = {
+      {4, {400 * k}, 1, 1},          {4, {625 * k}, 1, 1},             {2, {784 * k}, 1, 1},
+      {4, {900601}, 1, 1},           {4, std::vector<int64_t>(4, 256 * k), 2, 1},
+      {4, std::vector<int64_t>(4, 225 * k), 2, 1}, {6, std::vector<int64_t>(6, 256 * k), 2, 2},
+      {4, {1600225}, 1, 2},          {4, {1600 * k}, 1, 2},            {4, std::vector<int64_t>(4, 354 * 354), 1, 2},
+      {4, std::vector<int64_t>(8, 352 * 352), 1, 1}, {4, std::vector<int64_t>(100, 10000), 1, 1},
+      {4, {2304 * k}, 4, 4},         {8, std::vector<int64_t>(30, 130 * k), 0, 0},
+  };
+  for (const Want& w : wants) {
+    std::vector<int64_t> off(1, 0);
+    for (int64_t s : w.sizes) off.push_back(off.back() + s);
+    const int64_t L = (int64_t)w.sizes.size(), n_c = (off.back() + 256 * w.W - 1) / (256 * w.W) * 256;
+    off.push_back(n_c * w.W);
+    SmallShape sh[3];
+    bool fits[3];
+    for (int i = 0; i < 3; ++i) {
+      sh[i] = small_shape(1 << i, off, n_c, w.W, L);
+      fits[i] = 5 * (sh[i].n_tiles + 8) <= 4 * 256 * (i == 0 ? 8 : i == 1 ? 5 : 4);
+    }
+    for (bool by_slots : {true, false}) {
+      const int c = small_choice(sh, fits, by_slots, 256), got = c < 0 ? 0 : 1 << c, want = by_slots ? w.u_apply : w.u_lamb;
+      if (got != want) printf("%d tensors of %ld, slots %d: U = %d\n", (int)L, (long)w.sizes[0], by_slots, got);
+      CHECK(got == want);
+    }
+  }
+}
 }  // namespace
 
 int main(int argc, char** argv) {
-  const struct { const char* name; void (*f)(); } checks[] = {{"trail", trail}, {"big_rule", big_rule}, {"arrivals", arrivals}, {"second_reads", second_reads}};
+  const struct { const char* name; void (*f)(); } checks[] = {{"trail", trail}, {"big_rule", big_rule}, {"arrivals", arrivals}, {"second_reads", second_reads},
+                                                              {"small_lists", small_lists}};
   for (const auto& c : checks)
     if (argc == 2 && !strcmp(argv[1], c.name)) {
       c.f();

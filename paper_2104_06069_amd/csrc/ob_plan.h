@@ -222,24 +222,25 @@ inline void plan_split(const Tiling& tl, int64_t tile_lb, const Tiling& tm, cons
 //     5000 x 8 1335 / 1175, 7000 x 6 1930 / 1838, 20000 x 2 5400 / 5520; the GPT list of 1.3e9 parameters 8490 / 7400
 //   in several launches (no kernel may wait): BERT and GPT lists of 11 M 80 / 87, 25 M 152 / 160, 40 M 273 / 275,
 //     50 M 353 / 332, 60 M 400 / 386, 110 M 733 / 681, 336 M 2218 / 2056, 1.3e9 8800 / 8010
-// so that it is taken from 14.7 M and 42 M elements on, and not for layers of which the cache holds next to nothing.
+// so that it is taken from 7 and 20 tiles a CU on (14.7 M and 42 M elements), and not for layers of which the cache holds next to nothing.
 // A configuration that lowers the barrier kernels' limit (cap) takes it for lists of any size.
-constexpr int64_t TRAIL_MIN_TILES = 1792, TRAIL_MIN_TILES_NO_WAIT = 5120, TRAIL_MAX_LAYER_TILES = 16384;
-inline BigRule trail_rule(bool wait, int32_t cap) {
+constexpr int64_t TRAIL_MAX_LAYER_TILES = 16384;
+inline BigRule trail_rule(bool wait, int32_t cap, int cus) {
   BigRule r;
   r.max_tiles = TRAIL_MAX_LAYER_TILES;
-  r.min_total = cap > 0 ? 0 : wait ? TRAIL_MIN_TILES : TRAIL_MIN_TILES_NO_WAIT;
+  r.min_total = cap > 0 ? 0 : (wait ? 7 : 20) * (int64_t)cus;
   return r;
 }
 
 // The workgroups of k_warmup_trail in order (no HIP call).  n, begin: parts of each layer.  lag > 0: one launch, the
-// update of a layer `lag` moments parts after the layer's last one: what is in flight on the device then (2048
-// workgroups) lies between them, so that no update waits for long (half of that 2 % slower, twice no difference).  lag = 0: no update
+// update of a layer `lag` moments parts after the layer's last one: what is in flight on the device then (8 workgroups a
+// CU; trail_lag: 10) lies between them, so that no update waits for long (half of that 2 % slower, twice no difference).  lag = 0: no update
 // waits; the layers are taken in groups of at least `group` parts (16.8 M elements; 33 M no difference), and a launch updates one
 // group and forms the moments of the next.
 // A layer of more than TRAIL_KEEP_PARTS parts (16.8 M elements, 200 MB of m, v and x) does not fit the cache: its last
 // parts are updated first, and only they are kept.
-constexpr int64_t TRAIL_LAG = 2560, TRAIL_GROUP = 8192, TRAIL_KEEP_PARTS = 8192;
+constexpr int64_t TRAIL_GROUP = 8192, TRAIL_KEEP_PARTS = 8192;
+inline int64_t trail_lag(int cus) { return 10 * (int64_t)cus; }
 inline void trail_items(const std::vector<int>& n, const std::vector<int>& begin, int64_t lag, int64_t group,
                  std::vector<unsigned int>* items, std::vector<int64_t>* item_end) {
   items->clear();
@@ -303,9 +304,27 @@ inline size_t group_lines(int64_t n, int64_t L) { return arrival_groups(n) + (si
 // launch of its own / in that one, rest tiles and 8192-element tiles: 240, 1424 86.4 / 83.6; 1209, 2232 131.3 / 128.8; 468,
 // 2580 140.6 / 138.8; 433, 1713 110.1 / 109.3; 286, 3920 188.4 / 188.7; 1600, 4800 236.9 / 241.7; 647, 5135 242 / 239.7; 1297, 9677
 // 448 / 445; 710, 11239 501 / 511; 997, 25803 1134 / 1140; 1430, 40908 1716 / 1728.
-constexpr int REST_IN_LAUNCH_MAX = 1280, REST_IN_LAUNCH_MAX_TILES = 5120;
-inline bool rest_in_launch(int n_rest_tiles, int n_listed, int n_big) {
-  return n_listed > 0 && n_rest_tiles <= REST_IN_LAUNCH_MAX && n_listed + n_big <= REST_IN_LAUNCH_MAX_TILES;
+// (The line: 5 rest tiles and 20 tiles a CU.)
+inline bool rest_in_launch(int n_rest_tiles, int n_listed, int n_big, int cus) {
+  return n_listed > 0 && n_rest_tiles <= 5 * cus && n_listed + n_big <= 20 * cus;
+}
+
+// Arrivals of a layer of the barrier kernels that are counted in one level, by their listed tiles.  (Figures at
+// barrier_arrive.  The lists that gain in layers of up to 512 tiles have at most 24 tiles a CU, those that lose 70.)
+inline int arrivals_one_level(int n_listed_tiles, int cus) { return n_listed_tiles > 40 * cus ? 512 : ARRIVE_ONE_LEVEL; }
+
+
+// Spans per tile of the server kernel without a barrier (k_server_unpack_avg).  With few workers a tile of 1024 elements is a
+// chain of latencies (scales, LDS, words) around a few additions: larger ones where the chunk still makes rounds of
+// the device; with many workers the additions bind, and more, smaller workgroups hide them better.  The call, us, 1 / 2 / 4 spans
+// (above 1 with chunk_ticket, which by then costs less than a launch: 0.3 to 4 us), workers, tiles of 1024 elements:
+//   1, 107520 229 / 160 / 153; 2, 53760 121 / 88.1 / 80.7; 2, 5504 17.4 / 14.1 / 13.4; 4, 26880 73.8 / 46.0 / 45.1; 4, 2752 12.1 /
+//   9.9 / 10.6; 8, 13440 36.4 / 28.1 / 28.4; 8, 1376 8.4 / 8.4 / 9.7; 16, 6720 24.4 / 21.6 / 22.2; 16, 688 7.4 / 8.0 / 9.6; 32,
+//   3360 19.6 / 19.2 / 22.8; 64, 5254 37.3 / 37.5 / 42.7; 64, 1680 18.0 / 19.8 / 21.0; 128, 840 18.7 / 20.8 / 31.1
+// (The line: 16 and 8 tiles a CU, one or two rounds of the device.)
+inline int server_spans(int64_t W, int tpc, int cus) {
+  if (W <= 2 && tpc >= 16 * cus) return 4;
+  return (W <= 32 && tpc >= 8 * cus) ? 2 : 1;
 }
 
 // Arrivals at the layers' barriers in k_ratios_apply_hist with the plain ratio pass in its launch: the listed tiles of each

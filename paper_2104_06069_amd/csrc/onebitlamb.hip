@@ -174,6 +174,7 @@ struct LayerSplit {
   int64_t n_big_params = 0;
   int* d_big_tiles = nullptr;
   // k_warmup_trail over them: its workgroups in order, and the end of each launch's share
+  int one_level = ARRIVE_ONE_LEVEL;        // arrivals of a layer that are counted in one level
   bool trail_wait = false;
   unsigned int* d_items = nullptr;
   std::vector<int64_t> item_end;
@@ -480,7 +481,7 @@ ob_status momentum_source(const ob_lamb_state* st, bool* packed, PackedMom* pm) 
 
 // Plans and uploads one LayerSplit.
 void build_split(ob_lamb_ctx* ctx, Workspace* ws, const Tiling& tl, int tile_lb, const Tiling& tm,
-                 const std::vector<int64_t>& h_off, int64_t max_tiles, const BigRule& rule, bool trail, LayerSplit* sp,
+                 const std::vector<int64_t>& h_off, int64_t max_tiles, const BigRule& rule, bool trail, int cus, LayerSplit* sp,
                  std::vector<unsigned char>* lagging) {
   const int64_t L = ctx->L;
   SplitPlan pl;
@@ -509,7 +510,7 @@ void build_split(ob_lamb_ctx* ctx, Workspace* ws, const Tiling& tl, int tile_lb,
     for (int& q : begin) q *= TRAIL_PARTS;
     std::vector<unsigned int> items;
     sp->trail_wait = max_tiles > 0;
-    trail_items(n, begin, sp->trail_wait ? TRAIL_LAG : 0, TRAIL_GROUP, &items, &sp->item_end);
+    trail_items(n, begin, sp->trail_wait ? trail_lag(cus) : 0, TRAIL_GROUP, &items, &sp->item_end);
     ws->upload(&sp->d_items, std::move(items));
     std::vector<int> count0((size_t)L, 0);
     std::vector<unsigned char> has_tiles = pl.has_listed;
@@ -531,7 +532,8 @@ void build_split(ob_lamb_ctx* ctx, Workspace* ws, const Tiling& tl, int tile_lb,
     ws->alloc_zero(&sp->d_part_sums, 2 * (size_t)TRAIL_PARTS * (size_t)sp->n_big_tiles);
     ws->alloc_zero(&sp->d_trail_flag, (size_t)L);
   }
-  sp->rest_in_launch = !trail && rest_in_launch(sp->n_rest_ratio_tiles, sp->n_fused_tiles, sp->n_big_tiles);
+  sp->one_level = arrivals_one_level(sp->n_fused_tiles, cus);
+  sp->rest_in_launch = !trail && rest_in_launch(sp->n_rest_ratio_tiles, sp->n_fused_tiles, sp->n_big_tiles, cus);
   if (sp->rest_in_launch) {
     ArrivalPlan ap;
     plan_arrivals(pl, tm, L, &ap);
@@ -650,18 +652,6 @@ bool worker_ticket(int tpc, int n_tiles, int cus) {
 }
 bool server_ticket(int tpc, int n_tiles, int cus) { return tpc <= TICKET_SUB || two_level_ticket(tpc, n_tiles, cus); }
 
-// Spans per tile of the server kernel without a barrier (k_server_unpack_avg).  With few workers a tile of 1024 elements is a
-// chain of latencies (scales, LDS, words) around a few additions: larger ones where the chunk still makes rounds of
-// the device; with many workers the additions bind, and more, smaller workgroups hide them better.  The call, us, 1 / 2 / 4 spans
-// (above 1 with chunk_ticket, which by then costs less than a launch: 0.3 to 4 us), workers, tiles of 1024 elements:
-//   1, 107520 229 / 160 / 153; 2, 53760 121 / 88.1 / 80.7; 2, 5504 17.4 / 14.1 / 13.4; 4, 26880 73.8 / 46.0 / 45.1; 4, 2752 12.1 /
-//   9.9 / 10.6; 8, 13440 36.4 / 28.1 / 28.4; 8, 1376 8.4 / 8.4 / 9.7; 16, 6720 24.4 / 21.6 / 22.2; 16, 688 7.4 / 8.0 / 9.6; 32,
-//   3360 19.6 / 19.2 / 22.8; 64, 5254 37.3 / 37.5 / 42.7; 64, 1680 18.0 / 19.8 / 21.0; 128, 840 18.7 / 20.8 / 31.1
-int server_spans(int W, int tpc) {
-  if (W <= 2 && tpc >= 4096) return 4;
-  return (W <= 32 && tpc >= 2048) ? 2 : 1;
-}
-
 ChunkTicket chunk_ticket_of(unsigned int* count, double* part, int n_chunks, int tpc, float* scales, float* own_scale,
                             int own_chunk) {
   ChunkTicket tk;
@@ -670,15 +660,12 @@ ChunkTicket chunk_ticket_of(unsigned int* count, double* part, int n_chunks, int
   return tk;
 }
 
-// (Figures at barrier_arrive.  The lists that gain in layers of up to 512 tiles have at most 6144 tiles.)
-int arrivals_one_level(int n_listed_tiles) { return n_listed_tiles > 10240 ? 512 : ARRIVE_ONE_LEVEL; }
-
 ListedTiles listed_tiles(const ob_lamb_ctx* ctx, const LayerSplit& sp) {
   ListedTiles lt;
   lt.tile_list = sp.d_fused_tiles; lt.list_begin = sp.d_list_begin; lt.n_listed = sp.d_n_listed;
   lt.seg_first = sp.d_seg_first; lt.seg_end = sp.d_seg_end; lt.layer_seg0 = ctx->d_layer_seg0;
   lt.n_c = ctx->n_c; lt.tpc = sp.tpc; lt.tpc_span = ctx->tpc;
-  lt.one_level = arrivals_one_level(sp.n_fused_tiles);
+  lt.one_level = sp.one_level;
   return lt;
 }
 
@@ -964,8 +951,6 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
   const int64_t tpc_srv = (ctx->n_c + TILE_SRV - 1) / TILE_SRV;
   if (tpc_srv > 0x7fffffff) return OB_ERR_ARG;
   ctx->tpc_srv = (int)tpc_srv;
-  ctx->u_srv = server_spans(ctx->W, ctx->tpc_srv);
-  ctx->n_srv = (int)((tpc_srv + ctx->u_srv - 1) / ctx->u_srv);
 
   const std::vector<int64_t> h_off = host_offsets(cfg);
   Tiling tm, tl, tw;
@@ -1012,6 +997,8 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
     // gives up without polling, all kernels still run to their end)
     if (cfg->spin_limit == OB_SPIN_NONE) ctx->spin_limit = 0;
     else if (cfg->spin_limit > 0 && cfg->spin_limit < ctx->spin_limit) ctx->spin_limit = cfg->spin_limit;
+    ctx->u_srv = server_spans(ctx->W, ctx->tpc_srv, cus);
+    ctx->n_srv = (ctx->tpc_srv + ctx->u_srv - 1) / ctx->u_srv;
     const bool two_pass = (cfg->flags & OB_CFG_TWO_PASS_COMPRESS) != 0;
     ctx->resident = ok && !two_pass && 5 * (tpc_res + 8) <= 4 * slots;
     // the single-pass server kernel: same rule for the one chunk it covers
@@ -1058,8 +1045,9 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
     const int64_t max_w = (cfg->flags & OB_CFG_TWO_PASS_WARMUP)
                               ? 0 : split_max_tiles(std::min(per_cu_w, OB_WU_MINW), cus, cfg->fused_max_tiles);
     std::vector<unsigned char> lagging, unused;
-    build_split(ctx, &ws, tl, TILE_LB, tm, h_off, max_a, BigRule(), false, &ctx->sp_apply, &lagging);
-    build_split(ctx, &ws, tw, TILE_WU, tm, h_off, max_w, trail_rule(max_w > 0, cfg->fused_max_tiles), true, &ctx->sp_warm, &unused);
+    build_split(ctx, &ws, tl, TILE_LB, tm, h_off, max_a, BigRule(), false, cus, &ctx->sp_apply, &lagging);
+    build_split(ctx, &ws, tw, TILE_WU, tm, h_off, max_w, trail_rule(max_w > 0, cfg->fused_max_tiles, cus), true, cus, &ctx->sp_warm,
+                &unused);
     ctx->sp_apply.in_lds = lh_in_lds(ctx->sp_apply.n_fused_tiles, cus);
     // one launch instead of three or four where the whole list fits on the device at once (unless the
     // configuration lowers what the barrier kernels may take)

@@ -92,7 +92,7 @@ void trail() {
       begin.push_back(n.back() ? at : 0);
       at += n.back();
     }
-    for (int64_t lag : {TRAIL_LAG, (int64_t)pick(1, 6000), (int64_t)0}) check_trail(n, begin, lag, it % 2 ? TRAIL_GROUP : pick(1, 9000));
+    for (int64_t lag : {trail_lag(256), (int64_t)pick(1, 6000), (int64_t)0}) check_trail(n, begin, lag, it % 2 ? TRAIL_GROUP : pick(1, 9000));
   }
 }
 
@@ -121,9 +121,15 @@ void big_rule() {
     }
     CHECK(got == (total >= rule.min_total ? total : 0) && got == (int64_t)pl.big_tiles.size());
   }
-  // without waits from 5120 tiles on, with them from 1792; a lowered limit takes lists of any size
-  CHECK(trail_rule(true, 0).min_total == 1792 && trail_rule(false, 0).min_total == 5120);
-  CHECK(trail_rule(true, 8).min_total == 0 && trail_rule(false, 8).min_total == 0);
+  // by the device's size: without waits from 20 tiles a CU on, with them from 7; a lowered limit takes lists of any size
+  for (int cus : {256, 64}) {
+    CHECK(trail_rule(true, 0, cus).min_total == 7 * cus && trail_rule(false, 0, cus).min_total == 20 * cus);
+    CHECK(trail_rule(true, 8, cus).min_total == 0 && trail_rule(false, 8, cus).min_total == 0);
+    CHECK(rest_in_launch(5 * cus, 20 * cus, 0, cus) && !rest_in_launch(5 * cus + 1, 1, 0, cus) && !rest_in_launch(1, cus, 19 * cus + 1, cus));
+    CHECK(server_spans(2, 16 * cus, cus) == 4 && server_spans(3, 16 * cus, cus) == 2 && server_spans(1, 16 * cus - 1, cus) == 2);
+    CHECK(server_spans(32, 8 * cus, cus) == 2 && server_spans(32, 8 * cus - 1, cus) == 1 && server_spans(33, 99 * cus, cus) == 1);
+    CHECK(arrivals_one_level(40 * cus, cus) == 256 && arrivals_one_level(40 * cus + 1, cus) == 512);
+  }
 }
 
 // Every arrival of a layer has a number of its own below the layer's count, whoever arrives for it (k_ratios_apply_hist's

@@ -1422,9 +1422,9 @@ struct LayerSync {
   float* r_prev;
   float* coeff_c;
   float one_m_thr, one_p_thr, r_min, r_max;
-  int n_lead;                   // leading workgroups of the launch: without rest_tiles one per layer, that
+  int n_lead;                   // leading workgroups of the launch: without REST one per layer, that
                                 // finish the layers without listed tiles (0: a kernel of its own has done that)
-  // k_ratios_apply_hist with the plain ratio pass in its launch (else rest_tiles = NULL): the leading workgroups
+  // k_ratios_apply_hist with the plain ratio pass in its launch (REST): the leading workgroups
   // finish the n_alone layers that have no arrivals and run the pass of the rest_tiles, whose segments arrive too
   const int* rest_tiles;
   const int* alone;
@@ -1820,11 +1820,22 @@ __device__ __forceinline__ void variance_terms_of_pair(const RatioArgs& ra, cons
   }
 }
 
-// The values of a tile, those of step s in lane s - 1 of each group of 8, from where the walk reads them: fetched from
-// the table (vt.t), or formed by these lanes, once for all steps, while the wavefront's loads are in flight.  Forming
-// them makes the launch before unnecessary; over 37000 tiles it costs more (6910 / 6970 us for four steps).  (A kernel of its
-// own for each form spares 40 scalar registers their spills, but the one with the table then spills 27 to 46 vector
-// registers at OB_LB_MINW workgroups per CU: 6830 / 7680 us.)
+// The two values of every step for a tile, from where the walk reads them.  StepTable: the table of the launch before.  StepTerms: formed
+// by the wavefront's lanes, those of step s in lane s - 1 of each group of 8, once for all steps, while its loads are in flight,
+// which makes that launch unnecessary; over 37000 tiles it costs more (6910 / 6970 us for four steps).
+// A kernel each: with both in one, k_ratios_apply_hist spilled 20 to 49 scalar registers and vector ones beside a 16-bit copy (four steps, us,
+// both / one each: 40 tensors of 1 M 922 / 910, 110 M and a bf16 copy 2445 / 2417, 336 M and larger within 0.1 %).
+// (A stride of 64 bits here makes k_ratios_apply_hist spill 13 to 27 vector registers at OB_LB_MINW workgroups per CU.)
+struct StepTable {
+  const float* tt;
+  int n_pairs;
+  __device__ __forceinline__ void find(const VTerms& vt, int c, int l) {
+    tt = vt.t + (int64_t)pair_of(vt, c, l) * 2;
+    n_pairs = vt.n_pairs;
+  }
+  __device__ __forceinline__ float t_same(int s) const { return tt[(int64_t)(s - 1) * n_pairs * 2]; }
+  __device__ __forceinline__ float t_diff(int s) const { return tt[(int64_t)(s - 1) * n_pairs * 2 + 1]; }
+};
 struct StepTerms {
   float same, diff;
   template <bool HAS_K>
@@ -1840,21 +1851,12 @@ struct StepTerms {
       }
     variance_terms<HAS_K>(ra, s_new, s_old, kt, &same, &diff);
   }
-  template <bool HAS_K>
-  __device__ __forceinline__ void get(const VTerms& vt, const RatioArgs& ra, const VfHist& h, int c, int l, float kt) {
-    if (vt.t) {   // uniform
-      const int s = (int)(threadIdx.x & 7) < h.n_old + 1 ? (int)(threadIdx.x & 7) : h.n_old;
-      const float2 t = reinterpret_cast<const float2*>(vt.t)[(int64_t)s * vt.n_pairs + pair_of(vt, c, l)];
-      same = t.x;
-      diff = t.y;
-    } else {
-      form<HAS_K>(ra, h, c, kt);
-    }
-  }
   // of step s, uniform
   __device__ __forceinline__ float t_same(int s) const { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(same), s - 1)); }
   __device__ __forceinline__ float t_diff(int s) const { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(diff), s - 1)); }
 };
+template <bool IN_PLACE>
+using Steps = typename std::conditional<IN_PLACE, StepTerms, StepTable>::type;
 
 // The terms and the plain ratio pass (momentum in 1-bit form, tile list) in one launch: the first n_lead
 // workgroups form the terms, the others run the plain ratio pass of tile_list[blockIdx.x - n_lead].
@@ -1917,7 +1919,7 @@ __global__ __launch_bounds__(BLOCK) void k_variance_dense(RatioArgs ra, VfHist h
 // walk through the steps as k_ratios_apply_hist.  The tile's maximum goes to the segment of its
 // first 1024-element span, 0 to the segments of its other spans (k_ratios_finalize takes the
 // maximum over all of a layer's segments).
-template <bool HAS_K>
+template <bool HAS_K, bool IN_PLACE>
 __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_big_hist(RatioArgs ra, VfHist h, VTerms vt, float* __restrict__ seg_max,
                                                            const int* __restrict__ big_tiles, int64_t n_c,
                                                            int tpc_big, int tpc_span, LayerTab lt,
@@ -1928,6 +1930,8 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_big_hist(RatioArgs
   const TilePos p = tile_pos<TILE>(n_c, tpc_big, big_tiles[blockIdx.x]);
   const int sp0 = p.c * tpc_span + (p.t - p.c * tpc_big) * U;  // the tile's first span
   const int l0 = lt.first_layer[sp0];  // the layer the tile lies in (lt.first_layer: of the 1024-element tiling)
+  Steps<IN_PLACE> st;
+  if constexpr (!IN_PLACE) st.find(vt, p.c, l0);
   const int a = h.n_old + 1;   // steps to apply
   const int o0 = threadIdx.x * 4;
   const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
@@ -1950,8 +1954,7 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_big_hist(RatioArgs
       VZ[u] = ld4(ra.v_frozen + p.tile0 + o);
     }
   }
-  StepTerms st;
-  st.get<HAS_K>(vt, ra, h, p.c, l0, HAS_K ? lt.mom_scale[l0] : 1.0f);
+  if constexpr (IN_PLACE) st.template form<HAS_K>(ra, h, p.c, HAS_K ? lt.mom_scale[l0] : 1.0f);
 #pragma unroll
   for (int s = VF_MAX_OLD + 1; s >= 1; --s)
     if (s <= a) Wq[s] ^= Wq[s - 1];
@@ -2003,26 +2006,30 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_big_hist(RatioArgs
 // 6 spans: 72 to 79 registers instead of 96, so that 6 workgroups fit on a CU instead of 5.  Which form a
 // list takes: lh_in_lds in the host code.
 constexpr int LH_WG_LDS = 6;   // workgroups per CU with S > 0
-template <bool HAS_K, bool LPX, int S>
+template <bool HAS_K, bool LPX, int S, bool REST>
 __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratios_apply_hist(
     RatioArgs ra, VfHist h, VTerms vt, ApplyArgs aa, LayerSync ls, LayerTab lt) {
   constexpr int U = 8;
   constexpr int TILE = SPAN * U;
   __shared__ float lds[BLOCK / WAVE];
-  __shared__ unsigned long long bc, bc_rest[2];
+  __shared__ unsigned long long bc;
   __shared__ v4f zs[S > 0 ? S * BLOCK : 1];
   const int bid = (int)blockIdx.x - ls.n_lead;   // position in tile_list
   if (bid < 0) {
-    const int lead = (int)blockIdx.x - ls.n_alone;   // (uniform branches)
-    if (!ls.rest_tiles) {
-      lead_finalize(ls, lds);
-    } else if (lead < 0) {
-      ratios_finalize_layer<BLOCK>(ls.alone[blockIdx.x], ls.seg_max, ls.lt.layer_seg0, ls.c_avg, ls.r_prev, ls.coeff_c,
-                                   ls.one_m_thr, ls.one_p_thr, ls.r_min, ls.r_max, lds);
+    if constexpr (REST) {
+      __shared__ unsigned long long bc_rest[2];
+      const int lead = (int)blockIdx.x - ls.n_alone;
+      if (lead < 0) {   // (uniform)
+        ratios_finalize_layer<BLOCK>(ls.alone[blockIdx.x], ls.seg_max, ls.lt.layer_seg0, ls.c_avg, ls.r_prev, ls.coeff_c,
+                                     ls.one_m_thr, ls.one_p_thr, ls.r_min, ls.r_max, lds);
+      } else {
+        const int tile = ls.rest_tiles[lead];
+        ratios_pass_tile<1, HAS_K, true, true, true>(ra, ls.seg_max, ls.lt.n_c, ls.lt.tpc_span, lt, ls.tile_seg0, ls.seg_layer,
+                                                     tile, lds);
+        rest_arrive(ls, tile, lds, bc_rest);
+      }
     } else {
-      const int tile = ls.rest_tiles[lead];
-      ratios_pass_tile<1, HAS_K, true, true, true>(ra, ls.seg_max, ls.lt.n_c, ls.lt.tpc_span, lt, ls.tile_seg0, ls.seg_layer, tile, lds);
-      rest_arrive(ls, tile, lds, bc_rest);
+      lead_finalize(ls, lds);
     }
     return;
   }
@@ -2034,7 +2041,9 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
   const float ss = ra.sscales[p.c];
   const LayerParts lp = layer_parts(ls.lt, l0);
   const float rp = ls.r_prev[l0], ca = ls.c_avg[l0];
-  const int first = ls.rest_tiles ? ls.arr0[l0] : lp.lb;
+  const int first = REST ? ls.arr0[l0] : lp.lb;
+  Steps<REST> st;
+  if constexpr (!REST) st.find(vt, p.c, l0);
   const int a = h.n_old + 1;   // steps to apply
   const int o0 = threadIdx.x * 4;
   const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
@@ -2060,8 +2069,7 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
       else VZ[u] = ld4(ra.v_frozen + p.tile0 + o);
     }
   }
-  StepTerms st;
-  st.get<HAS_K>(vt, ra, h, p.c, l0, kt);
+  if constexpr (REST) st.template form<HAS_K>(ra, h, p.c, kt);
   // flips between consecutive planes, formed on the words as loaded; plane 0 stays (line 21 needs it)
 #pragma unroll
   for (int s = VF_MAX_OLD + 1; s >= 1; --s)
@@ -2104,7 +2112,7 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
   }
   r = block_max(r, lds);
   // before any store: nothing to wait for
-  layer_arrive(ls, bid, l0, lp, first, ls.rest_tiles ? layer_arrivals(lp.nl, lp.a, lp.s_first, lp.s_end, lp.b) : lp.nl, rp, ca, r,
+  layer_arrive(ls, bid, l0, lp, first, REST ? layer_arrivals(lp.nl, lp.a, lp.s_first, lp.s_end, lp.b) : lp.nl, rp, ca, r,
                lds, &bc);
   if (h.write_v) {   // uniform
 #pragma unroll

@@ -1034,10 +1034,10 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
          hip_ok(ctx, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device),
                 "hipDeviceGetAttribute");
     int per_cu_h = 0;   // the same tiles go through the kernel with the variance in deferred form
-    ok = ok && hip_ok(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_h, k_ratios_apply_hist<true, false, 0>, BLOCK, 0),
+    ok = ok && hip_ok(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_h, k_ratios_apply_hist<true, false, 0, true>, BLOCK, 0),
                       "hipOccupancyMaxActiveBlocksPerMultiprocessor");
     per_cu_a = std::min(per_cu_a, per_cu_h);
-    ok = ok && hip_ok(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_h, k_ratios_apply_hist<true, false, S_LH>, BLOCK, 0),
+    ok = ok && hip_ok(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu_h, k_ratios_apply_hist<true, false, S_LH, true>, BLOCK, 0),
                       "hipOccupancyMaxActiveBlocksPerMultiprocessor");
     per_cu_a = std::min(per_cu_a, per_cu_h);
     const int64_t max_a = (cfg->flags & OB_CFG_NO_FUSED_APPLY)
@@ -1614,7 +1614,7 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
   // the history (leading workgroups) and the plain ratio pass outside the tiles that work from the history
   const bool hk = st->mom_scale != nullptr;
   const bool rest_in_launch = sp.on && sp.rest_in_launch;
-  const VTerms vt = vterms(ctx);   // (vt.t = NULL: each wavefront forms its own)
+  const VTerms vt = vterms(ctx);
   if (!rest_in_launch) {
     const int n_lead_vt = (ctx->n_pairs + BLOCK - 1) / BLOCK;
     dispatch1(hk, [&](auto k_) {
@@ -1625,8 +1625,8 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
   }
   // launch 2: ratio pass of the layers that are too large for the barrier kernel, from the history
   if (sp.big_on)
-    dispatch1(hk, [&](auto k_) {
-      OB_LAUNCH(la, KID_RATIOS_BIG_HIST, (k_ratios_big_hist<decltype(k_)::value>), sp.n_big_tiles, ra, vh, vt, ctx->d_seg_max,
+    dispatch2(hk, rest_in_launch, [&](auto k_, auto in_place) {
+      OB_LAUNCH(la, KID_RATIOS_BIG_HIST, (k_ratios_big_hist<decltype(k_)::value, decltype(in_place)::value>), sp.n_big_tiles, ra, vh, vt, ctx->d_seg_max,
                 sp.d_big_tiles, ctx->n_c, sp.tpc, ctx->tpc, lt, ctx->d_tile_seg0);
     });
   if (!sp.on) {
@@ -1653,9 +1653,10 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
     ls.counter = sp.d_counter_rest; ls.sub = sp.d_sub_rest; ls.flag = sp.d_flag_rest;
   }
   dispatch2(hk, xl.p != nullptr, [&](auto k_, auto lx) {
-    dispatch1(sp.in_lds, [&](auto in_lds) {
+    dispatch2(sp.in_lds, rest_in_launch, [&](auto in_lds, auto rest) {
       OB_LAUNCH(la, sp.in_lds ? KID_RATIOS_APPLY_HIST_LDS : KID_RATIOS_APPLY_HIST,
-                (k_ratios_apply_hist<decltype(k_)::value, decltype(lx)::value, decltype(in_lds)::value ? S_LH : 0>),
+                (k_ratios_apply_hist<decltype(k_)::value, decltype(lx)::value, decltype(in_lds)::value ? S_LH : 0,
+                                     decltype(rest)::value>),
                 sp.n_fused_tiles + ls.n_lead, ra, vh, vt, aa, ls, lt);
     });
   });

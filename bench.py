@@ -554,7 +554,8 @@ def main():
     ms_ms = e0.elapsed_time(e1) / 5
     out["reference_calls"] = {
         "warmup_step_ms": round(wu_ms, 4),
-        # 28 B/elem where g, m, v, x are read once, 24 + 16 in two passes (whose second may find its reads in a cache)
+        # 28 B/elem where g, m, v, x are read once, 24 + 16 in two passes: bytes asked for, not a rate of HBM, as the second pass of
+        # large layers finds its reads in the memory-side cache
         "warmup_step_GBps": round(((28.0 - g_less + x_more) * wfused + (40.0 - g_less + x_more) * (ds.n_pad - wfused))
                                   / (wu_ms * 1e-3) / 1e9, 1),
         "warmup_single_pass_params": wfused,

@@ -432,19 +432,12 @@ inline int64_t small_cost(int U, const SmallShape& sh, bool by_slots, int cus) {
     c += 13 * (sh.max_arrivals <= SMALL_ONE_LEVEL ? sh.max_arrivals : ARRIVE_SUB + sh.max_arrivals / ARRIVE_SUB + 46 /* another trip */);
   return c;
 }
-// The index in U = 1, 2, 4 of the lowest cost among those that fit, the smallest of equals; -1 if none does.  fits(i): the tiles
-// of sh[i] fit on the device.  It asks the runtime for a kernel's occupancy, so it is asked of the cheapest
-// first and of no other once one fits (all of them: 0.1 to 0.16 ms more of the 0.7 to 0.8 that setting up a small list takes).
-template <class F>
-int small_choice(const SmallShape (&sh)[3], bool by_slots, int cus, F fits) {
-  bool left[3] = {sh[0].n_tiles > 0, sh[1].n_tiles > 0, sh[2].n_tiles > 0};
-  for (;;) {
-    int best = -1;
-    for (int i = 0; i < 3; ++i)
-      if (left[i] && (best < 0 || small_cost(1 << i, sh[i], by_slots, cus) < small_cost(1 << best, sh[best], by_slots, cus))) best = i;
-    if (best < 0 || fits(best)) return best;
-    left[best] = false;
-  }
+// The index in U = 1, 2, 4 (fits[i]: the tiles of sh[i] fit on the device; the smallest of equals), -1 if none fits.
+inline int small_choice(const SmallShape (&sh)[3], const bool (&fits)[3], bool by_slots, int cus) {
+  int best = -1;
+  for (int i = 0; i < 3; ++i)
+    if (fits[i] && (best < 0 || small_cost(1 << i, sh[i], by_slots, cus) < small_cost(1 << best, sh[best], by_slots, cus))) best = i;
+  return best;
 }
 // A list all of whose parameters lie in 8192-element tiles of layers that the barrier kernels take keeps those where one layer
 // has more than this many 1024-element spans.  Steps of one tensor, or two, us, in one launch / in the barrier kernel, with the

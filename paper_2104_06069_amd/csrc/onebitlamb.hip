@@ -572,19 +572,22 @@ bool build_small(ob_lamb_ctx* ctx, Workspace* ws, SmallTilings* tilings, const s
                  const std::vector<unsigned char>& lagging, const LayerSplit& split, int vals, int tables, bool by_slots, int cus,
                  F slots, SmallPlan* sp) {
   static_assert(TILE_MAIN == SPAN, "the TILE_MAIN tiling is that of U = 1");
-  bool ok = true;
-  int choice = small_choice(tilings->sh, by_slots, cus, [&](int i) {
+  bool fits[3] = {false, false, false};
+  size_t lds_bytes[3] = {0, 0, 0};
+  for (int i = 0; i < 3; ++i) {
     const SmallShape& s = tilings->sh[i];
-    sp->lds_bytes = 4 * ((size_t)vals * (SPAN << i) + (size_t)tables * (size_t)s.max_seg);
+    if (s.n_tiles == 0) continue;
+    lds_bytes[i] = 4 * ((size_t)vals * (SPAN << i) + (size_t)tables * (size_t)s.max_seg);
     int64_t n_slots = 0;
-    ok = ok && slots(1 << i, sp->lds_bytes, &n_slots);
-    return ok && 5 * (s.n_tiles + 8) <= 4 * n_slots;
-  });
-  if (!ok) return false;
+    if (!slots(1 << i, lds_bytes[i], &n_slots)) return false;
+    fits[i] = 5 * (s.n_tiles + 8) <= 4 * n_slots;
+  }
+  int choice = small_choice(tilings->sh, fits, by_slots, cus);
   if (choice >= 0 && split.on && split.n_rest_tiles == 0 && ((int64_t)tilings->sh[choice].max_arrivals << choice) > SMALL_MAX_SPANS)
     choice = -1;
   const int best = choice < 0 ? 0 : 1 << choice;
   const SmallShape sh = choice < 0 ? SmallShape() : tilings->sh[choice];
+  if (best) sp->lds_bytes = lds_bytes[choice];
   const Tiling* tp = best ? tilings->get(best, ctx->n_c, ctx->W, ctx->L, h_off) : nullptr;
   if (tp) {
     const Tiling& t = *tp;

@@ -222,17 +222,9 @@ void small_lists() {
       fits[i] = 5 * (sh[i].n_tiles + 8) <= 4 * 256 * (i == 0 ? 8 : i == 1 ? 5 : 4);
     }
     for (bool by_slots : {true, false}) {
-      int asked = 0;
-      const int c = small_choice(sh, by_slots, 256, [&](int i) { ++asked; return fits[i]; });
-      const int got = c < 0 ? 0 : 1 << c, want = by_slots ? w.u_apply : w.u_lamb;
+      const int c = small_choice(sh, fits, by_slots, 256), got = c < 0 ? 0 : 1 << c, want = by_slots ? w.u_apply : w.u_lamb;
       if (got != want) printf("%d tensors of %ld, slots %d: U = %d\n", (int)L, (long)w.sizes[0], by_slots, got);
       CHECK(got == want);
-      int worse = 0;   // than the choice: not asked for
-      for (int i = 0; c >= 0 && i < 3; ++i) {
-        const int64_t more = small_cost(1 << i, sh[i], by_slots, 256) - small_cost(1 << c, sh[c], by_slots, 256);
-        worse += i != c && (more > 0 || (more == 0 && i > c));
-      }
-      CHECK(asked == 3 - worse);
     }
   }
 }

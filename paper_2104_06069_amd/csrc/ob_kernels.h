@@ -1826,7 +1826,7 @@ __device__ __forceinline__ void variance_terms_of_pair(const RatioArgs& ra, cons
 // The two values of every step for a tile, from where the walk reads them.  StepTable: the table of the launch before.  StepTerms: formed
 // by the wavefront's lanes, those of step s in lane s - 1 of each group of 8, once for all steps, while its loads are in flight,
 // which makes that launch unnecessary; over 37000 tiles it costs more (6910 / 6970 us for four steps).
-// A kernel each: with both in one, k_ratios_apply_hist spilled 20 to 49 scalar registers and vector ones beside a 16-bit copy (four steps, us,
+// k_ratios_apply_hist is a kernel each: with both in one it spilled 20 to 49 scalar registers and vector ones beside a 16-bit copy (four steps, us,
 // both / one each: 40 tensors of 1 M 922 / 910, 110 M and a bf16 copy 2445 / 2417, 336 M and larger within 0.1 %).
 // (A stride of 64 bits here makes k_ratios_apply_hist spill 13 to 27 vector registers at OB_LB_MINW workgroups per CU.)
 struct StepTable {
@@ -1854,12 +1854,24 @@ struct StepTerms {
       }
     variance_terms<HAS_K>(ra, s_new, s_old, kt, &same, &diff);
   }
+  // From the table, or formed where the launch before has not (vt.t = NULL): k_ratios_big_hist, which keeps its registers with both.
+  // StepTable's loads from within the
+  // walk cost it 0.4 us of 10 (316 tiles; in long lists up to 1 %); with only the table's half of this it spills 24 registers (4 to 9 % of a step).
+  template <bool HAS_K>
+  __device__ __forceinline__ void get(const VTerms& vt, const RatioArgs& ra, const VfHist& h, int c, int l, float kt) {
+    if (vt.t) {   // uniform
+      const int s = (int)(threadIdx.x & 7) < h.n_old + 1 ? (int)(threadIdx.x & 7) : h.n_old;
+      const float2 t = reinterpret_cast<const float2*>(vt.t)[(int64_t)s * vt.n_pairs + pair_of(vt, c, l)];
+      same = t.x;
+      diff = t.y;
+    } else {
+      form<HAS_K>(ra, h, c, kt);
+    }
+  }
   // of step s, uniform
   __device__ __forceinline__ float t_same(int s) const { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(same), s - 1)); }
   __device__ __forceinline__ float t_diff(int s) const { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(diff), s - 1)); }
 };
-template <bool IN_PLACE>
-using Steps = typename std::conditional<IN_PLACE, StepTerms, StepTable>::type;
 
 // The terms and the plain ratio pass (momentum in 1-bit form, tile list) in one launch: the first n_lead
 // workgroups form the terms, the others run the plain ratio pass of tile_list[blockIdx.x - n_lead].
@@ -1922,7 +1934,7 @@ __global__ __launch_bounds__(BLOCK) void k_variance_dense(RatioArgs ra, VfHist h
 // walk through the steps as k_ratios_apply_hist.  The tile's maximum goes to the segment of its
 // first 1024-element span, 0 to the segments of its other spans (k_ratios_finalize takes the
 // maximum over all of a layer's segments).
-template <bool HAS_K, bool IN_PLACE>
+template <bool HAS_K>
 __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_big_hist(RatioArgs ra, VfHist h, VTerms vt, float* __restrict__ seg_max,
                                                            const int* __restrict__ big_tiles, int64_t n_c,
                                                            int tpc_big, int tpc_span, LayerTab lt,
@@ -1933,8 +1945,6 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_big_hist(RatioArgs
   const TilePos p = tile_pos<TILE>(n_c, tpc_big, big_tiles[blockIdx.x]);
   const int sp0 = p.c * tpc_span + (p.t - p.c * tpc_big) * U;  // the tile's first span
   const int l0 = lt.first_layer[sp0];  // the layer the tile lies in (lt.first_layer: of the 1024-element tiling)
-  Steps<IN_PLACE> st;
-  if constexpr (!IN_PLACE) st.find(vt, p.c, l0);
   const int a = h.n_old + 1;   // steps to apply
   const int o0 = threadIdx.x * 4;
   const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
@@ -1957,7 +1967,8 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_big_hist(RatioArgs
       VZ[u] = ld4(ra.v_frozen + p.tile0 + o);
     }
   }
-  if constexpr (IN_PLACE) st.template form<HAS_K>(ra, h, p.c, HAS_K ? lt.mom_scale[l0] : 1.0f);
+  StepTerms st;
+  st.get<HAS_K>(vt, ra, h, p.c, l0, HAS_K ? lt.mom_scale[l0] : 1.0f);
 #pragma unroll
   for (int s = VF_MAX_OLD + 1; s >= 1; --s)
     if (s <= a) Wq[s] ^= Wq[s - 1];
@@ -2045,7 +2056,7 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
   const LayerParts lp = layer_parts(ls.lt, l0);
   const float rp = ls.r_prev[l0], ca = ls.c_avg[l0];
   const int first = REST ? ls.arr0[l0] : lp.lb;
-  Steps<REST> st;
+  typename std::conditional<REST, StepTerms, StepTable>::type st;
   if constexpr (!REST) st.find(vt, p.c, l0);
   const int a = h.n_old + 1;   // steps to apply
   const int o0 = threadIdx.x * 4;

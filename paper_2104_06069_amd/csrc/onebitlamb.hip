@@ -1614,7 +1614,7 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
   // the history (leading workgroups) and the plain ratio pass outside the tiles that work from the history
   const bool hk = st->mom_scale != nullptr;
   const bool rest_in_launch = sp.on && sp.rest_in_launch;
-  const VTerms vt = vterms(ctx);
+  const VTerms vt = vterms(ctx);   // (vt.t = NULL where the ratio pass runs in the barrier kernel's launch)
   if (!rest_in_launch) {
     const int n_lead_vt = (ctx->n_pairs + BLOCK - 1) / BLOCK;
     dispatch1(hk, [&](auto k_) {
@@ -1625,8 +1625,8 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
   }
   // launch 2: ratio pass of the layers that are too large for the barrier kernel, from the history
   if (sp.big_on)
-    dispatch2(hk, rest_in_launch, [&](auto k_, auto in_place) {
-      OB_LAUNCH(la, KID_RATIOS_BIG_HIST, (k_ratios_big_hist<decltype(k_)::value, decltype(in_place)::value>), sp.n_big_tiles, ra, vh, vt, ctx->d_seg_max,
+    dispatch1(hk, [&](auto k_) {
+      OB_LAUNCH(la, KID_RATIOS_BIG_HIST, (k_ratios_big_hist<decltype(k_)::value>), sp.n_big_tiles, ra, vh, vt, ctx->d_seg_max,
                 sp.d_big_tiles, ctx->n_c, sp.tpc, ctx->tpc, lt, ctx->d_tile_seg0);
     });
   if (!sp.on) {

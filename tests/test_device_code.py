@@ -20,6 +20,11 @@ HIST = """
 HIST(false, false, 0) HIST(false, true, 0) HIST(true, false, 0) HIST(true, true, 0)
 HIST(false, false, 6) HIST(false, true, 6) HIST(true, false, 6) HIST(true, true, 6)
 """
+BIG = """
+#define BIG(K) template __global__ void obk::k_ratios_big_hist<K>(RatioArgs, VfHist, VTerms, float*, const int*, int64_t, int, int, \\
+                                                                  LayerTab, const int*);
+BIG(false) BIG(true)
+"""
 
 
 def assembly(tmp_path, kernels):
@@ -43,9 +48,11 @@ def test_second_reads_are_kept_only_where_asked_for(tmp_path):
     assert hints == [3, 2], hints
 
 
-def test_kernel_of_the_large_lists_keeps_its_registers(tmp_path):
-    """k_ratios_apply_hist without the rest tiles in its launch has no spills at the occupancy that it is built for."""
-    text = assembly(tmp_path, HIST)
-    counts = re.findall(r"\.name:\s+_ZN3obk19k_ratios_apply_hist.*?\.sgpr_spill_count:\s+(\d+).*?\.vgpr_spill_count:\s+(\d+)",
+@pytest.mark.parametrize("name,kernels,n", [("k_ratios_apply_hist", HIST, 8), ("k_ratios_big_hist", BIG, 2)])
+def test_kernels_of_the_large_lists_keep_their_registers(tmp_path, name, kernels, n):
+    """k_ratios_apply_hist without the rest tiles in its launch and k_ratios_big_hist have no spills at the occupancy that they are
+    built for."""
+    text = assembly(tmp_path, kernels)
+    counts = re.findall(r"\.name:\s+_ZN3obk%d%s.*?\.sgpr_spill_count:\s+(\d+).*?\.vgpr_spill_count:\s+(\d+)" % (len(name), name),
                         text, re.S)
-    assert len(counts) == 8 and all(c == ("0", "0") for c in counts), counts
+    assert len(counts) == n and all(c == ("0", "0") for c in counts), counts

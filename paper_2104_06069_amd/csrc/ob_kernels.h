@@ -129,12 +129,43 @@ __device__ __forceinline__ void st4_lp(void* __restrict__ base, int64_t i, v4f v
   __builtin_nontemporal_store(h, reinterpret_cast<v4h*>(reinterpret_cast<unsigned short*>(base) + i));
 }
 
+// Reductions over a wavefront, valid in lane 0: the lanes' halves, rows of 16 and parts of a row meet by register moves
+// (whole wavefronts only).  Through LDS (ds_bpermute) each of the six steps is a round trip of some 130 clocks, twice that for a
+// double, at the end of every tile's chain.  A step, us, LDS / moves: four 512x512 tensors 23.4 / 22.3, 336 M parameters with bf16 gradient
+// and copy 1775 / 1737, fp32 1707 / 1696; a LAMB step of 3 M 27.0 / 26.5.
+template <int STEP>   // lane i's value of lane i + 32 >> STEP, for the lanes that lane 0's result is made of
+__device__ __forceinline__ unsigned int lane_down(unsigned int v) {
+  if constexpr (STEP == 0) return __builtin_amdgcn_permlane32_swap(v, v, false, false)[1];
+  else if constexpr (STEP == 1) return __builtin_amdgcn_permlane16_swap(v, v, false, false)[1];
+  else return __builtin_amdgcn_update_dpp(0u, v, 0x100 + (32 >> STEP) /* row_shl */, 0xf, 0xf, true);
+}
+template <int STEP>
+__device__ __forceinline__ float lane_down(float v) { return __uint_as_float(lane_down<STEP>(__float_as_uint(v))); }
+template <int STEP>
+__device__ __forceinline__ double lane_down(double v) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
+  const unsigned long long r = (unsigned long long)lane_down<STEP>((unsigned int)b) |
+                               (unsigned long long)lane_down<STEP>((unsigned int)(b >> 32)) << 32;
+  return __builtin_bit_cast(double, r);
+}
+template <class T, class F>
+__device__ __forceinline__ T wave_reduce(T v, F f) {
+  v = f(v, lane_down<0>(v));
+  v = f(v, lane_down<1>(v));
+  v = f(v, lane_down<2>(v));
+  v = f(v, lane_down<3>(v));
+  v = f(v, lane_down<4>(v));
+  return f(v, lane_down<5>(v));
+}
+__device__ __forceinline__ double wave_sum(double v) { return wave_reduce(v, [](double a, double b) { return a + b; }); }
+// of non-NaN values
+__device__ __forceinline__ float wave_max(float v) { return wave_reduce(v, [](float a, float b) { return (b > a) ? b : a; }); }
+
 // Sum of one double per thread over a workgroup of NT threads, in a fixed order; result valid in
 // thread 0.  lds: [NT / WAVE] doubles.
 template <int NT = BLOCK>
 __device__ __forceinline__ double block_sum(double v, double* lds) {
-#pragma unroll
-  for (int o = WAVE / 2; o > 0; o >>= 1) v += __shfl_down(v, o, WAVE);
+  v = wave_sum(v);
   const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
   __syncthreads();  // protects lds against the previous use
   if (lane == 0) lds[wv] = v;
@@ -151,11 +182,7 @@ __device__ __forceinline__ double block_sum(double v, double* lds) {
 // thread 0.  lds: [NT / WAVE] floats.
 template <int NT = BLOCK>
 __device__ __forceinline__ float block_max(float v, float* lds) {
-#pragma unroll
-  for (int o = WAVE / 2; o > 0; o >>= 1) {
-    const float w = __shfl_down(v, o, WAVE);
-    v = (w > v) ? w : v;
-  }
+  v = wave_max(v);
   const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
   __syncthreads();
   if (lane == 0) lds[wv] = v;
@@ -178,9 +205,9 @@ __device__ __forceinline__ int walk_layer(int l, int64_t i, const int64_t* __res
 // the group).  Element 4*lane + k of the 256-element span is bit 4*(lane%8) + k of word lane/8.
 __device__ __forceinline__ unsigned int gather_word(unsigned int nibble) {
   unsigned int v = nibble << (4 * (threadIdx.x & 7));
-  v |= __shfl_xor(v, 1, WAVE);
-  v |= __shfl_xor(v, 2, WAVE);
-  v |= __shfl_xor(v, 4, WAVE);
+  v |= __builtin_amdgcn_update_dpp(0u, v, 0xb1 /* quad_perm 1 0 3 2 */, 0xf, 0xf, true);
+  v |= __builtin_amdgcn_update_dpp(0u, v, 0x4e /* quad_perm 2 3 0 1 */, 0xf, 0xf, true);
+  v |= __builtin_amdgcn_update_dpp(0u, v, 0x141 /* row_half_mirror */, 0xf, 0xf, true);
   return v;
 }
 
@@ -376,12 +403,7 @@ __device__ __forceinline__ bool ticket_arrive(unsigned int* counter, unsigned in
     last = (__hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, OB_AGENT) + 1u == n);
     if (last) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, OB_AGENT);
   }
-  return __shfl(last, 0, WAVE) != 0;
-}
-__device__ __forceinline__ double wave_sum(double v) {   // valid in lane 0
-#pragma unroll
-  for (int o = WAVE / 2; o > 0; o >>= 1) v += __shfl_down(v, o, WAVE);
-  return v;
+  return __builtin_amdgcn_readfirstlane(last) != 0;
 }
 // s: the tile's partial (lane 0); first wavefront only
 __device__ __forceinline__ void chunk_ticket(const ChunkTicket& tk, double* partials, const TilePos& p, int tpc,
@@ -2440,11 +2462,7 @@ __global__ __launch_bounds__(BLOCK, small_min_wg(U)) void k_ratios_apply_small(
       float r = 0.0f;
       for (int o = (s ? sg.end[s - 1] : 0) + lane; o < sg.end[s]; o += WAVE)
         if (vals[o] > r) r = vals[o];
-#pragma unroll
-      for (int o = WAVE / 2; o > 0; o >>= 1) {
-        const float w = __shfl_down(r, o, WAVE);
-        r = (w > r) ? w : r;
-      }
+      r = wave_max(r);
       if (lane == 0) sg.coeff[s] = r;
     }
     __syncthreads();
@@ -3060,7 +3078,7 @@ __device__ __forceinline__ bool trail_arrive(unsigned int* counter, unsigned int
     last = (__hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, OB_AGENT) + 1u == n);
     if (last) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, OB_AGENT);
   }
-  return __shfl(last, 0, WAVE) != 0;
+  return __builtin_amdgcn_readfirstlane(last) != 0;
 }
 // l, lp, c0, ca: the layer, its ranges, first counter and c_avg (read early, where their latency hides).
 __device__ __forceinline__ void trail_finish(const TrailTab& tt, const WarmClip& wc, int part, int l, const LayerParts& lp,
@@ -3310,11 +3328,8 @@ __global__ __launch_bounds__(BLOCK, small_min_wg(U)) void k_warmup_small(
         tx += (double)val_x[o] * (double)val_x[o];
         tu += (double)val_u[o] * (double)val_u[o];
       }
-#pragma unroll
-      for (int o = WAVE / 2; o > 0; o >>= 1) {
-        tx += __shfl_down(tx, o, WAVE);
-        tu += __shfl_down(tu, o, WAVE);
-      }
+      tx = wave_sum(tx);
+      tu = wave_sum(tu);
       if (lane == 0) {
         if (s == 0 || s == last_seg) {
           const int e = (s == 0) ? 0 : 1;

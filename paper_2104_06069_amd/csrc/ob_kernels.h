@@ -1641,123 +1641,6 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_apply_resident(
   }
 }
 
-// The same step for tiles of U spans with U too large to hold v_fresh, v_frozen and x of the whole
-// tile at once: the ratio pass streams the tile G spans at a time (v_fresh is written back as it
-// goes, the last group after the arrival) and keeps only v_frozen -- turned into
-// m_t/(sqrt(v_frozen)+eta) while the layer completes -- and one sign nibble per span; x is fetched
-// only after the layer's coefficient is known, G spans at a time.  Per element 4 bytes live across
-// the barrier instead of 8, so a layer of twice the size fits on the device.
-template <int U, int G, bool HAS_K, bool LPX = false>
-__global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_apply_stream(
-    RatioArgs ra, ApplyArgs aa, LayerSync ls, LayerTab lt) {
-  static_assert(U % G == 0 && U % 8 == 0, "tile shape");
-  constexpr int TILE = SPAN * U;
-  __shared__ float lds[BLOCK / WAVE];
-  __shared__ unsigned long long bc;
-  const int64_t n_c = ls.lt.n_c;
-  const int tpc = ls.lt.tpc;
-  const TilePos p = tile_pos<TILE>(n_c, tpc, ls.lt.tile_list[blockIdx.x]);
-  const int sp0 = p.c * ls.lt.tpc_span + (p.t - p.c * tpc) * U;  // the tile's first span
-  const int l0 = lt.first_layer[sp0];  // the layer the tile lies in
-  const float ss = ra.sscales[p.c];
-  const float s_prev = ra.pm.scales[p.c];
-  const float kt = HAS_K ? lt.mom_scale[l0] : 1.0f;
-  const LayerParts lp = layer_parts(ls.lt, l0);
-  const float rp = ls.r_prev[l0], ca = ls.c_avg[l0];
-  const int o0 = threadIdx.x * 4;
-  // the two magnitudes the reconstructed gradient can take (see RatioTile::uniform_pass)
-  const float sp = HAS_K ? ss / kt : ss;
-  const float bm = ra.beta1 * (HAS_K ? s_prev / kt : s_prev);
-  const float g_same = (sp - bm) / ra.omb1;
-  const float g_diff = (sp - (-bm)) / ra.omb1;
-  const float t_same = ra.omb2 * (g_same * g_same);
-  const float t_diff = ra.omb2 * (g_diff * g_diff);
-  v4f VZ[U];
-  unsigned int NBP[U / 8];   // the new momentum's sign nibbles, 8 spans to a register
-  v4f VFl[G];                // fresh variance of the last group: stored after the arrival
-#pragma unroll
-  for (int i = 0; i < U / 8; ++i) NBP[i] = 0u;
-  float r = 0.0f;
-#pragma unroll
-  for (int u0 = 0; u0 < U; u0 += G) {
-    unsigned int NB[G], OBt[G];
-    v4f VF[G];
-#pragma unroll
-    for (int j = 0; j < G; ++j) {
-      const int u = u0 + j, o = u * SPAN + o0;
-      NB[j] = 0u; OBt[j] = 0u; VF[j] = 0.0f; VZ[u] = 0.0f;
-      if (o < p.len) {
-        NB[j] = load_nibble(ra.packed, p.tile0 + u * SPAN);
-        OBt[j] = load_nibble(ra.pm.bits, p.tile0 + u * SPAN);
-        VF[j] = ld4(ra.v_fresh + p.tile0 + o);
-        VZ[u] = ld4(ra.v_frozen + p.tile0 + o);
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < G; ++j) {
-      const int u = u0 + j, o = u * SPAN + o0;
-      if (o < p.len) {
-        v4f vf;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const float t = (((NB[j] ^ OBt[j]) >> k) & 1u) ? t_diff : t_same;
-          vf[k] = ra.beta2 * VF[j][k] + t;
-          const float q = VZ[u][k] / vf[k];
-          if (q > r) r = q;
-        }
-        if (u0 + G < U) st4(ra.v_fresh + p.tile0 + o, vf);
-        else VFl[j] = vf;
-        NBP[u / 8] |= (NB[j] & 15u) << (4 * (u % 8));
-      }
-    }
-  }
-  r = block_max(r, lds);
-  layer_arrive(ls, (int)blockIdx.x, l0, lp, lp.lb, lp.nl, rp, ca, r, lds, &bc);
-#pragma unroll
-  for (int j = 0; j < G; ++j) {
-    const int o = (U - G + j) * SPAN + o0;
-    if (o < p.len) st4(ra.v_fresh + p.tile0 + o, VFl[j]);
-  }
-  // m_t/(sqrt(v_frozen)+eta) in place of v_frozen while the layer completes (the same operations on
-  // the same operands as apply_uniform's)
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int o = u * SPAN + o0;
-    if (o < p.len) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float mt = ((NBP[u / 8] >> (4 * (u % 8) + k)) & 1u) ? sp : -sp;
-        float uu = mt / (sqrtf(VZ[u][k]) + aa.eta);
-        asm volatile("" : "+v"(uu));   // evaluated here, not sunk below the wait
-        VZ[u][k] = uu;
-      }
-    }
-  }
-  const float c = layer_wait(ls, l0, &bc);
-  const float a = aa.lr * c;
-#pragma unroll
-  for (int u0 = 0; u0 < U; u0 += G) {
-    v4f X[G];
-#pragma unroll
-    for (int j = 0; j < G; ++j) {
-      const int o = (u0 + j) * SPAN + o0;
-      X[j] = 0.0f;
-      if (o < p.len) X[j] = ld4(aa.x + p.tile0 + o);
-    }
-#pragma unroll
-    for (int j = 0; j < G; ++j) {
-      const int o = (u0 + j) * SPAN + o0;
-      if (o < p.len) {
-        v4f xn;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) xn[k] = X[j][k] - a * VZ[u0 + j][k];
-        st4(aa.x + p.tile0 + o, xn);
-        if (LPX) st4_lp(aa.x_lp, p.tile0 + o, xn, aa.x_lp_bf16);
-      }
-    }
-  }
-}
-
 // ---------------------------------------------------------------------------------------------
 // The fresh variance in deferred form (Algorithm 1 line 16 evaluated every step, stored every few).
 //

@@ -62,14 +62,6 @@ constexpr int S_LH = 6;        // spans in LDS in the LDS form of k_ratios_apply
 #ifndef OB_U_WU
 #define OB_U_WU 8
 #endif
-// 1: the ratio+update kernel streams its tile and fetches x after the layer's coefficient is known
-// (k_ratios_apply_stream; half the registers per element across the barrier), OB_G_LB spans at a time
-#ifndef OB_LB_STREAM
-#define OB_LB_STREAM 0
-#endif
-#ifndef OB_G_LB
-#define OB_G_LB 2
-#endif
 // safety margin, in tiles, under 80 % of the device's workgroup slots for the largest layer a
 // barrier kernel takes
 #ifndef OB_SPLIT_MARGIN
@@ -1022,11 +1014,7 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
   if (ok) {
     int per_cu_a = 0, per_cu_w = 0, cus = 0;
     ok = hip_ok(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(
-#if OB_LB_STREAM
-                         &per_cu_a, k_ratios_apply_stream<U_LB, OB_G_LB, true>, BLOCK, 0),
-#else
                          &per_cu_a, k_ratios_apply_resident<U_LB, true>, BLOCK, 0),
-#endif
                 "hipOccupancyMaxActiveBlocksPerMultiprocessor") &&
          hip_ok(ctx, hipOccupancyMaxActiveBlocksPerMultiprocessor(
                          &per_cu_w, k_warmup_resident<U_WU, G_WU, 0, false>, BLOCK, 0),
@@ -1502,13 +1490,9 @@ ob_status ob_lamb_ratios_apply_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st, con
   // 1. ratio pass over everything outside the listed tiles; its segment maxima wait in seg_max: of
   //    the layers with listed tiles for the layer barrier, of the others (the ratio of an empty layer,
   //    0, still goes through the clips) for the leading workgroups of the same launch
-#if OB_LB_STREAM
-  const int n_lead = 0;
-#else
   const int n_lead = (sp.n_layers < ctx->L) ? (int)ctx->L : 0;   // (finished by the barrier kernel's leading workgroups)
-#endif
   launch_ratios(la, ctx, st, packed_all, server_scales, packed_m, pm, sp.d_rest_tiles, sp.n_rest_tiles,
-                sp.d_has_listed, n_lead == 0 && sp.n_layers < ctx->L);
+                sp.d_has_listed, false);
   // 2. the listed tiles: ratio pass, layer barrier, update
   LayerSync ls{};
   ls.seg_max = ctx->d_seg_max; ls.listed_max = sp.d_listed_max; ls.lt = listed_tiles(ctx, sp);
@@ -1518,15 +1502,9 @@ ob_status ob_lamb_ratios_apply_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st, con
   ls.one_m_thr = ctx->one_m_thr; ls.one_p_thr = ctx->one_p_thr; ls.r_min = ctx->r_min; ls.r_max = ctx->r_max;
   ls.n_lead = n_lead;
   dispatch2(hk, xl.p != nullptr, [&](auto k_, auto lx) {
-#if OB_LB_STREAM
-    OB_LAUNCH(la, KID_RATIOS_APPLY_RESIDENT,
-              (k_ratios_apply_stream<U_LB, OB_G_LB, decltype(k_)::value, decltype(lx)::value>), sp.n_fused_tiles,
-              ra, aa, ls, lt);
-#else
     OB_LAUNCH(la, KID_RATIOS_APPLY_RESIDENT,
               (k_ratios_apply_resident<U_LB, decltype(k_)::value, decltype(lx)::value>), sp.n_fused_tiles + n_lead,
               ra, aa, ls, lt);
-#endif
   });
   // 3. update of everything outside the listed tiles, with the coefficients of steps 1 and 2
   launch_apply(la, ctx, st, packed_all, server_scales, lr, sp.d_rest_tiles, sp.n_rest_tiles, xl);

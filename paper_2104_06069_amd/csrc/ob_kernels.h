@@ -122,11 +122,12 @@ __device__ __forceinline__ v4f grad_value(const GradSrc& gs, v4h h) {
 template <int GT>
 __device__ __forceinline__ v4f load_grad(const GradSrc& gs, int64_t i) { return grad_value(gs, grad_request<GT>(gs, i)); }
 
-__device__ __forceinline__ void st4_lp(void* __restrict__ base, int64_t i, v4f v, int bf16) {
+// (i0: uniform.  Addresses of the form uniform + lane's offset share the offset's register among all spans of a tile.)
+__device__ __forceinline__ void st4_lp(void* __restrict__ base, int64_t i0, int o, v4f v, int bf16) {
   v4h h;
 #pragma unroll
   for (int k = 0; k < 4; ++k) h[k] = float_to_lp(v[k], bf16);
-  __builtin_nontemporal_store(h, reinterpret_cast<v4h*>(reinterpret_cast<unsigned short*>(base) + i));
+  __builtin_nontemporal_store(h, reinterpret_cast<v4h*>(reinterpret_cast<unsigned short*>(base) + i0 + o));
 }
 
 // Reductions over a wavefront, valid in lane 0: the lanes' halves, rows of 16 and parts of a row meet by register moves
@@ -1003,6 +1004,93 @@ __global__ __launch_bounds__(BLOCK, (U >= 4 ? 7 : 8)) void k_server_resident(
 // per tile, (s' - beta1 s)/(1-beta1) and (s' + beta1 s)/(1-beta1), whose squares are hoisted.
 // The tile's registers and the two evaluation paths are shared with the fused ratio+update kernel.
 // ---------------------------------------------------------------------------------------------
+// bit ? a : b on the bit patterns, with the bit taken from position `pos` of `word` (two vector
+// instructions: a signed one-bit field extract gives the all-ones / all-zeros mask)
+__device__ __forceinline__ float select_by_bit(unsigned int word, int pos, float a, float b) {
+  const unsigned int m = (unsigned int)__builtin_amdgcn_sbfe((int)word, (unsigned int)pos, 1u);
+  float r;
+  asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "v"(m), "v"(a), "v"(b));   // (in C the compiler makes three of it: and, compare, select)
+  return r;
+}
+
+// The largest quotient n/d (each correctly rounded; NaN not taken) of a tile, of which only what exceeds `bound` matters: a
+// wavefront's largest so far, or what the clips of lines 18-19 raise every smaller ratio to.  A division is a dozen instructions,
+// one of them at quarter rate; whether n/d can exceed the bound is one fma, whose sign is that of n - bound*d: negative means
+// n/d < bound for d > 0 (a rounded quotient is then at most the bound), and where it is not, or d is not positive or
+// not finite, the quotients are formed.  Underflow of the fma gives a zero, which counts as not negative.
+// Measured with UpdateTerm and select_by_bit's two instructions, four steps, us, before / after: 11 M parameters 327 / 322, 336 M fp32 6785 /
+// 6748, bf16 6946 / 6876 (the vector work of k_ratios_apply_hist, 82 instructions an element, then 50, next to memory at 88 % of
+// a copy's rate).
+struct MaxQuotient {
+  float bound;   // uniform over the wavefront
+  float r;       // the lane's
+  // lo: what line 18 raises a ratio to at least; r_min: line 19
+  __device__ __forceinline__ void start(float lo, float r_min) {
+    const float b = fmaxf(fmaxf(lo, r_min), 0.0f);
+    bound = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(b)));
+    r = 0.0f;
+  }
+  // all lanes of the wavefront; later: more follows
+  __device__ __forceinline__ void add(const v4f& n, const v4f& d, bool later) {
+    const float t = fmaxf(fmaxf(fmaf(-bound, d[0], n[0]), fmaf(-bound, d[1], n[1])),
+                          fmaxf(fmaf(-bound, d[2], n[2]), fmaf(-bound, d[3], n[3])));
+    if (__ballot(!(t < 0.0f)) == 0ull) return;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float q = n[k] / d[k];
+      if (q > r) r = q;
+    }
+    if (later) bound = fmaxf(bound, __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(wave_max(r)))));
+  }
+};
+
+// m_t/(sqrt(v_frozen)+eta) of line 21 with m_t = +-sp: the correctly rounded square root and quotient, as sqrtf and operator/ give
+// them, without what those do for operands at the ends of the number range.  In range: v_frozen at most 2^60 and not
+// negative, |sp| zero or within [2^-80, 2^40], eta within [2^-22, 2^20]; values of v_frozen below 2^-96 count as that (their
+// root is then less than half a unit of eta's last place).  The root: Newton's step on v_rsq_f32's estimate, equal to sqrtf for
+// every one of the 1.6e9 values of [2^-96, 2^96); the quotient: two residuals after one step on v_rcp_f32's (Markstein),
+// which is operator/'s own sequence between its scalings.
+struct UpdateTerm {
+  float sp, eta;
+  unsigned int top;   // the lane's largest bit pattern of v_frozen
+  __device__ __forceinline__ void start(float sp_, float eta_) { sp = sp_; eta = eta_; top = 0u; }
+  __device__ __forceinline__ void see(const v4f& v) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) top = __float_as_uint(v[k]) > top ? __float_as_uint(v[k]) : top;
+  }
+  __device__ __forceinline__ bool in_range() const {   // uniform; all lanes of the wavefront
+    const float a = fabsf(sp);
+    const bool ok = (a == 0.0f || (a >= 0x1p-80f && a <= 0x1p40f)) && eta >= 0x1p-22f && eta <= 0x1p20f && top <= 0x5d800000u /* 2^60 */;
+    return __ballot(!ok) == 0ull;
+  }
+  // v: four values of v_frozen, replaced by their terms; bits pos .. pos + 3 of word: the signs of m_t
+  __device__ __forceinline__ void terms(v4f& v, unsigned int word, int pos, bool in_range) const {
+    if (in_range) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float z = fmaxf(v[k], 0x1p-96f), y = __builtin_amdgcn_rsqf(z), g = z * y;
+        const float d = fmaf(fmaf(-g, g, z), 0.5f * y, g) + eta;
+        const float r0 = __builtin_amdgcn_rcpf(d), r = fmaf(fmaf(-d, r0, 1.0f), r0, r0);
+        const float q0 = sp * r, q1 = fmaf(fmaf(-d, q0, sp), r, q0);
+        const float q = fmaf(fmaf(-d, q1, sp), r, q1);
+        v[k] = __uint_as_float(__float_as_uint(q) ^ (~(word << (31 - pos - k)) & 0x80000000u));
+      }
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float mt = ((word >> (pos + k)) & 1u) ? sp : -sp;
+        v[k] = mt / (sqrtf(v[k]) + eta);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      float q = v[k];
+      asm volatile("" : "+v"(q));   // evaluated here, not sunk below a wait that follows
+      v[k] = q;
+    }
+  }
+};
+
 struct RatioArgs {
   const uint32_t* __restrict__ packed;   // [N_pad/32] the W recompressed chunks
   const float* __restrict__ sscales;     // [W] their scales
@@ -1011,6 +1099,8 @@ struct RatioArgs {
   float* __restrict__ v_fresh;
   const float* __restrict__ v_frozen;
   float beta1, omb1, beta2, omb2;
+  const float* __restrict__ r_prev;      // [L], and the bounds of lines 18-19 (k_ratios_big_hist, whose launch changes no ratio)
+  float one_m_thr, r_min;
 };
 
 template <int U, bool HAS_K, bool PACKED_M>
@@ -1028,9 +1118,9 @@ struct RatioTile {
       if (o < p.len) {
         NB[u] = load_nibble(ra.packed, p.tile0 + u * SPAN);
         if (PACKED_M) OB[u] = load_nibble(ra.pm.bits, p.tile0 + u * SPAN);
-        else M[u] = ld4(ra.m + p.tile0 + o);
-        VF[u] = ld4(ra.v_fresh + p.tile0 + o);
-        VZ[u] = ld4_keep_if<KEEP_V_FROZEN>(ra.v_frozen + p.tile0 + o);
+        else M[u] = ld4(ra.m + (p.tile0 + u * SPAN) + o0);
+        VF[u] = ld4(ra.v_fresh + (p.tile0 + u * SPAN) + o0);
+        VZ[u] = ld4_keep_if<KEEP_V_FROZEN>(ra.v_frozen + (p.tile0 + u * SPAN) + o0);
       }
     }
   }
@@ -1039,9 +1129,10 @@ struct RatioTile {
   // VZ keeps v_frozen.  DEFER: the new v_fresh stays in VF for store_v_fresh() instead of being
   // stored at once (a barrier arrival that follows then does not wait for these stores).
   // ss, s_prev: new and previous server scale of the chunk; kt: k of the layer (1 without HAS_K).
+  // lo, r_min (DEFER): of MaxQuotient, which the others do without (one span, and bound by memory).
   template <bool DEFER = false>
   __device__ __forceinline__ float uniform_pass(const RatioArgs& ra, const TilePos& p, float ss,
-                                                float s_prev, float kt) {
+                                                float s_prev, float kt, float lo = 0.0f, float r_min = 0.0f) {
     const int o0 = threadIdx.x * 4;
     const float sp = HAS_K ? ss / kt : ss;
     float t_same = 0.0f, t_diff = 0.0f;
@@ -1053,6 +1144,8 @@ struct RatioTile {
       t_diff = ra.omb2 * (g_diff * g_diff);
     }
     float r = 0.0f;
+    MaxQuotient mq;
+    if (DEFER) mq.start(lo, r_min);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int o = u * SPAN + o0;
@@ -1062,21 +1155,27 @@ struct RatioTile {
         for (int k = 0; k < 4; ++k) {
           float t;
           if (PACKED_M) {
-            t = (((NB[u] ^ OB[u]) >> k) & 1u) ? t_diff : t_same;
+            t = select_by_bit(NB[u] ^ OB[u], k, t_diff, t_same);
           } else {
             const float mt = ((NB[u] >> k) & 1u) ? sp : -sp;
             const float gr = (mt - ra.beta1 * M[u][k]) / ra.omb1;
             t = ra.omb2 * (gr * gr);
           }
           vf[k] = ra.beta2 * VF[u][k] + t;
-          const float q = VZ[u][k] / vf[k];
-          if (q > r) r = q;
+          if (!DEFER) {
+            const float q = VZ[u][k] / vf[k];
+            if (q > r) r = q;
+          }
         }
-        if (DEFER) VF[u] = vf;
-        else st4(ra.v_fresh + p.tile0 + o, vf);
+        if (DEFER) {
+          mq.add(VZ[u], vf, u + 1 < U);
+          VF[u] = vf;
+        } else {
+          st4(ra.v_fresh + (p.tile0 + u * SPAN) + o0, vf);
+        }
       }
     }
-    return r;
+    return DEFER ? mq.r : r;
   }
 
   __device__ __forceinline__ void store_v_fresh(const RatioArgs& ra, const TilePos& p) const {
@@ -1084,7 +1183,7 @@ struct RatioTile {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int o = u * SPAN + o0;
-      if (o < p.len) st4(ra.v_fresh + p.tile0 + o, VF[u]);
+      if (o < p.len) st4(ra.v_fresh + (p.tile0 + u * SPAN) + o0, VF[u]);
     }
   }
 
@@ -1299,7 +1398,7 @@ __device__ __forceinline__ void apply_uniform(const ApplyArgs& aa, const TilePos
         mn[k] = mt;
       }
       st4(aa.x + p.tile0 + o, xn);
-      if (LPX) st4_lp(aa.x_lp, p.tile0 + o, xn, aa.x_lp_bf16);
+      if (LPX) st4_lp(aa.x_lp, p.tile0 + u * SPAN, o0, xn, aa.x_lp_bf16);
       if (WRITE_M) st4(aa.m + p.tile0 + o, mn);
     }
   }
@@ -1598,7 +1697,7 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_apply_resident(
   const int o0 = threadIdx.x * 4;
   RatioTile<U, HAS_K, true> rt;
   rt.load(ra, p);
-  float r = rt.template uniform_pass<true>(ra, p, ss, s_prev, kt);
+  float r = rt.template uniform_pass<true>(ra, p, ss, s_prev, kt, ls.one_m_thr * rp, ls.r_min);
   r = block_max(r, lds);
   layer_arrive(ls, bid, l0, lp, lp.lb, lp.nl, rp, ca, r, lds, &bc);   // before the stores of v_fresh: nothing to wait for
   rt.store_v_fresh(ra, p);
@@ -1607,24 +1706,23 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_apply_resident(
   for (int u = 0; u < U; ++u) {  // x is fetched while the layer completes
     const int o = u * SPAN + o0;
     X[u] = 0.0f;
-    if (o < p.len) X[u] = ld4(aa.x + p.tile0 + o);
+    if (o < p.len) X[u] = ld4(aa.x + (p.tile0 + u * SPAN) + o0);
   }
   // m_t/(sqrt(v_frozen)+eta) does not depend on the layer's coefficient: it is formed now, in place
   // of v_frozen, so that the square root and the division run while the layer completes instead
   // of after it (the same operations on the same operands as apply_uniform's)
-  const float sp = HAS_K ? ss / kt : ss;
+  UpdateTerm ut;
+  ut.start(HAS_K ? ss / kt : ss, aa.eta);
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int o = u * SPAN + o0;
-    if (o < p.len) {
+    if (o < p.len) ut.see(rt.VZ[u]);
+  }
+  const bool in_range = ut.in_range();   // uniform
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float mt = ((rt.NB[u] >> k) & 1u) ? sp : -sp;
-        float uu = mt / (sqrtf(rt.VZ[u][k]) + aa.eta);
-        asm volatile("" : "+v"(uu));   // evaluated here, not sunk below the wait
-        rt.VZ[u][k] = uu;
-      }
-    }
+  for (int u = 0; u < U; ++u) {
+    const int o = u * SPAN + o0;
+    if (o < p.len) ut.terms(rt.VZ[u], rt.NB[u], 0, in_range);
   }
   const float c = layer_wait(ls, l0, &bc);
   const float a = aa.lr * c;
@@ -1635,8 +1733,8 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_apply_resident(
       v4f xn;
 #pragma unroll
       for (int k = 0; k < 4; ++k) xn[k] = X[u][k] - a * rt.VZ[u][k];
-      st4(aa.x + p.tile0 + o, xn);
-      if (LPX) st4_lp(aa.x_lp, p.tile0 + o, xn, aa.x_lp_bf16);
+      st4(aa.x + (p.tile0 + u * SPAN) + o0, xn);
+      if (LPX) st4_lp(aa.x_lp, p.tile0 + u * SPAN, o0, xn, aa.x_lp_bf16);
     }
   }
 }
@@ -1677,13 +1775,6 @@ __device__ __forceinline__ void variance_terms(const RatioArgs& ra, float s_new,
   const float g_diff = (sp - (-bm)) / ra.omb1;  // of opposite sign
   *t_same = ra.omb2 * (g_same * g_same);
   *t_diff = ra.omb2 * (g_diff * g_diff);
-}
-
-// bit ? a : b on the bit patterns, with the bit taken from position `pos` of `word` (two vector
-// instructions: a signed one-bit field extract gives the all-ones / all-zeros mask)
-__device__ __forceinline__ float select_by_bit(unsigned int word, int pos, float a, float b) {
-  const unsigned int m = (unsigned int)(((int)(word << (31 - pos))) >> 31);
-  return __uint_as_float((m & __float_as_uint(a)) | (~m & __float_as_uint(b)));
 }
 
 // scale of plane q (newest first) for chunk c; q is a compile-time constant where it is called
@@ -1850,6 +1941,7 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_big_hist(RatioArgs
   const TilePos p = tile_pos<TILE>(n_c, tpc_big, big_tiles[blockIdx.x]);
   const int sp0 = p.c * tpc_span + (p.t - p.c * tpc_big) * U;  // the tile's first span
   const int l0 = lt.first_layer[sp0];  // the layer the tile lies in (lt.first_layer: of the 1024-element tiling)
+  const float rp = ra.r_prev[l0];
   const int a = h.n_old + 1;   // steps to apply
   const int o0 = threadIdx.x * 4;
   const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
@@ -1868,8 +1960,8 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_big_hist(RatioArgs
     const int o = u * SPAN + o0;
     V[u] = 0.0f; VZ[u] = 0.0f;
     if (o < p.len) {
-      V[u] = ld4(ra.v_fresh + p.tile0 + o);
-      VZ[u] = ld4(ra.v_frozen + p.tile0 + o);
+      V[u] = ld4(ra.v_fresh + (p.tile0 + u * SPAN) + o0);
+      VZ[u] = ld4(ra.v_frozen + (p.tile0 + u * SPAN) + o0);
     }
   }
   StepTerms st;
@@ -1898,20 +1990,17 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_big_hist(RatioArgs
         for (int k = 0; k < 4; ++k) V[u][k] = ra.beta2 * V[u][k] + select_by_bit(Wq[s], 4 * u + k, t_diff, t_same);
     }
   }
-  float r = 0.0f;
+  MaxQuotient mq;
+  mq.start(ra.one_m_thr * rp, ra.r_min);
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int o = u * SPAN + o0;
     if (o < p.len) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float q = VZ[u][k] / V[u][k];
-        if (q > r) r = q;
-      }
-      if (h.write_v) st4(ra.v_fresh + p.tile0 + o, V[u]);
+      mq.add(VZ[u], V[u], u + 1 < U);
+      if (h.write_v) st4(ra.v_fresh + (p.tile0 + u * SPAN) + o0, V[u]);
     }
   }
-  r = block_max(r, lds);
+  const float r = block_max(mq.r, lds);
   const int nspan = (p.len + SPAN - 1) / SPAN;
   if (threadIdx.x < nspan) seg_max[tile_seg0[sp0 + threadIdx.x]] = (threadIdx.x == 0) ? r : 0.0f;
 }
@@ -1983,9 +2072,9 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
     const int o = u * SPAN + o0;
     V[u] = 0.0f; VZ[u] = 0.0f;
     if (o < p.len) {   // all lanes of a wavefront or none
-      V[u] = ld4(ra.v_fresh + p.tile0 + o);
-      if (u < S) lds_load16(ra.v_frozen + p.tile0 + o, &zs[u * BLOCK + wv_u * WAVE]);
-      else VZ[u] = ld4(ra.v_frozen + p.tile0 + o);
+      V[u] = ld4(ra.v_fresh + (p.tile0 + u * SPAN) + o0);
+      if (u < S) lds_load16(ra.v_frozen + (p.tile0 + u * SPAN) + o0, &zs[u * BLOCK + wv_u * WAVE]);
+      else VZ[u] = ld4(ra.v_frozen + (p.tile0 + u * SPAN) + o0);
     }
   }
   if constexpr (REST) st.template form<HAS_K>(ra, h, p.c, kt);
@@ -2015,21 +2104,21 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
         for (int k = 0; k < 4; ++k) V[u][k] = ra.beta2 * V[u][k] + select_by_bit(Wq[s], 4 * u + k, t_diff, t_same);
     }
   }
-  float r = 0.0f;
+  MaxQuotient mq;
+  mq.start(ls.one_m_thr * rp, ls.r_min);
+  UpdateTerm ut;
+  ut.start(HAS_K ? ss / kt : ss, aa.eta);
   if (S > 0) lds_loads_done();
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int o = u * SPAN + o0;
     if (o < p.len) {
       const v4f vz = (u < S) ? zs[u * BLOCK + threadIdx.x] : VZ[u];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float q = vz[k] / V[u][k];
-        if (q > r) r = q;
-      }
+      mq.add(vz, V[u], u + 1 < U);
+      ut.see(vz);
     }
   }
-  r = block_max(r, lds);
+  const float r = block_max(mq.r, lds);
   // before any store: nothing to wait for
   layer_arrive(ls, bid, l0, lp, first, REST ? layer_arrivals(lp.nl, lp.a, lp.s_first, lp.s_end, lp.b) : lp.nl, rp, ca, r,
                lds, &bc);
@@ -2037,7 +2126,7 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int o = u * SPAN + o0;
-      if (o < p.len) st4(ra.v_fresh + p.tile0 + o, V[u]);
+      if (o < p.len) st4(ra.v_fresh + (p.tile0 + u * SPAN) + o0, V[u]);
     }
   }
   v4f X[U];
@@ -2045,23 +2134,17 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
   for (int u = 0; u < U; ++u) {  // x is fetched while the layer completes
     const int o = u * SPAN + o0;
     X[u] = 0.0f;
-    if (o < p.len) X[u] = ld4(aa.x + p.tile0 + o);
+    if (o < p.len) X[u] = ld4(aa.x + (p.tile0 + u * SPAN) + o0);
   }
   // m_t/(sqrt(v_frozen)+eta), formed in place of v_frozen while the layer completes (the same
   // operations on the same operands as apply_uniform's)
-  const float sp = HAS_K ? ss / kt : ss;
+  const bool in_range = ut.in_range();   // uniform
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int o = u * SPAN + o0;
     if (o < p.len) {
       v4f z = (u < S) ? zs[u * BLOCK + threadIdx.x] : VZ[u];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const float mt = ((Wq[0] >> (4 * u + k)) & 1u) ? sp : -sp;
-        float uu = mt / (sqrtf(z[k]) + aa.eta);
-        asm volatile("" : "+v"(uu));   // evaluated here, not sunk below the wait
-        z[k] = uu;
-      }
+      ut.terms(z, Wq[0], 4 * u, in_range);
       if (u < S) zs[u * BLOCK + threadIdx.x] = z;
       else VZ[u] = z;
     }
@@ -2076,8 +2159,8 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
       v4f xn;
 #pragma unroll
       for (int k = 0; k < 4; ++k) xn[k] = X[u][k] - al * z[k];
-      st4(aa.x + p.tile0 + o, xn);
-      if (LPX) st4_lp(aa.x_lp, p.tile0 + o, xn, aa.x_lp_bf16);
+      st4(aa.x + (p.tile0 + u * SPAN) + o0, xn);
+      if (LPX) st4_lp(aa.x_lp, p.tile0 + u * SPAN, o0, xn, aa.x_lp_bf16);
     }
   }
 }
@@ -2441,7 +2524,7 @@ __global__ __launch_bounds__(BLOCK, small_min_wg(U)) void k_ratios_apply_small(
 #pragma unroll
         for (int k = 0; k < 4; ++k) xn[k] = X[u][k] - al * VZ[u][k];
         st4(aa.x + p.tile0 + o, xn);
-        if (LPX) st4_lp(aa.x_lp, p.tile0 + o, xn, aa.x_lp_bf16);
+        if (LPX) st4_lp(aa.x_lp, p.tile0 + u * SPAN, o0, xn, aa.x_lp_bf16);
       }
     }
   } else {
@@ -2712,7 +2795,7 @@ __global__ __launch_bounds__(BLOCK) void k_warmup_apply(
         for (int k = 0; k < 4; ++k)
           xn[k] = X[u][k] - a * lamb_u(M[u][k], V[u][k], X[u][k], eta, wd);
         st4(x + p.tile0 + o, xn);
-        if (LPX) st4_lp(x_lp, p.tile0 + o, xn, x_lp_bf16);
+        if (LPX) st4_lp(x_lp, p.tile0 + u * SPAN, o0, xn, x_lp_bf16);
       }
     }
   } else {
@@ -2806,9 +2889,9 @@ __global__ __launch_bounds__(BLOCK, OB_WU_MINW) void k_warmup_resident(
       X[u0 + j] = 0.0f; UU[u0 + j] = 0.0f;
       if (o < p.len) {
         Gr[j] = load_grad<GT>(g, p.tile0 + o);
-        M[j] = ld4(m + p.tile0 + o);
-        V[j] = ld4(v + p.tile0 + o);
-        X[u0 + j] = ld4(x + p.tile0 + o);
+        M[j] = ld4(m + (p.tile0 + (u0 + j) * SPAN) + o0);
+        V[j] = ld4(v + (p.tile0 + (u0 + j) * SPAN) + o0);
+        X[u0 + j] = ld4(x + (p.tile0 + (u0 + j) * SPAN) + o0);
       }
     }
 #pragma unroll
@@ -2821,8 +2904,8 @@ __global__ __launch_bounds__(BLOCK, OB_WU_MINW) void k_warmup_resident(
           V[j][k] = beta2 * V[j][k] + omb2 * (Gr[j][k] * Gr[j][k]);
         }
         if (u0 + G < U) {
-          st4(m + p.tile0 + o, M[j]);
-          st4(v + p.tile0 + o, V[j]);
+          st4(m + (p.tile0 + (u0 + j) * SPAN) + o0, M[j]);
+          st4(v + (p.tile0 + (u0 + j) * SPAN) + o0, V[j]);
         } else {
           Ml[j] = M[j];
           Vl[j] = V[j];
@@ -2856,8 +2939,8 @@ __global__ __launch_bounds__(BLOCK, OB_WU_MINW) void k_warmup_resident(
   for (int j = 0; j < G; ++j) {
     const int o = (U - G + j) * SPAN + o0;
     if (o < p.len) {
-      st4(m + p.tile0 + o, Ml[j]);
-      st4(v + p.tile0 + o, Vl[j]);
+      st4(m + (p.tile0 + (U - G + j) * SPAN) + o0, Ml[j]);
+      st4(v + (p.tile0 + (U - G + j) * SPAN) + o0, Vl[j]);
     }
   }
   float c;
@@ -2898,8 +2981,8 @@ __global__ __launch_bounds__(BLOCK, OB_WU_MINW) void k_warmup_resident(
       v4f xn;
 #pragma unroll
       for (int k = 0; k < 4; ++k) xn[k] = xo[k] - a * UU[u][k];
-      st4(x + p.tile0 + o, xn);
-      if (LPX) st4_lp(x_lp, p.tile0 + o, xn, x_lp_bf16);
+      st4(x + (p.tile0 + u * SPAN) + o0, xn);
+      if (LPX) st4_lp(x_lp, p.tile0 + u * SPAN, o0, xn, x_lp_bf16);
     }
   }
 }
@@ -3065,7 +3148,7 @@ __global__ __launch_bounds__(BLOCK, 8) void k_warmup_trail(
 #pragma unroll
         for (int k = 0; k < 4; ++k) xn[k] = X[u][k] - a * lamb_u(M[u][k], V[u][k], X[u][k], eta, wd);
         st4(x + p.tile0 + o, xn);
-        if (LPX) st4_lp(x_lp, p.tile0 + o, xn, x_lp_bf16);
+        if (LPX) st4_lp(x_lp, p.tile0 + u * SPAN, o0, xn, x_lp_bf16);
       }
     }
     return;
@@ -3293,7 +3376,7 @@ __global__ __launch_bounds__(BLOCK, small_min_wg(U)) void k_warmup_small(
 #pragma unroll
         for (int k = 0; k < 4; ++k) xn[k] = X[u][k] - a * UU[u][k];
         st4(x + p.tile0 + o, xn);
-        if (LPX) st4_lp(x_lp, p.tile0 + o, xn, x_lp_bf16);
+        if (LPX) st4_lp(x_lp, p.tile0 + u * SPAN, o0, xn, x_lp_bf16);
       } else {
         int s = sg.find(ti.nseg, o);
 #pragma unroll

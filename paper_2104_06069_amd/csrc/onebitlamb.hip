@@ -688,16 +688,23 @@ int64_t split_max_tiles(int per_cu, int cus, int32_t cap) {
   return max_tiles < 0 ? 0 : max_tiles;
 }
 
+RatioArgs ratio_args(const ob_lamb_ctx* ctx, const ob_lamb_state* st, const uint32_t* packed_all,
+                     const float* server_scales, const PackedMom& pm) {
+  RatioArgs ra;
+  ra.packed = packed_all; ra.sscales = server_scales; ra.m = st->m; ra.pm = pm;
+  ra.v_fresh = st->v_fresh; ra.v_frozen = st->v_frozen;
+  ra.beta1 = ctx->beta1; ra.omb1 = ctx->omb1; ra.beta2 = ctx->beta2; ra.omb2 = ctx->omb2;
+  ra.r_prev = st->r_prev; ra.one_m_thr = ctx->one_m_thr; ra.r_min = ctx->r_min;
+  return ra;
+}
+
 // Launches of the plain ratio pass and finalize kernels.  tiles: the 1024-element tiles to cover
 // (NULL: all, in order), n_launch_tiles of them; layers with done_elsewhere[l] != 0 (NULL: none) are
 // left to be finished by the kernel with the per-layer barrier.
 void launch_ratios(Launch& la, ob_lamb_ctx* ctx, const ob_lamb_state* st, const uint32_t* packed_all,
                    const float* server_scales, bool packed_m, const PackedMom& pm, const int* tiles,
                    int n_launch_tiles, const unsigned char* done_elsewhere, bool finalize) {
-  RatioArgs ra;
-  ra.packed = packed_all; ra.sscales = server_scales; ra.m = st->m; ra.pm = pm;
-  ra.v_fresh = st->v_fresh; ra.v_frozen = st->v_frozen;
-  ra.beta1 = ctx->beta1; ra.omb1 = ctx->omb1; ra.beta2 = ctx->beta2; ra.omb2 = ctx->omb2;
+  const RatioArgs ra = ratio_args(ctx, st, packed_all, server_scales, pm);
   const LayerTab lt = layer_tab(ctx, st, ctx->d_first_layer);
   dispatch2(st->mom_scale != nullptr, packed_m, [&](auto hk, auto pk) {
     dispatch1(keeps_second_reads(ctx->N, ctx->W), [&](auto kp) {
@@ -731,15 +738,6 @@ void launch_apply(Launch& la, ob_lamb_ctx* ctx, const ob_lamb_state* st, const u
                 n_launch_tiles, aa, ctx->n_c, ctx->tpc, lt, tiles);
     });
   });
-}
-
-RatioArgs ratio_args(const ob_lamb_ctx* ctx, const ob_lamb_state* st, const uint32_t* packed_all,
-                     const float* server_scales, const PackedMom& pm) {
-  RatioArgs ra;
-  ra.packed = packed_all; ra.sscales = server_scales; ra.m = st->m; ra.pm = pm;
-  ra.v_fresh = st->v_fresh; ra.v_frozen = st->v_frozen;
-  ra.beta1 = ctx->beta1; ra.omb1 = ctx->omb1; ra.beta2 = ctx->beta2; ra.omb2 = ctx->omb2;
-  return ra;
 }
 
 void launch_ratios_apply_small(Launch& la, ob_lamb_ctx* ctx, const ob_lamb_state* st, const RatioArgs& ra,
@@ -1480,10 +1478,7 @@ ob_status ob_lamb_ratios_apply_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st, con
     launch_apply(la, ctx, st, packed_all, server_scales, lr, nullptr, ctx->n_tiles, xl);
     return la.ok ? OB_OK : OB_ERR_HIP;
   }
-  RatioArgs ra;
-  ra.packed = packed_all; ra.sscales = server_scales; ra.m = st->m; ra.pm = pm;
-  ra.v_fresh = st->v_fresh; ra.v_frozen = st->v_frozen;
-  ra.beta1 = ctx->beta1; ra.omb1 = ctx->omb1; ra.beta2 = ctx->beta2; ra.omb2 = ctx->omb2;
+  const RatioArgs ra = ratio_args(ctx, st, packed_all, server_scales, pm);
   const ApplyArgs aa = apply_args(ctx, st, packed_all, server_scales, lr, xl);
   const bool hk = st->mom_scale != nullptr;  // (here the momentum is in 1-bit form and st->m is NULL)
   const LayerTab lt = layer_tab(ctx, st, ctx->d_first_layer);

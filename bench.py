@@ -460,12 +460,14 @@ def main():
         lag = (wl.fused_params + wl.big_params) / float(ds.n_pad)     # what a list in one launch keeps behind, too
         KB["ratios_apply_small"] = (lag * KB["ratios_apply_hist"][0] + (1.0 - lag) * KB["ratios_apply_small"][0], "n_pad")
         KB["ratios_big_hist"] = (hist_big_ratio_bytes_per_param(ages_prof, ds.vf_period), "big")
+        if "ratios_trail" in kern:   # ratio pass and update in one launch (of these 4.125 come from the memory-side cache where it holds them)
+            KB["ratios_trail"] = (KB["ratios_big_hist"][0] + KERNEL_BYTES[mode]["decompress_apply"][0], "big")
     g_less = 2.0 if args.grad_dtype != "f32" else 0.0     # 16-bit gradient read
     x_more = 2.0 if args.x_lp != "none" else 0.0          # 16-bit parameter copy written
     for k in ("compress_resident", "compress_deferred", "momentum_z_sumsq", "warmup_moments", "warmup_resident", "warmup_small"):
         KB[k] = (KB[k][0] - g_less, KB[k][1])
     for k in ("decompress_apply", "ratios_apply_resident", "ratios_apply_hist", "ratios_apply_hist_lds", "ratios_apply_small",
-              "warmup_apply", "warmup_resident", "warmup_small"):
+              "ratios_trail", "warmup_apply", "warmup_resident", "warmup_small"):
         if k in KB:
             KB[k] = (KB[k][0] + x_more, KB[k][1])
     fused_params, wfused = wl.fused_params, wl.wfused
@@ -477,7 +479,7 @@ def main():
     if ds.fused_apply and (fused_params or wl.big_params):   # the plain ratio/update kernels then cover only what is left
         KB["ratios_pass"] = (KB["ratios_pass"][0], "rest_ratio")
         KB["decompress_apply"] = (KB["decompress_apply"][0], "rest")
-        units["rest"] = ds.n_pad - fused_params
+        units["rest"] = ds.n_pad - fused_params - (wl.big_params if "ratios_trail" in kern else 0)
         units["rest_ratio"] = ds.n_pad - fused_params - wl.big_params
     for k, v in kern.items():
         if k in KB:

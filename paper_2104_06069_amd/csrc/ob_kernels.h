@@ -1548,6 +1548,7 @@ struct LayerSync {
   float one_m_thr, one_p_thr, r_min, r_max;
   int n_lead;                   // leading workgroups of the launch: without REST one per layer, that
                                 // finish the layers without listed tiles (0: a kernel of its own has done that)
+  const unsigned char* done;    // [L] 1 for those of them that an earlier launch has finished (NULL: none)
   // k_ratios_apply_hist with the plain ratio pass in its launch (REST): the leading workgroups
   // finish the n_alone layers that have no arrivals and run the pass of the rest_tiles, whose segments arrive too
   const int* rest_tiles;
@@ -1660,7 +1661,7 @@ __device__ __forceinline__ float layer_wait(const LayerSync& ls, int l, unsigned
 // in this launch reads what is written here -- in the shadow of this launch instead of in a launch of its own.
 __device__ __forceinline__ void lead_finalize(const LayerSync& ls, float* lds) {
   const int l = (int)blockIdx.x;
-  if (ls.lt.n_listed[l] == 0)
+  if (ls.lt.n_listed[l] == 0 && !(ls.done && ls.done[l]))
     ratios_finalize_layer<BLOCK>(l, ls.seg_max, ls.lt.layer_seg0, ls.c_avg, ls.r_prev, ls.coeff_c, ls.one_m_thr,
                                  ls.one_p_thr, ls.r_min, ls.r_max, lds);
 }
@@ -1870,7 +1871,7 @@ struct StepTerms {
 };
 
 // The terms and the plain ratio pass (momentum in 1-bit form, tile list) in one launch: the first n_lead
-// workgroups form the terms, the others run the plain ratio pass of tile_list[blockIdx.x - n_lead].
+// workgroups form the terms and clear flags, the others run the plain ratio pass of tile_list[blockIdx.x - n_lead].
 // Neither reads what the other writes; both are over before the kernels that use the terms start.
 template <int U, bool HAS_K>
 __global__ __launch_bounds__(BLOCK) void k_ratios_pass_vterms(RatioArgs ra, float* __restrict__ seg_max,
@@ -1878,10 +1879,13 @@ __global__ __launch_bounds__(BLOCK) void k_ratios_pass_vterms(RatioArgs ra, floa
                                                               const int* __restrict__ tile_seg0,
                                                               const int* __restrict__ seg_layer,
                                                               const int* __restrict__ tile_list, VfHist h,
-                                                              VTerms vt, float* __restrict__ vt_out, int n_lead) {
+                                                              VTerms vt, float* __restrict__ vt_out, int n_lead,
+                                                              unsigned long long* __restrict__ clear_flag, int n_flags) {
   __shared__ float lds[BLOCK / WAVE];
   const int bid = (int)blockIdx.x - n_lead;
   if (bid < 0) {
+    const int f = (int)(blockIdx.x * BLOCK + threadIdx.x);
+    if (f < n_flags) clear_flag[f] = 0ull;   // (k_ratios_trail's, of the call before)
     variance_terms_of_pair<HAS_K>(ra, h, vt, lt.mom_scale, vt_out, (int)(blockIdx.x * BLOCK + threadIdx.x));
     return;
   }
@@ -1930,24 +1934,38 @@ __global__ __launch_bounds__(BLOCK) void k_variance_dense(RatioArgs ra, VfHist h
 // walk through the steps as k_ratios_apply_hist.  The tile's maximum goes to the segment of its
 // first 1024-element span, 0 to the segments of its other spans (k_ratios_finalize takes the
 // maximum over all of a layer's segments).
+// The lane's word of a plane: span lane/8, word lane%8 of the wavefront's 8 words (256 elements) of that span, as an index
+// into the plane; and the lane's own nibbles of the 8 spans, packed into one register, from the words that the lanes hold.
+__device__ __forceinline__ int64_t lane_word(const TilePos& p, bool* have) {
+  const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
+  const int e0 = (lane >> 3) * SPAN + wv * (WAVE * 4) + (lane & 7) * 32;
+  *have = (e0 < p.len);   // len is a multiple of 256: a wavefront's part of a span is all there or all missing
+  return (p.tile0 + e0) >> 5;
+}
+__device__ __forceinline__ unsigned int lane_nibbles(unsigned int word) {
+  const int lane = threadIdx.x & (WAVE - 1), src = lane >> 3;   // src + 8*u: the lane that holds this lane's word of span u
+  const unsigned int sh = 4u * (lane & 7);
+  unsigned int packed = 0u;
+#pragma unroll
+  for (int u = 0; u < 8; ++u) packed |= ((__shfl(word, 8 * u + src, WAVE) >> sh) & 15u) << (4 * u);
+  return packed;
+}
+
 template <bool HAS_K>
 __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_big_hist(RatioArgs ra, VfHist h, VTerms vt, float* __restrict__ seg_max,
                                                            const int* __restrict__ big_tiles, int64_t n_c,
                                                            int tpc_big, int tpc_span, LayerTab lt,
                                                            const int* __restrict__ tile_seg0) {
   constexpr int U = 8;
-  constexpr int TILE = SPAN * U;
   __shared__ float lds[BLOCK / WAVE];
-  const TilePos p = tile_pos<TILE>(n_c, tpc_big, big_tiles[blockIdx.x]);
+  const TilePos p = tile_pos<SPAN * U>(n_c, tpc_big, big_tiles[blockIdx.x]);
   const int sp0 = p.c * tpc_span + (p.t - p.c * tpc_big) * U;  // the tile's first span
   const int l0 = lt.first_layer[sp0];  // the layer the tile lies in (lt.first_layer: of the 1024-element tiling)
   const float rp = ra.r_prev[l0];
   const int a = h.n_old + 1;   // steps to apply
   const int o0 = threadIdx.x * 4;
-  const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
-  const int e0 = (lane >> 3) * SPAN + wv * (WAVE * 4) + (lane & 7) * 32;
-  const bool have_word = (e0 < p.len);
-  const int64_t wi = (p.tile0 + e0) >> 5;
+  bool have_word;
+  const int64_t wi = lane_word(p, &have_word);
   unsigned int Wq[VF_MAX_OLD + 2];
 #pragma unroll
   for (int q = 0; q < VF_MAX_OLD + 2; ++q) {
@@ -1969,17 +1987,9 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_big_hist(RatioArgs
 #pragma unroll
   for (int s = VF_MAX_OLD + 1; s >= 1; --s)
     if (s <= a) Wq[s] ^= Wq[s - 1];
-  const int src = lane >> 3;
-  const unsigned int sh = 4u * (lane & 7);
 #pragma unroll
-  for (int q = 1; q < VF_MAX_OLD + 2; ++q) {   // (plane 0 itself is not needed here: only the flips)
-    if (q <= a) {   // uniform
-      unsigned int packed = 0u;
-#pragma unroll
-      for (int u = 0; u < U; ++u) packed |= ((__shfl(Wq[q], 8 * u + src, WAVE) >> sh) & 15u) << (4 * u);
-      Wq[q] = packed;
-    }
-  }
+  for (int q = 1; q < VF_MAX_OLD + 2; ++q)   // (plane 0 itself is not needed here: only the flips)
+    if (q <= a) Wq[q] = lane_nibbles(Wq[q]);   // uniform
 #pragma unroll
   for (int s = VF_MAX_OLD + 1; s >= 1; --s) {
     if (s <= a) {   // uniform: the step from plane s to plane s-1
@@ -2003,6 +2013,197 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_big_hist(RatioArgs
   const float r = block_max(mq.r, lds);
   const int nspan = (p.len + SPAN - 1) / SPAN;
   if (threadIdx.x < nspan) seg_max[tile_seg0[sp0 + threadIdx.x]] = (threadIdx.x == 0) ? r : 0.0f;
+}
+
+// The same pass, and the update of the same layers, as two kinds of workgroups of one launch: a layer's update follows its
+// ratio pass closely enough to find v_frozen in the 256 MB memory-side cache, and the two take turns, so that the device
+// reads and writes alike at any time.
+// `items` lists the workgroups in the order of dispatch: the tiles in position order for the ratio pass, and from
+// some way after a layer's last tile on parts of its tiles for the update (ratios_trail_items in the host code, which says
+// when this is taken and what it gives).  The last ratio workgroup of a layer
+// to finish takes the maximum over all of the layer (arrivals counted in two levels, as in chunk_ticket), finishes lines 18-20
+// and publishes c_t in flag[l], which an earlier launch of the call has cleared.  An update workgroup requests v_frozen, x and
+// the signs, none of which a ratio workgroup writes, forms m_t/(sqrt(v_frozen)+eta) and then waits for that flag, which by then
+// is normally there.  Ratio workgroups wait for nothing and an update workgroup only for ones dispatched before it: progress needs
+// in-order dispatch, not co-residency; the wait is bounded (errflag).
+// Bound by HBM and the memory-side cache together: 17.8 bytes per element from one (four-step average), 4 from the other.  1.21e9 elements in layers of
+// 12.6, 16.8 and 103 M: 3.65 ms a step, 7.2 TB/s of what is asked for; 4.04 in two kernels; with v_frozen not kept 4.4.
+// (The ratio pass stands in both kernels: as a function of its own it makes each of them spill 306 vector registers.)
+struct RatioTrailTab {
+  const unsigned int* items;    // flags above | tile's position in lt.tile_list
+  ListedTiles lt;               // the tiles of these layers (positions as for the barrier kernel)
+  const int* count0;            // [L] the layer's first counter: second level, then the first-level ones
+  unsigned int* count;          // lines of CTR_STRIDE 8-byte words
+  float* sub_max;               // [counters] of the first-level groups
+  float* tile_max;              // [tiles]
+  unsigned long long* flag;     // [L] 2^32 | bits of c_t once known
+  const float* seg_max;         // maxima left by the plain ratio pass
+  unsigned int* errflag;
+  int spin_limit;
+  const float* c_avg;
+  float* r_prev;
+  float* coeff_c;
+  float one_m_thr, one_p_thr, r_min, r_max;
+};
+// First wavefront of a ratio workgroup; pos: the tile's position, r: its maximum (lane 0).  rp, ca: r_prev[l] and c_avg[l].
+__device__ __forceinline__ void ratios_trail_finish(const RatioTrailTab& tt, int pos, int l, const LayerParts& lp, int64_t c0,
+                                                    float rp, float ca, float r) {
+  constexpr int LINE = 2 * CTR_STRIDE;
+  const int lane = threadIdx.x & (WAVE - 1);
+  auto arrive = [&](unsigned int* counter, unsigned int n, float* payload, float v) {
+    int last = 0;
+    if (lane == 0) {
+      __hip_atomic_store(payload, v, __ATOMIC_RELAXED, OB_AGENT);
+      payload_before_arrival();
+      last = (__hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, OB_AGENT) + 1u == n);
+      if (last) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, OB_AGENT);
+    }
+    return __builtin_amdgcn_readfirstlane(last) != 0;
+  };
+  const int sub = (pos - lp.lb) / TICKET_SUB, first = sub * TICKET_SUB;
+  const int n = (lp.nl - first < TICKET_SUB) ? lp.nl - first : TICKET_SUB;
+  const int n_sub = (lp.nl + TICKET_SUB - 1) / TICKET_SUB;
+  const int64_t cs = c0 + 1 + sub;
+  if (!arrive(tt.count + cs * LINE, (unsigned int)n, &tt.tile_max[pos], r)) return;
+  float q = 0.0f;
+  if (lane < n) q = __hip_atomic_load(&tt.tile_max[lp.lb + first + lane], __ATOMIC_RELAXED, OB_AGENT);
+  q = wave_max(q);
+  if (!arrive(tt.count + c0 * LINE, (unsigned int)n_sub, &tt.sub_max[cs], q)) return;
+  q = 0.0f;
+  const float* sub_max = tt.sub_max + c0 + 1;
+  for (int s = lane; s < n_sub; s += 4 * WAVE) {   // four in flight (the maxima are >= +0: missing ones as 0 change nothing)
+    float v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      v[j] = (s + j * WAVE < n_sub) ? __hip_atomic_load(&sub_max[s + j * WAVE], __ATOMIC_RELAXED, OB_AGENT) : 0.0f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (v[j] > q) q = v[j];
+  }
+  for (int s = lp.a + lane; s < lp.s_first; s += WAVE)    // written by an earlier kernel
+    if (tt.seg_max[s] > q) q = tt.seg_max[s];
+  for (int s = lp.s_end + lane; s < lp.b; s += WAVE)
+    if (tt.seg_max[s] > q) q = tt.seg_max[s];
+  q = wave_max(q);
+  if (lane == 0) {
+    const float c = ratio_clip_commit(q, l, rp, ca, tt.r_prev, tt.coeff_c, tt.one_m_thr, tt.one_p_thr, tt.r_min, tt.r_max);
+    __hip_atomic_store(&tt.flag[l], (1ull << 32) | (unsigned long long)__float_as_uint(c), __ATOMIC_RELAXED, OB_AGENT);
+  }
+}
+
+template <bool HAS_K, bool LPX>
+__global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_trail(RatioArgs ra, VfHist h, VTerms vt, ApplyArgs aa,
+                                                                    RatioTrailTab tt, LayerTab lt) {
+  constexpr int U = 8;
+  __shared__ float lds[BLOCK / WAVE];
+  __shared__ float c_of_layer;
+  const unsigned int item = tt.items[blockIdx.x];
+  const int pos = (int)(item & (RATIOS_TRAIL_PART - 1u)), part = (int)((item & ~TRAIL_UPDATE) / RATIOS_TRAIL_PART);
+  const TilePos p = tile_pos<SPAN * U>(tt.lt.n_c, tt.lt.tpc, tt.lt.tile_list[pos]);
+  const int sp0 = p.c * tt.lt.tpc_span + (p.t - p.c * tt.lt.tpc) * U;  // the tile's first span
+  const int l0 = lt.first_layer[sp0];  // the layer the tile lies in (lt.first_layer: of the 1024-element tiling)
+  if (item & TRAIL_UPDATE) {
+    constexpr int U = RATIOS_TRAIL_U;
+    TilePos q = p;
+    const int in_tile = part * (U * SPAN);
+    q.tile0 += in_tile;
+    q.len -= in_tile;            // (a short tile may lack its last parts: <= 0)
+    if (q.len <= 0) return;
+    const float ss = aa.sscales[q.c];
+    const float kt = HAS_K ? lt.mom_scale[l0] : 1.0f;
+    const int o0 = threadIdx.x * 4;
+    unsigned int NB[U];
+    v4f VZ[U], X[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int o = u * SPAN + o0;
+      NB[u] = 0u; VZ[u] = 0.0f; X[u] = 0.0f;
+      if (o < q.len) {
+        NB[u] = load_nibble(aa.packed, q.tile0 + u * SPAN);
+        VZ[u] = ld4(aa.v_frozen + (q.tile0 + u * SPAN) + o0);
+        X[u] = ld4(aa.x + (q.tile0 + u * SPAN) + o0);
+      }
+    }
+    UpdateTerm ut;
+    ut.start(HAS_K ? ss / kt : ss, aa.eta);
+#pragma unroll
+    for (int u = 0; u < U; ++u) ut.see(VZ[u]);   // (zeros where there is nothing)
+    const bool in_range = ut.in_range();   // uniform
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int o = u * SPAN + o0;
+      if (o < q.len) ut.terms(VZ[u], NB[u], 0, in_range);
+    }
+    if (threadIdx.x == 0)
+      c_of_layer = __uint_as_float((unsigned int)(barrier_wait(&tt.flag[l0], 1u, tt.errflag, tt.spin_limit) & 0xffffffffull));
+    __syncthreads();
+    const float al = aa.lr * c_of_layer;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int o = u * SPAN + o0;
+      if (o < q.len) {
+        v4f xn;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) xn[k] = X[u][k] - al * VZ[u][k];
+        st4(aa.x + (q.tile0 + u * SPAN) + o0, xn);
+        if (LPX) st4_lp(aa.x_lp, q.tile0 + u * SPAN, o0, xn, aa.x_lp_bf16);
+      }
+    }
+    return;
+  }
+  const LayerParts lp = layer_parts(tt.lt, l0);
+  const int64_t c0 = tt.count0[l0];
+  const float rp = tt.r_prev[l0], ca = tt.c_avg[l0];
+  const int a = h.n_old + 1;   // steps to apply
+  const int o0 = threadIdx.x * 4;
+  bool have_word;
+  const int64_t wi = lane_word(p, &have_word);
+  unsigned int Wq[VF_MAX_OLD + 2];
+#pragma unroll
+  for (int q = 0; q < VF_MAX_OLD + 2; ++q) {
+    Wq[q] = 0u;
+    if (q <= a && have_word) Wq[q] = plane_bits(ra, h, q)[wi];
+  }
+  v4f V[U], VZ[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int o = u * SPAN + o0;
+    V[u] = 0.0f; VZ[u] = 0.0f;
+    if (o < p.len) {
+      V[u] = ld4(ra.v_fresh + (p.tile0 + u * SPAN) + o0);
+      VZ[u] = ld4_keep(ra.v_frozen + (p.tile0 + u * SPAN) + o0);
+    }
+  }
+  StepTerms st;
+  st.get<HAS_K>(vt, ra, h, p.c, l0, HAS_K ? lt.mom_scale[l0] : 1.0f);
+#pragma unroll
+  for (int s = VF_MAX_OLD + 1; s >= 1; --s)
+    if (s <= a) Wq[s] ^= Wq[s - 1];
+#pragma unroll
+  for (int q = 1; q < VF_MAX_OLD + 2; ++q)   // (plane 0 itself is not needed here: only the flips)
+    if (q <= a) Wq[q] = lane_nibbles(Wq[q]);   // uniform
+#pragma unroll
+  for (int s = VF_MAX_OLD + 1; s >= 1; --s) {
+    if (s <= a) {   // uniform: the step from plane s to plane s-1
+      const float t_same = st.t_same(s), t_diff = st.t_diff(s);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) V[u][k] = ra.beta2 * V[u][k] + select_by_bit(Wq[s], 4 * u + k, t_diff, t_same);
+    }
+  }
+  MaxQuotient mq;
+  mq.start(ra.one_m_thr * rp, ra.r_min);
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int o = u * SPAN + o0;
+    if (o < p.len) {
+      mq.add(VZ[u], V[u], u + 1 < U);
+      if (h.write_v) st4(ra.v_fresh + (p.tile0 + u * SPAN) + o0, V[u]);
+    }
+  }
+  const float r = block_max(mq.r, lds);
+  if (threadIdx.x < WAVE) ratios_trail_finish(tt, pos, l0, lp, c0, rp, ca, r);
 }
 
 // k_ratios_apply_resident with the variance in deferred form.  A wavefront's part of a tile is 64
@@ -2054,11 +2255,8 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
   if constexpr (!REST) st.find(vt, p.c, l0);
   const int a = h.n_old + 1;   // steps to apply
   const int o0 = threadIdx.x * 4;
-  const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
-  // the lane's word of each plane: span lane/8, word lane%8 of the wavefront's 8 words (256 elements) of that span
-  const int e0 = (lane >> 3) * SPAN + wv * (WAVE * 4) + (lane & 7) * 32;
-  const bool have_word = (e0 < p.len);   // len is a multiple of 256: a wavefront's part of a span is all there or all missing
-  const int64_t wi = (p.tile0 + e0) >> 5;
+  bool have_word;
+  const int64_t wi = lane_word(p, &have_word);
   unsigned int Wq[VF_MAX_OLD + 2];
 #pragma unroll
   for (int q = 0; q < VF_MAX_OLD + 2; ++q) {
@@ -2066,7 +2264,7 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
     if (q <= a && have_word) Wq[q] = plane_bits(ra, h, q)[wi];
   }
   v4f V[U], VZ[U];   // (VZ[0 .. S): unused)
-  const int wv_u = __builtin_amdgcn_readfirstlane(wv);
+  const int wv_u = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int o = u * SPAN + o0;
@@ -2083,17 +2281,9 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
   for (int s = VF_MAX_OLD + 1; s >= 1; --s)
     if (s <= a) Wq[s] ^= Wq[s - 1];
   // the lanes' own nibbles of every span, 8 to a register
-  const int src = lane >> 3;               // + 8*u: the lane that holds this lane's word of span u
-  const unsigned int sh = 4u * (lane & 7);
 #pragma unroll
-  for (int q = 0; q < VF_MAX_OLD + 2; ++q) {
-    if (q <= a) {   // uniform
-      unsigned int packed = 0u;
-#pragma unroll
-      for (int u = 0; u < U; ++u) packed |= ((__shfl(Wq[q], 8 * u + src, WAVE) >> sh) & 15u) << (4 * u);
-      Wq[q] = packed;
-    }
-  }
+  for (int q = 0; q < VF_MAX_OLD + 2; ++q)
+    if (q <= a) Wq[q] = lane_nibbles(Wq[q]);   // uniform
 #pragma unroll
   for (int s = VF_MAX_OLD + 1; s >= 1; --s) {
     if (s <= a) {   // uniform: the step from plane s to plane s-1

@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <cstdint>
 #include <limits>
+#include <numeric>
 #include <vector>
 
 #ifndef OB_BIG_MIN_TILES
@@ -233,66 +234,97 @@ inline BigRule trail_rule(bool wait, int32_t cap, int cus) {
 }
 
 // The workgroups of k_warmup_trail in order (no HIP call).  n, begin: parts of each layer.  lag > 0: one launch, the
-// update of a layer `lag` moments parts after the layer's last one: what is in flight on the device then (8 workgroups a
+// update of a layer from `lag` moments parts after the layer's last one on: what is in flight on the device then (8 workgroups a
 // CU; trail_lag: 10) lies between them, so that no update waits for long (half of that 2 % slower, twice no difference).  lag = 0: no update
 // waits; the layers are taken in groups of at least `group` parts (16.8 M elements; 33 M no difference), and a launch updates one
 // group and forms the moments of the next.
+// Updates and moments take turns, TRAIL_BATCH of each at a time (of the updates the more, the more are due: one batch for
+// every `spread` of them), so that at any time the device reads and writes alike; batches are a multiple of the 8 XCDs,
+// to which consecutive workgroups go in turn: one by one, all updates would be half of the XCDs'.
 // A layer of more than TRAIL_KEEP_PARTS parts (16.8 M elements, 200 MB of m, v and x) does not fit the cache: its last
-// parts are updated first, and only they are kept.
-constexpr int64_t TRAIL_GROUP = 8192, TRAIL_KEEP_PARTS = 8192;
+// parts are updated first, and only they are kept; the moments of the next layer wait for all of its updates (spread_large: they do not).
+// A LAMB step, us, a layer's updates all at once / in batches of 32, one for every 2048 (of 8: 7360 to 7560; every 4096, 8192, 16384 in batches of 8:
+// 7430, 7670, 9030): the GPT list of 1.3e9 parameters 7350-7416 / 7240-7315, 5000 x 8 1156 / 1142, 3600 x 3 236.4 / 233.4, 3300 x 2
+// 141.2 / 139.8; layers beyond the cache, spread too: 7000 x 6 1825 / 1843, 10000 x 4 2631 / 2653.
+constexpr int64_t TRAIL_GROUP = 8192, TRAIL_KEEP_PARTS = 8192, TRAIL_SPREAD = 2048, TRAIL_BATCH = 32;
 inline int64_t trail_lag(int cus) { return 10 * (int64_t)cus; }
 inline void trail_items(const std::vector<int>& n, const std::vector<int>& begin, int64_t lag, int64_t group,
-                 std::vector<unsigned int>* items, std::vector<int64_t>* item_end) {
+                 std::vector<unsigned int>* items, std::vector<int64_t>* item_end, int64_t keep_parts = TRAIL_KEEP_PARTS,
+                 int64_t spread = TRAIL_SPREAD, bool spread_large = false) {
   items->clear();
   item_end->clear();
-  auto moments = [&](int64_t l) {
-    const int64_t keep = n[(size_t)l] - std::min<int64_t>(n[(size_t)l], TRAIL_KEEP_PARTS);
-    for (int64_t j = 0; j < n[(size_t)l]; ++j)
-      items->push_back((unsigned int)(begin[(size_t)l] + j) | (j >= keep ? TRAIL_KEEP : 0u));
-  };
+  std::vector<unsigned int> due;   // the updates that may run, in order; due[0 .. at) are in the list
+  size_t at = 0, at_once = 0;      // due[at .. at_once): not spread
+  auto kept_from = [&](int64_t l) { return n[(size_t)l] - std::min<int64_t>(n[(size_t)l], keep_parts); };
   auto update = [&](int64_t l) {
-    const int64_t keep = n[(size_t)l] - std::min<int64_t>(n[(size_t)l], TRAIL_KEEP_PARTS);
-    for (int64_t j = keep; j < n[(size_t)l]; ++j) items->push_back((unsigned int)(begin[(size_t)l] + j) | TRAIL_UPDATE);
-    for (int64_t j = 0; j < keep; ++j) items->push_back((unsigned int)(begin[(size_t)l] + j) | TRAIL_UPDATE);
+    const int64_t keep = kept_from(l);
+    for (int64_t j = keep; j < n[(size_t)l]; ++j) due.push_back((unsigned int)(begin[(size_t)l] + j) | TRAIL_UPDATE);
+    for (int64_t j = 0; j < keep; ++j) due.push_back((unsigned int)(begin[(size_t)l] + j) | TRAIL_UPDATE);
+    if (keep > 0 && !spread_large) at_once = due.size();
+  };
+  auto take = [&](int64_t k) {
+    for (; k > 0 && at < due.size(); --k) items->push_back(due[at++]);
   };
   std::vector<int64_t> layers;
   for (size_t l = 0; l < n.size(); ++l)
     if (n[l] > 0) layers.push_back((int64_t)l);
   if (layers.empty()) return;
-  if (lag > 0) {
-    size_t done = 0;   // layers whose update is in the list
-    for (size_t i = 0; i < layers.size(); ++i) {
-      const size_t first = items->size();
-      moments(layers[i]);
-      // the updates that become due among this layer's moments parts go in between
-      const std::vector<unsigned int> tiles(items->begin() + (int64_t)first, items->end());
-      items->resize(first);
-      const int64_t at0 = begin[(size_t)layers[i]];   // moments parts before this layer
-      size_t j = 0;
-      for (; done < i; ++done) {
-        const int64_t due = begin[(size_t)layers[done]] + n[(size_t)layers[done]] + lag;
-        if (due > at0 + (int64_t)tiles.size()) break;
-        for (; at0 + (int64_t)j < due; ++j) items->push_back(tiles[j]);
-        update(layers[done]);
-      }
-      for (; j < tiles.size(); ++j) items->push_back(tiles[j]);
+  size_t done = 0, launched = 0;   // layers whose update is due; whose moments lie in earlier launches
+  int64_t pos = 0, in_group = 0;   // moments parts in the list; of the present group
+  for (size_t i = 0; i < layers.size(); ++i) {
+    const int64_t l = layers[i], keep = kept_from(l);
+    if (lag == 0 && in_group >= group) {
+      take((int64_t)due.size());
+      item_end->push_back((int64_t)items->size());
+      launched = i;
+      in_group = 0;
     }
-    for (; done < layers.size(); ++done) update(layers[done]);
-    item_end->push_back((int64_t)items->size());
-    return;
+    in_group += n[(size_t)l];
+    for (int64_t j = 0; j < n[(size_t)l]; ++j) {
+      items->push_back((unsigned int)(begin[(size_t)l] + j) | (j >= keep ? TRAIL_KEEP : 0u));
+      ++pos;
+      while (done < (lag > 0 ? layers.size() : launched) &&
+             (lag == 0 || begin[(size_t)layers[done]] + n[(size_t)layers[done]] + lag <= pos))
+        update(layers[done++]);
+      const int64_t pending = (int64_t)(due.size() - at);
+      if (at < at_once) take((int64_t)(at_once - at));
+      else if (pos % TRAIL_BATCH == 0) take((pending + spread - 1) / spread * TRAIL_BATCH);
+    }
   }
-  size_t from = 0, updated = 0;
-  while (from < layers.size()) {
-    size_t to = from;
-    int64_t tiles = 0;
-    while (to < layers.size() && tiles < group) tiles += n[(size_t)layers[to++]];
-    for (; updated < from; ++updated) update(layers[updated]);
-    for (size_t i = from; i < to; ++i) moments(layers[i]);
+  if (lag == 0) {
+    take((int64_t)due.size());
     item_end->push_back((int64_t)items->size());
-    from = to;
   }
-  for (; updated < layers.size(); ++updated) update(layers[updated]);
+  while (done < layers.size()) update(layers[done++]);
+  take((int64_t)due.size());
   item_end->push_back((int64_t)items->size());
+}
+
+// k_ratios_trail: whole tiles for the ratio pass, in parts of RATIOS_TRAIL_U spans for the update, in the same order (what the cache is to
+// hold is v_frozen alone).  Four steps, us, k_ratios_big_hist and k_decompress_apply / k_ratios_trail (256 CUs): squares of
+// 3300 x 2 571 / 557, 3600 x 3 933 / 908, 5000 x 2 1179 / 1137, 5000 x 8 4400 / 4228, 7000 x 6 6438 / 6335, 20000 x 2 17990 / 17760, the
+// GPT list of 1.3e9 parameters 27900 / 26400, lists of its shape with one block, three quarters of their large layers one word embedding,
+// 2749 / 2715, 3225 / 3175, 3608 / 3555; but with no other large layer, in which to spread the embedding's update, 110 M 2301 / 2310,
+// 336 M 6728 / 6761.  So it is taken where an eighth of the large layers' tiles lies outside the largest of them (and there are more
+// than a lowered limit of the barrier kernel may leave).
+// GPT list, by the order: a layer's updates all at once 27590, parts of 2 spans in that 28160; one by one in turn with the ratio pass 28380 (the XCDs; see
+// above), in batches 26550, 26470, 26660 with parts of 8, 4 and 2 spans; batches of 64, one for every 1024 or 4096, lag of 1 to 12, and
+// 4096 to 8192 kept: 26440 to 26760.
+constexpr int64_t RATIOS_TRAIL_KEEP = 6144, RATIOS_TRAIL_SPREAD = 2048;
+constexpr int RATIOS_TRAIL_U = 4;
+constexpr unsigned int RATIOS_TRAIL_PART = 1u << 27;   // the part, above the tile's position
+inline bool ratios_trail(const std::vector<int>& n, int cus) {
+  const int64_t total = std::accumulate(n.begin(), n.end(), (int64_t)0), most = n.empty() ? 0 : *std::max_element(n.begin(), n.end());
+  return total >= 4 * (int64_t)cus && total < (int64_t)RATIOS_TRAIL_PART && 8 * (total - most) >= total;
+}
+inline void ratios_trail_items(const std::vector<int>& n, const std::vector<int>& begin, int cus, std::vector<unsigned int>* items) {
+  std::vector<unsigned int> tiles;
+  std::vector<int64_t> end;
+  trail_items(n, begin, 6 * (int64_t)cus, 0, &tiles, &end, RATIOS_TRAIL_KEEP, RATIOS_TRAIL_SPREAD, true);
+  items->clear();
+  for (unsigned int i : tiles)
+    for (unsigned int part = 0; part < ((i & TRAIL_UPDATE) ? 8u / RATIOS_TRAIL_U : 1u); ++part)
+      items->push_back((i & ~TRAIL_KEEP) | part * RATIOS_TRAIL_PART);
 }
 
 // Group counters of a barrier with n arrivals, and of the barriers of L layers with n together (group_line).

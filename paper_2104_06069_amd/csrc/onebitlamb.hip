@@ -94,6 +94,7 @@ enum KernelId {
   KID_WARMUP_SMALL,
   KID_VARIANCE_DENSE,
   KID_RATIOS_BIG_HIST,
+  KID_RATIOS_TRAIL,
   KID_MOMENTUM_DENSE,
   KID_ERROR_DENSE,
   KID_MOMENTUM_SCALE,
@@ -109,7 +110,7 @@ enum KernelId {
 const char* const kKernelNames[KID_COUNT] = {
     "momentum_z_sumsq", "compress_resident", "chunk_scale",     "sign_pack_error", "compress_deferred", "server_unpack_avg",
     "server_scale",     "server_sign_pack", "server_resident", "ratios_pass",     "ratios_finalize",
-    "decompress_apply", "ratios_apply_resident", "ratios_apply_hist", "ratios_apply_hist_lds", "ratios_apply_small", "warmup_small", "variance_dense", "ratios_big_hist", "momentum_dense", "error_dense", "momentum_scale", "warmup_moments",   "warmup_coeff",    "warmup_apply",
+    "decompress_apply", "ratios_apply_resident", "ratios_apply_hist", "ratios_apply_hist_lds", "ratios_apply_small", "warmup_small", "variance_dense", "ratios_big_hist", "ratios_trail", "momentum_dense", "error_dense", "momentum_scale", "warmup_moments",   "warmup_coeff",    "warmup_apply",
     "warmup_resident",  "warmup_trail", "fill",            "copy"};
 
 // Single-launch form of a list whose tiles all fit on the device at once (k_ratios_apply_small,
@@ -169,6 +170,7 @@ struct LayerSplit {
   int one_level = ARRIVE_ONE_LEVEL;        // arrivals of a layer that are counted in one level
   bool trail_wait = false;
   unsigned int* d_items = nullptr;
+  int n_items = 0;
   std::vector<int64_t> item_end;
   int* d_big_n = nullptr;                  // [L] big tiles of each layer
   int* d_big_begin = nullptr;              // [L] position of the first
@@ -178,6 +180,10 @@ struct LayerSplit {
   unsigned int* d_count = nullptr;         // [counters] lines
   double* d_sub_sums = nullptr;            // [2 * counters]
   double* d_part_sums = nullptr;           // [2 * parts]
+  // k_ratios_trail over them, the same way
+  bool ratios_trail = false;
+  float* d_sub_max = nullptr;              // [counters]
+  float* d_tile_max = nullptr;             // [big tiles]
   unsigned long long* d_trail_flag = nullptr;   // [L]
   unsigned char* d_has_tiles = nullptr;    // [L] 1 for layers with listed or big tiles
   // k_ratios_apply_hist with the plain ratio pass in its launch (LayerSync), which counts arrivals of its own
@@ -495,14 +501,23 @@ void build_split(ob_lamb_ctx* ctx, Workspace* ws, const Tiling& tl, int tile_lb,
   sp->n_rest_ratio_tiles = (int)pl.rest_ratio_tiles.size();
   lagging->assign((size_t)tm.n_tiles, 0);
   for (int t : cov) (*lagging)[(size_t)t] = 1;
-  if (trail && sp->big_on) {
-    static_assert(TILE_WU == 8 * SPAN, "k_warmup_trail's tiles");
+  sp->one_level = arrivals_one_level(sp->n_fused_tiles, cus);
+  sp->trail_wait = max_tiles > 0;
+  // (where both are possible, four steps, us, rest_in_launch / k_ratios_trail: 3880 large and 560 listed tiles 904 / 894, 3800 and 1150
+  // 960 / 955, 2500 and 2030 903 / 910)
+  const bool rest = !trail && rest_in_launch(sp->n_rest_ratio_tiles, sp->n_fused_tiles, sp->n_big_tiles, cus);
+  sp->ratios_trail = !trail && sp->trail_wait && ratios_trail(pl.big_n, cus) && (!rest || sp->n_big_tiles >= 3 * sp->n_fused_tiles);
+  sp->rest_in_launch = rest && !sp->ratios_trail;
+  if ((trail && sp->big_on) || sp->ratios_trail) {
+    static_assert(TILE_WU == 8 * SPAN && TILE_LB == 8 * SPAN, "tiles of k_warmup_trail and k_ratios_trail");
+    const int parts = trail ? TRAIL_PARTS : 1;   // of a tile
     std::vector<int> n = pl.big_n, begin = pl.big_begin;   // in parts
-    for (int& q : n) q *= TRAIL_PARTS;
-    for (int& q : begin) q *= TRAIL_PARTS;
+    for (int& q : n) q *= parts;
+    for (int& q : begin) q *= parts;
     std::vector<unsigned int> items;
-    sp->trail_wait = max_tiles > 0;
-    trail_items(n, begin, sp->trail_wait ? trail_lag(cus) : 0, TRAIL_GROUP, &items, &sp->item_end);
+    if (trail) trail_items(n, begin, sp->trail_wait ? trail_lag(cus) : 0, TRAIL_GROUP, &items, &sp->item_end);
+    else ratios_trail_items(n, begin, cus, &items);
+    sp->n_items = (int)items.size();
     ws->upload(&sp->d_items, std::move(items));
     std::vector<int> count0((size_t)L, 0);
     std::vector<unsigned char> has_tiles = pl.has_listed;
@@ -520,12 +535,15 @@ void build_split(ob_lamb_ctx* ctx, Workspace* ws, const Tiling& tl, int tile_lb,
     ws->upload(&sp->d_big_seg_first, std::move(pl.big_seg_first));
     ws->upload(&sp->d_big_seg_end, std::move(pl.big_seg_end));
     ws->alloc_zero(&sp->d_count, (size_t)counters * 2 * CTR_STRIDE);
-    ws->alloc_zero(&sp->d_sub_sums, 2 * (size_t)counters);
-    ws->alloc_zero(&sp->d_part_sums, 2 * (size_t)TRAIL_PARTS * (size_t)sp->n_big_tiles);
+    if (trail) {
+      ws->alloc_zero(&sp->d_sub_sums, 2 * (size_t)counters);
+      ws->alloc_zero(&sp->d_part_sums, 2 * (size_t)TRAIL_PARTS * (size_t)sp->n_big_tiles);
+    } else {
+      ws->alloc_zero(&sp->d_sub_max, (size_t)counters);
+      ws->alloc_zero(&sp->d_tile_max, (size_t)sp->n_big_tiles);
+    }
     ws->alloc_zero(&sp->d_trail_flag, (size_t)L);
   }
-  sp->one_level = arrivals_one_level(sp->n_fused_tiles, cus);
-  sp->rest_in_launch = !trail && rest_in_launch(sp->n_rest_ratio_tiles, sp->n_fused_tiles, sp->n_big_tiles, cus);
   if (sp->rest_in_launch) {
     ArrivalPlan ap;
     plan_arrivals(pl, tm, L, &ap);
@@ -658,6 +676,14 @@ ListedTiles listed_tiles(const ob_lamb_ctx* ctx, const LayerSplit& sp) {
   lt.seg_first = sp.d_seg_first; lt.seg_end = sp.d_seg_end; lt.layer_seg0 = ctx->d_layer_seg0;
   lt.n_c = ctx->n_c; lt.tpc = sp.tpc; lt.tpc_span = ctx->tpc;
   lt.one_level = sp.one_level;
+  return lt;
+}
+
+// ... of the layers that are too large for the barrier kernel
+ListedTiles big_tiles(const ob_lamb_ctx* ctx, const LayerSplit& sp) {
+  ListedTiles lt = listed_tiles(ctx, sp);
+  lt.tile_list = sp.d_big_tiles; lt.list_begin = sp.d_big_begin; lt.n_listed = sp.d_big_n;
+  lt.seg_first = sp.d_big_seg_first; lt.seg_end = sp.d_big_seg_end;
   return lt;
 }
 
@@ -1210,9 +1236,7 @@ ob_status ob_lamb_warmup_step_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st, cons
   // 2. the layers that are too large for the kernel with the per-layer barrier
   if (sp.big_on) {
     TrailTab tt;
-    tt.lt = listed_tiles(ctx, sp);
-    tt.lt.tile_list = sp.d_big_tiles; tt.lt.list_begin = sp.d_big_begin; tt.lt.n_listed = sp.d_big_n;
-    tt.lt.seg_first = sp.d_big_seg_first; tt.lt.seg_end = sp.d_big_seg_end;
+    tt.lt = big_tiles(ctx, sp);
     tt.count0 = sp.d_count0; tt.count = sp.d_count; tt.sub_sums = sp.d_sub_sums; tt.part_sums = sp.d_part_sums;
     tt.flag = sp.d_trail_flag; tt.seg_sums = ctx->d_seg_sums;
     tt.errflag = ctx->d_errflag; tt.spin_limit = ctx->spin_limit; tt.wait = sp.trail_wait ? 1 : 0;
@@ -1589,15 +1613,28 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
   const bool rest_in_launch = sp.on && sp.rest_in_launch;
   const VTerms vt = vterms(ctx);   // (vt.t = NULL where the ratio pass runs in the barrier kernel's launch)
   if (!rest_in_launch) {
-    const int n_lead_vt = (ctx->n_pairs + BLOCK - 1) / BLOCK;
+    const int n_flags = sp.ratios_trail ? (int)ctx->L : 0;
+    const int n_lead_vt = (std::max(ctx->n_pairs, n_flags) + BLOCK - 1) / BLOCK;
     dispatch1(hk, [&](auto k_) {
       OB_LAUNCH(la, KID_RATIOS_PASS, (k_ratios_pass_vterms<U_MAIN, decltype(k_)::value>),
                 sp.n_rest_ratio_tiles + n_lead_vt, ra, ctx->d_seg_max, ctx->n_c, ctx->tpc, lt, ctx->d_tile_seg0,
-                ctx->d_seg_layer, sp.d_rest_ratio_tiles, vh, vt, ctx->d_vterms, n_lead_vt);
+                ctx->d_seg_layer, sp.d_rest_ratio_tiles, vh, vt, ctx->d_vterms, n_lead_vt, sp.d_trail_flag, n_flags);
     });
   }
-  // launch 2: ratio pass of the layers that are too large for the barrier kernel, from the history
-  if (sp.big_on)
+  // launch 2: the layers that are too large for the barrier kernel: ratio pass from the history and update, or the ratio pass alone
+  if (sp.ratios_trail) {
+    RatioTrailTab tt;
+    tt.items = sp.d_items;
+    tt.lt = big_tiles(ctx, sp);
+    tt.count0 = sp.d_count0; tt.count = sp.d_count; tt.sub_max = sp.d_sub_max; tt.tile_max = sp.d_tile_max;
+    tt.flag = sp.d_trail_flag; tt.seg_max = ctx->d_seg_max; tt.errflag = ctx->d_errflag; tt.spin_limit = ctx->spin_limit;
+    tt.c_avg = st->c_avg; tt.r_prev = st->r_prev; tt.coeff_c = st->coeff_c;
+    tt.one_m_thr = ctx->one_m_thr; tt.one_p_thr = ctx->one_p_thr; tt.r_min = ctx->r_min; tt.r_max = ctx->r_max;
+    dispatch2(hk, xl.p != nullptr, [&](auto k_, auto lx) {
+      OB_LAUNCH(la, KID_RATIOS_TRAIL, (k_ratios_trail<decltype(k_)::value, decltype(lx)::value>), sp.n_items, ra, vh, vt,
+                aa, tt, lt);
+    });
+  } else if (sp.big_on)
     dispatch1(hk, [&](auto k_) {
       OB_LAUNCH(la, KID_RATIOS_BIG_HIST, (k_ratios_big_hist<decltype(k_)::value>), sp.n_big_tiles, ra, vh, vt, ctx->d_seg_max,
                 sp.d_big_tiles, ctx->n_c, sp.tpc, ctx->tpc, lt, ctx->d_tile_seg0);
@@ -1605,8 +1642,9 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
   if (!sp.on) {
     OB_LAUNCH_B(la, KID_RATIOS_FINALIZE, k_ratios_finalize, (int)ctx->L, FBLOCK, ctx->d_seg_max,
                 ctx->d_layer_seg0, st->c_avg, st->r_prev, st->coeff_c, ctx->one_m_thr, ctx->one_p_thr,
-                ctx->r_min, ctx->r_max, (const unsigned char*)nullptr);
-    launch_apply(la, ctx, st, packed_all, server_scales, lr, nullptr, ctx->n_tiles, xl);
+                ctx->r_min, ctx->r_max, (const unsigned char*)(sp.ratios_trail ? sp.d_has_tiles : nullptr));
+    if (sp.ratios_trail) launch_apply(la, ctx, st, packed_all, server_scales, lr, sp.d_rest_ratio_tiles, sp.n_rest_ratio_tiles, xl);
+    else launch_apply(la, ctx, st, packed_all, server_scales, lr, nullptr, ctx->n_tiles, xl);
     return la.ok ? OB_OK : OB_ERR_HIP;
   }
   // launch 3: the barrier kernel; its leading workgroups run launch 1's pass or finish the layers without listed tiles
@@ -1618,6 +1656,7 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
   ls.c_avg = st->c_avg; ls.r_prev = st->r_prev; ls.coeff_c = st->coeff_c;
   ls.one_m_thr = ctx->one_m_thr; ls.one_p_thr = ctx->one_p_thr; ls.r_min = ctx->r_min; ls.r_max = ctx->r_max;
   ls.n_lead = (sp.n_layers < ctx->L) ? (int)ctx->L : 0;
+  if (sp.ratios_trail) ls.done = sp.d_has_tiles;
   if (rest_in_launch) {
     ls.n_alone = sp.n_alone; ls.n_lead = sp.n_alone + sp.n_rest_ratio_tiles;
     ls.rest_tiles = sp.d_rest_ratio_tiles; ls.alone = sp.d_alone; ls.arr0 = sp.d_arr0;
@@ -1633,7 +1672,8 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
                 sp.n_fused_tiles + ls.n_lead, ra, vh, vt, aa, ls, lt);
     });
   });
-  launch_apply(la, ctx, st, packed_all, server_scales, lr, sp.d_rest_tiles, sp.n_rest_tiles, xl);
+  if (sp.ratios_trail) launch_apply(la, ctx, st, packed_all, server_scales, lr, sp.d_rest_ratio_tiles, sp.n_rest_ratio_tiles, xl);
+  else launch_apply(la, ctx, st, packed_all, server_scales, lr, sp.d_rest_tiles, sp.n_rest_tiles, xl);
   return la.ok ? OB_OK : OB_ERR_HIP;
 }
 
@@ -1754,7 +1794,7 @@ ob_status ob_lamb_check_device_status(ob_lamb_ctx* ctx, void* hip_stream) {
   (void)hipMemset(ctx->d_flag_srv, 0, sizeof(unsigned long long));
   for (LayerSplit* sp : {&ctx->sp_apply, &ctx->sp_warm}) {
     sp->on = false;
-    sp->big_on = false;   // (no wait in that pass; but after an expiry every call takes the plain kernels)
+    sp->big_on = sp->ratios_trail = false;   // (after an expiry every call takes the plain kernels)
     (void)hipMemset(sp->d_counter, 0, line * (size_t)ctx->L);
     (void)hipMemset(sp->d_sub, 0, line * group_lines(sp->n_fused_tiles, ctx->L));
     (void)hipMemset(sp->d_flag, 0, sizeof(unsigned long long) * (size_t)ctx->L);

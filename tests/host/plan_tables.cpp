@@ -96,6 +96,48 @@ void trail() {
   }
 }
 
+// k_ratios_trail: every tile once for the ratio pass and in all its parts for the update, those of a layer after its last tile
+// and some way behind it; updates next to each other in no more than batches while nothing large is due; and its rule.
+void ratios_trail_order() {
+  for (int it = 0; it < 200; ++it) {
+    std::vector<int> n, begin;
+    int at = 0;
+    const int L = (int)pick(1, 9);
+    for (int l = 0; l < L; ++l) {
+      const int64_t kinds[] = {0, pick(64, 300), pick(1017, 2100), pick(6000, 7000)};
+      n.push_back((int)kinds[rng() % 4]);
+      begin.push_back(n.back() ? at : 0);
+      at += n.back();
+    }
+    std::vector<unsigned int> items;
+    ratios_trail_items(n, begin, 256, &items);
+    const int parts = 8 / RATIOS_TRAIL_U;
+    CHECK((int64_t)items.size() == (int64_t)at * (1 + parts));
+    std::vector<int64_t> ratio((size_t)at, -1), first((size_t)at, -1);
+    std::vector<int> seen((size_t)at, 0);
+    int64_t n_ratio = 0;
+    for (unsigned int i : items) {
+      const unsigned int pos = i & (RATIOS_TRAIL_PART - 1u), part = (i & ~TRAIL_UPDATE) / RATIOS_TRAIL_PART;
+      CHECK((int)pos < at && (int)part < parts);
+      if (i & TRAIL_UPDATE) {
+        CHECK(seen[pos] == (1 << part) - 1);
+        seen[pos] |= 1 << part;
+        if (first[pos] < 0) first[pos] = n_ratio;
+      } else {
+        CHECK(part == 0 && ratio[pos] < 0);
+        ratio[pos] = n_ratio++;
+      }
+    }
+    for (size_t l = 0; l < n.size(); ++l)
+      for (int p = begin[l]; p < begin[l] + n[l]; ++p) {
+        CHECK(seen[(size_t)p] == (1 << parts) - 1);
+        CHECK(first[(size_t)p] >= std::min<int64_t>(ratio[(size_t)(begin[l] + n[l] - 1)] + 1 + 6 * 256, at));
+      }
+    const int64_t most = *std::max_element(n.begin(), n.end());
+    CHECK(ratios_trail(n, 256) == (at >= 1024 && 8 * (at - most) >= at));
+  }
+}
+
 // Which layers that rule takes: all those with enough whole tiles and not too many, or none at all below the total.
 void big_rule() {
   for (int it = 0; it < 150; ++it) {
@@ -231,7 +273,7 @@ void small_lists() {
 }  // namespace
 
 int main(int argc, char** argv) {
-  const struct { const char* name; void (*f)(); } checks[] = {{"trail", trail}, {"big_rule", big_rule}, {"arrivals", arrivals}, {"second_reads", second_reads},
+  const struct { const char* name; void (*f)(); } checks[] = {{"trail", trail}, {"ratios_trail", ratios_trail_order}, {"big_rule", big_rule}, {"arrivals", arrivals}, {"second_reads", second_reads},
                                                               {"small_lists", small_lists}};
   for (const auto& c : checks)
     if (argc == 2 && !strcmp(argv[1], c.name)) {

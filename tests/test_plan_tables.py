@@ -18,7 +18,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("check", ["trail", "big_rule", "arrivals", "second_reads", "small_lists"])
+@pytest.mark.parametrize("check", ["trail", "ratios_trail", "big_rule", "arrivals", "second_reads", "small_lists"])
 def test_plan(program, check):
     r = subprocess.run([program, check], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout == "ok\n", (r.stdout, r.stderr[-2000:])

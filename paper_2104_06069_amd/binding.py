@@ -118,7 +118,7 @@ def lib():
 
 
 def _addr(t):
-    if t is None or type(t) is int:
+    if type(t) is int or t is None:
         return t
     try:
         data_ptr = t.data_ptr
@@ -136,7 +136,7 @@ def make_state(**buffers):
 
 
 def _check(status, ctx, where):
-    if status != OB_OK:
+    if status:      # (OB_OK is 0)
         detail = lib().ob_lamb_last_hip_error(ctx).decode() if ctx else ""
         raise ObLambError(status, where, detail)
 

@@ -504,9 +504,10 @@ void build_split(ob_lamb_ctx* ctx, Workspace* ws, const Tiling& tl, int tile_lb,
   sp->one_level = arrivals_one_level(sp->n_fused_tiles, cus);
   sp->trail_wait = max_tiles > 0;
   // (where both are possible, four steps, us, rest_in_launch / k_ratios_trail: 3880 large and 560 listed tiles 904 / 894, 3800 and 1150
-  // 960 / 955, 2500 and 2030 903 / 910)
+  // 960 / 955, 2500 and 2030 903 / 910; the line: three times the listed tiles and 12 tiles a CU)
   const bool rest = !trail && rest_in_launch(sp->n_rest_ratio_tiles, sp->n_fused_tiles, sp->n_big_tiles, cus);
-  sp->ratios_trail = !trail && sp->trail_wait && ratios_trail(pl.big_n, cus) && (!rest || sp->n_big_tiles >= 3 * sp->n_fused_tiles);
+  sp->ratios_trail = !trail && sp->trail_wait && ratios_trail(pl.big_n, cus) &&
+                     (!rest || (sp->n_big_tiles >= 3 * sp->n_fused_tiles && sp->n_big_tiles >= 12 * cus));
   sp->rest_in_launch = rest && !sp->ratios_trail;
   if ((trail && sp->big_on) || sp->ratios_trail) {
     static_assert(TILE_WU == 8 * SPAN && TILE_LB == 8 * SPAN, "tiles of k_warmup_trail and k_ratios_trail");

@@ -13,11 +13,12 @@ from workloads import foreign_server_chunks, foreign_worker_chunks, gradient  # 
 pytestmark = pytest.mark.gpu
 
 T = 8192
-LISTS = {   # sizes, workers (the barrier kernel's layers: up to 8 tiles)
+LISTS = {   # sizes, workers (the barrier kernel's layers: up to 8 tiles; with enough tiles in none of the kernels' layers that the plain ratio
+    # pass is a launch of its own, or no listed layer)
     # the second layer's tiles are fewer than what the updates lag behind; layers of the other kernels between them, an empty one
-    "two_layers": ([300, 900 * T + 5, 0, 5 * T + 1, 150 * T - 1, 100_003, 3], 1),
+    "two_layers": ([300, 900 * T + 5, 0, 5 * T + 1, 150 * T - 1, 60 * T, 100_003, 50 * T, 55 * T, 3], 1),
     # chunk ends that cut tiles short, tensors that start anywhere; more tiles than that before the last one
-    "lagging": ([330 * T + 77 * i + 1 for i in range(7)] + [13, 3 * T], 61),
+    "lagging": ([330 * T + 77 * i + 1 for i in range(7)] + [13, 3 * T, 60 * T + 1, 59 * T, 58 * T], 61),
     # no layer of the barrier kernel
     "none_listed": ([520 * T, 600 * T + 4000], 3),
 }

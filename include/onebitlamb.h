@@ -400,7 +400,7 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
  * ob_lamb_ratios_apply and ob_lamb_warmup_step have such forms too (per chunk / per layer; on small
  * lists the last two are one launch in which all tiles of the list are resident); in
  * ob_lamb_warmup_step and ob_lamb_ratios_apply_hist, workgroups that update a large layer, and in the latter on lists of few tiles
- * those of a layer, also wait for workgroups of the same launch that were dispatched before them and wait for
+ * those of a layer and those that update what lies outside the 8192-element tiles, also wait for workgroups of the same launch that were dispatched before them and wait for
  * nothing themselves, which need not be resident together.  All forms compute the same operations in the same order per element; the two sum-of-squares
  * reductions add the same fp64 terms grouped by different tile sizes, so a scale or norm can differ
  * in its last binary32 bit between forms (about once in 10^8 reductions) -- within the 1e-6 bar,

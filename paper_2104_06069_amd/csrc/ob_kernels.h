@@ -1559,10 +1559,29 @@ struct LayerSync {
   const int* skip_end;
   const int* tile_seg0;
   const int* seg_layer;
+  // ... and the update of the rest tiles in its last workgroups (n_events = 0: a launch of its own)
+  int n_tiles;                  // workgroups before them
+  unsigned int n_events;        // after which every c_t is there (coefficient_events)
+  unsigned int* events;
+  unsigned long long* launches; // 2^32 * launches whose c_t were all there
+  unsigned int* tail_launches;  // [rest tiles] launches that the tile's update has been through
 };
+
+// One of those events (thread 0; its c_t have been stored at agent scope): the last one of the launch lets the updates go.
+__device__ __forceinline__ void coefficient_event(const LayerSync& ls) {
+  payload_before_arrival();
+  if (__hip_atomic_fetch_add(ls.events, 1u, __ATOMIC_RELAXED, OB_AGENT) + 1u != ls.n_events) return;
+  __hip_atomic_store(ls.events, 0u, __ATOMIC_RELAXED, OB_AGENT);
+  const unsigned long long n = __hip_atomic_load(ls.launches, __ATOMIC_RELAXED, OB_AGENT);   // (nobody else writes it)
+  __hip_atomic_store(ls.launches, n + (1ull << 32), __ATOMIC_RELAXED, OB_AGENT);
+}
+__device__ __forceinline__ void store_coeff(float* coeff_c, int l, float c) {
+  __hip_atomic_store(&coeff_c[l], c, __ATOMIC_RELAXED, OB_AGENT);
+}
 
 // All of layer l's maxima, the two clips (lines 18-19), and the publication of c_t (a layer that is one segment of a rest
 // tile has no barrier): by the whole workgroup that arrived last of n.
+template <bool REST = false>
 __device__ __forceinline__ void layer_finish(const LayerSync& ls, int l, const LayerParts& lp, float rp, float ca, int n,
                                              unsigned int want, float* lds) {
   float q = 0.0f;
@@ -1588,6 +1607,10 @@ __device__ __forceinline__ void layer_finish(const LayerSync& ls, int l, const L
                                       ls.one_p_thr, ls.r_min, ls.r_max);
     if (n > 1 || lp.nl > 0)
       (void)barrier_publish(&ls.flag[l], &ls.counter[(int64_t)l * CTR_STRIDE], n, want, __float_as_uint(c), ls.lt.one_level);
+    if (REST && ls.n_events) {
+      store_coeff(ls.coeff_c, l, c);
+      coefficient_event(ls);
+    }
   }
 }
 
@@ -1595,6 +1618,7 @@ __device__ __forceinline__ void layer_finish(const LayerSync& ls, int l, const L
 // tile_list) and arrives; if this was the layer's last arrival, finishes the layer.  All threads call; r is valid
 // in thread 0.  lp, rp, ca: the layer's ranges, r_prev[l] and c_avg[l], read at the start of the kernel; first, n: the
 // layer's first arrival in the numbering of all, and how many it has.
+template <bool REST = false>
 __device__ __forceinline__ void layer_arrive(const LayerSync& ls, int bid, int l, const LayerParts& lp, int first, int n,
                                              float rp, float ca, float r, float* lds, unsigned long long* bc) {
   if (threadIdx.x == 0) {
@@ -1606,7 +1630,7 @@ __device__ __forceinline__ void layer_arrive(const LayerSync& ls, int bid, int l
   const bool last = ((*bc & 1ull) != 0ull);
   const unsigned int want = (unsigned int)(*bc >> 32);
   __syncthreads();
-  if (last) layer_finish(ls, l, lp, rp, ca, n, want, lds);
+  if (last) layer_finish<REST>(ls, l, lp, rp, ca, n, want, lds);
   // every thread leaves with the generation to wait for in *bc's high word (the last arriver too)
 }
 
@@ -1634,8 +1658,14 @@ __device__ __forceinline__ void rest_arrive(const LayerSync& ls, int tile, float
   for (int sg = s0 + 1 + (int)threadIdx.x; sg < s1 - 1; sg += BLOCK) {
     const int l = ls.seg_layer[sg];
     const float r = __hip_atomic_load(&ls.seg_max[sg], __ATOMIC_RELAXED, OB_AGENT);
-    (void)ratio_clip_commit(r, l, ls.r_prev[l], ls.c_avg[l], ls.r_prev, ls.coeff_c, ls.one_m_thr, ls.one_p_thr, ls.r_min,
-                            ls.r_max);
+    const float c = ratio_clip_commit(r, l, ls.r_prev[l], ls.c_avg[l], ls.r_prev, ls.coeff_c, ls.one_m_thr, ls.one_p_thr, ls.r_min,
+                                      ls.r_max);
+    store_coeff(ls.coeff_c, l, c);
+  }
+  if (ls.n_events && s1 - s0 > 2) {   // uniform
+    payload_before_arrival();
+    __syncthreads();
+    if (threadIdx.x == 0) coefficient_event(ls);
   }
   for (int q = 0; q < n_end; ++q) {   // uniform
     if ((bc[q] & 1ull) == 0ull) continue;
@@ -1643,7 +1673,69 @@ __device__ __forceinline__ void rest_arrive(const LayerSync& ls, int tile, float
     const LayerParts lp = layer_parts(ls.lt, l);
     int a, b;
     const int n = arrivals(lp, l, &a, &b);
-    layer_finish(ls, l, lp, ls.r_prev[l], ls.c_avg[l], n, (unsigned int)(bc[q] >> 32), lds);
+    layer_finish<true>(ls, l, lp, ls.r_prev[l], ls.c_avg[l], n, (unsigned int)(bc[q] >> 32), lds);
+  }
+}
+
+// The update of rest tile number i (whole workgroup), in the launch that forms its layers' c_t: everything is loaded and, in a tile inside one layer,
+// m_t/(sqrt(v_frozen)+eta) formed before the wait.  The tile's own count of launches says which one this is.
+template <bool HAS_K, bool LPX>
+__device__ __forceinline__ void rest_update(const ApplyArgs& aa, const LayerSync& ls, const LayerTab& lt, int i) {
+  const TilePos p = tile_pos<SPAN>(ls.lt.n_c, ls.lt.tpc_span, ls.rest_tiles[i]);
+  const int l0 = lt.first_layer[p.t];
+  const unsigned int want = ls.tail_launches[i] + 1u;
+  const float ss = aa.sscales[p.c];
+  const float kt = HAS_K ? lt.mom_scale[l0] : 1.0f;
+  const bool uniform = (p.tile0 + p.len <= lt.off[l0 + 1]);
+  const int o = threadIdx.x * 4;
+  unsigned int nib = 0u;
+  v4f X, VZ;
+  X = 0.0f; VZ = 0.0f;
+  if (o < p.len) {
+    nib = load_nibble(aa.packed, p.tile0);
+    VZ = ld4(aa.v_frozen + p.tile0 + o);
+    X = ld4(aa.x + p.tile0 + o);
+  }
+  if (uniform) {
+    UpdateTerm ut;
+    ut.start(HAS_K ? ss / kt : ss, aa.eta);
+    ut.see(VZ);
+    ut.terms(VZ, nib, 0, ut.in_range());
+  }
+  if (threadIdx.x == 0) {
+    (void)barrier_wait(ls.launches, want, ls.errflag, ls.spin_limit);
+    ls.tail_launches[i] = want;
+  }
+  __syncthreads();
+  if (o >= p.len) return;
+  auto coeff = [&](int l) { return __hip_atomic_load(&ls.coeff_c[l], __ATOMIC_RELAXED, OB_AGENT); };   // past this XCD's caches
+  if (uniform) {
+    const float a = aa.lr * coeff(l0);
+    v4f xn;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) xn[k] = X[k] - a * VZ[k];
+    st4(aa.x + p.tile0 + o, xn);
+    if (LPX) st4_lp(aa.x_lp, p.tile0, o, xn, aa.x_lp_bf16);
+    return;
+  }
+  const int64_t N = lt.off[lt.L];
+  int l = l0, cur = -1;
+  float sp = 0.0f, a = 0.0f;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int64_t j = p.tile0 + o + k;
+    if (j < N) {
+      l = walk_layer(l, j, lt.off);
+      if (l != cur) {
+        cur = l;
+        sp = HAS_K ? ss / lt.mom_scale[l] : ss;
+        a = aa.lr * coeff(l);
+      }
+      const float mt = ((nib >> k) & 1u) ? sp : -sp;
+      const float xn = X[k] - a * (mt / (sqrtf(VZ[k]) + aa.eta));
+      aa.x[j] = xn;
+      if (LPX) reinterpret_cast<unsigned short*>(aa.x_lp)[j] = float_to_lp(xn, aa.x_lp_bf16);
+    }
   }
 }
 
@@ -2229,8 +2321,13 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
       __shared__ unsigned long long bc_rest[2];
       const int lead = (int)blockIdx.x - ls.n_alone;
       if (lead < 0) {   // (uniform)
-        ratios_finalize_layer<BLOCK>(ls.alone[blockIdx.x], ls.seg_max, ls.lt.layer_seg0, ls.c_avg, ls.r_prev, ls.coeff_c,
+        const int l = ls.alone[blockIdx.x];
+        ratios_finalize_layer<BLOCK>(l, ls.seg_max, ls.lt.layer_seg0, ls.c_avg, ls.r_prev, ls.coeff_c,
                                      ls.one_m_thr, ls.one_p_thr, ls.r_min, ls.r_max, lds);
+        if (ls.n_events && threadIdx.x == 0) {
+          store_coeff(ls.coeff_c, l, ls.coeff_c[l]);   // (this thread's own)
+          coefficient_event(ls);
+        }
       } else {
         const int tile = ls.rest_tiles[lead];
         ratios_pass_tile<1, HAS_K, true, true, true>(ra, ls.seg_max, ls.lt.n_c, ls.lt.tpc_span, lt, ls.tile_seg0, ls.seg_layer,
@@ -2241,6 +2338,12 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
       lead_finalize(ls, lds);
     }
     return;
+  }
+  if constexpr (REST) {
+    if (bid >= ls.n_tiles) {   // (uniform)
+      rest_update<HAS_K, LPX>(aa, ls, lt, bid - ls.n_tiles);
+      return;
+    }
   }
   const int tpc = ls.lt.tpc;
   const TilePos p = tile_pos<TILE>(ls.lt.n_c, tpc, ls.lt.tile_list[bid]);
@@ -2310,7 +2413,7 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
   }
   const float r = block_max(mq.r, lds);
   // before any store: nothing to wait for
-  layer_arrive(ls, bid, l0, lp, first, REST ? layer_arrivals(lp.nl, lp.a, lp.s_first, lp.s_end, lp.b) : lp.nl, rp, ca, r,
+  layer_arrive<REST>(ls, bid, l0, lp, first, REST ? layer_arrivals(lp.nl, lp.a, lp.s_first, lp.s_end, lp.b) : lp.nl, rp, ca, r,
                lds, &bc);
   if (h.write_v) {   // uniform
 #pragma unroll

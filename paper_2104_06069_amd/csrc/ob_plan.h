@@ -337,8 +337,14 @@ inline size_t group_lines(int64_t n, int64_t L) { return arrival_groups(n) + (si
 // 2580 140.6 / 138.8; 433, 1713 110.1 / 109.3; 286, 3920 188.4 / 188.7; 1600, 4800 236.9 / 241.7; 647, 5135 242 / 239.7; 1297, 9677
 // 448 / 445; 710, 11239 501 / 511; 997, 25803 1134 / 1140; 1430, 40908 1716 / 1728.
 // (The line: 5 rest tiles and 20 tiles a CU.)
-inline bool rest_in_launch(int n_rest_tiles, int n_listed, int n_big, int cus) {
-  return n_listed > 0 && n_rest_tiles <= 5 * cus && n_listed + n_big <= 20 * cus;
+// Since the rest tiles' update is in that launch too, where there are no large tiles (four steps, us, a launch of its own / in that one: 11 M 319.5 / 309.8,
+// 30 M 692 / 681, 18 M with a 16-bit copy 507.5 / 500, 27 M 683.6 / 668.6, 4.2 M 187.0 / 180.4, five of 2800x2800 950.6 / 945.5), that line lies at
+// 40 tiles a CU for layers that leave room for others beside them (of at most 2 tiles a CU on average), us: 26 and 40 of 1300x1300 946.5 /
+// 930, 1388.6 / 1375.6; BERT shapes of 49 to 59 M 1068 / 1058, 1274 / 1262, with a 16-bit copy 1287 / 1263; a GPT shape of 75 M 1608 / 1602; but
+// eight of 2801x2801 1464 / 1479.
+inline bool rest_in_launch(int n_rest_tiles, int n_listed, int n_big, int cus, int64_t n_layers = 0 /* listed */) {
+  const int line = (n_big == 0 && n_listed <= 2 * cus * n_layers) ? 40 : 20;
+  return n_listed > 0 && n_rest_tiles <= 5 * cus && n_listed + n_big <= line * cus;
 }
 
 // Arrivals of a layer of the barrier kernels that are counted in one level, by their listed tiles.  (Figures at
@@ -382,6 +388,21 @@ inline void plan_arrivals(const SplitPlan& pl, const Tiling& tm, int64_t L, Arri
     if (n == 0) ap->alone.push_back((int)l);
     ap->n_arrivals += n;
   }
+}
+
+// The update of the rest tiles in that launch too: its last workgroups wait until every c_t is there.  How many events that takes: a
+// layer without arrivals; a layer that its last arrival finishes; a rest tile that finishes layers of its own between
+// its first and its last segment.
+inline int64_t coefficient_events(const SplitPlan& pl, const Tiling& tm, int64_t L, const ArrivalPlan& ap) {
+  std::vector<char> finished(pl.has_listed.begin(), pl.has_listed.end());   // by its last arrival
+  int64_t n = (int64_t)ap.alone.size();
+  for (int t : pl.rest_ratio_tiles) {
+    const int s0 = tm.tile_seg0[(size_t)t], s1 = tm.tile_seg0[(size_t)t + 1];
+    finished[(size_t)tm.seg_layer[(size_t)s0]] = finished[(size_t)tm.seg_layer[(size_t)s1 - 1]] = 1;
+    n += (s1 - s0 > 2);
+  }
+  for (int64_t l = 0; l < L; ++l) n += finished[(size_t)l];
+  return n;
 }
 
 // The tiles and segments of one SmallPlan (no HIP call).  lagging: per 1024-element span (tm's tiling).

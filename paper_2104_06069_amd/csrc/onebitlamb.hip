@@ -197,6 +197,10 @@ struct LayerSplit {
   unsigned long long* d_counter_rest = nullptr;
   unsigned long long* d_sub_rest = nullptr;
   unsigned long long* d_flag_rest = nullptr;
+  int64_t n_events = 0;                    // 0: the update of the rest tiles is a launch of its own
+  unsigned int* d_events = nullptr;
+  unsigned long long* d_launches = nullptr;
+  unsigned int* d_tail_launches = nullptr; // [rest tiles]
   int n_rest_ratio_tiles = 0;              // TILE_MAIN tiles outside the listed and the big tiles
   int* d_rest_ratio_tiles = nullptr;
   int n_cov_tiles = 0;                     // TILE_MAIN tiles inside the listed or the big tiles
@@ -505,7 +509,7 @@ void build_split(ob_lamb_ctx* ctx, Workspace* ws, const Tiling& tl, int tile_lb,
   sp->trail_wait = max_tiles > 0;
   // (where both are possible, four steps, us, rest_in_launch / k_ratios_trail: 3880 large and 560 listed tiles 904 / 894, 3800 and 1150
   // 960 / 955, 2500 and 2030 903 / 910; the line: three times the listed tiles and 12 tiles a CU)
-  const bool rest = !trail && rest_in_launch(sp->n_rest_ratio_tiles, sp->n_fused_tiles, sp->n_big_tiles, cus);
+  const bool rest = !trail && rest_in_launch(sp->n_rest_ratio_tiles, sp->n_fused_tiles, sp->n_big_tiles, cus, sp->n_layers);
   sp->ratios_trail = !trail && sp->trail_wait && ratios_trail(pl.big_n, cus) &&
                      (!rest || (sp->n_big_tiles >= 3 * sp->n_fused_tiles && sp->n_big_tiles >= 12 * cus));
   sp->rest_in_launch = rest && !sp->ratios_trail;
@@ -550,6 +554,12 @@ void build_split(ob_lamb_ctx* ctx, Workspace* ws, const Tiling& tl, int tile_lb,
     plan_arrivals(pl, tm, L, &ap);
     sp->n_arrivals = ap.n_arrivals;
     sp->n_alone = (int)ap.alone.size();
+    if (!sp->big_on && sp->n_rest_ratio_tiles > 0) {
+      sp->n_events = coefficient_events(pl, tm, L, ap);
+      ws->alloc_zero(&sp->d_events, 2 * CTR_STRIDE);
+      ws->alloc_zero(&sp->d_launches, CTR_STRIDE);
+      ws->alloc_zero(&sp->d_tail_launches, (size_t)sp->n_rest_ratio_tiles);
+    }
     ws->upload(&sp->d_alone, std::move(ap.alone));
     ws->upload(&sp->d_arr0, std::move(ap.arr0));
     ws->upload(&sp->d_skip_first, std::move(ap.skip_first));
@@ -1648,7 +1658,8 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
     else launch_apply(la, ctx, st, packed_all, server_scales, lr, nullptr, ctx->n_tiles, xl);
     return la.ok ? OB_OK : OB_ERR_HIP;
   }
-  // launch 3: the barrier kernel; its leading workgroups run launch 1's pass or finish the layers without listed tiles
+  // launch 3: the barrier kernel; its leading workgroups run launch 1's pass (its last ones then the update of the same tiles, where there
+  // are no large ones beside them) or finish the layers without listed tiles
   // (lines 18-20 from the segment maxima that launches 1 and 2 left), the others the listed tiles
   LayerSync ls{};
   ls.seg_max = ctx->d_seg_max; ls.listed_max = sp.d_listed_max; ls.lt = listed_tiles(ctx, sp);
@@ -1664,15 +1675,18 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
     ls.skip_first = sp.d_skip_first; ls.skip_end = sp.d_skip_end;
     ls.tile_seg0 = ctx->d_tile_seg0; ls.seg_layer = ctx->d_seg_layer;
     ls.counter = sp.d_counter_rest; ls.sub = sp.d_sub_rest; ls.flag = sp.d_flag_rest;
+    ls.n_tiles = sp.n_fused_tiles; ls.n_events = (unsigned int)sp.n_events; ls.events = sp.d_events; ls.launches = sp.d_launches;
+    ls.tail_launches = sp.d_tail_launches;
   }
   dispatch2(hk, xl.p != nullptr, [&](auto k_, auto lx) {
     dispatch2(sp.in_lds, rest_in_launch, [&](auto in_lds, auto rest) {
       OB_LAUNCH(la, sp.in_lds ? KID_RATIOS_APPLY_HIST_LDS : KID_RATIOS_APPLY_HIST,
                 (k_ratios_apply_hist<decltype(k_)::value, decltype(lx)::value, decltype(in_lds)::value ? S_LH : 0,
                                      decltype(rest)::value>),
-                sp.n_fused_tiles + ls.n_lead, ra, vh, vt, aa, ls, lt);
+                sp.n_fused_tiles + ls.n_lead + (ls.n_events ? sp.n_rest_ratio_tiles : 0), ra, vh, vt, aa, ls, lt);
     });
   });
+  if (ls.n_events) return la.ok ? OB_OK : OB_ERR_HIP;   // (the rest tiles are updated in that launch)
   if (sp.ratios_trail) launch_apply(la, ctx, st, packed_all, server_scales, lr, sp.d_rest_ratio_tiles, sp.n_rest_ratio_tiles, xl);
   else launch_apply(la, ctx, st, packed_all, server_scales, lr, sp.d_rest_tiles, sp.n_rest_tiles, xl);
   return la.ok ? OB_OK : OB_ERR_HIP;

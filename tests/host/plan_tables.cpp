@@ -220,6 +220,18 @@ void arrivals() {
       next += (int64_t)seen[i].size();
     }
     CHECK(next == ap.n_arrivals && line_end <= (int64_t)group_lines(ap.n_arrivals, s.L));
+    // what the last workgroups wait for, event by event: the arrivals in any order
+    std::vector<int> left((size_t)s.L);
+    for (int l = 0; l < s.L; ++l) left[(size_t)l] = (int)seen[(size_t)l].size() - pl.n_listed[(size_t)l];
+    int64_t events = (int64_t)ap.alone.size();
+    for (int l = 0; l < s.L; ++l) events += pl.n_listed[(size_t)l] > 0 && left[(size_t)l] == 0;
+    for (int tile : pl.rest_ratio_tiles) {
+      const int s0 = s.tm.tile_seg0[(size_t)tile], s1 = s.tm.tile_seg0[(size_t)tile + 1];
+      events += --left[(size_t)s.tm.seg_layer[(size_t)s0]] == 0;
+      if (s1 - s0 > 1) events += --left[(size_t)s.tm.seg_layer[(size_t)s1 - 1]] == 0;
+      events += s1 - s0 > 2;
+    }
+    CHECK(events == coefficient_events(pl, s.tm, s.L, ap));
   }
 }
 

@@ -180,8 +180,9 @@ struct LayerSplit {
   unsigned int* d_count = nullptr;         // [counters] lines
   double* d_sub_sums = nullptr;            // [2 * counters]
   double* d_part_sums = nullptr;           // [2 * parts]
+  bool hist_each_step = false;             // ob_lamb_ratios_apply takes ob_lamb_ratios_apply_hist's kernels
   // k_ratios_trail over them, the same way
-  bool ratios_trail = false;
+  bool ratios_trail = false, trail_even = false;   // trail_even: the largest of these layers is at most a quarter of them
   float* d_sub_max = nullptr;              // [counters]
   float* d_tile_max = nullptr;             // [big tiles]
   unsigned long long* d_trail_flag = nullptr;   // [L]
@@ -513,6 +514,7 @@ void build_split(ob_lamb_ctx* ctx, Workspace* ws, const Tiling& tl, int tile_lb,
   sp->ratios_trail = !trail && sp->trail_wait && ratios_trail(pl.big_n, cus) &&
                      (!rest || (sp->n_big_tiles >= 3 * sp->n_fused_tiles && sp->n_big_tiles >= 12 * cus));
   sp->rest_in_launch = rest && !sp->ratios_trail;
+  sp->trail_even = sp->big_on && 4 * (int64_t)*std::max_element(pl.big_n.begin(), pl.big_n.end()) <= sp->n_big_tiles;
   if ((trail && sp->big_on) || sp->ratios_trail) {
     static_assert(TILE_WU == 8 * SPAN && TILE_LB == 8 * SPAN, "tiles of k_warmup_trail and k_ratios_trail");
     const int parts = trail ? TRAIL_PARTS : 1;   // of a tile
@@ -714,6 +716,21 @@ constexpr int LH_LDS_MIN_ROUNDS = 2, LH_LDS_MAX_ROUNDS = 6;
 bool lh_in_lds(int64_t n_tiles, int cus) {
   const int64_t r = (int64_t)OB_LB_MINW * cus, l = (int64_t)LH_WG_LDS * cus;
   return (n_tiles > r && n_tiles <= l) || (n_tiles >= LH_LDS_MIN_ROUNDS * r && n_tiles <= LH_LDS_MAX_ROUNDS * l);
+}
+
+// Whether ob_lamb_ratios_apply, which rewrites the variance at every step, takes ob_lamb_ratios_apply_hist's kernels with no history: the
+// same bytes, in fewer launches or in the form of the kernel that the list's rounds favour.  A step, us, k_ratios_apply_resident and the plain
+// kernels around it / these (256 CUs):
+//   rest tiles' passes in the launch: 4.2 M 50.4 / 41.5, 11 M 95.3 / 81.4, 15 M 117 / 110, 30 M 190.7 / 182, 49 M with a 16-bit copy 315.5 / 298.5
+//   v_frozen in LDS: 21 M 135.2 / 134.4, 32 M 201 / 192, 42 M 252.3 / 247, 63 M 378.6 / 367
+//   neither: 4.2 M without rest tiles 39.8 / 40.5, 260 M 1422.4 / 1423.8, 215 M with a 16-bit copy 1254 / 1262, 314 M 1785.6 / 1790.5
+//   k_ratios_trail: 1.3e9 in layers of which the largest is a twelfth 7370 / 7240, 300 M with one of more than a third 1523.6 / 1528.5
+//   k_ratios_big_hist: 110 M 626.5 / 637.5, 336 M 1818 / 1827.5
+// (Lists of less than a tile a CU come here only where a configuration asks for the larger lists' launches.)
+bool hist_each_step(const LayerSplit& sp, int cus) {
+  if (!sp.on || sp.n_fused_tiles < cus) return false;
+  if (sp.big_on) return sp.ratios_trail && sp.trail_even;
+  return sp.in_lds || (sp.rest_in_launch && sp.n_rest_ratio_tiles > 0);
 }
 
 // Largest number of one layer's tiles that a barrier kernel with `per_cu` resident workgroups per
@@ -1072,6 +1089,7 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
     build_split(ctx, &ws, tw, TILE_WU, tm, h_off, max_w, trail_rule(max_w > 0, cfg->fused_max_tiles, cus), true, cus, &ctx->sp_warm,
                 &unused);
     ctx->sp_apply.in_lds = lh_in_lds(ctx->sp_apply.n_fused_tiles, cus);
+    ctx->sp_apply.hist_each_step = hist_each_step(ctx->sp_apply, cus);
     // one launch instead of three or four where the whole list fits on the device at once (unless the
     // configuration lowers what the barrier kernels may take)
     auto slots_of = [&](auto kernel, size_t bytes, int min_per_cu, int64_t* out) {
@@ -1506,6 +1524,8 @@ ob_status ob_lamb_ratios_apply_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st, con
     return la.ok ? OB_OK : OB_ERR_HIP;
   }
   LayerSplit& sp = ctx->sp_apply;
+  if (packed_m && sp.on && sp.hist_each_step)
+    return ob_lamb_ratios_apply_hist_lp(ctx, st, packed_all, server_scales, lr, nullptr, x_lp, x_dtype, hip_stream);
   if (!sp.on || !packed_m) {
     // no tile qualifies, or the momentum is a dense array (the barrier kernel reads and commits the 1-bit
     // form only): the two plain kernels

@@ -1016,7 +1016,7 @@ __device__ __forceinline__ float select_by_bit(unsigned int word, int pos, float
 // The largest quotient n/d (each correctly rounded; NaN not taken) of a tile, of which only what exceeds `bound` matters: a
 // wavefront's largest so far, or what the clips of lines 18-19 raise every smaller ratio to.  A division is a dozen instructions,
 // one of them at quarter rate; whether n/d can exceed the bound is one fma, whose sign is that of n - bound*d: negative means
-// n/d < bound for d > 0 (a rounded quotient is then at most the bound), and where it is not, or d is not positive or
+// n/d < bound for d > 0 (a rounded quotient is then at most the bound), and where it is not, or a d has its sign bit set or is
 // not finite, the quotients are formed.  Underflow of the fma gives a zero, which counts as not negative.
 // Measured with UpdateTerm and select_by_bit's two instructions, four steps, us, before / after: 11 M parameters 327 / 322, 336 M fp32 6785 /
 // 6748, bf16 6946 / 6876 (the vector work of k_ratios_apply_hist, 82 instructions an element, then 50, next to memory at 88 % of
@@ -1034,7 +1034,8 @@ struct MaxQuotient {
   __device__ __forceinline__ void add(const v4f& n, const v4f& d, bool later) {
     const float t = fmaxf(fmaxf(fmaf(-bound, d[0], n[0]), fmaf(-bound, d[1], n[1])),
                           fmaxf(fmaf(-bound, d[2], n[2]), fmaf(-bound, d[3], n[3])));
-    if (__ballot(!(t < 0.0f)) == 0ull) return;
+    const unsigned int sign = __float_as_uint(d[0]) | __float_as_uint(d[1]) | __float_as_uint(d[2]) | __float_as_uint(d[3]);
+    if (__ballot(!(t < 0.0f) || (int)sign < 0) == 0ull) return;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const float q = n[k] / d[k];

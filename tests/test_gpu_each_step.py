@@ -39,3 +39,25 @@ def test_steps(name):
             assert torch.equal(dev.x_lp[:dev.N].view(torch.int16), dev.t["x"][:dev.N].to(lp).view(torch.int16))
     assert kernel in kernels_of(dev)
     finish(dev)
+
+
+@pytest.mark.parametrize("period", [0, 2])
+def test_quotient_of_two_negative_variances(period):
+    """No step makes one, but what the ratio of such a state was, it stays: their quotient is positive and counts."""
+    _need_gpu()
+    cfg = config("negative", [300 * T + 5, 3 * T, 40 * T], 1)
+    st, ref, dev = start_pair(cfg, seed=62, two_pass=True, packed=True, fused=True, fused_max_tiles=1 << 20, deferred=True,
+                              deferred_variance=period)
+    for t in range(2):
+        step(cfg, st, ref, dev, t, lambda g: dev.step(g, 1e-3))
+    ref.t["v_fresh"][:] = 2 * ref.t["v_frozen"]  # every other ratio below what the clips raise it to ...
+    ref.t["v_frozen"][7 * T] = -1.08
+    ref.t["v_fresh"][7 * T] = -1.0               # ... and this one the largest of its layer
+    ref.t["r_prev"][:] = 1.0
+    for k in ("v_fresh", "v_frozen", "r_prev"):
+        dev.load_state({k: ref.t[k]})
+    step(cfg, st, ref, dev, 2, lambda g: dev.step(g, 1e-3))
+    assert ref.t["r_prev"][0] > 1.05
+    for k in ("r_prev", "coeff_c"):
+        assert_close(dev.get(k), ref.t[k], k)
+    finish(dev)

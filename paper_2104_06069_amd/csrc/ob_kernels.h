@@ -164,9 +164,14 @@ __device__ __forceinline__ float wave_max(float v) { return wave_reduce(v, [](fl
 
 // Sum of one double per thread over a workgroup of NT threads, in a fixed order; result valid in
 // thread 0.  lds: [NT / WAVE] doubles.
-template <int NT = BLOCK>
+template <int NT = BLOCK, bool THROUGH_LDS = false>
 __device__ __forceinline__ double block_sum(double v, double* lds) {
-  v = wave_sum(v);
+  if constexpr (THROUGH_LDS) {
+#pragma unroll
+    for (int o = WAVE / 2; o > 0; o >>= 1) v += __shfl_down(v, o, WAVE);
+  } else {
+    v = wave_sum(v);
+  }
   const int lane = threadIdx.x & (WAVE - 1), wv = threadIdx.x / WAVE;
   __syncthreads();  // protects lds against the previous use
   if (lane == 0) lds[wv] = v;
@@ -204,8 +209,18 @@ __device__ __forceinline__ int walk_layer(int l, int64_t i, const int64_t* __res
 
 // Sign nibble of the lane's 4 elements -> the 32-bit word of its 8-lane group (in every lane of
 // the group).  Element 4*lane + k of the 256-element span is bit 4*(lane%8) + k of word lane/8.
+// THROUGH_LDS (here and in block_sum): by ds_bpermute, as k_compress_resident does, whose 16 spans a tile leave a barrier together: with register
+// moves its large lists are slower (plain form, a step, us, moves / LDS: 214 M elements 1728 / 1710, 100 M 781 / 772, 54 M 422 / 417, 34 M 263 / 259.5,
+// 18 M 147.5 / 147, 4.4 M 56.7 / 56.0, with a bf16 gradient 54.4 / 55.7); either one alone changes nothing.
+template <bool THROUGH_LDS = false>
 __device__ __forceinline__ unsigned int gather_word(unsigned int nibble) {
   unsigned int v = nibble << (4 * (threadIdx.x & 7));
+  if constexpr (THROUGH_LDS) {
+    v |= __shfl_xor(v, 1, WAVE);
+    v |= __shfl_xor(v, 2, WAVE);
+    v |= __shfl_xor(v, 4, WAVE);
+    return v;
+  }
   v |= __builtin_amdgcn_update_dpp(0u, v, 0xb1 /* quad_perm 1 0 3 2 */, 0xf, 0xf, true);
   v |= __builtin_amdgcn_update_dpp(0u, v, 0x4e /* quad_perm 2 3 0 1 */, 0xf, 0xf, true);
   v |= __builtin_amdgcn_update_dpp(0u, v, 0x141 /* row_half_mirror */, 0xf, 0xf, true);
@@ -535,6 +550,7 @@ __global__ __launch_bounds__(BLOCK) void k_error_dense(const float* __restrict__
 // the thread's elements are span0 + 4*threadIdx.x + k.
 // own: if not NULL, the words are also written there at word index own_word0 + (thread's word) (the
 // copy of this rank's own chunk in its server's input).
+template <bool THROUGH_LDS = false>   // (gather_word)
 __device__ __forceinline__ void sign_pack_store(v4f z, float s, float* __restrict__ err,
                                                 uint32_t* __restrict__ packed, int64_t span0,
                                                 uint32_t* __restrict__ own = nullptr, int64_t own_word0 = 0) {
@@ -547,7 +563,7 @@ __device__ __forceinline__ void sign_pack_store(v4f z, float s, float* __restric
     e[k] = z[k] - (b ? s : -s);
   }
   st4(err + span0 + threadIdx.x * 4, e);
-  const unsigned int word = gather_word(nib);
+  const unsigned int word = gather_word<THROUGH_LDS>(nib);
   if ((threadIdx.x & 7) == 0) {
     (packed + (span0 >> 5))[threadIdx.x >> 3] = word;
     if (own) (own + own_word0)[threadIdx.x >> 3] = word;
@@ -698,6 +714,7 @@ __device__ __forceinline__ unsigned long long barrier_wait(const unsigned long l
   return f;
 }
 
+template <bool THROUGH_LDS = false>   // (block_sum)
 __device__ __forceinline__ float chunk_barrier_scale(const ChunkSync& cs, int tile, int c, int tpc,
                                                      int64_t n_c, double part, double* lds,
                                                      unsigned long long* bc,
@@ -726,7 +743,7 @@ __device__ __forceinline__ float chunk_barrier_scale(const ChunkSync& cs, int ti
 #pragma unroll
       for (int q = 0; q < 4; ++q) a += v[q];
     }
-    const double S = block_sum(a, lds);
+    const double S = block_sum<BLOCK, THROUGH_LDS>(a, lds);
     if (threadIdx.x == 0) {
       const float sc = (float)sqrt(S / (double)n_c);
       scale_out[c] = sc;
@@ -795,15 +812,15 @@ __global__ __launch_bounds__(BLOCK, MINW) void k_compress_resident(
   // that path in the same loop all tiles ran 9 % slower.
   if (HAS_K && zt.uniform) stream(std::true_type{});
   else stream(std::false_type{});
-  const double part = block_sum(acc, lds);
-  const float s = chunk_barrier_scale(cs, p.t, p.c, tpc, n_c, part, lds, &bc, scales);
+  const double part = block_sum<BLOCK, true>(acc, lds);
+  const float s = chunk_barrier_scale<true>(cs, p.t, p.c, tpc, n_c, part, lds, &bc, scales);
   uint32_t* own = (oc.packed && p.c == oc.chunk) ? oc.packed : nullptr;   // uniform
   const int64_t own_tile0 = (p.tile0 - (int64_t)p.c * n_c) >> 5;           // the tile's first word within its chunk
   if (own && p.t == p.c * tpc && threadIdx.x == 0) *oc.scale = s;
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int o = u * SPAN + o0;
-    if (o < p.len) sign_pack_store(Z[u], s, err, packed, p.tile0 + u * SPAN, own, own_tile0 + u * (SPAN / 32));
+    if (o < p.len) sign_pack_store<true>(Z[u], s, err, packed, p.tile0 + u * SPAN, own, own_tile0 + u * (SPAN / 32));
   }
 }
 

@@ -106,6 +106,47 @@ def algorithmic_step_bytes_per_param(W, mode, fused_frac, compress_form, server_
     return (compress + fused_frac * fb + big + (1.0 - fused_frac - big_frac) * separate + server)
 
 
+def launch_bytes(ran, mode, W, n_pad, n_c, fused_params, big_params, ages, period, fused_apply, deferred_error,
+                 g_less=0.0, x_more=0.0):
+    """{kernel: algorithmic bytes of its launches in one compression step}, for the kernels `ran` (names) of a profiled
+    step.  Which elements a kernel covers follows from what ran beside it: ob_lamb_ratios_apply takes the kernels of the
+    variance's history on some lists, too, and a list's small tiles have launches of their own or none.
+    fused_params, big_params: elements in the tiles of the kernel with the per-layer barrier and in those of the larger layers;
+    ages, period: as for hist_kernel_bytes_per_param ({} and 0: the array is rewritten at every step)."""
+    kb = KERNEL_BYTES[mode]
+    if not period:
+        ages, period = {1: 1}, 1
+    hist, big_ratio = hist_kernel_bytes_per_param(ages, period), hist_big_ratio_bytes_per_param(ages, period)
+    rewrite, update = kb["ratios_pass"][0], kb["decompress_apply"][0] + x_more
+    barrier = ran & {"ratios_apply_hist", "ratios_apply_hist_lds", "ratios_apply_resident"}
+    fused = fused_params if fused_apply and barrier else 0
+    from_history = big_params if ran & {"ratios_big_hist", "ratios_trail"} else 0
+    rest_ratio = n_pad - fused - from_history
+    rest_update = n_pad - fused - (from_history if "ratios_trail" in ran else 0)
+    out = {
+        "compress_resident": (kb["compress_resident"][0] - g_less) * n_pad,
+        "compress_deferred": (kb["compress_deferred"][0] - g_less) * n_pad,
+        "momentum_z_sumsq": (kb["momentum_z_sumsq"][0] - g_less) * n_pad,
+        "sign_pack_error": KERNEL_BYTES["both"]["sign_pack_error"][0] * n_pad,
+        "server_unpack_avg": (W / 8.0 + (8.375 if deferred_error else 8.0)) * n_c,
+        "server_resident": (W / 8.0 + 8.125) * n_c,   # R W*bits, err (4) + W err (4), bits (1/8)
+        "server_sign_pack": KERNEL_BYTES["both"]["server_sign_pack"][0] * n_c,
+        "ratios_pass": rewrite * rest_ratio,
+        "decompress_apply": update * rest_update,
+        "ratios_big_hist": big_ratio * from_history,
+        "ratios_trail": (big_ratio + update) * from_history,   # (v_frozen, 4, and the signs a second time: mostly from the memory-side cache)
+        "ratios_apply_resident": (kb["ratios_apply_resident"][0] + x_more) * fused,
+    }
+    if "ratios_apply_small" in kb:
+        lag = (fused_params + big_params) / float(n_pad)     # what a list in one launch keeps behind, too
+        out["ratios_apply_small"] = (lag * hist + (1.0 - lag) * kb["ratios_apply_small"][0] + x_more) * n_pad
+    # the small tiles' ratio pass and update, where no launch of their own did them
+    in_launch = (0.0 if "ratios_pass" in ran else rewrite * rest_ratio) + (0.0 if "decompress_apply" in ran else update * rest_update)
+    for k in ("ratios_apply_hist", "ratios_apply_hist_lds"):
+        out[k] = (hist + x_more) * fused + in_launch
+    return {k: out[k] for k in ran if k in out}
+
+
 class Workload:
     """One benchmark configuration resident in HBM: state, a few gradients, what the other ranks send."""
 
@@ -151,8 +192,7 @@ class Workload:
         # (with a dense momentum ob_lamb_ratios_apply runs the two plain kernels for every layer)
         self.fused_params = ob.ob_lamb_fused_params(ds.ctx) if (ds.fused_apply and self.mode == "packed") else 0
         self.wfused = ob.ob_lamb_warmup_fused_params(ds.ctx)
-        # (only ob_lamb_ratios_apply_hist treats the large layers' whole tiles differently from the rest)
-        self.big_params = ob.ob_lamb_big_tile_params(ds.ctx) if ds.vf_period else 0
+        self.big_params = ob.ob_lamb_big_tile_params(ds.ctx) if (ds.fused_apply and self.mode == "packed") else 0
 
     @staticmethod
     def variance_period(args):
@@ -161,6 +201,20 @@ class Workload:
         if args.dense_momentum or args.separate_calls:
             return 0
         return k
+
+    def profiled(self, steps):
+        """{kernel: (milliseconds, launches)} of `steps` steps, from the library's own events."""
+        ob, ds = self.ob, self.ds
+        ob.ob_lamb_profile_enable(ds.ctx, True)
+        for t in range(steps):
+            self.one_step(t)
+        prof = ob.ob_lamb_profile_read(ds.ctx)
+        ob.ob_lamb_profile_enable(ds.ctx, False)
+        return prof
+
+    def big_tiles_used(self, ran):
+        """Elements in tiles of the large layers, if the kernels `ran` treat them differently from the rest."""
+        return self.big_params if set(ran) & {"ratios_big_hist", "ratios_trail"} else 0
 
     def ages_since(self, before):
         """{momentum steps applied: steps} of the ratio+update calls since the snapshot `before`."""
@@ -303,7 +357,7 @@ def brief(name, args, torch, steps, graph_too=False):
            "step_algorithmic_bytes": b,
            "step_algorithmic_pct_of_hbm_peak": round(100 * b / (mean * 1e-3) / 1e9 / HBM_PEAK_GBS, 2),
            "fused_share": round(w.fused_params / float(w.ds.n_pad), 4),
-           "big_tile_share": round(w.big_params / float(w.ds.n_pad), 4),
+           "big_tile_share": round(w.big_tiles_used(w.profiled(1)) / float(w.ds.n_pad), 4),
            "compress_form": w.compress_form(),
            "server_single_pass": int(w.ob.ob_lamb_server_single_pass(w.ds.ctx))}
     out["variance_period"] = w.ds.vf_period
@@ -415,13 +469,9 @@ def main():
     # per-kernel durations (the library's own events: each kernel's start and end on the device) and
     # per-call times (events on the launch stream), both straight after the timed steps so that the
     # device never pauses in between
-    ob.ob_lamb_profile_enable(ds.ctx, True)
     ages0 = dict(ds.vf_ages)
-    for t in range(args.profile_steps):
-        wl.one_step(t)
+    prof = wl.profiled(args.profile_steps)
     ages_prof = wl.ages_since(ages0)
-    prof = ob.ob_lamb_profile_read(ds.ctx)
-    ob.ob_lamb_profile_enable(ds.ctx, False)
     for t in range(5):
         wl.one_step(t)
     calls = {}
@@ -450,43 +500,15 @@ def main():
     if mode == "packed":
         scratch_dst.zero_()
     kern = {k: {"avg_ms": round(v[0] / v[1], 4), "launches": v[1]} for k, v in prof.items()}
-    KB = dict(KERNEL_BYTES["both"])
-    KB.update(KERNEL_BYTES[mode])
-    KB["server_unpack_avg"] = (W / 8.0 + (8.375 if ds.deferred_error else 8.0), "n_c")
-    KB["server_resident"] = (W / 8.0 + 8.125, "n_c")   # R W*bits, err (4) + W err (4), bits (1/8)
-    if ages_prof:   # mean over the profiled launches, which differ in how many momentum steps they applied
-        KB["ratios_apply_hist"] = (hist_kernel_bytes_per_param(ages_prof, ds.vf_period), "fused")
-        KB["ratios_apply_hist_lds"] = KB["ratios_apply_hist"]
-        lag = (wl.fused_params + wl.big_params) / float(ds.n_pad)     # what a list in one launch keeps behind, too
-        KB["ratios_apply_small"] = (lag * KB["ratios_apply_hist"][0] + (1.0 - lag) * KB["ratios_apply_small"][0], "n_pad")
-        KB["ratios_big_hist"] = (hist_big_ratio_bytes_per_param(ages_prof, ds.vf_period), "big")
-        if "ratios_trail" in kern:   # ratio pass and update in one launch (of these 4.125 come from the memory-side cache where it holds them)
-            KB["ratios_trail"] = (KB["ratios_big_hist"][0] + KERNEL_BYTES[mode]["decompress_apply"][0], "big")
     g_less = 2.0 if args.grad_dtype != "f32" else 0.0     # 16-bit gradient read
     x_more = 2.0 if args.x_lp != "none" else 0.0          # 16-bit parameter copy written
-    for k in ("compress_resident", "compress_deferred", "momentum_z_sumsq", "warmup_moments", "warmup_resident", "warmup_small"):
-        KB[k] = (KB[k][0] - g_less, KB[k][1])
-    for k in ("decompress_apply", "ratios_apply_resident", "ratios_apply_hist", "ratios_apply_hist_lds", "ratios_apply_small",
-              "ratios_trail", "warmup_apply", "warmup_resident", "warmup_small"):
-        if k in KB:
-            KB[k] = (KB[k][0] + x_more, KB[k][1])
-    fused_params, wfused = wl.fused_params, wl.wfused
-    units = {"n_pad": ds.n_pad, "n_c": ds.n_c, "fused": fused_params, "wfused": wfused, "big": wl.big_params}
-    if wfused:   # the two-pass warmup kernels then cover only the remaining layers (two launches each)
-        for k in ("warmup_moments", "warmup_apply"):
-            KB[k] = (KB[k][0], "rest_w")
-        units["rest_w"] = ds.n_pad - wfused
-    if ds.fused_apply and (fused_params or wl.big_params):   # the plain ratio/update kernels then cover only what is left
-        KB["ratios_pass"] = (KB["ratios_pass"][0], "rest_ratio")
-        KB["decompress_apply"] = (KB["decompress_apply"][0], "rest")
-        units["rest"] = ds.n_pad - fused_params - (wl.big_params if "ratios_trail" in kern else 0)
-        units["rest_ratio"] = ds.n_pad - fused_params - wl.big_params
+    algo = launch_bytes(set(kern), mode, W, ds.n_pad, ds.n_c, wl.fused_params, wl.big_params, ages_prof, ds.vf_period,
+                        ds.fused_apply, ds.deferred_error, g_less, x_more)
     for k, v in kern.items():
-        if k in KB:
-            bpe, unit = KB[k]
+        if k in algo:
             # (should a call cover its elements with several launches of one kernel: per-launch mean)
-            per_call = max(1, round(v["launches"] / args.profile_steps)) if unit in ("rest", "rest_w", "rest_ratio") else 1
-            v["algo_bytes"] = bpe * units[unit] / per_call
+            per_call = max(1, round(v["launches"] / args.profile_steps)) if k in ("ratios_pass", "decompress_apply") else 1
+            v["algo_bytes"] = algo[k] / per_call
             v["GBps"] = round(v["algo_bytes"] / (v["avg_ms"] * 1e-3) / 1e9, 1)
             v["frac_of_hbm_peak"] = round(v["GBps"] / HBM_PEAK_GBS, 4)
             v["frac_of_copy_ceiling"] = round(v["GBps"] / ceiling["GBps"], 4)
@@ -522,7 +544,7 @@ def main():
                    "mom_scale": bool(args.mom_scale), "momentum": mode,
                    "grad_dtype": args.grad_dtype, "x_lp": args.x_lp, "graph_replay": bool(args.graph),
                    "fused_ratios_apply": ds.fused_apply, "fused_layers": ob.ob_lamb_fused_layers(ds.ctx),
-                   "fused_params": fused_params, "big_tile_params": wl.big_params,
+                   "fused_params": wl.fused_params, "big_tile_params": wl.big_tiles_used(kern),
                    "compress_form": wl.compress_form(),
                    "server_single_pass": ob.ob_lamb_server_single_pass(ds.ctx),
                    "variance_period": ds.vf_period,
@@ -558,9 +580,9 @@ def main():
         "warmup_step_ms": round(wu_ms, 4),
         # 28 B/elem where g, m, v, x are read once, 24 + 16 in two passes: bytes asked for, not a rate of HBM, as the second pass of
         # large layers finds its reads in the memory-side cache
-        "warmup_step_GBps": round(((28.0 - g_less + x_more) * wfused + (40.0 - g_less + x_more) * (ds.n_pad - wfused))
+        "warmup_step_GBps": round(((28.0 - g_less + x_more) * wl.wfused + (40.0 - g_less + x_more) * (ds.n_pad - wl.wfused))
                                   / (wu_ms * 1e-3) / 1e9, 1),
-        "warmup_single_pass_params": wfused,
+        "warmup_single_pass_params": wl.wfused,
         "warmup_step_params_per_s": round(pl.N / (wu_ms * 1e-3), 1),
         "momentum_scale_ms": round(ms_ms, 4),
         "momentum_scale_GBps": round(4.0 * ds.n_pad / (ms_ms * 1e-3) / 1e9, 1)}

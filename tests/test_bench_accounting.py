@@ -3,6 +3,8 @@ kernel and step times into fractions of the HBM peak."""
 import importlib.util
 import os
 
+import pytest
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
@@ -67,3 +69,47 @@ def test_bytes_with_the_variance_in_deferred_form():
     step = b.algorithmic_step_bytes_per_param(W, "packed", 0.5, "deferred", False, fused_bytes=17.0, big_frac=0.3,
                                               big_ratio_bytes=9.5)
     assert abs(step - (12.375 + 0.5 * 17.0 + 0.3 * (9.5 + 12.125) + 0.2 * (12.25 + 12.125) + bit + 8.375 / W)) < 1e-12
+
+
+# which kernels a step's ratio and update call ran, elements in listed and in large tiles, {momentum steps applied: steps}, period
+CALLS = {
+    "barrier_kernel": ({"ratios_pass", "ratios_apply_resident", "decompress_apply"}, 900, 60, {}, 0),
+    "history_each_step": ({"ratios_pass", "ratios_apply_hist", "ratios_trail", "decompress_apply"}, 80, 919, {}, 0),
+    "history_each_step_one_launch": ({"ratios_apply_hist"}, 985, 0, {}, 0),
+    "history": ({"ratios_pass", "ratios_big_hist", "ratios_apply_hist", "decompress_apply"}, 900, 60, {1: 1, 2: 1, 3: 1, 4: 1}, 4),
+    "history_trail": ({"ratios_pass", "ratios_trail", "ratios_apply_hist_lds", "decompress_apply"}, 80, 919, {1: 2, 2: 1}, 2),
+    "history_one_launch": ({"ratios_apply_hist_lds"}, 985, 0, {1: 1, 2: 1, 3: 1, 4: 1}, 4),
+    "history_rest_pass_in_launch": ({"ratios_apply_hist", "ratios_big_hist", "decompress_apply"}, 700, 280, {1: 1, 2: 1}, 2),
+    "wait_free": ({"ratios_pass", "ratios_big_hist", "ratios_finalize", "decompress_apply"}, 0, 960, {1: 1, 2: 1}, 2),
+    "plain": ({"ratios_pass", "ratios_finalize", "decompress_apply"}, 900, 60, {}, 0),
+}
+
+
+@pytest.mark.parametrize("x_more", [0.0, 2.0])
+@pytest.mark.parametrize("call", list(CALLS))
+def test_kernels_of_a_step_move_the_step_s_bytes(call, x_more):
+    """Every element's ratio pass and update is counted once, in the kernel that ran it, whatever period the step has."""
+    b = _bench()
+    ran, fused, big, ages, period = CALLS[call]
+    unit, W = 1024, 64
+    n = 1000 * unit
+    got = b.launch_bytes(ran | {"compress_deferred", "server_unpack_avg"}, "packed", W, n, n // W, fused * unit, big * unit, ages,
+                         period, call != "plain", True, 0.0, x_more)
+    tail = sum(v for k, v in got.items() if k in ran)
+    applied, K = (ages, period) if period else ({1: 1}, 1)
+    hist, rewrite = b.hist_kernel_bytes_per_param(applied, K), 12.25
+    # elements whose two passes are one kernel, whose ratio pass is one from the history, and the rest
+    one = fused if ran & {"ratios_apply_hist", "ratios_apply_hist_lds", "ratios_apply_resident"} else 0
+    from_history = big if ran & {"ratios_big_hist", "ratios_trail"} else 0
+    want = (one * hist + from_history * (b.hist_big_ratio_bytes_per_param(applied, K) + 12.125)
+            + (1000 - one - from_history) * (rewrite + 12.125) + 1000 * x_more) * unit
+    assert abs(tail - want) < 1e-6 * want
+    # no kernel is credited with elements of another one
+    if "ratios_pass" in got:
+        assert abs(got["ratios_pass"] - (1000 - one - from_history) * unit * rewrite) < 1
+    if "decompress_apply" in got:
+        updated = one + (big if "ratios_trail" in ran else 0)
+        assert abs(got["decompress_apply"] - (1000 - updated) * unit * (12.125 + x_more)) < 1
+    if "ratios_trail" in ran:
+        assert abs(got["ratios_trail"] - big * unit * (b.hist_big_ratio_bytes_per_param(applied, K) + 12.125 + x_more)) < 1
+    assert not ran - {"ratios_finalize"} - set(got), "a kernel without its bytes"

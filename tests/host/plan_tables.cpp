@@ -38,6 +38,41 @@ List random_list() {
   return s;
 }
 
+// Moments and updates take turns: behind every TRAIL_BATCH moments parts (on all XCDs alike) a batch of the updates that are due, one for
+// each `spread` of them, and none elsewhere, but for those up to a layer of more than `keep` parts that are due at once (at_once).  What is
+// left of them stands behind the moments of the list, or of the launch.  update, launch: of each item.
+void check_turns(const std::vector<char>& update, const std::vector<int64_t>& launch, const std::vector<int>& n, const std::vector<int>& begin,
+                 int64_t lag, int64_t keep, int64_t spread, bool at_once) {
+  CHECK(TRAIL_BATCH % 8 == 0);
+  std::vector<int64_t> left(launch.empty() ? 0 : (size_t)launch.back() + 1, 0);   // moments parts of each launch
+  for (size_t i = 0; i < update.size(); ++i) left[(size_t)launch[i]] += !update[i];
+  int64_t pos = 0, due = 0, once = 0, taken = 0, launch_start = 0, in_launch = -1;
+  size_t next = 0;   // the next layer to become due
+  for (size_t i = 0; i < update.size();) {
+    if (update[i]) {   // (behind a launch's moments)
+      CHECK(left[(size_t)launch[i]] == 0);
+      ++taken, ++i;
+      continue;
+    }
+    if (launch[i] != in_launch) in_launch = launch[i], launch_start = pos;
+    ++pos;
+    const int64_t left_now = --left[(size_t)launch[i]];
+    for (; next < n.size(); ++next) {
+      if (n[next] == 0) continue;
+      if (begin[next] + n[next] + lag > (lag > 0 ? pos : launch_start)) break;
+      due += n[next];
+      if (at_once && n[next] > keep) once = due;
+    }
+    int64_t run = 0;
+    for (++i; i < update.size() && update[i] && launch[i] == in_launch; ++i) ++run;
+    const int64_t pending = due - taken;
+    const int64_t want = once > taken ? once - taken : pos % TRAIL_BATCH ? 0 : std::min(pending, (pending + spread - 1) / spread * TRAIL_BATCH);
+    if (left_now > 0) CHECK(run == want);
+    taken += run;
+  }
+  CHECK(taken == pos);
+}
+
 // Every part once as moments and once as update, the update after all moments of its layer (no later workgroup is waited
 // for), `lag` moments parts behind them while there are any, in a later launch where nothing waits; what is kept is at most what the cache holds, and updated first.
 void check_trail(const std::vector<int>& n, const std::vector<int>& begin, int64_t lag, int64_t group) {
@@ -59,6 +94,13 @@ void check_trail(const std::vector<int>& n, const std::vector<int>& begin, int64
     at[(size_t)p] = (int64_t)i;
     if (!(items[i] & TRAIL_UPDATE)) kept[(size_t)p] = (items[i] & TRAIL_KEEP) != 0;
   }
+  std::vector<char> update;
+  std::vector<int64_t> launch;
+  for (size_t i = 0; i < items.size(); ++i) {
+    update.push_back((items[i] & TRAIL_UPDATE) != 0);
+    launch.push_back(std::upper_bound(end.begin(), end.end(), (int64_t)i) - end.begin());
+  }
+  check_turns(update, launch, n, begin, lag, TRAIL_KEEP_PARTS, TRAIL_SPREAD, true);
   auto launch_of = [&](int64_t i) { return std::upper_bound(end.begin(), end.end(), i) - end.begin(); };
   for (size_t l = 0; l < n.size(); ++l) {
     if (n[l] == 0) continue;
@@ -97,7 +139,7 @@ void trail() {
 }
 
 // k_ratios_trail: every tile once for the ratio pass and in all its parts for the update, those of a layer after its last tile
-// and some way behind it; updates next to each other in no more than batches while nothing large is due; and its rule.
+// and some way behind it; the turns; and its rule.
 void ratios_trail_order() {
   for (int it = 0; it < 200; ++it) {
     std::vector<int> n, begin;
@@ -115,10 +157,15 @@ void ratios_trail_order() {
     CHECK((int64_t)items.size() == (int64_t)at * (1 + parts));
     std::vector<int64_t> ratio((size_t)at, -1), first((size_t)at, -1);
     std::vector<int> seen((size_t)at, 0);
+    std::vector<char> update;   // by tile
     int64_t n_ratio = 0;
+    unsigned int before = 0;
     for (unsigned int i : items) {
       const unsigned int pos = i & (RATIOS_TRAIL_PART - 1u), part = (i & ~TRAIL_UPDATE) / RATIOS_TRAIL_PART;
       CHECK((int)pos < at && (int)part < parts);
+      if (part == 0) update.push_back((i & TRAIL_UPDATE) != 0);
+      else CHECK(i == before + RATIOS_TRAIL_PART);   // the parts of a tile stand together
+      before = i;
       if (i & TRAIL_UPDATE) {
         CHECK(seen[pos] == (1 << part) - 1);
         seen[pos] |= 1 << part;
@@ -133,6 +180,7 @@ void ratios_trail_order() {
         CHECK(seen[(size_t)p] == (1 << parts) - 1);
         CHECK(first[(size_t)p] >= std::min<int64_t>(ratio[(size_t)(begin[l] + n[l] - 1)] + 1 + 6 * 256, at));
       }
+    check_turns(update, std::vector<int64_t>(update.size(), 0), n, begin, 6 * 256, RATIOS_TRAIL_KEEP, RATIOS_TRAIL_SPREAD, false);
     const int64_t most = *std::max_element(n.begin(), n.end());
     CHECK(ratios_trail(n, 256) == (at >= 1024 && 8 * (at - most) >= at));
   }
@@ -168,6 +216,10 @@ void big_rule() {
     CHECK(trail_rule(true, 0, cus).min_total == 7 * cus && trail_rule(false, 0, cus).min_total == 20 * cus);
     CHECK(trail_rule(true, 8, cus).min_total == 0 && trail_rule(false, 8, cus).min_total == 0);
     CHECK(rest_in_launch(5 * cus, 20 * cus, 0, cus) && !rest_in_launch(5 * cus + 1, 1, 0, cus) && !rest_in_launch(1, cus, 19 * cus + 1, cus));
+    // layers of at most two tiles a CU on average and no large ones: up to 40 tiles a CU
+    CHECK(rest_in_launch(1, 40 * cus, 0, cus, 20) && !rest_in_launch(1, 40 * cus + 1, 0, cus, 99) && rest_in_launch(5 * cus, 30 * cus, 0, cus, 15));
+    CHECK(!rest_in_launch(1, 30 * cus, 0, cus, 14) && rest_in_launch(1, 20 * cus, 0, cus, 1) && !rest_in_launch(1, 20 * cus + 1, 0, cus, 10));
+    CHECK(!rest_in_launch(1, 20 * cus, 1, cus, 99) && !rest_in_launch(5 * cus + 1, 30 * cus, 0, cus, 99) && !rest_in_launch(1, 0, 0, cus, 9));
     CHECK(server_spans(2, 16 * cus, cus) == 4 && server_spans(3, 16 * cus, cus) == 2 && server_spans(1, 16 * cus - 1, cus) == 2);
     CHECK(server_spans(32, 8 * cus, cus) == 2 && server_spans(32, 8 * cus - 1, cus) == 1 && server_spans(33, 99 * cus, cus) == 1);
     CHECK(arrivals_one_level(40 * cus, cus) == 256 && arrivals_one_level(40 * cus + 1, cus) == 512);

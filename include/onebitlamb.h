@@ -337,7 +337,7 @@ int64_t ob_lamb_fused_layers(const ob_lamb_ctx* ctx);
 /* ... and the number of parameters in its tiles. */
 int64_t ob_lamb_fused_params(const ob_lamb_ctx* ctx);
 /* Number of parameters in the 8192-element tiles of the layers that are too large for that kernel,
- * where ob_lamb_ratios_apply_hist also works from the history (ratio pass only). */
+ * whose ratio pass ob_lamb_ratios_apply_hist also runs from the history. */
 int64_t ob_lamb_big_tile_params(const ob_lamb_ctx* ctx);
 /* The same two counts for ob_lamb_warmup_step, which reads g, m, v and x once (one kernel with a
  * per-layer barrier that keeps eq. (1)'s update direction and x on the chip while the layer's
@@ -420,12 +420,12 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
  * polls, so a kernel in which a wait expires still ends about 2 s after its last workgroup started.
  *
  * An expired wait does NOT stop the kernel: the workgroup goes on with whatever the flag word last
- * held (a stale scale or coefficient), raises a device-side flag, and the step's outputs are
- * undefined.  The buffers updated in place are then corrupt and must be restored from a copy that
+ * held (a stale scale or coefficient) or, where it waits for all coefficients of the launch, with what
+ * coeff_c holds; it raises a device-side flag, and the step's outputs are undefined.  The buffers updated in place are then corrupt and must be restored from a copy that
  * the CALLER holds -- the library keeps none:
  *   ob_lamb_compress_local   err_worker (and packed_out, scales_out)
  *   ob_lamb_server_reduce    err_server (and packed_out, scale_out)
- *   ob_lamb_ratios_apply     x, v_fresh, r_prev, coeff_c
+ *   ob_lamb_ratios_apply     x, v_fresh, r_prev, coeff_c (ob_lamb_ratios_apply_hist: the same)
  *   ob_lamb_warmup_step      x, m, v_fresh, c_avg, coeff_c
  * No step call returns OB_ERR_STATE by itself (none of them synchronises).  The caller learns of an
  * expiry from ob_lamb_check_device_status, which synchronises `hip_stream`, reads the flag and

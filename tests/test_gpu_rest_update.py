@@ -1,12 +1,13 @@
 """The update of the tiles outside the 8192-element ones in the last workgroups of k_ratios_apply_hist's launch, over the 16-bit copy,
-replays of a captured graph and the lists that only this form takes into that launch."""
+replays of a captured graph, the lists that only this form takes into that launch, and a wait that expires."""
 import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
 
 from tests.test_gpu_hard_values import config  # noqa: E402
-from tests.test_gpu_parity import _need_gpu, assert_close, finish, kernels_of, push_wire, start_pair  # noqa: E402
+from tests.refstep import HYPER  # noqa: E402
+from tests.test_gpu_parity import DeviceStep, _need_gpu, assert_close, finish, kernels_of, push_wire, start_pair  # noqa: E402
 from workloads import foreign_server_chunks, foreign_worker_chunks, gradient  # noqa: E402
 
 pytestmark = pytest.mark.gpu
@@ -90,3 +91,36 @@ def test_replayed_from_a_captured_graph():
             assert torch.equal(dev.t[k], eager.t[k]), (rep, k)
     finish(dev)
     finish(eager)
+
+
+@pytest.mark.parametrize("period", [0, 2])
+def test_expired_wait_is_reported_and_recovered(period):
+    """With no polls allowed the updates of the listed tiles and of the rest go on with what they find (every access stays in
+    bounds) and the status call says so; the context then takes the kernels that wait for nothing."""
+    _need_gpu()
+    import paper_2104_06069_amd as ob
+    cfg = config("rest_update", SMALL, 3)
+    st, ref, ok = start_pair(cfg, seed=53, two_pass=True, packed=True, fused=True, fused_max_tiles=1 << 20, deferred=True,
+                             deferred_variance=period)
+    finish(ok)
+    dev = DeviceStep(cfg["plist"].offsets, cfg["W"], cfg["server_chunk"], two_pass=True, packed_momentum=True, fused_apply=True,
+                     fused_max_tiles=1 << 20, deferred_error=True, deferred_variance=period, spin_limit=0, **HYPER)
+    dev.load_state(ref.t)
+    for t in range(2):      # (the first one reads the dense momentum)
+        dev.begin_step()
+        if t == 1:
+            ob.ob_lamb_profile_enable(dev.ctx, True)
+        dev.step(torch.from_numpy(gradient(st, cfg, t)).to(dev.device), 1e-3)
+    names = kernels_of(dev)
+    assert names & {"ratios_apply_hist", "ratios_apply_hist_lds"} and not names & {"ratios_pass", "decompress_apply"}, names
+    with pytest.raises(ob.ObLambError) as e:
+        ob.ob_lamb_check_device_status(dev.ctx, dev.stream)
+    assert e.value.status == -4
+    dev.load_state(ref.t)
+    for t in range(2, 4):
+        step(cfg, st, ref, dev, t, lambda g: dev.step(g, 1e-3))
+        for k in ("x", "r_prev", "coeff_c", "v_fresh"):
+            assert_close(dev.get(k), ref.t[k], f"step {t}: {k}")
+    names = kernels_of(dev)
+    assert not names & {"ratios_apply_hist", "ratios_apply_hist_lds", "ratios_apply_resident", "ratios_trail"}, names
+    finish(dev)

@@ -1033,8 +1033,10 @@ __device__ __forceinline__ float select_by_bit(unsigned int word, int pos, float
 // The largest quotient n/d (each correctly rounded; NaN not taken) of a tile, of which only what exceeds `bound` matters: a
 // wavefront's largest so far, or what the clips of lines 18-19 raise every smaller ratio to.  A division is a dozen instructions,
 // one of them at quarter rate; whether n/d can exceed the bound is one fma, whose sign is that of n - bound*d: negative means
-// n/d < bound for d > 0 (a rounded quotient is then at most the bound), and where it is not, or a d has its sign bit set or is
-// not finite, the quotients are formed.  Underflow of the fma gives a zero, which counts as not negative.
+// n/d < bound for d > 0 (a rounded quotient is then at most the bound), and where it is not, or a d has its sign bit set, the
+// quotients are formed.  Underflow of the fma gives a zero, which counts as not negative.  What may pass unformed besides: an infinite d, whose
+// quotient is 0 or NaN; a NaN n or d, whose product fmaxf ignores and whose quotient is a NaN, not taken; with the bound at 0, n = anything over
+// d = inf (the fma a NaN), the same 0 or NaN; with the bound at infinity everything, as nothing exceeds it.
 // Measured with UpdateTerm and select_by_bit's two instructions, four steps, us, before / after: 11 M parameters 327 / 322, 336 M fp32 6785 /
 // 6748, bf16 6946 / 6876 (the vector work of k_ratios_apply_hist, 82 instructions an element, then 50, next to memory at 88 % of
 // a copy's rate).
@@ -1062,12 +1064,27 @@ struct MaxQuotient {
   }
 };
 
-// m_t/(sqrt(v_frozen)+eta) of line 21 with m_t = +-sp: the correctly rounded square root and quotient, as sqrtf and operator/ give
-// them, without what those do for operands at the ends of the number range.  In range: v_frozen at most 2^60 and not
-// negative, |sp| zero or within [2^-80, 2^40], eta within [2^-22, 2^20]; values of v_frozen below 2^-96 count as that (their
-// root is then less than half a unit of eta's last place).  The root: Newton's step on v_rsq_f32's estimate, equal to sqrtf for
-// every one of the 1.6e9 values of [2^-96, 2^96); the quotient: two residuals after one step on v_rcp_f32's (Markstein),
-// which is operator/'s own sequence between its scalings.
+// n/(sqrt(v)+eta) as sqrtf and operator/ give it, without what those do for operands at the ends of the number range: the correctly
+// rounded square root and quotient for v at most 2^60 and not negative, |n| zero or within [2^-80, 2^40], eta within [2^-22 = 2.4e-7, 2^20];
+// values of v below 2^-96 count as that (their root is then less than half a unit of eta's last place, which is 2^-45 or more).  With a
+// smaller eta every wavefront pays the check and takes the long form: a step, us, eta = 1e-6 / 1e-8, on the same buffers: 11 M parameters 77.0 / 78.9,
+// 336 M 1702 / 1709, 1.3e9 6702 / 6800; a LAMB step of 3 M 22.5 / 23.2, of 336 M 1687 / 1690.
+// The root: Newton's step on v_rsq_f32's estimate, equal to sqrtf for every one of the 1.3e9 values of [2^-96, 2^60] (compared one by one
+// on the device; the tests have every mantissa of two binades and 1.7e7 values over all of them).  The quotient: two residuals after
+// one step on v_rcp_f32's (Markstein), which is operator/'s own sequence between its scalings; no residual is subnormal in these ranges.
+constexpr float SHORT_V_LOW = 0x1p-96f, SHORT_V_TOP = 0x1p60f, SHORT_N_LOW = 0x1p-80f, SHORT_N_TOP = 0x1p40f, SHORT_ETA_LOW = 0x1p-22f, SHORT_ETA_TOP = 0x1p20f;
+constexpr unsigned int SHORT_V_TOP_BITS = __builtin_bit_cast(unsigned int, SHORT_V_TOP), SHORT_N_LOW_BITS = __builtin_bit_cast(unsigned int, SHORT_N_LOW);
+__device__ __forceinline__ float short_denominator(float v, float eta) {   // sqrtf(v) + eta
+  const float z = fmaxf(v, SHORT_V_LOW), y = __builtin_amdgcn_rsqf(z), g = z * y;
+  return fmaf(fmaf(-g, g, z), 0.5f * y, g) + eta;
+}
+__device__ __forceinline__ float short_quotient(float n, float d) {   // n / d; a zero without its sign where n is -0
+  const float r0 = __builtin_amdgcn_rcpf(d), r = fmaf(fmaf(-d, r0, 1.0f), r0, r0);
+  const float q0 = n * r, q1 = fmaf(fmaf(-d, q0, n), r, q0);
+  return fmaf(fmaf(-d, q1, n), r, q1);
+}
+
+// m_t/(sqrt(v_frozen)+eta) of line 21 with m_t = +-sp.
 struct UpdateTerm {
   float sp, eta;
   unsigned int top;   // the lane's largest bit pattern of v_frozen
@@ -1078,7 +1095,7 @@ struct UpdateTerm {
   }
   __device__ __forceinline__ bool in_range() const {   // uniform; all lanes of the wavefront
     const float a = fabsf(sp);
-    const bool ok = (a == 0.0f || (a >= 0x1p-80f && a <= 0x1p40f)) && eta >= 0x1p-22f && eta <= 0x1p20f && top <= 0x5d800000u /* 2^60 */;
+    const bool ok = (a == 0.0f || (a >= SHORT_N_LOW && a <= SHORT_N_TOP)) && eta >= SHORT_ETA_LOW && eta <= SHORT_ETA_TOP && top <= SHORT_V_TOP_BITS;
     return __ballot(!ok) == 0ull;
   }
   // v: four values of v_frozen, replaced by their terms; bits pos .. pos + 3 of word: the signs of m_t
@@ -1086,11 +1103,7 @@ struct UpdateTerm {
     if (in_range) {
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const float z = fmaxf(v[k], 0x1p-96f), y = __builtin_amdgcn_rsqf(z), g = z * y;
-        const float d = fmaf(fmaf(-g, g, z), 0.5f * y, g) + eta;
-        const float r0 = __builtin_amdgcn_rcpf(d), r = fmaf(fmaf(-d, r0, 1.0f), r0, r0);
-        const float q0 = sp * r, q1 = fmaf(fmaf(-d, q0, sp), r, q0);
-        const float q = fmaf(fmaf(-d, q1, sp), r, q1);
+        const float q = short_quotient(sp, short_denominator(v[k], eta));
         v[k] = __uint_as_float(__float_as_uint(q) ^ (~(word << (31 - pos - k)) & 0x80000000u));
       }
     } else {
@@ -2916,9 +2929,8 @@ __device__ __forceinline__ float lamb_u(float mn, float vn, float x, float eta, 
   return u;
 }
 
-// lamb_u of four elements, by all lanes of a wavefront: UpdateTerm's shorter root and quotient where every lane's operands lie in their range
-// (here the numerator, m, differs from element to element: zero or within [2^-80, 2^40]; its sign is put back at the end, as a
-// residual of zero loses that of -0).  A LAMB step, us, lamb_u / this: 3 M parameters in one launch 24.9 / 23.45, 11 M 76.2 / 75.8, 110 M with a 16-bit
+// lamb_u of four elements, by all lanes of a wavefront: the shorter root and quotient where every lane's operands lie in their range
+// (here the numerator, m, differs from element to element; its sign is put back at the end, as a residual of zero loses that of -0).  A LAMB step, us, lamb_u / this: 3 M parameters in one launch 24.9 / 23.45, 11 M 76.2 / 75.8, 110 M with a 16-bit
 // copy 589.3 / 588.6, 336 M 1678.6 / 1679.9, which memory bounds.
 __device__ __forceinline__ v4f lamb_u4(const v4f& m, const v4f& v, const v4f& x, float eta, float wd) {
   unsigned int top = 0u, low = 0xffffffffu;
@@ -2930,18 +2942,11 @@ __device__ __forceinline__ v4f lamb_u4(const v4f& m, const v4f& v, const v4f& x,
     low = mb < low ? mb : low;
     big = fmaxf(big, fabsf(m[k]));   // (a NaN stays one in either form)
   }
-  const bool ok = top <= 0x5d800000u /* 2^60 */ && low >= 2u * 0x17800000u - 1u /* 2^-80 */ && big <= 0x1p40f && eta >= 0x1p-22f && eta <= 0x1p20f;
+  const bool ok = top <= SHORT_V_TOP_BITS && low >= 2u * SHORT_N_LOW_BITS - 1u && big <= SHORT_N_TOP && eta >= SHORT_ETA_LOW && eta <= SHORT_ETA_TOP;
   v4f u;
   if (__ballot(!ok) == 0ull) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const float z = fmaxf(v[k], 0x1p-96f), y = __builtin_amdgcn_rsqf(z), g = z * y;
-      const float d = fmaf(fmaf(-g, g, z), 0.5f * y, g) + eta;
-      const float n = fabsf(m[k]);
-      const float r0 = __builtin_amdgcn_rcpf(d), r = fmaf(fmaf(-d, r0, 1.0f), r0, r0);
-      const float q0 = n * r, q1 = fmaf(fmaf(-d, q0, n), r, q0);
-      u[k] = __builtin_copysignf(fmaf(fmaf(-d, q1, n), r, q1), m[k]);
-    }
+    for (int k = 0; k < 4; ++k) u[k] = __builtin_copysignf(short_quotient(fabsf(m[k]), short_denominator(v[k], eta)), m[k]);
   } else {
 #pragma unroll
     for (int k = 0; k < 4; ++k) u[k] = m[k] / (sqrtf(v[k]) + eta);

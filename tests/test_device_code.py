@@ -25,6 +25,19 @@ BIG = """
                                                                   LayerTab, const int*);
 BIG(false) BIG(true)
 """
+RESIDENT = """
+#define RESIDENT(K, LP) template __global__ void obk::k_ratios_apply_resident<8, K, LP>(RatioArgs, ApplyArgs, LayerSync, LayerTab);
+RESIDENT(false, false) RESIDENT(false, true) RESIDENT(true, false) RESIDENT(true, true)
+"""
+TRAIL = """
+#define TRAIL(K, LP) template __global__ void obk::k_ratios_trail<K, LP>(RatioArgs, VfHist, VTerms, ApplyArgs, RatioTrailTab, LayerTab);
+TRAIL(false, false) TRAIL(false, true) TRAIL(true, false) TRAIL(true, true)
+"""
+LAMB = """
+#define LAMB(GT, LP) template __global__ void obk::k_warmup_resident<8, 1, GT, LP>( \\
+    GradSrc, float*, float*, float*, WarmSync, float, float, float, float, float, float, float, LayerTab, void*, int);
+LAMB(0, false) LAMB(0, true) LAMB(1, false) LAMB(1, true)
+"""
 
 
 def assembly(tmp_path, kernels):
@@ -48,11 +61,21 @@ def test_second_reads_are_kept_only_where_asked_for(tmp_path):
     assert hints == [3, 2], hints
 
 
-@pytest.mark.parametrize("name,kernels,n", [("k_ratios_apply_hist", HIST, 8), ("k_ratios_big_hist", BIG, 2)])
-def test_kernels_of_the_large_lists_keep_their_registers(tmp_path, name, kernels, n):
-    """k_ratios_apply_hist without the rest tiles in its launch and k_ratios_big_hist have no spills at the occupancy that they are
-    built for."""
-    text = assembly(tmp_path, kernels)
+def spills(tmp_path, name, kernels):
+    """(scalar, vector) registers that each instantiation of the kernel spills at the occupancy that it is built for."""
     counts = re.findall(r"\.name:\s+_ZN3obk%d%s.*?\.sgpr_spill_count:\s+(\d+).*?\.vgpr_spill_count:\s+(\d+)" % (len(name), name),
-                        text, re.S)
-    assert len(counts) == n and all(c == ("0", "0") for c in counts), counts
+                        assembly(tmp_path, kernels), re.S)
+    return [(int(a), int(b)) for a, b in counts]
+
+
+@pytest.mark.parametrize("name,kernels,n", [("k_ratios_apply_hist", HIST, 8), ("k_ratios_big_hist", BIG, 2), ("k_ratios_apply_resident", RESIDENT, 4),
+                                            ("k_ratios_trail", TRAIL, 4), ("k_warmup_resident", LAMB, 4)])
+def test_kernels_of_the_large_lists_keep_their_registers(tmp_path, name, kernels, n):
+    """The kernels of the large lists (k_ratios_apply_hist without the rest tiles in its launch) have no spills."""
+    assert spills(tmp_path, name, kernels) == [(0, 0)] * n
+
+
+def test_rest_tiles_in_the_launch_spill_no_vector_registers(tmp_path):
+    """With the rest tiles in its launch k_ratios_apply_hist spills scalar registers, into the lanes of one vector register (64)."""
+    counts = spills(tmp_path, "k_ratios_apply_hist", HIST.replace("S, false>", "S, true>"))
+    assert len(counts) == 8 and all(a <= 64 and b == 0 for a, b in counts), counts

@@ -209,9 +209,11 @@ __device__ __forceinline__ int walk_layer(int l, int64_t i, const int64_t* __res
 
 // Sign nibble of the lane's 4 elements -> the 32-bit word of its 8-lane group (in every lane of
 // the group).  Element 4*lane + k of the 256-element span is bit 4*(lane%8) + k of word lane/8.
-// THROUGH_LDS (here and in block_sum): by ds_bpermute, as k_compress_resident does, whose 16 spans a tile leave a barrier together: with register
-// moves its large lists are slower (plain form, a step, us, moves / LDS: 214 M elements 1728 / 1710, 100 M 781 / 772, 54 M 422 / 417, 34 M 263 / 259.5,
-// 18 M 147.5 / 147, 4.4 M 56.7 / 56.0, with a bf16 gradient 54.4 / 55.7); either one alone changes nothing.
+// THROUGH_LDS (here and in block_sum): by ds_bpermute, as k_compress_resident does, whose 16 spans a tile leave a barrier together.  A step of the plain
+// form on the same buffers, us, register moves / LDS: 214 M elements 1703 / 1687, 100 M 786 / 781, 54 M 419 / 412, 34 M 265 / 261, 18 M 146.3 /
+// 145.6, 4.4 M 55.8 / 54.9; with a bf16 gradient 54 M 393 / 394, 18 M 138.2 / 138.9, 4.4 M 54.0 / 54.8; either one alone changes nothing.  Occupancy (5
+// workgroups) and spills (none) are alike; what differs is how closely the 16 spans' stores follow each other.  k_server_resident, of 1 to 4 spans and with
+// the same barrier, keeps the moves: its call 8.7 / 9.1 (8 workers, 1.4 M elements), 17.1 / 17.5 (64, 1.7 M), 37.1 / 37.5 (256, 1.3 M).
 template <bool THROUGH_LDS = false>
 __device__ __forceinline__ unsigned int gather_word(unsigned int nibble) {
   unsigned int v = nibble << (4 * (threadIdx.x & 7));
@@ -1038,8 +1040,8 @@ __device__ __forceinline__ float select_by_bit(unsigned int word, int pos, float
 // quotient is 0 or NaN; a NaN n or d, whose product fmaxf ignores and whose quotient is a NaN, not taken; with the bound at 0, n = anything over
 // d = inf (the fma a NaN), the same 0 or NaN; with the bound at infinity everything, as nothing exceeds it.
 // Measured with UpdateTerm and select_by_bit's two instructions, four steps, us, before / after: 11 M parameters 327 / 322, 336 M fp32 6785 /
-// 6748, bf16 6946 / 6876 (the vector work of k_ratios_apply_hist, 82 instructions an element, then 50, next to memory at 88 % of
-// a copy's rate).
+// 6748, bf16 6946 / 6876 (the vector work of k_ratios_apply_hist, counted over four launches of a period 71 instructions an element, then 53, next
+// to memory at 88 % of a copy's rate).
 struct MaxQuotient {
   float bound;   // uniform over the wavefront
   float r;       // the lane's
@@ -2149,8 +2151,8 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_big_hist(RatioArgs
 // the signs, none of which a ratio workgroup writes, forms m_t/(sqrt(v_frozen)+eta) and then waits for that flag, which by then
 // is normally there.  Ratio workgroups wait for nothing and an update workgroup only for ones dispatched before it: progress needs
 // in-order dispatch, not co-residency; the wait is bounded (errflag).
-// Bound by HBM and the memory-side cache together: 17.8 bytes per element from one (four-step average), 4 from the other.  1.21e9 elements in layers of
-// 12.6, 16.8 and 103 M: 3.65 ms a step, 7.2 TB/s of what is asked for; 4.04 in two kernels; with v_frozen not kept 4.4.
+// Bound by HBM and the memory-side cache together: 21.6 bytes per element are asked for (four-step average), 4.1 of them a second time.  1.21e9 elements
+// in layers of 12.6, 16.8 and 103 M: 3.64 ms a step, 7.2 TB/s of what is asked for, 5.8 without the second reads; 4.04 in two kernels; with v_frozen not kept 4.4.
 // (The ratio pass stands in both kernels: as a function of its own it makes each of them spill 306 vector registers.)
 struct RatioTrailTab {
   const unsigned int* items;    // flags above | tile's position in lt.tile_list

@@ -355,10 +355,13 @@ inline int arrivals_one_level(int n_listed_tiles, int cus) { return n_listed_til
 // Spans per tile of the server kernel without a barrier (k_server_unpack_avg).  With few workers a tile of 1024 elements is a
 // chain of latencies (scales, LDS, words) around a few additions: larger ones where the chunk still makes rounds of
 // the device; with many workers the additions bind, and more, smaller workgroups hide them better.  The call, us, 1 / 2 / 4 spans
-// (above 1 with chunk_ticket, which by then costs less than a launch: 0.3 to 4 us), workers, tiles of 1024 elements:
-//   1, 107520 229 / 160 / 153; 2, 53760 121 / 88.1 / 80.7; 2, 5504 17.4 / 14.1 / 13.4; 4, 26880 73.8 / 46.0 / 45.1; 4, 2752 12.1 /
-//   9.9 / 10.6; 8, 13440 36.4 / 28.1 / 28.4; 8, 1376 8.4 / 8.4 / 9.7; 16, 6720 24.4 / 21.6 / 22.2; 16, 688 7.4 / 8.0 / 9.6; 32,
-//   3360 19.6 / 19.2 / 22.8; 64, 5254 37.3 / 37.5 / 42.7; 64, 1680 18.0 / 19.8 / 21.0; 128, 840 18.7 / 20.8 / 31.1
+// (above 1 with chunk_ticket, which costs less than a launch by then), workers, tiles of 1024 elements:
+//   1, 107520 202 / 157 / 151; 2, 53760 111 / 86.7 / 78.6; 2, 5504 16.0 / 13.4 / 12.8; 4, 26880 67.3 / 43.6 / 43.7; 4, 2752 11.4 /
+//   9.4 / 9.9; 8, 13440 31.3 / 26.2 / 26.6; 8, 4096 13.1 / 11.4 / 12.6; 8, 2048 10.5 / 8.9 / 9.2; 8, 1376 10.2 / 7.9 / 9.1; 16, 6720 21.3 / 19.8 / 20.3;
+//   16, 2048 10.0 / 10.5 / 11.1; 16, 688 10.2 / 8.1 / 9.3; 32, 3360 17.2 / 17.2 / 21.0; 32, 2048 12.3 / 13.3 / 13.9; 64, 5254 33.7 / 34.4 / 39.9; 64, 1680
+//   15.7 / 18.1 / 19.2; 128, 840 15.2 / 17.7 / 30.0
+// with one span and the ticket: 8, 2048 8.9; 8, 1376 8.0; 16, 2048 9.6; 16, 688 7.7; 32, 2048 12.2; 64, 1680 15.5 (single calls in a row: a second launch
+// costs what it does not in a step, whose kernels follow each other).
 // (The line: 16 and 8 tiles a CU, one or two rounds of the device.)
 inline int server_spans(int64_t W, int tpc, int cus) {
   if (W <= 2 && tpc >= 16 * cus) return 4;
@@ -461,22 +464,29 @@ inline SmallShape small_shape(int U, const std::vector<int64_t>& h_off, int64_t 
 // finish in turn, and many workgroups.  k_ratios_apply_small reads a slot for every tile of its layer, which costs next to nothing; only
 // workgroups of several layers side by side cost it time (those of one layer, up to 1600, do not).  k_warmup_small's arrivals queue
 // at a counter, in two levels from SMALL_ONE_LEVEL on.
-// Compression steps and LAMB steps at U = 1 / 2 / 4, us (256 CUs; four steps in 20 or so of the lists; -: does not fit):
+// Compression steps and LAMB steps at U = 1 / 2 / 4, us (256 CUs; -: does not fit; those below 20 us are bound by the host):
 //   elements, tensors      steps with the variance's history       steps without             LAMB steps
-//   0.41 M, one            21.2 / 22.1 / 24.5                      20.0 / 20.6 / 22.8        8.6 / 8.8 / 10.3
-//   0.50 M, four           22.5 / 22.8 / 27.2                      21.6 / 21.9 / 26.8        10.6 / 9.0 / 15.5
-//   0.52 M, eight          21.3 / 22.2 / 25.0                      20.3 / 21.2 / 23.3        8.1 / 8.5 / 9.9
-//   0.80 M, one            24.5 / 25.2 / 25.8                      24.3 / 24.5 / 24.3        10.1 / 10.4 / 10.9
-//   0.90 M, one, padded    24.0 / 25.9 / 30.3                      23.5 / 25.1 / 30.2        11.1 / 12.3 / 17.5
-//   0.99 M, eight, shared  25.7 / 26.5 / 31.3                      25.5 / 25.9 / 31.3        10.0 / 13.5 / 19.2
-//   1.05 M, four           25.6 / 24.7 / 26.3                      25.1 / 23.3 / 24.6        10.3 / 10.8 / 11.2
-//   1.31 M, five           28.1 / 26.9 / 28.0                      28.0 / 25.5 / 26.5
-//   1.57 M, six            30.2 / 28.0 / 29.1                      31.2 / 26.7 / 27.6
-//   1.60 M, one, padded    30.0 / 30.7 / 32.0                      29.6 / 28.8 / 31.7        13.8 / 13.2 / 17.5
-//   1.64 M, one            29.5 / 30.2 / 29.9                      29.0 / 28.5 / 28.3        13.4 / 13.2 / 13.6
-//   1.6 M, 109 tensors     29.9 / 32.2 / 36.2                      30.3 / 31.5 / 35.9        14.8 / 16.9 / 22.9
-//   0.18 M, 46 tensors     19.8 / 21.6 / 27.2                      18.4 / 21.1 / 26.2        10.6 / 12.6 / 19.2
-// The choice is the fastest of these lists and 20 like them or within 4 %, on average within 0.2 %.
+//   0.18 M, 46 tensors     18.8 / 19.1 / 23.5                      17.6 / 18.8 / 23.8        9.2 / 11.3 / 16.9
+//   0.41 M, one            18.5 / 18.7 / 20.2                      17.5 / 18.7 / 20.0        7.2 / 7.2 / 9.0
+//   0.50 M, four, shared   19.4 / 19.4 / 23.4                      19.0 / 19.4 / 23.7        8.8 / 7.6 / 13.5
+//   0.52 M, eight          18.7 / 18.8 / 20.9                      18.0 / 18.5 / 20.8        6.8 / 7.0 / 8.6
+//   0.64 M, one            19.3 / 20.1 / 21.8                      19.1 / 19.8 / 21.2        8.3 / 8.3 / 9.7
+//   0.90 M, one, padded    20.5 / 22.2 / 26.4                      20.2 / 22.2 / 27.0        9.3 / 10.6 / 14.6
+//   0.92 M, four           21.8 / 21.7 / 22.7                      22.6 / 21.1 / 21.8        8.0 / 8.5 / 9.2
+//   0.99 M, eight, shared  22.1 / 23.1 / 27.9                      22.3 / 23.2 / 27.7        8.1 / 11.1 / 16.3
+//   1.00 M, hundred        21.6 / 24.0 / 28.8                      21.5 / 23.9 / 28.9        10.5 / 12.8 / 17.4
+//   1.05 M, four           21.1 / 21.0 / 23.2                      20.9 / 20.2 / 22.3        7.9 / 8.6 / 9.1
+//   1.2 M, three           22.9 / 23.4 / 23.8                      23.6 / 23.4 / 22.9        8.9 / 9.1 / 10.5
+//   1.31 M, five           23.7 / 23.4 / 25.0                      23.9 / 22.7 / 24.1        8.8 / 9.5 / 10.9
+//   1.5 M, 110 tensors     25.5 / 26.8 / 31.5                      25.6 / 26.4 / 31.4        12.3 / 14.2 / 19.6
+//   1.57 M, six            25.7 / 24.1 / 25.0                      26.8 / 23.3 / 24.1        9.5 / 10.0 / 11.3
+//   1.60 M, one, padded    25.6 / 25.6 / 27.3                      24.7 / 24.4 / 27.5        12.4 / 11.0 / 15.0
+//   1.64 M, one            25.0 / 25.4 / 25.4                      24.3 / 24.4 / 24.3        11.5 / 11.1 / 12.1
+//   1.64 M, sixteen        26.4 / 24.8 / 24.8                      26.7 / 23.9 / 24.0        9.8 / 9.7 / 11.2
+//   1.84 M, seven          - / 25.6 / 25.7                         - / 24.6 / 24.6           - / 10.8 / 11.5
+//   2.4 M, one             - / - / 30.9                            - / - / 29.7              - / - / 14.2
+// The choice is the fastest of these and of six lists like them or within 3.4 %, on average within half a per cent, but for the LAMB step of 1.57 M in six
+// tensors (two spans, 5 % behind one).
 constexpr int SMALL_ONE_LEVEL = 128;   // (figures at k_warmup_small)
 inline int64_t small_cost(int U, const SmallShape& sh, bool by_slots, int cus) {
   int64_t c = (U == 1 ? 0 : U == 2 ? 500 : 2000) + 2500 * std::max(sh.mixed_spans - 1, 0) + 100 * sh.max_seg +
@@ -494,9 +504,10 @@ inline int small_choice(const SmallShape (&sh)[3], const bool (&fits)[3], bool b
 }
 // A list all of whose parameters lie in 8192-element tiles of layers that the barrier kernels take keeps those where one layer
 // has more than this many 1024-element spans.  Steps of one tensor, or two, us, in one launch / in the barrier kernel, with the
-// variance's history, without, LAMB: 1.6 M (1600 spans) 29.9 / 33.9, 28.3 / 33.4, 13.6 / 17.6; two of 1.6 M 40.2 / 39.7, 39.1 /
-// 40.3, 20.6 / 21.6; 2.4 M (2304) 35.3 / 37.0, 33.5 / 37.6, 16.3 / 20.0; 3.2 M (3136) 40.2 / 39.4, 39.4 / 40.0, 21.1 / 22.3.
-// (One limit for both calls; compression steps with the history are what runs most.)
+// variance's history, without, LAMB: 1.6 M (1600 spans) 25.5 / 28.8, 24.8 / 29.4, 11.3 / 16.3; two of 1.6 M 36.8 / 36.7, 35.9 /
+// 37.3, 16.7 / 19.4; 2.4 M (2304) 31.2 / 33.0, 30.4 / 34.2, 15.3 / 18.9; 2.9 M (2880) 33.4 / 34.8, 32.9 / 36.3, 15.6 / 19.8; 3.2 M (3136) 36.4 / 36.0, 35.5 /
+// 37.8, 17.2 / 20.4.  (One limit for all calls; compression steps with the history are what runs most.  By these figures it could lie at 3000 spans, and
+// nowhere for the LAMB step.)
 constexpr int64_t SMALL_MAX_SPANS = 2800;
 
 // Tilings of the tile sizes that a SmallPlan may take, formed when first asked for, and their shapes.

@@ -663,12 +663,14 @@ void dispatch_u(int u, F f) {
 // a returning atomic before it retires, and the last ones of up to 64 tiles a second one where a chunk has more
 // than 64 (TICKET_SUB).  n_tiles: the worker's 1024-element tiles; a round: 8 workgroups per CU.  A step, us, with
 // a launch / with the ticket in the worker's call (256 CUs):
-//   chunks of at most 64 tiles: 1024 tiles 30.2 / 28.6, 4096 50.0 / 49.0, 8192 76.4 / 74.9, 16384 119.0 / 120.6
-//   more:  640 tiles 27.2 / 26.0, 1536 30.8 / 30.0, 2560 44.0 / 44.3, 3072 45.8 / 45.3, 6144 58.8 / 58.6,
-//          8192 67.5 / 68.0, 14336 98.9 / 101.6, 24576 161.6 / 165.7, 40960 248.1 / 255.0
+//   chunks of at most 64 tiles: 1024 tiles 26.4 / 22.6, 2048 28.8 / 27.7, 4096 41.2 / 41.0, 8192 61.8 / 61.0, 16384 110.2 / 110.3
+//   more:  640 tiles 27.1 / 23.3, 1536 26.7 / 23.9, 2560 31.6 / 31.2, 3072 32.8 / 33.2, 6144 50.3 / 50.1, 8192 59.0 / 59.4,
+//          14336 93.2 / 94.0, 24576 137.2 / 140.8, 40960 220.1 / 227.1; chunks of 512 39.7 / 40.2, of 1376 75.1 / 74.4
 // and in the server's, whose grid is the one chunk:
-//   at most 64 tiles: of 1024 30.2 / 28.8, of 4096 50.0 / 49.1, of 16384 119.0 / 117.3
-//   more:  of 640 27.2 / 25.9, of 2048 41.2 / 41.5, of 6144 58.8 / 59.0, of 8192 67.5 / 68.4, of 16384 110.2 / 111.6
+//   at most 64 tiles: of 1024 26.4 / 22.8, of 4096 41.2 / 41.3, of 8192 61.8 / 61.3, of 16384 110.2 / 108.7
+//   more:  of 640 27.1 / 23.4, of 2560 31.6 / 32.0, of 6144 50.3 / 50.7, of 8192 59.0 / 59.3, of 24576 137.2 / 139.4, of 40960 220.1 /
+//          221.8; but chunks of 1376 75.1 / 74.0 (eight workers), of 2048 102.9 / 101.7, which the line leaves with a launch
+// (Steps with the host in them; lists of less than 1000 tiles are bound by it.)
 bool two_level_ticket(int tpc, int n_tiles, int cus) { return tpc <= 256 && n_tiles <= 3 * 8 * cus; }
 bool worker_ticket(int tpc, int n_tiles, int cus) {
   return (tpc <= TICKET_SUB && n_tiles <= 5 * 8 * cus) || two_level_ticket(tpc, n_tiles, cus);

@@ -458,7 +458,8 @@ __device__ __forceinline__ void chunk_ticket(const ChunkTicket& tk, double* part
 // scale itself follows from the tile partials, in k_chunk_scale or (TICKET) in the last workgroup of
 // the chunk to finish.  packed_out / pe.bits may be the same buffer: a word is read and rewritten by
 // the same 8 lanes, in program order.
-template <int U, bool HAS_K, bool PACKED_M, int GT = 0, bool DEFER = false, bool TICKET = false>
+// SUM_LDS: worker_sum_lds in the host code.
+template <int U, bool HAS_K, bool PACKED_M, int GT = 0, bool DEFER = false, bool TICKET = false, bool SUM_LDS = false>
 __global__ __launch_bounds__(BLOCK) void k_momentum_z_sumsq(
     GradSrc g, const float* __restrict__ m, PackedMom pm,
     float* __restrict__ err, double* __restrict__ partials, int64_t n_c, int tpc, float beta1,
@@ -510,7 +511,7 @@ __global__ __launch_bounds__(BLOCK) void k_momentum_z_sumsq(
       }
     }
   }
-  const double s = block_sum(acc, lds);
+  const double s = block_sum<BLOCK, SUM_LDS>(acc, lds);
   if (TICKET) {
     if (threadIdx.x < WAVE) chunk_ticket(tk, partials, p, tpc, n_c, s);
   } else if (threadIdx.x == 0) {

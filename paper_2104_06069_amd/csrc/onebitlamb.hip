@@ -270,6 +270,7 @@ struct ob_lamb_ctx {
   LayerSplit sp_apply;                     // ob_lamb_ratios_apply
   LayerSplit sp_warm;                      // ob_lamb_warmup_step
   SmallPlan sm_apply, sm_warm;             // the same calls on lists small enough for one launch
+  bool sum_lds = false;                    // worker_sum_lds
   unsigned int* d_ticket = nullptr;        // chunk_ticket: counters of the worker's chunks (NULL: not used)
   unsigned int* d_ticket_srv = nullptr;    // ... of the served chunk
   double* d_ticket_part = nullptr;
@@ -1044,6 +1045,7 @@ static ob_status create_ctx(const ob_lamb_config* cfg, ob_lamb_ctx** out) {
     if (cfg->spin_limit == OB_SPIN_NONE) ctx->spin_limit = 0;
     else if (cfg->spin_limit > 0 && cfg->spin_limit < ctx->spin_limit) ctx->spin_limit = cfg->spin_limit;
     ctx->u_srv = server_spans(ctx->W, ctx->tpc_srv, cus);
+    ctx->sum_lds = worker_sum_lds(ctx->n_tiles, cus);
     ctx->n_srv = (ctx->tpc_srv + ctx->u_srv - 1) / ctx->u_srv;
     const bool two_pass = (cfg->flags & OB_CFG_TWO_PASS_COMPRESS) != 0;
     ctx->resident = ok && !two_pass && 5 * (tpc_res + 8) <= 4 * slots;
@@ -1346,15 +1348,19 @@ ob_status ob_lamb_compress_local_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st, c
     if (packed_m && st->m_packed == st->err_packed) return OB_ERR_ARG;
     const LayerTab lt = layer_tab(ctx, st, ctx->d_first_layer);
     const ChunkTicket tk = chunk_ticket_of(ctx->d_ticket, ctx->d_ticket_part, ctx->W, ctx->tpc, scales_out, oc.scale, oc.chunk);
-    dispatch2(st->mom_scale != nullptr, packed_m, [&](auto hk, auto pk) {
-      dispatch2(lpg, tk.count != nullptr, [&](auto lg, auto ti) {
-        OB_LAUNCH(la, KID_COMPRESS_DEFERRED,
-                  (k_momentum_z_sumsq<U_MAIN, decltype(hk)::value, decltype(pk)::value,
-                                      decltype(lg)::value ? 1 : 0, true, decltype(ti)::value>),
-                  ctx->n_tiles, gs, st->m, pm, st->err_worker, ctx->d_partials, ctx->n_c, ctx->tpc,
-                  ctx->beta1, ctx->omb1, lt, pe, packed_out, oc, tk);
+    if (ctx->sum_lds && lpg && packed_m && !st->mom_scale && !tk.count)
+      OB_LAUNCH(la, KID_COMPRESS_DEFERRED, (k_momentum_z_sumsq<U_MAIN, false, true, 1, true, false, true>), ctx->n_tiles, gs, st->m,
+                pm, st->err_worker, ctx->d_partials, ctx->n_c, ctx->tpc, ctx->beta1, ctx->omb1, lt, pe, packed_out, oc, tk);
+    else
+      dispatch2(st->mom_scale != nullptr, packed_m, [&](auto hk, auto pk) {
+        dispatch2(lpg, tk.count != nullptr, [&](auto lg, auto ti) {
+          OB_LAUNCH(la, KID_COMPRESS_DEFERRED,
+                    (k_momentum_z_sumsq<U_MAIN, decltype(hk)::value, decltype(pk)::value,
+                                        decltype(lg)::value ? 1 : 0, true, decltype(ti)::value>),
+                    ctx->n_tiles, gs, st->m, pm, st->err_worker, ctx->d_partials, ctx->n_c, ctx->tpc,
+                    ctx->beta1, ctx->omb1, lt, pe, packed_out, oc, tk);
+        });
       });
-    });
     if (!tk.count)
       OB_LAUNCH_B(la, KID_CHUNK_SCALE, k_chunk_scale, ctx->W, FBLOCK, ctx->d_partials, ctx->tpc, ctx->n_c, scales_out,
                   oc.scale, oc.chunk);

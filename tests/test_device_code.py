@@ -25,6 +25,11 @@ BIG = """
                                                                   LayerTab, const int*);
 BIG(false) BIG(true)
 """
+WORKER = """
+#define WORKER(K, GT, LDS) template __global__ void obk::k_momentum_z_sumsq<1, K, true, GT, true, false, LDS>( \
+    GradSrc, const float*, PackedMom, float*, double*, int64_t, int, float, float, LayerTab, PackedErr, uint32_t*, OwnCopy, ChunkTicket);
+WORKER(false, 0, false) WORKER(false, 1, false) WORKER(true, 1, false) WORKER(false, 1, true)
+"""
 RESIDENT = """
 #define RESIDENT(K, LP) template __global__ void obk::k_ratios_apply_resident<8, K, LP>(RatioArgs, ApplyArgs, LayerSync, LayerTab);
 RESIDENT(false, false) RESIDENT(false, true) RESIDENT(true, false) RESIDENT(true, true)
@@ -59,6 +64,15 @@ def test_second_reads_are_kept_only_where_asked_for(tmp_path):
         body = re.search(r"^_ZN3obk13k_ratios_passILi1ELb0ELb0ELb%s\w*:[^\n]*$(.*?)s_endpgm" % keep, text, re.S | re.M).group(1)
         hints.append(len(re.findall(r"global_load_dwordx4 .* nt$", body, re.M)))
     assert hints == [3, 2], hints
+
+
+def test_worker_s_sum_of_squares_goes_through_lds_only_where_asked_for(tmp_path):
+    """k_momentum_z_sumsq: six doubles by ds_bpermute, or none, and nothing else through LDS that way."""
+    text = assembly(tmp_path, WORKER)
+    for k, gt, lds in ((0, 0, 0), (0, 1, 0), (1, 1, 0), (0, 1, 1)):
+        body = re.search(r"^_ZN3obk18k_momentum_z_sumsqILi1ELb%dELb1ELi%dELb1ELb0ELb%dE\w*:[^\n]*$(.*?)^\.Lfunc_end" % (k, gt, lds), text,
+                         re.S | re.M).group(1)
+        assert len(re.findall(r"^\s+ds_bpermute_b32", body, re.M)) == 12 * lds, (k, gt, lds)
 
 
 def spills(tmp_path, name, kernels):

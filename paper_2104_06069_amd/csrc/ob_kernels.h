@@ -458,7 +458,7 @@ __device__ __forceinline__ void chunk_ticket(const ChunkTicket& tk, double* part
 // scale itself follows from the tile partials, in k_chunk_scale or (TICKET) in the last workgroup of
 // the chunk to finish.  packed_out / pe.bits may be the same buffer: a word is read and rewritten by
 // the same 8 lanes, in program order.
-// SUM_LDS: worker_sum_lds in the host code.
+// SUM_LDS (and the sign words): worker_sum_lds in the host code.
 template <int U, bool HAS_K, bool PACKED_M, int GT = 0, bool DEFER = false, bool TICKET = false, bool SUM_LDS = false>
 __global__ __launch_bounds__(BLOCK) void k_momentum_z_sumsq(
     GradSrc g, const float* __restrict__ m, PackedMom pm,
@@ -502,7 +502,7 @@ __global__ __launch_bounds__(BLOCK) void k_momentum_z_sumsq(
         if (DEFER) nib |= ((z[k] >= 0.0f) ? 1u : 0u) << k;
       }
       if (DEFER) {
-        const unsigned int word = gather_word(nib);
+        const unsigned int word = gather_word<SUM_LDS>(nib);
         if ((threadIdx.x & 7) == 0) {
           const int64_t span0 = p.tile0 + u * SPAN;
           (packed_out + (span0 >> 5))[threadIdx.x >> 3] = word;

@@ -52,12 +52,14 @@ constexpr int tile_from_end(unsigned int b, unsigned int n) {
 constexpr int64_t KEEP_MIN_CHUNK = 64 * SPAN, KEEP_MIN = 8000000;
 constexpr bool keeps_second_reads(int64_t n, int64_t W) { return n >= (W * KEEP_MIN_CHUNK < KEEP_MIN ? W * KEEP_MIN_CHUNK : KEEP_MIN); }
 
-// Whether the worker's pass with a 16-bit gradient and no momentum scaling sums its tile's squares through LDS instead of by register moves: the code
-// before the sum is the same, and so are registers and occupancy; what differs is when the workgroups leave, and so how the next ones' loads meet
-// the stores.  A step on the same buffers, us, register moves / LDS: 6 M elements 50.7 / 50.9 and 53.3 / 53.7, 8 M 62.7 / 63.2, 13 M 93.7 / 93.0, 28 M 154.5 / 155.2,
-// 50 M 249.3 / 250.5, 80 M 403.3 / 402.2, 110 M 552 / 549.5, 150 M 820 / 814, 336 M 1675 / 1654, 700 M 3528 / 3466; the call alone 110 M 200 / 196, 336 M 596 / 579,
-// 1000 M 1773 / 1705.  With momentum scaling the moves are faster everywhere (336 M 564 / 577), and in fp32 (660 / 663).
-inline bool worker_sum_lds(int64_t n_tiles, int cus) { return n_tiles >= 256 * (int64_t)cus; }
+// Whether the worker's pass with a 16-bit gradient and no momentum scaling sums its tile's squares and forms its sign words through LDS
+// instead of by register moves: the code before is the same, and so are registers and occupancy; what differs is when the workgroups leave, and so how
+// the next ones' loads meet the stores.  The call on the same buffers, us, register moves / LDS (8 workers): 6 M elements 13.8 / 14.6, 12 M 23.8 / 24.3, 18 M
+// 34.2 / 33.9, 27 M 50.6 / 49.4, 36 M 68.0 / 65.3, 50 M 94.2 / 89.7, 110 M 194.4 / 187, 336 M 591 / 554, 700 M 1218 / 1152; 780 lists of 13 to 73 M with 1 to 256
+// workers, mean of moves over LDS by tiles a CU: 50 to 60 0.989, 60 to 80 1.000, 80 to 100 1.016, 120 to 240 1.028, 240 to 256 1.031.  (The sum alone through
+// LDS: 336 M 574, 700 M 1177.)  With momentum scaling the moves are faster everywhere (336 M 566 / 581), and in fp32 not slower (18 M 38.8 / 38.8, 50 M 98.3 /
+// 98.8, 336 M 660 / 659).
+inline bool worker_sum_lds(int64_t n_tiles, int cus) { return n_tiles >= 80 * (int64_t)cus; }
 
 // Arrivals at a layer's barrier with nl listed tiles, whose segments are seg0 .. seg1-1 and of which those from skip_first to
 // skip_end-1 lie in listed or big tiles; the number of the arrival of one of the others, sg (the listed tiles come first).

@@ -222,7 +222,7 @@ void big_rule() {
     CHECK(!rest_in_launch(1, 20 * cus, 1, cus, 99) && !rest_in_launch(5 * cus + 1, 30 * cus, 0, cus, 99) && !rest_in_launch(1, 0, 0, cus, 9));
     CHECK(server_spans(2, 16 * cus, cus) == 4 && server_spans(3, 16 * cus, cus) == 2 && server_spans(1, 16 * cus - 1, cus) == 2);
     CHECK(server_spans(32, 8 * cus, cus) == 2 && server_spans(32, 8 * cus - 1, cus) == 1 && server_spans(33, 99 * cus, cus) == 1);
-    CHECK(worker_sum_lds(256 * cus, cus) && !worker_sum_lds(256 * cus - 1, cus));
+    CHECK(worker_sum_lds(80 * cus, cus) && !worker_sum_lds(80 * cus - 1, cus));
     CHECK(arrivals_one_level(40 * cus, cus) == 256 && arrivals_one_level(40 * cus + 1, cus) == 512);
   }
 }

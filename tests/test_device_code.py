@@ -67,12 +67,12 @@ def test_second_reads_are_kept_only_where_asked_for(tmp_path):
 
 
 def test_worker_s_sum_of_squares_goes_through_lds_only_where_asked_for(tmp_path):
-    """k_momentum_z_sumsq: six doubles by ds_bpermute, or none, and nothing else through LDS that way."""
+    """k_momentum_z_sumsq: six doubles and the sign word's three steps by ds_bpermute, or none."""
     text = assembly(tmp_path, WORKER)
     for k, gt, lds in ((0, 0, 0), (0, 1, 0), (1, 1, 0), (0, 1, 1)):
         body = re.search(r"^_ZN3obk18k_momentum_z_sumsqILi1ELb%dELb1ELi%dELb1ELb0ELb%dE\w*:[^\n]*$(.*?)^\.Lfunc_end" % (k, gt, lds), text,
                          re.S | re.M).group(1)
-        assert len(re.findall(r"^\s+ds_bpermute_b32", body, re.M)) == 12 * lds, (k, gt, lds)
+        assert len(re.findall(r"^\s+ds_bpermute_b32", body, re.M)) == 15 * lds, (k, gt, lds)
 
 
 def spills(tmp_path, name, kernels):

@@ -1,5 +1,5 @@
-"""The worker's pass with a 16-bit gradient on both sides of the list length from which it sums the squares of its tiles through LDS
-(256 tiles of 1024 elements a CU), against binary32 arithmetic in numpy: error and sign words bit for bit, scales of the same sum."""
+"""The worker's pass with a 16-bit gradient on both sides of the list length from which it sums the squares of its tiles and
+forms their sign words through LDS (80 tiles of 1024 elements a CU), against binary32 arithmetic in numpy: error and sign words bit for bit, scales of the same sum."""
 import numpy as np
 import pytest
 
@@ -11,7 +11,8 @@ f32 = np.float32
 SPAN = 1024
 
 
-@pytest.mark.parametrize("tiles_of_chunk,cut,W", [(65536, 256, 1), (65535, 768, 1), (21846, 512, 3), (21845, 0, 3)])
+@pytest.mark.parametrize("tiles_of_chunk,cut,W", [(65536, 256, 1), (65535, 768, 1), (21846, 512, 3), (21845, 0, 3),
+                                                  (20480, 256, 1), (20479, 768, 1), (6827, 512, 3), (6826, 0, 3)])
 def test_pass(tiles_of_chunk, cut, W):
     import torch
     from paper_2104_06069_amd.step import DeviceStep

@@ -122,7 +122,7 @@ __device__ __forceinline__ v4f grad_value(const GradSrc& gs, v4h h) {
 template <int GT>
 __device__ __forceinline__ v4f load_grad(const GradSrc& gs, int64_t i) { return grad_value(gs, grad_request<GT>(gs, i)); }
 
-// (i0: uniform.  Addresses of the form uniform + lane's offset share the offset's register among all spans of a tile.)
+// (i0: uniform.)
 __device__ __forceinline__ void st4_lp(void* __restrict__ base, int64_t i0, int o, v4f v, int bf16) {
   v4h h;
 #pragma unroll
@@ -2104,8 +2104,8 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_big_hist(RatioArgs
     const int o = u * SPAN + o0;
     V[u] = 0.0f; VZ[u] = 0.0f;
     if (o < p.len) {
-      V[u] = ld4(ra.v_fresh + (p.tile0 + u * SPAN) + o0);
-      VZ[u] = ld4(ra.v_frozen + (p.tile0 + u * SPAN) + o0);
+      V[u] = ld4(ra.v_fresh + p.tile0 + o);
+      VZ[u] = ld4(ra.v_frozen + p.tile0 + o);
     }
   }
   StepTerms st;
@@ -2133,7 +2133,7 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_big_hist(RatioArgs
     const int o = u * SPAN + o0;
     if (o < p.len) {
       mq.add(VZ[u], V[u], u + 1 < U);
-      if (h.write_v) st4(ra.v_fresh + (p.tile0 + u * SPAN) + o0, V[u]);
+      if (h.write_v) st4(ra.v_fresh + p.tile0 + o, V[u]);
     }
   }
   const float r = block_max(mq.r, lds);
@@ -2340,6 +2340,12 @@ __global__ __launch_bounds__(BLOCK, OB_LB_MINW) void k_ratios_trail(RatioArgs ra
 // S > 0: v_frozen of S spans goes straight into LDS, and m/(sqrt(v_frozen)+eta) later in its place, 24 KB for
 // 6 spans: 72 to 79 registers instead of 96, so that 6 workgroups fit on a CU instead of 5.  Which form a
 // list takes: lh_in_lds in the host code.
+//
+// Here and in k_ratios_big_hist spans are addressed as tile0 + (span and lane): a scalar base and a 32-bit offset for every access.  As (tile0 + span) + lane,
+// which k_ratios_trail has (880 M elements in four layers 3412 / 3487 us the other way), they become 64-bit vector addresses, an addition with carry
+// or two before each load, which a list of few rounds waits for.  This kernel, us, so / as in k_ratios_trail: 4.3 M elements 21.8 / 22.8, 8.2 M 33.3 / 34.6, 11 M 40.5 /
+// 42.1, 42 M 93.1 / 95.2, 110 M 247.3 / 247.6, 336 M 887 / 883; the call on 61 drawn lists of 3 to 60 M
+// 1.9 % shorter on average (0.938 to 1.026 of the time; above 1 four that rewrite the variance at every step), above 60 M the same.
 constexpr int LH_WG_LDS = 6;   // workgroups per CU with S > 0
 template <bool HAS_K, bool LPX, int S, bool REST>
 __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratios_apply_hist(
@@ -2407,9 +2413,9 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
     const int o = u * SPAN + o0;
     V[u] = 0.0f; VZ[u] = 0.0f;
     if (o < p.len) {   // all lanes of a wavefront or none
-      V[u] = ld4(ra.v_fresh + (p.tile0 + u * SPAN) + o0);
-      if (u < S) lds_load16(ra.v_frozen + (p.tile0 + u * SPAN) + o0, &zs[u * BLOCK + wv_u * WAVE]);
-      else VZ[u] = ld4(ra.v_frozen + (p.tile0 + u * SPAN) + o0);
+      V[u] = ld4(ra.v_fresh + p.tile0 + o);
+      if (u < S) lds_load16(ra.v_frozen + p.tile0 + o, &zs[u * BLOCK + wv_u * WAVE]);
+      else VZ[u] = ld4(ra.v_frozen + p.tile0 + o);
     }
   }
   if constexpr (REST) st.template form<HAS_K>(ra, h, p.c, kt);
@@ -2453,7 +2459,7 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int o = u * SPAN + o0;
-      if (o < p.len) st4(ra.v_fresh + (p.tile0 + u * SPAN) + o0, V[u]);
+      if (o < p.len) st4(ra.v_fresh + p.tile0 + o, V[u]);
     }
   }
   v4f X[U];
@@ -2461,7 +2467,7 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
   for (int u = 0; u < U; ++u) {  // x is fetched while the layer completes
     const int o = u * SPAN + o0;
     X[u] = 0.0f;
-    if (o < p.len) X[u] = ld4(aa.x + (p.tile0 + u * SPAN) + o0);
+    if (o < p.len) X[u] = ld4(aa.x + p.tile0 + o);
   }
   // m_t/(sqrt(v_frozen)+eta), formed in place of v_frozen while the layer completes (the same
   // operations on the same operands as apply_uniform's)
@@ -2486,7 +2492,7 @@ __global__ __launch_bounds__(BLOCK, S > 0 ? LH_WG_LDS : OB_LB_MINW) void k_ratio
       v4f xn;
 #pragma unroll
       for (int k = 0; k < 4; ++k) xn[k] = X[u][k] - al * z[k];
-      st4(aa.x + (p.tile0 + u * SPAN) + o0, xn);
+      st4(aa.x + p.tile0 + o, xn);
       if (LPX) st4_lp(aa.x_lp, p.tile0 + u * SPAN, o0, xn, aa.x_lp_bf16);
     }
   }

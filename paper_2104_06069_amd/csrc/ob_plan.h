@@ -311,7 +311,7 @@ inline void trail_items(const std::vector<int>& n, const std::vector<int>& begin
 
 // k_ratios_trail: whole tiles for the ratio pass, in parts of RATIOS_TRAIL_U spans for the update, in the same order (what the cache is to
 // hold is v_frozen alone).  Four steps, us, k_ratios_big_hist and k_decompress_apply / k_ratios_trail (256 CUs): squares of
-// 3300 x 2 571 / 557, 3600 x 3 933 / 908, 5000 x 2 1179 / 1137, 5000 x 8 4400 / 4228, 7000 x 6 6438 / 6335, 20000 x 2 17990 / 17760, the
+// 3300 x 2 571 / 557, 3600 x 3 933 / 908, 5000 x 2 1179 / 1137, 5000 x 8 4400 / 4228, 7000 x 6 6438 / 6335, the
 // GPT list of 1.3e9 parameters 27900 / 26400, lists of its shape with one block, three quarters of their large layers one word embedding,
 // 2749 / 2715, 3225 / 3175, 3608 / 3555; but with no other large layer, in which to spread the embedding's update, 110 M 2301 / 2310,
 // 336 M 6728 / 6761.  So it is taken where an eighth of the large layers' tiles lies outside the largest of them (and there are more
@@ -325,6 +325,20 @@ constexpr unsigned int RATIOS_TRAIL_PART = 1u << 27;   // the part, above the ti
 inline bool ratios_trail(const std::vector<int>& n, int cus) {
   const int64_t total = std::accumulate(n.begin(), n.end(), (int64_t)0), most = n.empty() ? 0 : *std::max_element(n.begin(), n.end());
   return total >= 4 * (int64_t)cus && total < (int64_t)RATIOS_TRAIL_PART && 8 * (total - most) >= total;
+}
+// With a history, not where most of the elements lie in layers far beyond the cache: the two passes over one do not meet in it, and beside the ratio pass's reads
+// the update's, with a 16-bit copy above all, are only more streams at a time.  The call, us, period 4, two kernels / k_ratios_trail, squares (tiles of a layer):
+//   with a copy: 7500 x 10 (6867) 2054 / 1996, 8500 x 8 (8820) 2136 / 2122, 9500 x 6 (11017) 1983 / 2010 (but the step 3020 / 3015), 10000 x 8 (12208) 2907 /
+//   2964 (4456 / 4430), 10500 x 5 (13459) 2023 / 2063 (3072 / 3084), 11500 x 4 1925 / 1995 (2930 / 2971), 13000 x 3 1841 / 1927, 20000 x 2 2977 / 3134;
+//   without: 9500 x 6 1795 / 1788, 10500 x 5 1830 / 1842 (2996 / 2975), 11500 x 4 1738 / 1765 (2861 / 2864), 13000 x 3 1675 / 1704 (2759 / 2769),
+//   20000 x 2 2678 / 2715 (4406 / 4373), 20000 x 3 3977 / 4063 (6502 / 6522); period 2 as period 4; the array written at every step: no difference.
+// Lists by the share in layers above the line: with a copy 0.66 4201 / 4317 (6389 / 6434), 0.68 4087 / 4115 (6208 / 6174) and 4315 / 4322 (6573 / 6500), 0.81 2237 /
+// 2260 (3371 / 3361), 0.89 2564 / 2625 (3892 / 3904), 0.93 4040 / 4110 (6105 / 6128); without 0.81 2031 / 1994, 0.89 2314 / 2307, 0.93 3640 / 3631.
+constexpr int64_t RATIOS_TRAIL_LARGE = 2 * RATIOS_TRAIL_KEEP;
+inline bool ratios_trail_pays(const std::vector<int>& n, bool copy) {
+  int64_t total = 0, large = 0;
+  for (int q : n) total += q, large += q > RATIOS_TRAIL_LARGE ? q : 0;
+  return copy ? 4 * large <= 3 * total : 16 * large <= 15 * total;
 }
 inline void ratios_trail_items(const std::vector<int>& n, const std::vector<int>& begin, int cus, std::vector<unsigned int>* items) {
   std::vector<unsigned int> tiles;

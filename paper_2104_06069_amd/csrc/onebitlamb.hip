@@ -183,6 +183,7 @@ struct LayerSplit {
   bool hist_each_step = false;             // ob_lamb_ratios_apply takes ob_lamb_ratios_apply_hist's kernels
   // k_ratios_trail over them, the same way
   bool ratios_trail = false, trail_even = false;   // trail_even: the largest of these layers is at most a quarter of them
+  bool trail_pays[2] = {false, false};     // ratios_trail_pays, without and with a 16-bit copy
   float* d_sub_max = nullptr;              // [counters]
   float* d_tile_max = nullptr;             // [big tiles]
   unsigned long long* d_trail_flag = nullptr;   // [L]
@@ -514,6 +515,7 @@ void build_split(ob_lamb_ctx* ctx, Workspace* ws, const Tiling& tl, int tile_lb,
   const bool rest = !trail && rest_in_launch(sp->n_rest_ratio_tiles, sp->n_fused_tiles, sp->n_big_tiles, cus, sp->n_layers);
   sp->ratios_trail = !trail && sp->trail_wait && ratios_trail(pl.big_n, cus) &&
                      (!rest || (sp->n_big_tiles >= 3 * sp->n_fused_tiles && sp->n_big_tiles >= 12 * cus));
+  for (int copy = 0; copy < 2; ++copy) sp->trail_pays[copy] = ratios_trail_pays(pl.big_n, copy != 0);
   sp->rest_in_launch = rest && !sp->ratios_trail;
   sp->trail_even = sp->big_on && 4 * (int64_t)*std::max_element(pl.big_n.begin(), pl.big_n.end()) <= sp->n_big_tiles;
   if ((trail && sp->big_on) || sp->ratios_trail) {
@@ -1650,9 +1652,10 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
   // the history (leading workgroups) and the plain ratio pass outside the tiles that work from the history
   const bool hk = st->mom_scale != nullptr;
   const bool rest_in_launch = sp.on && sp.rest_in_launch;
+  const bool trail = sp.ratios_trail && (!h || sp.trail_pays[xl.p ? 1 : 0]);   // (no h: the array is written at every step)
   const VTerms vt = vterms(ctx);   // (vt.t = NULL where the ratio pass runs in the barrier kernel's launch)
   if (!rest_in_launch) {
-    const int n_flags = sp.ratios_trail ? (int)ctx->L : 0;
+    const int n_flags = trail ? (int)ctx->L : 0;
     const int n_lead_vt = (std::max(ctx->n_pairs, n_flags) + BLOCK - 1) / BLOCK;
     dispatch1(hk, [&](auto k_) {
       OB_LAUNCH(la, KID_RATIOS_PASS, (k_ratios_pass_vterms<U_MAIN, decltype(k_)::value>),
@@ -1661,7 +1664,7 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
     });
   }
   // launch 2: the layers that are too large for the barrier kernel: ratio pass from the history and update, or the ratio pass alone
-  if (sp.ratios_trail) {
+  if (trail) {
     RatioTrailTab tt;
     tt.items = sp.d_items;
     tt.lt = big_tiles(ctx, sp);
@@ -1681,8 +1684,8 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
   if (!sp.on) {
     OB_LAUNCH_B(la, KID_RATIOS_FINALIZE, k_ratios_finalize, (int)ctx->L, FBLOCK, ctx->d_seg_max,
                 ctx->d_layer_seg0, st->c_avg, st->r_prev, st->coeff_c, ctx->one_m_thr, ctx->one_p_thr,
-                ctx->r_min, ctx->r_max, (const unsigned char*)(sp.ratios_trail ? sp.d_has_tiles : nullptr));
-    if (sp.ratios_trail) launch_apply(la, ctx, st, packed_all, server_scales, lr, sp.d_rest_ratio_tiles, sp.n_rest_ratio_tiles, xl);
+                ctx->r_min, ctx->r_max, (const unsigned char*)(trail ? sp.d_has_tiles : nullptr));
+    if (trail) launch_apply(la, ctx, st, packed_all, server_scales, lr, sp.d_rest_ratio_tiles, sp.n_rest_ratio_tiles, xl);
     else launch_apply(la, ctx, st, packed_all, server_scales, lr, nullptr, ctx->n_tiles, xl);
     return la.ok ? OB_OK : OB_ERR_HIP;
   }
@@ -1696,7 +1699,7 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
   ls.c_avg = st->c_avg; ls.r_prev = st->r_prev; ls.coeff_c = st->coeff_c;
   ls.one_m_thr = ctx->one_m_thr; ls.one_p_thr = ctx->one_p_thr; ls.r_min = ctx->r_min; ls.r_max = ctx->r_max;
   ls.n_lead = (sp.n_layers < ctx->L) ? (int)ctx->L : 0;
-  if (sp.ratios_trail) ls.done = sp.d_has_tiles;
+  if (trail) ls.done = sp.d_has_tiles;
   if (rest_in_launch) {
     ls.n_alone = sp.n_alone; ls.n_lead = sp.n_alone + sp.n_rest_ratio_tiles;
     ls.rest_tiles = sp.d_rest_ratio_tiles; ls.alone = sp.d_alone; ls.arr0 = sp.d_arr0;
@@ -1715,7 +1718,7 @@ ob_status ob_lamb_ratios_apply_hist_lp(ob_lamb_ctx* ctx, const ob_lamb_state* st
     });
   });
   if (ls.n_events) return la.ok ? OB_OK : OB_ERR_HIP;   // (the rest tiles are updated in that launch)
-  if (sp.ratios_trail) launch_apply(la, ctx, st, packed_all, server_scales, lr, sp.d_rest_ratio_tiles, sp.n_rest_ratio_tiles, xl);
+  if (trail) launch_apply(la, ctx, st, packed_all, server_scales, lr, sp.d_rest_ratio_tiles, sp.n_rest_ratio_tiles, xl);
   else launch_apply(la, ctx, st, packed_all, server_scales, lr, sp.d_rest_tiles, sp.n_rest_tiles, xl);
   return la.ok ? OB_OK : OB_ERR_HIP;
 }

@@ -184,6 +184,10 @@ void ratios_trail_order() {
     const int64_t most = *std::max_element(n.begin(), n.end());
     CHECK(ratios_trail(n, 256) == (at >= 1024 && 8 * (at - most) >= at));
   }
+  const int line = (int)RATIOS_TRAIL_LARGE;   // at most 15/16 in layers above it, with a copy three quarters
+  CHECK(ratios_trail_pays({line, line, 0}, true) && !ratios_trail_pays({line + 1, line + 1}, false) && !ratios_trail_pays({0, line + 1, line / 3}, true));
+  CHECK(ratios_trail_pays({line + 1, line / 3 + 1}, true) && ratios_trail_pays({3 * line, line}, true) && !ratios_trail_pays({3 * line, line - 1}, true));
+  CHECK(ratios_trail_pays({3 * line, line - 1}, false) && ratios_trail_pays({15 * line, line}, false) && !ratios_trail_pays({15 * line, line - 1}, false));
 }
 
 // Which layers that rule takes: all those with enough whole tiles and not too many, or none at all below the total.

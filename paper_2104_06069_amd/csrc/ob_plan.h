@@ -335,10 +335,20 @@ inline bool ratios_trail(const std::vector<int>& n, int cus) {
 // Lists by the share in layers above the line: with a copy 0.66 4201 / 4317 (6389 / 6434), 0.68 4087 / 4115 (6208 / 6174) and 4315 / 4322 (6573 / 6500), 0.81 2237 /
 // 2260 (3371 / 3361), 0.89 2564 / 2625 (3892 / 3904), 0.93 4040 / 4110 (6105 / 6128); without 0.81 2031 / 1994, 0.89 2314 / 2307, 0.93 3640 / 3631.
 constexpr int64_t RATIOS_TRAIL_LARGE = 2 * RATIOS_TRAIL_KEEP;
+inline int64_t tiles_in_layers_above(const std::vector<int>& n, int64_t line) {
+  return std::accumulate(n.begin(), n.end(), (int64_t)0, [=](int64_t a, int q) { return a + (q > line ? q : 0); });
+}
 inline bool ratios_trail_pays(const std::vector<int>& n, bool copy) {
-  int64_t total = 0, large = 0;
-  for (int q : n) total += q, large += q > RATIOS_TRAIL_LARGE ? q : 0;
+  const int64_t total = tiles_in_layers_above(n, 0), large = tiles_in_layers_above(n, RATIOS_TRAIL_LARGE);
   return copy ? 4 * large <= 3 * total : 16 * large <= 15 * total;
+}
+// ... and where the array is written at every step: the largest layer at most a quarter of the tiles, and at most half of them in layers of more than 8192.
+// A step / the call, us, plain kernels around k_ratios_apply_resident / k_ratios_trail beside k_ratios_apply_hist, by that half's share: 0.11 6725 / 6698, 4361 / 4315; 0.17
+// 5819 / 5769, 3784 / 3755; 0.68 7021 / 7071, 4478 / 4571; 0.88 7510 / 7672, 4877 / 5024; 0.90 5314 / 5434, 3394 / 3526; with a copy 0.11 6970 / 6873, 4762 /
+// 4775; 0.17 5992 / 5876, 4111 / 4068; 0.68 7223 / 7216, 4962 / 5048; 0.88 7738 / 7852, 5281 / 5531; 0.90 5517 / 5537, 3789 / 3886.
+inline bool ratios_trail_each_step(const std::vector<int>& n) {
+  const int64_t total = tiles_in_layers_above(n, 0), most = n.empty() ? 0 : *std::max_element(n.begin(), n.end());
+  return 4 * most <= total && 2 * tiles_in_layers_above(n, 8192) <= total;
 }
 inline void ratios_trail_items(const std::vector<int>& n, const std::vector<int>& begin, int cus, std::vector<unsigned int>* items) {
   std::vector<unsigned int> tiles;

@@ -182,7 +182,7 @@ struct LayerSplit {
   double* d_part_sums = nullptr;           // [2 * parts]
   bool hist_each_step = false;             // ob_lamb_ratios_apply takes ob_lamb_ratios_apply_hist's kernels
   // k_ratios_trail over them, the same way
-  bool ratios_trail = false, trail_even = false;   // trail_even: the largest of these layers is at most a quarter of them
+  bool ratios_trail = false, trail_each_step = false;   // (ratios_trail_each_step)
   bool trail_pays[2] = {false, false};     // ratios_trail_pays, without and with a 16-bit copy
   float* d_sub_max = nullptr;              // [counters]
   float* d_tile_max = nullptr;             // [big tiles]
@@ -517,7 +517,7 @@ void build_split(ob_lamb_ctx* ctx, Workspace* ws, const Tiling& tl, int tile_lb,
                      (!rest || (sp->n_big_tiles >= 3 * sp->n_fused_tiles && sp->n_big_tiles >= 12 * cus));
   for (int copy = 0; copy < 2; ++copy) sp->trail_pays[copy] = ratios_trail_pays(pl.big_n, copy != 0);
   sp->rest_in_launch = rest && !sp->ratios_trail;
-  sp->trail_even = sp->big_on && 4 * (int64_t)*std::max_element(pl.big_n.begin(), pl.big_n.end()) <= sp->n_big_tiles;
+  sp->trail_each_step = sp->big_on && ratios_trail_each_step(pl.big_n);
   if ((trail && sp->big_on) || sp->ratios_trail) {
     static_assert(TILE_WU == 8 * SPAN && TILE_LB == 8 * SPAN, "tiles of k_warmup_trail and k_ratios_trail");
     const int parts = trail ? TRAIL_PARTS : 1;   // of a tile
@@ -734,7 +734,7 @@ bool lh_in_lds(int64_t n_tiles, int cus) {
 // (Lists of less than a tile a CU come here only where a configuration asks for the larger lists' launches.)
 bool hist_each_step(const LayerSplit& sp, int cus) {
   if (!sp.on || sp.n_fused_tiles < cus) return false;
-  if (sp.big_on) return sp.ratios_trail && sp.trail_even;
+  if (sp.big_on) return sp.ratios_trail && sp.trail_each_step;
   return sp.in_lds || (sp.rest_in_launch && sp.n_rest_ratio_tiles > 0);
 }
 

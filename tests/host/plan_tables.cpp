@@ -187,6 +187,8 @@ void ratios_trail_order() {
   const int line = (int)RATIOS_TRAIL_LARGE;   // at most 15/16 in layers above it, with a copy three quarters
   CHECK(ratios_trail_pays({line, line, 0}, true) && !ratios_trail_pays({line + 1, line + 1}, false) && !ratios_trail_pays({0, line + 1, line / 3}, true));
   CHECK(ratios_trail_pays({line + 1, line / 3 + 1}, true) && ratios_trail_pays({3 * line, line}, true) && !ratios_trail_pays({3 * line, line - 1}, true));
+  CHECK(ratios_trail_each_step({8192, 8192, 8192, 8192}) && !ratios_trail_each_step({8193, 8193, 8193, 8193}) && !ratios_trail_each_step({4000, 4000, 3999}));
+  CHECK(ratios_trail_each_step({9000, 9000, 8192, 8192, 1616}) && !ratios_trail_each_step({9000, 9000, 8192, 8192, 1615}));
   CHECK(ratios_trail_pays({3 * line, line - 1}, false) && ratios_trail_pays({15 * line, line}, false) && !ratios_trail_pays({15 * line, line - 1}, false));
 }
 

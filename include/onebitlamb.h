@@ -72,7 +72,8 @@ typedef struct ob_lamb_config {
   int32_t num_workers;          /* W >= 1 */
   int32_t server_chunk;         /* chunk this rank serves, 0..W-1 (which chunk ob_lamb_state.own_packed_in receives) */
   float beta1, beta2, beta3;    /* momentum, variance, coefficient moving average (Algorithm 1 line 1) */
-  float eta;                    /* added to sqrt(v) in eq. (1) and in line 21; 0 = line 21 as printed */
+  float eta;                    /* added to sqrt(v) in eq. (1) and in line 21; 0 = line 21 as printed (below 2^-22 = 2.4e-7
+                                   steps take up to 3 % longer: the shorter root and quotient do not hold there) */
   float c_min, c_max;           /* clip of LAMB's coefficient in eq. (1) (warmup only) */
   float r_min, r_max;           /* Algorithm 1 line 19 */
   float r_threshold;            /* Algorithm 1 line 18 */
